@@ -1,5 +1,6 @@
 // C ABI of the library: argument validation, workspace carving and the launch sequence of each
 // entry point.  Host code only; every arithmetic step runs in the kernels of this directory.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -146,7 +147,9 @@ fvar_status validate_indices(fvar_ctx *c, hipStream_t st, const int32_t *idx_kee
 }
 
 struct BlockWs {
-    char *x_keep, *u, *q, *att, *h1, *hid, *att_part, *gemm_part;
+    char *x_keep, *u, *q, *att, *h1, *hid, *att_part;
+    float *gemm_part;
+    fvar::GemmPlan qkv, o, fc1, fc2;          // how each linear layer runs at this row count
     size_t total;
 };
 
@@ -168,13 +171,13 @@ BlockWs carve(const fvar_ctx *c, void *ws, int B, int rows)
     w.att_part = part ? take(part * sizeof(float)) : nullptr;
     // partial tiles of the linear layers whose contraction axis is divided between workgroups
     const DType dt = dtype(c);
-    size_t gp = 0;
-    const size_t shapes[3][2] = {{d, d}, {F, d}, {d, F}};            // (N, K) of O, FC1, FC2
-    for (auto &sh : shapes) {
-        const size_t need = fvar::gemm_scratch_floats(dt, (int)R, (int)sh[0], (int)sh[1]) * sizeof(float);
-        if (need > gp) gp = need;
-    }
-    w.gemm_part = gp ? take(gp) : nullptr;
+    w.qkv = fvar::gemm_plan(dt, (int)R, (int)(3 * d), (int)d);
+    w.o = fvar::gemm_plan(dt, (int)R, (int)d, (int)d);
+    w.fc1 = fvar::gemm_plan(dt, (int)R, (int)F, (int)d);
+    w.fc2 = fvar::gemm_plan(dt, (int)R, (int)d, (int)F);
+    const size_t gp = std::max(std::max(w.qkv.scratch_floats, w.o.scratch_floats),
+                               std::max(w.fc1.scratch_floats, w.fc2.scratch_floats));
+    w.gemm_part = gp ? reinterpret_cast<float *>(take(gp * sizeof(float))) : nullptr;
     w.total = off;
     return w;
 }
@@ -247,7 +250,7 @@ fvar_status block_forward(fvar_ctx *c, hipStream_t st, const fvar_block_weights 
         e.bias = w->b_qkv; e.out0 = s.q; e.ld0 = d; e.split = d;
         e.kcache = kv->k; e.vcache = kv->v; e.hd = d; e.cap = kv->capacity; e.len = kv->len;
         e.rows_per_sample = rows;
-        fvar::launch_gemm(dt, s.u, w->w_qkv, R, 3 * d, d, e, st);
+        fvar::launch_gemm(dt, s.u, w->w_qkv, R, 3 * d, d, e, s.qkv, s.gemm_part, st);
     });
     timed(c, st, "attention", [&] {
         fvar::launch_attention(dt, s.q, kv->k, kv->v, B, rows, L, kv->capacity, H, Dh, c->scale, s.att,
@@ -257,8 +260,7 @@ fvar_status block_forward(fvar_ctx *c, hipStream_t st, const fvar_block_weights 
         fvar::GemmEpilogue e;
         e.bias = w->b_o; e.residual = resid; e.out0 = s.h1; e.ld0 = d; e.split = d;
         e.out_f32 = 1;
-        e.splitk_scratch = reinterpret_cast<float *>(s.gemm_part);
-        fvar::launch_gemm(dt, s.att, w->w_o, R, d, d, e, st);
+        fvar::launch_gemm(dt, s.att, w->w_o, R, d, d, e, s.o, s.gemm_part, st);
     });
     timed(c, st, "ln2", [&] {
         if (dt == DType::BF16)
@@ -270,14 +272,12 @@ fvar_status block_forward(fvar_ctx *c, hipStream_t st, const fvar_block_weights 
     timed(c, st, "gemm_fc1", [&] {
         fvar::GemmEpilogue e;
         e.bias = w->b_fc1; e.gelu = 1; e.out0 = s.hid; e.ld0 = F; e.split = F;
-        e.splitk_scratch = reinterpret_cast<float *>(s.gemm_part);
-        fvar::launch_gemm(dt, s.u, w->w_fc1, R, F, d, e, st);
+        fvar::launch_gemm(dt, s.u, w->w_fc1, R, F, d, e, s.fc1, s.gemm_part, st);
     });
     timed(c, st, "gemm_fc2", [&] {
         fvar::GemmEpilogue e;
         e.bias = w->b_fc2; e.residual = s.h1; e.res_f32 = 1; e.out0 = y; e.ld0 = d; e.split = d;
-        e.splitk_scratch = reinterpret_cast<float *>(s.gemm_part);
-        fvar::launch_gemm(dt, s.hid, w->w_fc2, R, d, F, e, st);
+        fvar::launch_gemm(dt, s.hid, w->w_fc2, R, d, F, e, s.fc2, s.gemm_part, st);
     });
     const fvar_status ls = launch_status(c, who);
     if (ls != FVAR_OK || !c->debug_checks) return ls;

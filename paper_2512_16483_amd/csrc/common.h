@@ -133,14 +133,15 @@ struct GemmEpilogue {
     // Used for the intermediate residual stream h = x + attention projection, which stays in
     // fp32 between the two halves of the block so that it is not rounded twice.
     int out_f32 = 0, res_f32 = 0;
-    // bf16 path: scratch of gemm_scratch_floats() floats for dividing the contraction axis between
-    // workgroups (every tile of a problem with too few tiles to fill the chip, or only the tiles
-    // beyond the last full round of workgroups), or null (never divide).
-    float *splitk_scratch = nullptr;
 };
-size_t gemm_scratch_floats(DType dt, int rows, int N, int K);
+// How a bf16 linear layer is run: kernel and tile (index into the tables of gemm.hip), workgroups that
+// share the contraction axis of every tile (nsplit) or of the tiles beyond the last whole round
+// (tail), and the floats of scratch that their partial tiles take.  A function of the shape alone.
+struct GemmPlan { int cfg, nsplit, tail; size_t scratch_floats; };
+GemmPlan gemm_plan(DType dt, int rows, int N, int K);
+// `part`: plan.scratch_floats floats (unused when 0)
 void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
-                 const GemmEpilogue &ep, hipStream_t st);
+                 const GemmEpilogue &ep, const GemmPlan &plan, float *part, hipStream_t st);
 
 // o[b,i,h,:] = softmax_t(scale * q[b,i,h,:] . K[b,t,h,:]) V[b,t,h,:], t in [0,L)
 //   q,o:[B,n,H,Dh]; K,V:[B,cap,H,Dh]

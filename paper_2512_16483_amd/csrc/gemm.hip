@@ -12,8 +12,9 @@
 // Workgroup ids are remapped so that each XCD (own L2) works on a compact patch of the tile
 // grid.  Bigger tiles cut the L1/LDS traffic per flop (a 128x128 tile needs the full 64 B/clk of
 // the CU's vector L1 at peak MFMA rate, a 256x256 tile half of it) but quantise badly on the few
-// thousand rows of a pruned scale, so the launcher picks the tile per problem with a small cost
-// model.
+// thousand rows of a pruned scale, and a few rows leave most CUs without a tile: eleven tiles from
+// 320x256 down to 64x64, a kernel without staging for a few rows, and divisions of the contraction
+// axis between workgroups, picked per problem by predicted time (gemm_plan, at the end).
 //
 // fp32: plain LDS-tiled FMA kernel, used only by the fp32 parity configuration.
 #include <cmath>
@@ -55,6 +56,32 @@ __device__ __forceinline__ T *epi_dst(const EpiParams &ep, int row, int col)
     int c = col - ep.split;
     if (c < ep.hd) return (T *)ep.kcache + crow * ep.hd + c;
     return (T *)ep.vcache + crow * ep.hd + (c - ep.hd);
+}
+
+// Epilogue of 4 consecutive output columns of one row held in fp32: bias, GELU, residual, bf16 or fp32
+// output, K / V columns to the cache.  For kernels that own their outputs as float4.
+__device__ __forceinline__ void finish_quad(const EpiParams &ep, int row, int col, float4 v)
+{
+    if (ep.bias) {
+        const uint2 b = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(ep.bias) + col);
+        v.x += bf16_lo(b.x); v.y += bf16_hi(b.x); v.z += bf16_lo(b.y); v.w += bf16_hi(b.y);
+    }
+    if (ep.gelu) { v.x = gelu_tanh(v.x); v.y = gelu_tanh(v.y); v.z = gelu_tanh(v.z); v.w = gelu_tanh(v.w); }
+    if (ep.residual) {
+        const size_t off = (size_t)row * ep.N + col;
+        if (ep.res_f32) {
+            const float4 r = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(ep.residual) + off);
+            v.x += r.x; v.y += r.y; v.z += r.z; v.w += r.w;
+        } else {
+            const uint2 r = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(ep.residual) + off);
+            v.x += bf16_lo(r.x); v.y += bf16_hi(r.x); v.z += bf16_lo(r.y); v.w += bf16_hi(r.y);
+        }
+    }
+    if (ep.out_f32)
+        *reinterpret_cast<float4 *>(reinterpret_cast<float *>(ep.out0) + (size_t)row * ep.ld0 + col) = v;
+    else
+        *reinterpret_cast<uint2 *>(epi_dst<uint16_t>(ep, row, col)) =
+            make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
 }
 
 // ------------------------------------------------------------------------------ bf16 MFMA
@@ -110,11 +137,11 @@ __device__ __forceinline__ void store_tile_epilogue(const floatx4_t (*acc)[FN][2
                     w32[(ii * 16 + 4 * q16 + e) * P32 + jj * 16 + c16] = acc[ii >> 1][j][ii & 1][bj][e] + bv;
         }
         asm volatile("" ::: "memory");       // staging stores and loads use different vector types
-        constexpr int CPR = TN / 4, RPI = 64 / CPR;
-        const int lc = (lane % CPR) * 4, col = wcol0 + lc;
+        constexpr int CPR = TN / 4;                         // chunks per row
 #pragma unroll
-        for (int it = 0; it < TM / RPI; ++it) {
-            const int lrow = it * RPI + lane / CPR, row = wrow0 + lrow;
+        for (int it = 0; it < TM * CPR / 64; ++it) {
+            const int lrow = (it * 64 + lane) / CPR, row = wrow0 + lrow;
+            const int lc = (it * 64 + lane) % CPR * 4, col = wcol0 + lc;
             float4 v = *reinterpret_cast<const float4 *>(w32 + lrow * P32 + lc);
             if (row >= rows || col >= N) continue;
             if (res) {
@@ -151,14 +178,14 @@ __device__ __forceinline__ void store_tile_epilogue(const floatx4_t (*acc)[FN][2
     // order, so no barrier is needed between the two phases (the compiler is kept from moving the
     // accesses across this point: the stores and loads use different vector types)
     asm volatile("" ::: "memory");
-    constexpr int CPR = TN / 8, RPI = 64 / CPR;             // chunks per row, rows per instruction
+    constexpr int CPR = TN / 8;                             // chunks per row
     const uint16_t *res = reinterpret_cast<const uint16_t *>(ep.residual);
     const bool routed = ep.split < N;                       // K/V columns go to the cache
     const float inv_rps = 1.0f / (float)ep.rows_per_sample;
-    const int lc = (lane % CPR) * 8, col = wcol0 + lc;
 #pragma unroll
-    for (int it = 0; it < TM / RPI; ++it) {
-        const int lrow = it * RPI + lane / CPR, row = wrow0 + lrow;
+    for (int it = 0; it < TM * CPR / 64; ++it) {
+        const int lrow = (it * 64 + lane) / CPR, row = wrow0 + lrow;
+        const int lc = (it * 64 + lane) % CPR * 8, col = wcol0 + lc;
         uint4 v = *reinterpret_cast<const uint4 *>(wlds + lrow * PITCH + lc);
         if (row >= rows || col >= N) continue;
         if (res) {
@@ -206,12 +233,11 @@ __device__ __forceinline__ void dma_b128(const void *base, uint32_t byte_off, ui
                  :: "s"(lds_addr), "v"(byte_off), "s"(base) : "memory", "m0");
 }
 
-// LDS needed after the main loop: k-split reduction buffer + one staging tile per wavefront.
+// LDS needed after the main loop: one staging tile per wavefront.
 // A wavefront sends its sub-tile through the epilogue in passes of a few 32-row fragments:
 // epi_frags() for bf16 output (a staging tile of at most 128 rows), epi_frags_f32() for fp32
 // output (as many fragments as fit the LDS with 4-byte elements, at least one).
 constexpr size_t kLdsLimit = 160 * 1024;
-constexpr size_t gemm_red_bytes(int BM, int BN, int KS) { return KS > 1 ? (size_t)BM * BN * 4 : 0; }
 constexpr int epi_frags(int FM) { return FM > 4 ? (FM + 1) / 2 : FM; }
 constexpr size_t epi_bytes_bf16(int BM, int BN, int WM, int WN)
 {
@@ -221,23 +247,19 @@ constexpr size_t epi_bytes_f32(int BN, int WM, int WN, int fe)
 {
     return (size_t)32 * fe * (BN / WN + 4) * 4 * WM * WN;
 }
-constexpr int epi_frags_f32(int BM, int BN, int WM, int WN, int KS)
+constexpr int epi_frags_f32(int BM, int BN, int WM, int WN)
 {
     int fe = epi_frags(BM / WM / 32);
-    while (fe > 1 && gemm_red_bytes(BM, BN, KS) + epi_bytes_f32(BN, WM, WN, fe) > kLdsLimit) --fe;
+    while (fe > 1 && epi_bytes_f32(BN, WM, WN, fe) > kLdsLimit) --fe;
     return fe;
 }
-constexpr size_t gemm_epi_lds_bytes(int BM, int BN, int WM, int WN, int KS)
+constexpr size_t gemm_epi_lds_bytes(int BM, int BN, int WM, int WN)
 {
     const size_t a = epi_bytes_bf16(BM, BN, WM, WN);
-    const size_t b = epi_bytes_f32(BN, WM, WN, epi_frags_f32(BM, BN, WM, WN, KS));
-    return gemm_red_bytes(BM, BN, KS) + (a > b ? a : b);
+    const size_t b = epi_bytes_f32(BN, WM, WN, epi_frags_f32(BM, BN, WM, WN));
+    return a > b ? a : b;
 }
 
-// KS > 1 splits every k-tile between KS groups of WM x WN wavefronts (group ks takes the 32-wide
-// k-steps ks, ks+KS, ...); the groups' partial accumulators are summed through LDS before the
-// epilogue.  This doubles the wavefronts per CU for problems that give a CU only one small tile.
-//
 // BKM ("B k-major"): the second operand is given as X[K][N] (row = contraction index, as a token
 // map is when the contraction runs over tokens: paper, Sec. "Random Projection (RP) for Low-Rank
 // Feature", Q^T X) instead of W[N][K].  Its tiles travel to LDS in their own row-major layout and
@@ -245,15 +267,15 @@ constexpr size_t gemm_epi_lds_bytes(int BM, int BN, int WM, int WN, int KS)
 // problems of one shape in one launch (operands and output `*_bstride` elements apart), whole
 // tiles only (no division of the contraction), K a multiple of 64 and N a multiple of 8.
 // nbatch > 1 is also available with the ordinary operand layout (whole tiles only).
-template <int BM, int BN, int WM, int WN, int STAGES, int KS, bool BKM = false>
-__global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(
+template <int BM, int BN, int WM, int WN, int STAGES, bool BKM = false>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     const uint16_t *__restrict__ A_in, const uint16_t *__restrict__ W_in, int rows, int N, int K,
     int tiles_m, int tiles_n, int group_m, EpiParams ep, int nsplit, float *__restrict__ part,
     int full_tiles, int tail_split, int nbatch, size_t a_bstride, size_t w_bstride,
     size_t o_bstride)
 {
     const uint16_t *A = A_in, *W = W_in;
-    constexpr int NW = WM * WN * KS;                   // wavefronts per workgroup
+    constexpr int NW = WM * WN;                        // wavefronts per workgroup
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int FM = TM / 32, FN = TN / 32;
     constexpr int NGA = BM / 8 / NW, NGB = BN / 8 / NW; // 1 KiB groups (8 rows) per wavefront
@@ -315,8 +337,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c16 = lane & 15, q16 = lane >> 4;
-    const int ks = wave / (WM * WN), wsub = wave % (WM * WN);
-    const int wm = wsub / WN, wn = wsub % WN;
+    const int wm = wave % NW / WN, wn = wave % NW % WN;     // the modulus saves the 320x256 tile a spill
 
     // ---- DMA assignment: wavefront w owns the 8-row groups w, w+NW, ... of each tile; lane l of a
     // group fills physical chunk l%8 of row 8*group + l/8, i.e. it fetches the logical chunk that
@@ -380,15 +401,23 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(
     // holds all fragments of k-tile kt in registers, so the same barrier frees that tile's stage
     // for the DMA of k-tile kt+STAGES.
     constexpr int FM16 = TM / 16, FN16 = TN / 16;
-    constexpr int SPW = BK / 32 / KS;                    // k-steps of this wavefront per k-tile
+    // a zero the compiler cannot see through: with constant fragment offsets it hoists every LDS
+    // address out of the loop, and the 320x256 tile, which has no register to spare, spills (-8 %)
+    int zero = 0;
+    asm volatile("" : "+s"(zero));
+    constexpr int SPW = BK / 32;                         // k-steps per k-tile
     constexpr int ROWS = SPW * FM16;
     static_assert(ROWS % 4 == 0 && ROWS >= 4, "ring of four A fragments");
     constexpr int SPREAD = ROWS >= 12 ? 6 : 1;           // rows over which a k-tile's DMA is issued
-    static_assert(STAGES == 2 || STAGES == 3, "wait counts below are written for 2 or 3 stages");
+    static_assert(STAGES >= 2 && STAGES <= 4, "wait counts below are written for 2 to 4 stages");
+    // rows at which the B fragments of the next k-step / of the next k-tile are fetched: after the
+    // last use of the buffer they go to, and (for this tile's) before the hand-over point
+    constexpr int B_NEXT_STEP = FM16 > 2 ? FM16 / 2 : 0;
+    constexpr int B_NEXT_TILE = ROWS - 3 > FM16 * (SPW - 1) ? ROWS - 3 : FM16 * (SPW - 1);
     auto load_a = [&](const uint16_t *tile, int row) {   // row of the walk -> fragment
         const int q = row / FM16, i = row % FM16;
         const int r = wm * TM + i * 16 + c16;
-        return *reinterpret_cast<const bf16x8_t *>(tile + lds_off(r, (q * KS + ks) * 4 + q16));
+        return *reinterpret_cast<const bf16x8_t *>(tile + lds_off(r, (q + zero) * 4 + q16));
     };
     auto load_b = [&](const uint16_t *tile, int q, bf16x8_t *b) {
         if constexpr (BKM) {
@@ -398,7 +427,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(
             // (+4 for the second half) and at columns 16j + 4*(l%4) .. +3.
             typedef short bkm_shortx4_t __attribute__((ext_vector_type(4)));
             typedef __attribute__((address_space(3))) bkm_shortx4_t lds_shortx4_t;
-            const int kr = (q * KS + ks) * 32 + 8 * q16 + (c16 >> 2);
+            const int kr = (q + zero) * 32 + 8 * q16 + (c16 >> 2);
 #pragma unroll
             for (int j = 0; j < FN16; ++j) {
                 const int chunk = (wn * TN + j * 16) / 8 + ((c16 & 3) >> 1);
@@ -411,16 +440,18 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(
 #pragma unroll
             for (int j = 0; j < FN16; ++j) {
                 const int r = wn * TN + j * 16 + c16;
-                b[j] = *reinterpret_cast<const bf16x8_t *>(tile + BM * BK + lds_off(r, (q * KS + ks) * 4 + q16));
+                b[j] = *reinterpret_cast<const bf16x8_t *>(tile + BM * BK + lds_off(r, (q + zero) * 4 + q16));
             }
         }
     };
 
     issue(0, 0);
     if (ktiles > 1) issue(1, 1);
-    if (STAGES == 3 && ktiles > 2) issue(2, 2);
+    if (STAGES >= 3 && ktiles > 2) issue(2, 2);
+    if (STAGES >= 4 && ktiles > 3) issue(3, 3);
     if (ktiles == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else if (STAGES == 3 && ktiles > 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NG) : "memory");
+    else if (STAGES >= 4 && ktiles > 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NG) : "memory");
+    else if (STAGES >= 3 && ktiles > 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NG) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NG) : "memory");
     __syncthreads();
 
@@ -441,11 +472,12 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(
                 // own reads of this stage are complete before the barrier says so
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 // k-tile kt+1 has landed once only the requests of the tiles after it are outstanding
-                if (STAGES == 3 && kt + 2 < ktiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NG) : "memory");
+                if (STAGES >= 4 && kt + 3 < ktiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NG) : "memory");
+                else if (STAGES >= 3 && kt + 2 < ktiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NG) : "memory");
                 else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __syncthreads();
-                if (SPW % 2 == 0) load_b(nxt, 0, bb[0]);
             }
+            if (row == B_NEXT_TILE && more) load_b(nxt, 0, bb[0]);
             // The DMA of k-tile kt+STAGES into the stage that the hand-over frees is issued a few
             // instructions per row over the SPREAD rows that follow the hand-over (they run into
             // the next k-tile): a burst of all NG instructions from all wavefronts at once fills
@@ -462,8 +494,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(
             }
             if (row + 3 < ROWS) ring[(row + 3) & 3] = load_a(cur, row + 3);
             else if (more) ring[(row + 3) & 3] = load_a(nxt, row + 3 - ROWS);
-            // B fragments of the next k-step of this tile, fetched in the middle of the current one
-            if (i == FM16 / 2 && q + 1 < SPW) load_b(cur, q + 1, bb[(q + 1) & 1]);
+            // B fragments of the next k-step of this tile
+            if (i == B_NEXT_STEP && q + 1 < SPW) load_b(cur, q + 1, bb[(q + 1) & 1]);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < FN16; ++j)
@@ -471,36 +503,13 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(
                     ring[row & 3], bb[q & 1][j], acc[i >> 1][j >> 1][i & 1][j & 1], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
-        // with an odd number of k-steps per tile the first B buffer is in use until the tile's end
-        if (SPW % 2 == 1 && more) load_b(nxt, 0, bb[0]);
         stage = nstage;
     }
     // the stage buffers are reused below: every wavefront must be past its last operand read
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();
     // every request has landed and every wavefront is past its last operand read (barrier above):
-    // the stage buffers are free for the k-split reduction and the epilogue's staging
-    constexpr int RED_FLOATS = KS > 1 ? WM * WN * FM * FN * 16 * 64 : 0;
-    if (KS > 1) {
-        // partial accumulators in lane-major order: entry (tile, e) of lane l at (tile*16+e)*64 + l
-        float *red = reinterpret_cast<float *>(lds_raw) + wsub * (FM * FN * 16 * 64) + lane;
-        if (ks != 0) {
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) red[((i * FN + j) * 16 + e) * 64] = acc[i][j][(e >> 3) & 1][(e >> 2) & 1][e & 3];
-        }
-        __syncthreads();
-        if (ks != 0) return;
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][(e >> 3) & 1][(e >> 2) & 1][e & 3] += red[((i * FN + j) * 16 + e) * 64];
-    }
+    // the stage buffers are free for the epilogue's staging
     if (ranges > 1) {
         // partial tile, fp32: 16 neighbouring lanes cover 64 contiguous bytes of a row.
         // Divided problem: [range][rows][N]; divided tail: [tail tile][range][BM][BN].
@@ -524,13 +533,13 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(
         }
         return;
     }
-    // per-wavefront staging region behind the reduction buffer; the sub-tile passes through it a few
+    // per-wavefront staging region; the sub-tile passes through it a few
     // fragments at a time (fewer per pass when the output is fp32)
-    constexpr int FE = epi_frags(FM), FE32 = epi_frags_f32(BM, BN, WM, WN, KS);
-    static_assert(gemm_red_bytes(BM, BN, KS) + epi_bytes_f32(BN, WM, WN, FE32) <= kLdsLimit, "fp32 staging");
-    char *stage_base = reinterpret_cast<char *>(lds_raw) + RED_FLOATS * 4;
+    constexpr int FE = epi_frags(FM), FE32 = epi_frags_f32(BM, BN, WM, WN);
+    static_assert(epi_bytes_f32(BN, WM, WN, FE32) <= kLdsLimit, "fp32 staging");
+    char *stage_base = reinterpret_cast<char *>(lds_raw);
     if (ep.out_f32) {
-        uint16_t *wlds = reinterpret_cast<uint16_t *>(stage_base + wsub * (FE32 * 32 * (TN + 4) * 4));
+        uint16_t *wlds = reinterpret_cast<uint16_t *>(stage_base + wave * (FE32 * 32 * (TN + 4) * 4));
 #pragma unroll
         for (int f0 = 0; f0 < FM; f0 += FE32) {
             constexpr int dummy = 0; (void)dummy;
@@ -543,7 +552,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(
         }
         return;
     }
-    uint16_t *wlds = reinterpret_cast<uint16_t *>(stage_base + wsub * (FE * 32 * (TN + 8) * 2));
+    uint16_t *wlds = reinterpret_cast<uint16_t *>(stage_base + wave * (FE * 32 * (TN + 8) * 2));
     store_tile_epilogue<FE, FN, false>(acc, ep, rows, N, row0 + wm * TM, col0 + wn * TN, lane, wlds);
     if constexpr (FE < FM)
         store_tile_epilogue<FM - FE, FN, false>(acc + FE, ep, rows, N, row0 + wm * TM + FE * 32,
@@ -577,32 +586,12 @@ __global__ __launch_bounds__(256) void gemm_tail_epilogue_kernel(const float *__
         const float4 p = *reinterpret_cast<const float4 *>(src + (size_t)s * BM * BN);
         v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
     }
-    if (ep.bias) {
-        const uint2 b = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(ep.bias) + col);
-        v.x += bf16_lo(b.x); v.y += bf16_hi(b.x); v.z += bf16_lo(b.y); v.w += bf16_hi(b.y);
-    }
-    if (ep.gelu) { v.x = gelu_tanh(v.x); v.y = gelu_tanh(v.y); v.z = gelu_tanh(v.z); v.w = gelu_tanh(v.w); }
-    const size_t off = (size_t)row * N + col;
-    if (ep.residual) {
-        if (ep.res_f32) {
-            const float4 r = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(ep.residual) + off);
-            v.x += r.x; v.y += r.y; v.z += r.z; v.w += r.w;
-        } else {
-            const uint2 r = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(ep.residual) + off);
-            v.x += bf16_lo(r.x); v.y += bf16_hi(r.x); v.z += bf16_lo(r.y); v.w += bf16_hi(r.y);
-        }
-    }
-    const size_t ooff = (size_t)row * ep.ld0 + col;
-    if (ep.out_f32)
-        *reinterpret_cast<float4 *>(reinterpret_cast<float *>(ep.out0) + ooff) = v;
-    else
-        *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(ep.out0) + ooff) =
-            make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+    finish_quad(ep, row, col, v);
 }
 
 // tail > 1: the tiles beyond the last full round of 256 are divided into `tail` ranges of the
 // contraction axis each (nsplit must be 1 then)
-template <int BM, int BN, int WM, int WN, int STAGES, int KS = 1>
+template <int BM, int BN, int WM, int WN, int STAGES>
 static void launch_gemm_bf16_cfg(const void *A, const void *W, int rows, int N, int K,
                                  const EpiParams &ep, hipStream_t st, int nsplit = 1,
                                  float *part = nullptr, int tail = 1)
@@ -613,9 +602,9 @@ static void launch_gemm_bf16_cfg(const void *A, const void *W, int rows, int N, 
     const int tail_units = (ntiles - full_tiles) * tail;
     const int grid = tail > 1 ? full_tiles + (tail_units + 7) / 8 * 8 : (ntiles * nsplit + 7) / 8 * 8;
     const size_t lds_stages = (size_t)STAGES * (BM + BN) * BK * sizeof(uint16_t);
-    const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN, KS);
+    const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN);
     const size_t lds = lds_stages > lds_epi ? lds_stages : lds_epi;
-    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, KS>;
+    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES>;
     // set on every launch: the attribute belongs to the current device's copy of the kernel
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -623,7 +612,7 @@ static void launch_gemm_bf16_cfg(const void *A, const void *W, int rows, int N, 
     // tiles reads g row strips (BM x K) and c column strips (BN x K), with g * c = tiles / 8
     int group_m = (int)lround(sqrt((double)ntiles * BN / (8.0 * BM)));
     group_m = group_m < 1 ? 1 : (group_m > tiles_m ? tiles_m : group_m);
-    launch(kern, dim3(grid), dim3(64 * WM * WN * KS), lds, st, (const uint16_t *)A,
+    launch(kern, dim3(grid), dim3(64 * WM * WN), lds, st, (const uint16_t *)A,
                        (const uint16_t *)W, rows, N, K, tiles_m, tiles_n, group_m, ep, nsplit, part,
                        full_tiles, tail, 1, (size_t)0, (size_t)0, (size_t)0);
     if (tail > 1) {
@@ -645,9 +634,9 @@ static void launch_kmajor_cfg(const void *A, size_t a_bstride, const void *X, in
     const int ntiles = tiles_m * tiles_n * nbatch;
     const int grid = (ntiles + 7) / 8 * 8;
     const size_t lds_stages = (size_t)STAGES * (BM + BN) * BK * sizeof(uint16_t);
-    const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN, 1);
+    const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN);
     const size_t lds = lds_stages > lds_epi ? lds_stages : lds_epi;
-    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, 1, true>;
+    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, true>;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     int group_m = (int)lround(sqrt((double)tiles_m * tiles_n * BN / (8.0 * BM)));
@@ -671,9 +660,9 @@ static void launch_batched_f32_cfg(const void *A, const void *W, int nbatch, int
     const int ntiles = tiles_m * tiles_n * nbatch;
     const int grid = (ntiles + 7) / 8 * 8;
     const size_t lds_stages = (size_t)STAGES * (BM + BN) * BK * sizeof(uint16_t);
-    const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN, 1);
+    const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN);
     const size_t lds = lds_stages > lds_epi ? lds_stages : lds_epi;
-    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, 1, false>;
+    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, false>;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     int group_m = (int)lround(sqrt((double)tiles_m * tiles_n * BN / (8.0 * BM)));
@@ -744,26 +733,106 @@ __global__ __launch_bounds__(256) void gemm_splitk_epilogue_kernel(const float *
         const float4 p = *reinterpret_cast<const float4 *>(part + (size_t)s * rows * N + off);
         v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
     }
-    if (ep.bias) {
-        const uint2 b = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(ep.bias) + col);
-        v.x += bf16_lo(b.x); v.y += bf16_hi(b.x); v.z += bf16_lo(b.y); v.w += bf16_hi(b.y);
-    }
-    if (ep.gelu) { v.x = gelu_tanh(v.x); v.y = gelu_tanh(v.y); v.z = gelu_tanh(v.z); v.w = gelu_tanh(v.w); }
-    if (ep.residual) {
-        if (ep.res_f32) {
-            const float4 r = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(ep.residual) + off);
-            v.x += r.x; v.y += r.y; v.z += r.z; v.w += r.w;
-        } else {
-            const uint2 r = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(ep.residual) + off);
-            v.x += bf16_lo(r.x); v.y += bf16_hi(r.x); v.z += bf16_lo(r.y); v.w += bf16_hi(r.y);
+    finish_quad(ep, row, col, v);
+}
+
+// Linear layer of a few rows: bound by the latency of the weights' one trip from HBM, not by MFMA.
+// No LDS staging and no barrier before the end: a workgroup owns 16*FT output features and 16*TT
+// rows, its NW wavefronts take NW contiguous shares of the contraction axis, and every operand
+// fragment goes from global memory straight to registers, two groups of U k-steps in flight (for
+// K = 2048 that is the wavefront's whole share).  Weights are the A operand of the 16x16x32 MFMA, so a
+// lane ends up with 4 consecutive features of one row; the wavefronts' partial tiles meet in LDS.
+// The rows are read again by every feature tile (L2 hits), which is what bounds the kernel from
+// about 64 rows on; there the staged tiles win.  Microseconds at 16 rows, hidden 2048, 128x128 tiles
+// (divided where that helped) -> here: QKV 20.2 -> 8.9, O 11.5 -> 6.3, FC1 15.0 -> 11.1; at 64 rows
+// O 13.5 -> 8.3 (25 MB of weights alone take 5.2 us at the rate of a large copy).
+template <int FT, int TT, int NW>
+__global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(
+    const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, int rows, int N, int K, int row_tiles,
+    int nsplit, EpiParams ep, float *__restrict__ part)
+{
+    constexpr int U = 4;                                // k-steps per load group
+    __shared__ float4 red[NW][FT * TT][64];
+    const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q16 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // each XCD takes one contiguous share of the (feature tile, split, row tile) units
+    const int units = row_tiles * nsplit * (N / (16 * FT));
+    const int per_xcd = (units + 7) / 8;
+    int pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (pid >= units || (int)(blockIdx.x >> 3) >= per_xcd) return;
+    const int rt = pid % row_tiles; pid /= row_tiles;
+    const int split = pid % nsplit, n0 = pid / nsplit * (16 * FT), row0 = rt * (16 * TT);
+
+    const int steps = K / 32, parts = nsplit * NW, pi = split * NW + wave;
+    const int s0 = (int)((long)steps * pi / parts), s1 = (int)((long)steps * (pi + 1) / parts);
+    const uint16_t *wp[FT], *ap[TT];
+#pragma unroll
+    for (int f = 0; f < FT; ++f) wp[f] = W + (size_t)(n0 + 16 * f + c16) * K + 8 * q16;
+#pragma unroll
+    for (int t = 0; t < TT; ++t) ap[t] = A + (size_t)min(row0 + 16 * t + c16, rows - 1) * K + 8 * q16;
+    floatx4_t acc[FT][TT];
+#pragma unroll
+    for (int f = 0; f < FT; ++f)
+#pragma unroll
+        for (int t = 0; t < TT; ++t) acc[f][t] = floatx4_t{0};
+    bf16x8_t wf[2][U][FT], af[2][U][TT];
+    auto load = [&](int s, int buf) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = min(s + u, s1 - 1) * 32;
+#pragma unroll
+            for (int f = 0; f < FT; ++f) wf[buf][u][f] = *reinterpret_cast<const bf16x8_t *>(wp[f] + k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = min(s + u, s1 - 1) * 32;
+#pragma unroll
+            for (int t = 0; t < TT; ++t) af[buf][u][t] = *reinterpret_cast<const bf16x8_t *>(ap[t] + k);
+        }
+    };
+    auto mac = [&](int s, int buf) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s + u < s1) {
+#pragma unroll
+                for (int f = 0; f < FT; ++f)
+#pragma unroll
+                    for (int t = 0; t < TT; ++t)
+                        acc[f][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[buf][u][f], af[buf][u][t],
+                                                                            acc[f][t], 0, 0, 0);
+            }
+    };
+    if (s0 < s1) {
+        load(s0, 0);
+        for (int s = s0; s < s1; s += 2 * U) {
+            if (s + U < s1) load(s + U, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            mac(s, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (s + 2 * U < s1) load(s + 2 * U, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (s + U < s1) mac(s + U, 1);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
-    const size_t ooff = (size_t)row * ep.ld0 + col;
-    if (ep.out_f32)
-        *reinterpret_cast<float4 *>(reinterpret_cast<float *>(ep.out0) + ooff) = v;
-    else
-        *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(ep.out0) + ooff) =
-            make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+#pragma unroll
+    for (int f = 0; f < FT; ++f)
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+            red[wave][f * TT + t][lane] = make_float4(acc[f][t][0], acc[f][t][1], acc[f][t][2], acc[f][t][3]);
+    __syncthreads();
+    for (int blk = wave; blk < FT * TT; blk += NW) {
+        float4 v = red[0][blk][lane];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
+            const float4 p = red[w][blk][lane];
+            v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+        }
+        const int row = row0 + (blk % TT) * 16 + c16, col = n0 + (blk / TT) * 16 + 4 * q16;
+        if (row >= rows) continue;
+        if (nsplit > 1) *reinterpret_cast<float4 *>(part + ((size_t)split * rows + row) * N + col) = v;
+        else finish_quad(ep, row, col, v);
+    }
 }
 
 // ------------------------------------------------------------------------------ fp32 FMA
@@ -820,78 +889,104 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
     }
 }
 
-// Tile configuration for a problem: rounds of workgroups over the 256 CUs (one workgroup per CU
-// at these LDS sizes) x time of one tile at the sustained rate of the configuration (TFLOP/s
-// measured on large problems).  With `allow_tail` the tiles beyond the last full round may be
-// divided along the contraction axis into 2..8 ranges (each at least 8 k-tiles long) so that
-// they fill the chip once more at a fraction of a tile's time; their fp32 partial tiles cost a
-// write and a read at about 4 TB/s.
-struct GemmPlan { int cfg; long tiles; int tail; size_t tail_floats; };
-static GemmPlan plan_bf16(int rows, int N, int K, bool allow_tail)
+// ------------------------------------------------------------------------------ plan
+// Which kernel, tile and division of the contraction axis a bf16 problem gets: the candidate with
+// the lowest predicted time.  The prediction is
+//     launch + rounds x (per tile + per k-tile x k-tiles of a workgroup) [+ merge of the partials]
+// with rounds of workgroups over the 256 CUs, never below the time in which the operands and the
+// output cross HBM.  Its constants are a least-squares fit to 8200 timings of every tile with every
+// division on 344 problems (rows 7 .. 15360, hidden 1024 .. 4096, the four layers of a block):
+// residual 4 % rms; the plan it picks is on average 2 % (worst 27 %) slower than the best
+// candidate of each problem, where one rate per tile and no small tiles cost 30 % (worst 3x).
+constexpr double kLaunchUs = 3.6;      // a launch by itself
+// Write and read of the partials (bytes / us) and the second launch.  A division of every tile leaves
+// at most a few MB, which stay in the caches (fitted); a divided last round of a large problem leaves
+// up to 84 MB of them among hundreds of MB of other traffic.  The line is drawn between two layers
+// with that much, measured inside their blocks: the last round of O at 6400 rows, hidden 4096
+// gains by the division (244 -> 229 us), that of QKV at 15360 rows, hidden 2048 makes its block
+// 0.7 % slower.
+constexpr double kMergeUs = 3.8, kMergeRate = 7.7e6;
+constexpr double kTailMergeUs = 6.0, kTailMergeRate = 5.0e6;
+constexpr double kHbmRate = 6.7e6;     // bytes / us, operands in and output out
+constexpr double kRowsRate = 11.9e6;   // bytes / us that gemm_rows_kernel's workgroups read, L2 hits included
+
+struct TileCfg { int bm, bn; double k_us, tile_us; };   // us per k-tile and per tile with all CUs at work
+constexpr TileCfg kTiles[] = {
+    {320, 256, 1.745, 4.9}, {256, 256, 1.491, 3.4}, {192, 256, 1.304, 2.0}, {256, 192, 1.289, 2.0},
+    {256, 128, 0.896, 1.9}, {128, 256, 0.891, 1.9}, {192, 128, 0.704, 1.3}, {128, 128, 0.537, 0.95},
+    {64, 128, 0.375, 0.3},  {128, 64, 0.364, 0.3},  {64, 64, 0.274, 0.1}};
+constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]), kSmallTile = kNumTiles - 1;
+struct RowsCfg { int ft, tt; double step_us, fixed_us; };   // us per k-step of a wavefront, and once
+constexpr RowsCfg kRows[] = {{1, 1, 0.174, 3.0}, {2, 1, 0.261, 3.3}, {2, 2, 0.281, 3.7}};
+constexpr int kNumRows = sizeof(kRows) / sizeof(kRows[0]);
+constexpr int kRowsWaves = 8, kRowsMax = 256;           // gemm_rows_kernel is not measured beyond 256 rows
+
+GemmPlan gemm_plan(DType dt, int rows, int N, int K)
 {
-    struct Cand { int bm, bn; double rate; };
-    const Cand cands[6] = {{256, 256, 1155.0}, {256, 128, 1045.0}, {128, 256, 1041.0},
-                           {128, 128, 1000.0}, {320, 256, 1300.0}, {192, 256, 1100.0}};
-    GemmPlan best{0, 0, 1, 0};
-    double best_cost = 1e300;
-    for (int i = 0; i < 6; ++i) {
-        const long tiles = (long)((rows + cands[i].bm - 1) / cands[i].bm) *
-                           ((N + cands[i].bn - 1) / cands[i].bn);
-        double rate = cands[i].rate;
-        if (i == 3 && tiles > 256) rate = 650.0;       // small tiles pay per round
-        const double area = (double)cands[i].bm * cands[i].bn;
-        const double t_tile = 2.0 * area * K * 256.0 / (rate * 1e6);     // microseconds on one CU
-        const double cost = (double)((tiles + 255) / 256) * t_tile;
-        if (cost < best_cost) { best_cost = cost; best = GemmPlan{i, tiles, 1, 0}; }
-        const long full = tiles / 256 * 256, rem = tiles - full;
-        if (!allow_tail || i == 3 || full == 0 || rem == 0) continue;
-        for (int s = 2; s <= 8; ++s) {
-            if (rem * s > 256 || K / BK / s < 8) break;
-            const double c2 = (double)(full / 256) * t_tile + t_tile / s + 10.0 +
-                              (double)rem * s * area * 8.0 / 4e6;
-            if (c2 < best_cost) {
-                best_cost = c2;
-                best = GemmPlan{i, tiles, s, (size_t)rem * s * (size_t)area};
-            }
+    GemmPlan best{0, 1, 1, 0};
+    if (dt != DType::BF16) return best;
+    double best_us = 1e300;
+    const int kt = K / BK;
+    const double hbm_us = 2.0 * ((double)rows * K + (double)N * K + (double)rows * N) / kHbmRate;
+    const auto part_us = [](double floats) { return kMergeUs + floats * 8.0 / kMergeRate; };
+    const auto tail_us = [](double floats) { return kTailMergeUs + floats * 8.0 / kTailMergeRate; };
+    for (int i = 0; i < kNumTiles; ++i) {
+        const TileCfg &c = kTiles[i];
+        const long tiles = (long)((rows + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+        const double area = (double)c.bm * c.bn;
+        for (int ns = 1; ns <= 8; ++ns) {
+            // every workgroup at least two k-tiles, none without any; one division beyond a full chip
+            const int per = (kt + ns - 1) / ns;
+            if (ns > 1 && (tiles * ns > 512 || kt / ns < 2 || (ns - 1) * per >= kt)) continue;
+            const double units = (double)tiles * ns / 256.0;
+            // three workgroups of the smallest tile share a CU, so its rounds are not whole
+            const double rounds = i == kSmallTile ? (units > 1.0 ? units : 1.0) : ceil(units);
+            double us = rounds * (c.tile_us + c.k_us * per);
+            us = kLaunchUs + (us > hbm_us ? us : hbm_us);
+            if (ns > 1) us += part_us((double)ns * rows * N);
+            if (us < best_us) { best_us = us; best = {i, ns, 1, ns > 1 ? (size_t)ns * rows * N : 0}; }
+        }
+        // whole rounds undivided, the tiles beyond them divided
+        const long full = tiles / 256, rem = tiles - full * 256;
+        if (full == 0 || rem == 0) continue;
+        for (int t = 2; t <= 8; ++t) {
+            const int per = (kt + t - 1) / t;
+            if (rem * t > 256 || kt / t < 4) break;
+            if ((t - 1) * per >= kt) continue;
+            double us = full * (c.tile_us + c.k_us * kt) + c.tile_us + c.k_us * per;
+            us = kLaunchUs + (us > hbm_us ? us : hbm_us) + tail_us((double)rem * t * area);
+            if (us < best_us) { best_us = us; best = {i, 1, t, (size_t)rem * t * (size_t)area}; }
+        }
+    }
+    if (rows > kRowsMax) return best;
+    for (int i = 0; i < kNumRows; ++i) {
+        const RowsCfg &c = kRows[i];
+        const int bm = 16 * c.tt, bn = 16 * c.ft;
+        const long tiles = (long)((rows + bm - 1) / bm) * (N / bn);
+        for (int ns = 1; ns <= 8; ns *= 2) {
+            if (ns > 1 && (tiles * ns > 1024 || K / 32 < ns * kRowsWaves)) break;
+            const int steps = (K / 32 + ns * kRowsWaves - 1) / (ns * kRowsWaves);
+            const double l2_us = (double)tiles * (bm + bn) * K * 2.0 / kRowsRate, w_us = 2.0 * N * K / kHbmRate;
+            double us = c.fixed_us + c.step_us * steps + (l2_us > w_us ? l2_us : w_us);
+            if (ns > 1) us += part_us((double)ns * rows * N);
+            if (us < best_us) { best_us = us; best = {kNumTiles + i, ns, 1, ns > 1 ? (size_t)ns * rows * N : 0}; }
         }
     }
     return best;
 }
-static int pick_bf16_config(int rows, int N, long *tiles_out)
-{
-    const GemmPlan p = plan_bf16(rows, N, BK * 64, false);
-    *tiles_out = p.tiles;
-    return p.cfg;
-}
 
-// Workgroups per tile along the contraction axis: only when the tiles cover at most half of the
-// CUs, every part at least 4 k-tiles long, at most 8 parts.
-int gemm_splits(DType dt, int rows, int N, int K)
+template <int FT, int TT>
+static void launch_gemm_rows(const void *A, const void *W, int rows, int N, int K, const EpiParams &ep,
+                             hipStream_t st, int nsplit, float *part)
 {
-    if (dt != DType::BF16) return 1;
-    long tiles;
-    (void)pick_bf16_config(rows, N, &tiles);
-    long s = 256 / tiles;
-    const long kmax = K / BK / 4;
-    if (s > kmax) s = kmax;
-    if (s > 8) s = 8;
-    if (s < 2) return 1;
-    const long kt = K / BK, per = (kt + s - 1) / s;
-    return (int)((kt + per - 1) / per);                  // no empty part
-}
-
-// Floats of scratch a bf16 linear layer may need for partial tiles (either way of dividing the
-// contraction axis); 0 when every tile is computed by one workgroup.
-size_t gemm_scratch_floats(DType dt, int rows, int N, int K)
-{
-    if (dt != DType::BF16) return 0;
-    const int ns = gemm_splits(dt, rows, N, K);
-    if (ns > 1) return (size_t)ns * rows * N;
-    return plan_bf16(rows, N, K, true).tail_floats;
+    const int row_tiles = (rows + 16 * TT - 1) / (16 * TT);
+    const int units = row_tiles * nsplit * (N / (16 * FT));
+    launch(gemm_rows_kernel<FT, TT, kRowsWaves>, dim3((units + 7) / 8 * 8), dim3(64 * kRowsWaves), 0, st,
+           (const uint16_t *)A, (const uint16_t *)W, rows, N, K, row_tiles, nsplit, ep, part);
 }
 
 void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
-                 const GemmEpilogue &e, hipStream_t st)
+                 const GemmEpilogue &e, const GemmPlan &plan, float *part, hipStream_t st)
 {
     EpiParams ep;
     ep.bias = e.bias; ep.residual = e.residual; ep.gelu = e.gelu;
@@ -903,20 +998,22 @@ void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
     ep.out_f32 = e.out_f32;
     ep.res_f32 = e.res_f32;
     if (dt == DType::BF16) {
-        // the K/V routing lives in the in-kernel epilogue only, so the routed launch is never divided
-        const bool may_divide = e.splitk_scratch && e.split == N;
-        const int ns = may_divide ? gemm_splits(dt, rows, N, K) : 1;
-        const GemmPlan plan = plan_bf16(rows, N, K, may_divide && ns == 1);
-        const int best = ns > 1 ? plan_bf16(rows, N, K, false).cfg : plan.cfg;
-        const int tail = ns > 1 ? 1 : plan.tail;
-        float *part = (ns > 1 || tail > 1) ? e.splitk_scratch : nullptr;
-        switch (best) {
-        case 0: launch_gemm_bf16_cfg<256, 256, 2, 4, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
-        case 1: launch_gemm_bf16_cfg<256, 128, 4, 2, 3>(A, W, rows, N, K, ep, st, ns, part, tail); break;
-        case 2: launch_gemm_bf16_cfg<128, 256, 2, 4, 3>(A, W, rows, N, K, ep, st, ns, part, tail); break;
-        case 4: launch_gemm_bf16_cfg<320, 256, 2, 4, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
-        case 5: launch_gemm_bf16_cfg<192, 256, 2, 4, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
-        default: launch_gemm_bf16_cfg<128, 128, 2, 2, 3, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        const int ns = plan.nsplit, tail = plan.tail;
+        switch (plan.cfg) {
+        case 0: launch_gemm_bf16_cfg<320, 256, 2, 4, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        case 1: launch_gemm_bf16_cfg<256, 256, 2, 4, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        case 2: launch_gemm_bf16_cfg<192, 256, 2, 4, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        case 3: launch_gemm_bf16_cfg<256, 192, 4, 2, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        case 4: launch_gemm_bf16_cfg<256, 128, 4, 2, 3>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        case 5: launch_gemm_bf16_cfg<128, 256, 2, 4, 3>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        case 6: launch_gemm_bf16_cfg<192, 128, 2, 4, 3>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        case 7: launch_gemm_bf16_cfg<128, 128, 2, 4, 4>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        case 8: launch_gemm_bf16_cfg<64, 128, 2, 4, 4>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        case 9: launch_gemm_bf16_cfg<128, 64, 4, 2, 4>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        case 10: launch_gemm_bf16_cfg<64, 64, 2, 2, 3>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        case kNumTiles + 0: launch_gemm_rows<1, 1>(A, W, rows, N, K, ep, st, ns, part); break;
+        case kNumTiles + 1: launch_gemm_rows<2, 1>(A, W, rows, N, K, ep, st, ns, part); break;
+        default: launch_gemm_rows<2, 2>(A, W, rows, N, K, ep, st, ns, part); break;
         }
         if (ns > 1) {
             const long total = (long)rows * (N / 4);
