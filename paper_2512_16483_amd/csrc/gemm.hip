@@ -907,6 +907,7 @@ constexpr double kLaunchUs = 3.6;      // a launch by itself
 // 0.7 % slower.
 constexpr double kMergeUs = 3.8, kMergeRate = 7.7e6;
 constexpr double kTailMergeUs = 6.0, kTailMergeRate = 5.0e6;
+constexpr double kDivide = 1.03;       // a division has to promise more than the prediction's error
 constexpr double kHbmRate = 6.7e6;     // bytes / us, operands in and output out
 constexpr double kRowsRate = 11.9e6;   // bytes / us that gemm_rows_kernel's workgroups read, L2 hits included
 
@@ -943,7 +944,7 @@ GemmPlan gemm_plan(DType dt, int rows, int N, int K)
             const double rounds = i == kSmallTile ? (units > 1.0 ? units : 1.0) : ceil(units);
             double us = rounds * (c.tile_us + c.k_us * per);
             us = kLaunchUs + (us > hbm_us ? us : hbm_us);
-            if (ns > 1) us += part_us((double)ns * rows * N);
+            if (ns > 1) us = (us + part_us((double)ns * rows * N)) * kDivide;
             if (us < best_us) { best_us = us; best = {i, ns, 1, ns > 1 ? (size_t)ns * rows * N : 0}; }
         }
         // whole rounds undivided, the tiles beyond them divided
@@ -954,7 +955,7 @@ GemmPlan gemm_plan(DType dt, int rows, int N, int K)
             if (rem * t > 256 || kt / t < 4) break;
             if ((t - 1) * per >= kt) continue;
             double us = full * (c.tile_us + c.k_us * kt) + c.tile_us + c.k_us * per;
-            us = kLaunchUs + (us > hbm_us ? us : hbm_us) + tail_us((double)rem * t * area);
+            us = (kLaunchUs + (us > hbm_us ? us : hbm_us) + tail_us((double)rem * t * area)) * kDivide;
             if (us < best_us) { best_us = us; best = {i, 1, t, (size_t)rem * t * (size_t)area}; }
         }
     }
@@ -968,7 +969,7 @@ GemmPlan gemm_plan(DType dt, int rows, int N, int K)
             const int steps = (K / 32 + ns * kRowsWaves - 1) / (ns * kRowsWaves);
             const double l2_us = (double)tiles * (bm + bn) * K * 2.0 / kRowsRate, w_us = 2.0 * N * K / kHbmRate;
             double us = c.fixed_us + c.step_us * steps + (l2_us > w_us ? l2_us : w_us);
-            if (ns > 1) us += part_us((double)ns * rows * N);
+            if (ns > 1) us = (us + part_us((double)ns * rows * N)) * kDivide;
             if (us < best_us) { best_us = us; best = {kNumTiles + i, ns, 1, ns > 1 ? (size_t)ns * rows * N : 0}; }
         }
     }
