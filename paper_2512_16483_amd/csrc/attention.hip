@@ -20,7 +20,7 @@
 //   * LDS is double buffered: the DMA of the next tile runs under the MFMAs of the current one,
 //     one barrier per tile.
 //
-// fp32 kernel: plain tiled FMA version for the fp32 parity configuration.
+// fp32 kernel: see there.
 #include <type_traits>
 
 #include "common.h"
@@ -296,7 +296,11 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t *__res
             for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[tb][j][i]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            // the other 32 lanes hold the other half of the keys: exchanged in registers (a shuffle
+            // is an LDS round trip in the serial part of the tile; without it 1294 -> 1266 us at
+            // 1600 rows x 12121 keys x 32 heads of 128, batch 4, 28.5 -> 27.0 us at head_dim 64)
+            const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+            mx = fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
             const float m_new = fmaxf(m_run[j], mx);
             const float alpha = __builtin_amdgcn_exp2f((m_run[j] - m_new) * c_log2);
             const float mc = m_new * c_log2;
@@ -568,78 +572,130 @@ static void launch_attn_bf16(const void *q, const void *K, const void *V, int B,
 }
 
 // ------------------------------------------------------------------------------ fp32
-template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__ q,
-                                                       const float *__restrict__ Kc,
-                                                       const float *__restrict__ Vc, int n, int L,
-                                                       int cap, int H, float scale,
-                                                       float *__restrict__ o)
+// Flash attention on the fp32 MFMA (16x16x4), for 16 queries per workgroup whose NW wavefronts take
+// NW contiguous shares of the key tiles and meet in LDS at the end.  Bound by the MFMA rate (no
+// faster than the vector units in fp32, but one operand register per MFMA instead of an LDS read per
+// few FMAs) and, at the sizes of the fp32 configuration, by filling the chip: 128 rows x 16 heads
+// are 128 workgroups of 8 wavefronts.  Nothing is staged: S^T = K Q^T takes its operands as float4 of
+// four consecutive head-dim values (the k-slots of four MFMAs), P stays in the registers S^T left
+// it in, and V rows are read as float4 across the head dim, which only permutes the rows of O^T.
+// 128 rows x 552 keys x 16 heads of 64: 109 us (one query row per 8 lanes, K / V through LDS) -> 11.9 us.
+template <int DH, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float *__restrict__ q,
+                                                           const float *__restrict__ Kc,
+                                                           const float *__restrict__ Vc, int n, int L,
+                                                           int cap, int H, float scale, int nqb,
+                                                           float *__restrict__ o)
 {
-    constexpr int TQ = 32, TK = 32, OC = DH / 8;
-    __shared__ float Qs[TQ][DH + 1];
-    __shared__ float Ks[TK][DH + 1];
-    __shared__ float Vs[TK][DH];
-    __shared__ float Ps[TQ][TK + 1];
-    const int tid = threadIdx.x, ty = tid >> 3, tx = tid & 7;     // row ty, 4 key columns at tx*4
-    const int h = blockIdx.y, b = blockIdx.z, q0 = blockIdx.x * TQ;
-    const size_t rowpitch = (size_t)H * DH;
-    for (int e = tid; e < TQ * DH; e += 256) {
-        const int r = e / DH, c = e % DH;
-        Qs[r][c] = q[((size_t)b * n + min(q0 + r, n - 1)) * rowpitch + (size_t)h * DH + c];
-    }
-    float acc[OC];
+    constexpr int KS = DH / 16, VB = DH / 64;                // float4 per key row and lane; 64-wide V blocks
+    __shared__ float4 red[NW][VB * 4][64];
+    __shared__ float red_ml[NW][2][16];
+    const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q16 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int unit = xcd_contiguous(blockIdx.x, gridDim.x);  // query blocks of a head share an L2
+    const int qb = unit % nqb, h = unit / nqb % H, b = unit / (nqb * H);
+    const size_t pitch = (size_t)H * DH;
+    const float *Kb = Kc + ((size_t)b * cap * H + h) * DH, *Vb = Vc + ((size_t)b * cap * H + h) * DH;
+    float4 qf[KS];
+    const int row = min(qb * 16 + c16, n - 1);
 #pragma unroll
-    for (int c = 0; c < OC; ++c) acc[c] = 0.f;
+    for (int s = 0; s < KS; ++s)
+        qf[s] = *reinterpret_cast<const float4 *>(q + ((size_t)b * n + row) * pitch + (size_t)h * DH + 16 * s + 4 * q16);
+    floatx4_t acc[VB * 4];
+#pragma unroll
+    for (int i = 0; i < VB * 4; ++i) acc[i] = floatx4_t{0};
     float m_run = -INFINITY, l_run = 0.f;
-    for (int t0 = 0; t0 < L; t0 += TK) {
-        __syncthreads();
-        for (int e = tid; e < TK * DH; e += 256) {
-            const int r = e / DH, c = e % DH;
-            const size_t off = ((size_t)b * cap + min(t0 + r, L - 1)) * rowpitch + (size_t)h * DH + c;
-            Ks[r][c] = Kc[off];
-            Vs[r][c] = Vc[off];
-        }
-        __syncthreads();
-        float s[4];
+    const int tiles = (L + 15) / 16;
+    const int t0 = (int)((long)tiles * wave / NW), t1 = (int)((long)tiles * (wave + 1) / NW);
+    float4 kf[KS], vf[VB][4];
+    auto load = [&](int t) {
+        const float *kr = Kb + (size_t)min(t * 16 + c16, L - 1) * pitch + 4 * q16;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            float d = 0.f;
-            for (int e = 0; e < DH; ++e) d = fmaf(Qs[ty][e], Ks[tx * 4 + c][e], d);
-            s[c] = (t0 + tx * 4 + c < L) ? d * scale : -INFINITY;
+        for (int s = 0; s < KS; ++s) kf[s] = *reinterpret_cast<const float4 *>(kr + 16 * s);
+    };
+    auto load_v = [&](int t) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float *vr = Vb + (size_t)min(t * 16 + 4 * q16 + e, L - 1) * pitch + 4 * c16;
+#pragma unroll
+            for (int v = 0; v < VB; ++v) vf[v][e] = *reinterpret_cast<const float4 *>(vr + 64 * v);
         }
-        float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-        mx = fmaxf(mx, __shfl_xor(mx, 1));
-        mx = fmaxf(mx, __shfl_xor(mx, 2));
-        mx = fmaxf(mx, __shfl_xor(mx, 4));
+    };
+    if (t0 < t1) { load(t0); load_v(t0); }
+    for (int t = t0; t < t1; ++t) {
+        // S^T: lane (c16, q16) ends up with keys 4 q16 .. +3 of query c16
+        floatx4_t s = {0};
+#pragma unroll
+        for (int i = 0; i < KS; ++i) {
+            s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i].x, qf[i].x, s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i].y, qf[i].y, s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i].z, qf[i].z, s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i].w, qf[i].w, s, 0, 0, 0);
+        }
+        if (t + 1 < t1) load(t + 1);
+        float p[4], mx = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            p[e] = t * 16 + 4 * q16 + e < L ? s[e] * scale : -INFINITY;
+            mx = fmaxf(mx, p[e]);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float m_new = fmaxf(m_run, mx);
-        const float alpha = expf(m_run - m_new);
-        float ps = 0.f;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float p = expf(s[c] - m_new);
-            Ps[ty][tx * 4 + c] = p;
-            ps += p;
-        }
-        ps += __shfl_xor(ps, 1);
-        ps += __shfl_xor(ps, 2);
-        ps += __shfl_xor(ps, 4);
-        l_run = l_run * alpha + ps;
+        const float base = m_new == -INFINITY ? 0.f : m_new;     // nothing finite yet: weights of 0
+        const float alpha = expf(m_run - base);
         m_run = m_new;
-        __syncthreads();
+        float sum = 0.f;
 #pragma unroll
-        for (int c = 0; c < OC; ++c) acc[c] *= alpha;
-        for (int t = 0; t < TK; ++t) {
-            const float p = Ps[ty][t];
+        for (int e = 0; e < 4; ++e) { p[e] = expf(p[e] - base); sum += p[e]; }
+        l_run = l_run * alpha + sum;
+        if (__any(alpha != 1.0f)) {
 #pragma unroll
-            for (int c = 0; c < OC; ++c) acc[c] = fmaf(p, Vs[t][tx * OC + c], acc[c]);
+            for (int i = 0; i < VB * 4; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][e] *= alpha;
         }
-    }
-    const int row = q0 + ty;
-    if (row < n) {
-        float *dst = o + ((size_t)b * n + row) * rowpitch + (size_t)h * DH + tx * OC;
-        const float inv = 1.0f / l_run;
+        // O^T += V^T P^T: MFMA row c16 of block (v, j) is head-dim 64 v + 4 c16 + j
 #pragma unroll
-        for (int c = 0; c < OC; ++c) dst[c] = acc[c] * inv;
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int v = 0; v < VB; ++v) {
+                acc[4 * v + 0] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[v][e].x, p[e], acc[4 * v + 0], 0, 0, 0);
+                acc[4 * v + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[v][e].y, p[e], acc[4 * v + 1], 0, 0, 0);
+                acc[4 * v + 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[v][e].z, p[e], acc[4 * v + 2], 0, 0, 0);
+                acc[4 * v + 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[v][e].w, p[e], acc[4 * v + 3], 0, 0, 0);
+            }
+        if (t + 1 < t1) load_v(t + 1);
+    }
+    l_run += __shfl_xor(l_run, 16);
+    l_run += __shfl_xor(l_run, 32);
+    // entry e of block (v, j): query c16, head-dim 64 v + 4 (4 q16 + e) + j; regrouped so that slot
+    // (v, e) holds the four consecutive values j = 0..3
+#pragma unroll
+    for (int v = 0; v < VB; ++v)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            red[wave][4 * v + e][lane] = make_float4(acc[4 * v][e], acc[4 * v + 1][e], acc[4 * v + 2][e], acc[4 * v + 3][e]);
+    if (q16 == 0) { red_ml[wave][0][c16] = m_run; red_ml[wave][1][c16] = l_run; }
+    __syncthreads();
+    if (qb * 16 + c16 >= n) return;
+    float m = red_ml[0][0][c16];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = fmaxf(m, red_ml[w][0][c16]);
+    float wgt[NW], den = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { wgt[w] = expf(red_ml[w][0][c16] - m); den += red_ml[w][1][c16] * wgt[w]; }
+    const float inv = 1.0f / den;
+    for (int i = wave; i < VB * 4; i += NW) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float4 x = red[w][i][lane];
+            v.x = fmaf(x.x, wgt[w], v.x); v.y = fmaf(x.y, wgt[w], v.y);
+            v.z = fmaf(x.z, wgt[w], v.z); v.w = fmaf(x.w, wgt[w], v.w);
+        }
+        float *dst = o + ((size_t)b * n + row) * pitch + (size_t)h * DH + 64 * (i / 4) + 4 * (4 * q16 + i % 4);
+        *reinterpret_cast<float4 *>(dst) = make_float4(v.x * inv, v.y * inv, v.z * inv, v.w * inv);
     }
 }
 
@@ -660,13 +716,14 @@ void launch_attention(DType dt, const void *q, const void *K, const void *V, int
             launch_attn_bf16<128, 1>(q, K, V, B, n, L, cap, H, scale, o, part, st);
         }
     } else {
-        dim3 grid((n + 31) / 32, H, B), block(256);
+        const int nqb = (n + 15) / 16;
+        const dim3 grid((unsigned)nqb * H * B), block(512);
         if (Dh == 64)
-            launch(attn_f32_kernel<64>, grid, block, 0, st, (const float *)q,
-                               (const float *)K, (const float *)V, n, L, cap, H, scale, (float *)o);
+            launch(attn_f32_kernel<64, 8>, grid, block, 0, st, (const float *)q, (const float *)K,
+                   (const float *)V, n, L, cap, H, scale, nqb, (float *)o);
         else
-            launch(attn_f32_kernel<128>, grid, block, 0, st, (const float *)q,
-                               (const float *)K, (const float *)V, n, L, cap, H, scale, (float *)o);
+            launch(attn_f32_kernel<128, 8>, grid, block, 0, st, (const float *)q, (const float *)K,
+                   (const float *)V, n, L, cap, H, scale, nqb, (float *)o);
     }
 }
 
