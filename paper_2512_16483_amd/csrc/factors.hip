@@ -4,99 +4,15 @@
 //     W_c = argmin_W || W G_c - C ||_F = (C G_c^T) (G_c G_c^T)^{-1},     G_c = Q^T C  as stored.
 //
 // Four kernels per call (the projection G_c itself is the kernel of rp.hip):
-//   t_kernel      T = C G_c^T            [M,r]  fp32; bf16 inputs on MFMA, the second pass over C
+//   T = C G_c^T   [M,r]  fp32; bf16 inputs on the tiled MFMA kernel of the linear layers, the second pass over C
 //   gram_kernel   S = G_c G_c^T          [r,r]  fp64 (bf16: MFMA per 64-element chunk, fp64 across)
-//   spd_inverse   S^{-1}                 Gauss-Jordan in registers, one workgroup per sample, fp64
-//   w_kernel      W_c = T S^{-1}         [M,r]  fp64 accumulation, rounded to the storage type
+//   spd_inverse   S^{-1}                 block sweep in registers, one workgroup per sample, fp64 MFMA
+//   w_kernel      W_c = T S^{-1}         [M,r]  fp64 MFMA, rounded to the storage type
 #include "common.h"
 
 namespace fvar {
 
-// ------------------------------------------------------------------ T = C G^T, bf16 on MFMA
-// Workgroup = 64 rows of C and one slice of the contraction axis: the 64-element chunks
-// c = part*4 + wave, + 4*parts, ... go to its four wavefronts (each reads a 128-byte segment of
-// every row per chunk, the next chunk's loads in flight under the current chunk's MFMAs); the
-// four partial 64 x r tiles are added through LDS and written to Tpart[part].  The slices are
-// summed by the kernel that consumes T.  RT = r / 32 rounded up.
-template <int RT>
-__global__ __launch_bounds__(256) void t_bf16_kernel(const uint16_t *__restrict__ cache,
-                                                     const uint16_t *__restrict__ g_c, int B, int M,
-                                                     int r, int d, float *__restrict__ Tpart)
-{
-    extern __shared__ float part_lds[];             // [4][64][32*RT]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int rl = lane & 31, g = lane >> 5;
-    const int row0 = blockIdx.x * 64, part = blockIdx.y, parts = gridDim.y, b = blockIdx.z;
-    const uint16_t *crow[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-        crow[i] = cache + ((size_t)b * M + min(row0 + 32 * i + rl, M - 1)) * d + 8 * g;
-    const uint16_t *G = g_c + (size_t)b * r * d;
-    const uint16_t *grow[RT];
-#pragma unroll
-    for (int j = 0; j < RT; ++j) grow[j] = G + (size_t)min(j * 32 + rl, r - 1) * d + 8 * g;
-
-    floatx16_t acc[2][RT];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < RT; ++j) acc[i][j] = floatx16_t{0};
-    const int nchunks = d / 64, stride = 4 * parts;
-    uint4 a[2][4], bv[RT][4];
-    auto load = [&](int c, uint4 (&av)[2][4], uint4 (&bw)[RT][4]) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int t = c * 64 + 16 * s;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) av[i][s] = *reinterpret_cast<const uint4 *>(crow[i] + t);
-#pragma unroll
-            for (int j = 0; j < RT; ++j) bw[j][s] = *reinterpret_cast<const uint4 *>(grow[j] + t);
-        }
-    };
-    int c = part * 4 + wave;
-    if (c < nchunks) load(c, a, bv);
-    for (; c < nchunks; c += stride) {
-        uint4 an[2][4], bn[RT][4];
-        const bool more = c + stride < nchunks;
-        if (more) load(c + stride, an, bn);
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < RT; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(bf16x8_t, a[i][s]), __builtin_bit_cast(bf16x8_t, bv[j][s]),
-                        acc[i][j], 0, 0, 0);
-        if (more) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-#pragma unroll
-                for (int i = 0; i < 2; ++i) a[i][s] = an[i][s];
-#pragma unroll
-                for (int j = 0; j < RT; ++j) bv[j][s] = bn[j][s];
-            }
-        }
-    }
-    constexpr int W = 32 * RT;
-    float *mine = part_lds + (size_t)wave * 64 * W;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < RT; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                mine[(32 * i + 8 * (e >> 2) + 4 * g + (e & 3)) * W + j * 32 + rl] = acc[i][j][e];
-    __syncthreads();
-    float *T = Tpart + (size_t)part * B * M * r;
-    for (int idx = tid; idx < 64 * W; idx += 256) {
-        const int lr = idx / W, col = idx % W;
-        const float v = (part_lds[idx] + part_lds[64 * W + idx]) +
-                        (part_lds[2 * 64 * W + idx] + part_lds[3 * 64 * W + idx]);
-        if (row0 + lr < M && col < r) T[((size_t)b * M + row0 + lr) * r + col] = v;
-    }
-}
-
+// ------------------------------------------------------------------ T = C G^T
 // fp32 storage: one row of C per workgroup, fp64 accumulation
 __global__ __launch_bounds__(256) void t_f32_kernel(const float *__restrict__ cache,
                                                     const float *__restrict__ g_c, int M, int r, int d,
@@ -190,201 +106,238 @@ __global__ __launch_bounds__(256) void gram_bf16_kernel(const uint16_t *__restri
 }
 
 // ------------------------------------------------------------------ S^{-1}
-// One workgroup per sample inverts the symmetric positive definite Gram matrix (the sum of the
-// `parts` partial matrices, plus ridge * trace / r on the diagonal) by in-place Gauss-Jordan
-// elimination without pivoting, in fp64.  The matrix is padded to RP x RP with an identity block
-// and lives in REGISTERS for the whole elimination: thread t owns the NC = RP*RP/256 consecutive
-// columns [cb*NC, cb*NC+NC) of row i = t / TPR, cb = t % TPR.
-//
-// Step j with pivot p = 1/a_jj turns   a_ik -> a_ik - a_ij p a_jk   (i != j, k != j),
-// a_ij -> -a_ij p,  a_jk -> a_jk p,  a_jj -> p.  It needs the pivot row, the pivot column and p
-// from other threads; their owners publish them in LDS at the end of step j-1 (two buffers in
-// turn, one barrier per step).  The published row carries a_jj + 1 at column j: then the general
-// update f - f p (a_jj + 1) = -f p also covers the pivot column, and only the threads of the
-// pivot row take a separate branch.  Steps are numbered j = jo*NC + ji with ji unrolled, so that
-// the column a thread has to publish is a compile-time register index.
-// A singular matrix yields non-finite output.
-template <int RP>
-__global__ __launch_bounds__(256) void spd_inverse_kernel(const double *__restrict__ S, int parts,
-                                                          int r, double ridge,
-                                                          double *__restrict__ Sinv)
+typedef double doublex4_t __attribute__((ext_vector_type(4)));
+
+// value of lane P of each 16-lane row, in every lane of the row
+template <int P> __device__ __forceinline__ double row_bcast(double v)
 {
-    constexpr int TPR = 256 / RP;                  // threads per row
-    constexpr int NC = RP / TPR;                   // columns per thread
-    __shared__ __attribute__((aligned(16))) double rowbuf[2][RP];
-    __shared__ double colbuf[2][RP], pinv[2], red[4];
-    const int tid = threadIdx.x, b = blockIdx.x;
-    const int i = tid / TPR, cb = tid % TPR, k0 = cb * NC;
-    const double *Sb = S + (size_t)b * parts * r * r;
-    double a[NC];
+    const int2 w = __builtin_bit_cast(int2, v);
+    int2 o;
+    o.x = __builtin_amdgcn_update_dpp(0, w.x, 0x150 + P, 0xf, 0xf, false);
+    o.y = __builtin_amdgcn_update_dpp(0, w.y, 0x150 + P, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, o);
+}
+
+// In-place Gauss-Jordan step P of a 16x16 matrix held by one wavefront in the fp64 MFMA's output layout:
+// entry e of lane (c, g) = (lane % 16, lane / 16) is row 4e + g, column c.
+template <int P> __device__ __forceinline__ void gauss_jordan_step(doublex4_t &a, int c, int g)
+{
+    const double row = __shfl(a[P >> 2], 16 * (P & 3) + c);          // pivot row at this lane's column
+    const double piv = row_bcast<P>(row);
+    double inv = __builtin_amdgcn_rcp(piv);                          // ~1e-8, two Newton steps to full precision
+    inv = fma(inv, fma(-piv, inv, 1.0), inv);
+    inv = fma(inv, fma(-piv, inv, 1.0), inv);
+    const double prow = c == P ? inv : row * inv;
 #pragma unroll
-    for (int q = 0; q < NC; ++q) {
-        const int k = k0 + q;
-        double v = (i == k) ? 1.0 : 0.0;           // identity padding
-        if (i < r && k < r) {
-            v = 0.0;
-            for (int p = 0; p < parts; ++p) v += Sb[((size_t)p * r + i) * r + k];
-        }
-        a[q] = v;
-    }
-    if (ridge != 0.0) {
-        double tr = 0.0;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) tr += (k0 + q == i && i < r) ? a[q] : 0.0;
-        tr = wave_sum(tr);
-        if ((tid & 63) == 0) red[tid >> 6] = tr;
-        __syncthreads();
-        const double add = ridge * ((red[0] + red[1]) + (red[2] + red[3])) / (double)r;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) a[q] += (k0 + q == i && i < r) ? add : 0.0;
-    }
-    // row and column jo*NC + JI of the current matrix, and the reciprocal pivot, into buffer `buf`
-#define FVAR_GJ_PUBLISH(jo_, JI, buf_)                                                            \
-    do {                                                                                           \
-        const bool own_col = cb == (jo_);                                                          \
-        if (own_col) colbuf[buf_][i] = a[JI];                                                      \
-        if (i == (jo_) * NC + (JI)) {                                                              \
-            _Pragma("unroll") for (int q = 0; q < NC; ++q)                                         \
-                rowbuf[buf_][k0 + q] = a[q] + ((own_col && q == (JI)) ? 1.0 : 0.0);                \
-            if (own_col) pinv[buf_] = 1.0 / a[JI];                                                 \
-        }                                                                                          \
-    } while (0)
-    FVAR_GJ_PUBLISH(0, 0, 0);
-    __syncthreads();
-    for (int jo = 0; jo * NC < r; ++jo) {
-#pragma unroll
-        for (int ji = 0; ji < NC; ++ji) {
-            const int j = jo * NC + ji;            // uniform
-            if (j < r) {
-                const int buf = ji & 1;            // NC is even, so the parity of j is that of ji
-                const double p = pinv[buf];
-                const double fp = colbuf[buf][i] * p;
-                if (i == j) {
-#pragma unroll
-                    for (int q = 0; q < NC; ++q) a[q] = (cb == jo && q == ji) ? p : a[q] * p;
-                } else {
-#pragma unroll
-                    for (int q = 0; q < NC; ++q) a[q] = fma(-fp, rowbuf[buf][k0 + q], a[q]);
-                }
-                if (j + 1 < r) FVAR_GJ_PUBLISH(jo + (ji + 1 == NC ? 1 : 0), (ji + 1) % NC, buf ^ 1);
-                __syncthreads();
-            }
-        }
-    }
-#undef FVAR_GJ_PUBLISH
-    if (i < r) {
-        double *out = Sinv + ((size_t)b * r + i) * r;
-#pragma unroll
-        for (int q = 0; q < NC; ++q)
-            if (k0 + q < r) out[k0 + q] = a[q];
+    for (int e = 0; e < 4; ++e) {
+        const double col = row_bcast<P>(a[e]);                       // pivot column at this entry's row
+        const double v = fma(-col, prow, c == P ? 0.0 : a[e]);
+        a[e] = (e == (P >> 2) && g == (P & 3)) ? prow : v;
     }
 }
 
+// One workgroup per sample inverts the symmetric positive definite Gram matrix (the sum of the
+// `parts` partial matrices, plus ridge * trace / r on the diagonal) in fp64, without pivoting: the
+// symmetric sweep, in blocks of 16.  Sweeping block j with P = A_jj, U = A_:j (so A_j: = U^T) and
+// V = U P^-1 turns
+//     A_ik -> A_ik - V_i U_k^T,   A_ij -> V_i,   A_jk -> V_k^T,   A_jj -> -P^-1     (i, k != j);
+// after every block has been swept the matrix is -S^-1.  The matrix is padded to 16*NB with an
+// identity block and stays in registers as 16x16 tiles in the fp64 MFMA's output layout, NB/2 tiles
+// of one tile row per wavefront; only U (one tile column) and P^-1 go through LDS, two barriers per
+// block.  That layout makes V^T = P^-1 U^T come out as the A operand of the update.
+// Bound by the serial chain: sixteen pivot steps of one wavefront per block, then 20 MFMAs per
+// wavefront of 64 clk each.  Rank 128, 4 samples: 71 us; one thread per half row, a barrier per
+// pivot and 64 unrolled steps of code that do not fit the instruction cache took 767.
+// A singular matrix yields non-finite output.
+template <int NB>
+__global__ __launch_bounds__(128 * NB) void spd_inverse_kernel(const double *__restrict__ S, int parts,
+                                                               int r, double ridge,
+                                                               double *__restrict__ Sinv)
+{
+    constexpr int TPW = NB / 2, NW = 2 * NB;
+    __shared__ double U[2][16 * NB][17];
+    __shared__ double Pi[16][17], red[NW];
+    const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, g = lane >> 4, b = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ti = wave >> 1, tk0 = (wave & 1) * TPW;                // tile row, first tile column
+    const double *Sb = S + (size_t)b * parts * r * r;
+    doublex4_t a[TPW];
+    double tr = 0.0;
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = 16 * ti + 4 * e + g, col = 16 * (tk0 + t) + c;
+            double v = row == col ? 1.0 : 0.0;                       // identity padding
+            if (row < r && col < r) {
+                v = 0.0;
+                for (int p = 0; p < parts; ++p) v += Sb[((size_t)p * r + row) * r + col];
+                if (row == col) tr += v;
+            }
+            a[t][e] = v;
+        }
+    if (ridge != 0.0) {
+        tr = wave_sum(tr);
+        if (lane == 0) red[wave] = tr;
+        __syncthreads();
+        double sum = 0.0;
+        for (int w = 0; w < NW; ++w) sum += red[w];
+        const double add = ridge * sum / (double)r;
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int row = 16 * ti + 4 * e + g;
+                if (row == 16 * (tk0 + t) + c && row < r) a[t][e] += add;
+            }
+    }
+    for (int j = 0; 16 * j < r; ++j) {
+        double (*Uj)[17] = U[j & 1];
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+            if (tk0 + t == j) {                                      // uniform
+#pragma unroll
+                for (int e = 0; e < 4; ++e) Uj[16 * ti + 4 * e + g][c] = a[t][e];
+            }
+        __syncthreads();
+        if (wave == 0) {
+            doublex4_t p;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] = Uj[16 * j + 4 * e + g][c];
+            gauss_jordan_step<0>(p, c, g); gauss_jordan_step<1>(p, c, g); gauss_jordan_step<2>(p, c, g);
+            gauss_jordan_step<3>(p, c, g); gauss_jordan_step<4>(p, c, g); gauss_jordan_step<5>(p, c, g);
+            gauss_jordan_step<6>(p, c, g); gauss_jordan_step<7>(p, c, g); gauss_jordan_step<8>(p, c, g);
+            gauss_jordan_step<9>(p, c, g); gauss_jordan_step<10>(p, c, g); gauss_jordan_step<11>(p, c, g);
+            gauss_jordan_step<12>(p, c, g); gauss_jordan_step<13>(p, c, g); gauss_jordan_step<14>(p, c, g);
+            gauss_jordan_step<15>(p, c, g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) Pi[4 * e + g][c] = p[e];
+        }
+        __syncthreads();
+        double pv[4], ui[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) { pv[s] = Pi[c][4 * s + g]; ui[s] = Uj[16 * ti + c][4 * s + g]; }
+        doublex4_t vt = {0.0, 0.0, 0.0, 0.0};                        // vt[e] = V_i[c][4e + g]
+#pragma unroll
+        for (int s = 0; s < 4; ++s) vt = __builtin_amdgcn_mfma_f64_16x16x4f64(pv[s], ui[s], vt, 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+            const int tk = tk0 + t;
+            double uk[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) uk[s] = Uj[16 * tk + c][4 * s + g];
+            if (ti == j && tk == j) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[t][e] = -Pi[4 * e + g][c];
+            } else if (ti == j || tk == j) {
+                a[t] = doublex4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    a[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(ti == j ? pv[s] : ui[s], ti == j ? uk[s] : pv[s],
+                                                                a[t], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    a[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-vt[s], uk[s], a[t], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = 16 * ti + 4 * e + g, col = 16 * (tk0 + t) + c;
+            if (row < r && col < r) Sinv[((size_t)b * r + row) * r + col] = -a[t][e];
+        }
+}
+
 // ------------------------------------------------------------------ W = T S^{-1}
-// Workgroup = 64 * RPL rows of T; S^{-1} is staged in LDS (fp64).  Wavefront w produces the w-th
-// quarter of the r columns, a lane owns RPL rows (64 apart): every lane of a wavefront reads the
-// same S^{-1} entries (LDS broadcast, one read serves RPL FMAs) and walks its own rows of T (the
-// sum of their one or two slices).  CQ = columns per wavefront (r / 4 rounded up).
-template <typename TT, int CQ, int RPL>
+// On the fp64 MFMA (16x16x4).  Workgroup = 64 rows of T, 16 per wavefront; S^{-1} is staged in LDS, zero
+// padded to 16*CT in both directions, its pitch such that the rows of the four k-slots fall on
+// different banks.  A lane takes 4 consecutive entries of its row of T (the sum of its one or two
+// slices) as the k-slots of four MFMAs.  Bound by the MFMA rate: 4*CT*CT MFMAs of 64 clk per
+// wavefront.  Rank 128, 4 x 4096 rows: 76 us with fp64 FMAs fed by LDS broadcasts -> 17 us.
+template <typename TT, int CT>
 __global__ __launch_bounds__(256) void w_kernel(const float *__restrict__ T, int t_parts,
                                                 size_t t_part_stride,
                                                 const double *__restrict__ Sinv, int M, int r,
                                                 TT *__restrict__ w_c)
 {
-    extern __shared__ double Si[];                 // [r][4*CQ], zero padded columns
-    constexpr int PW = 4 * CQ;
+    extern __shared__ double Si[];
+    constexpr int RP = 16 * CT, PITCH = RP + 4;
     const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = lane & 15, g = lane >> 4;
     const double *Sg = Sinv + (size_t)b * r * r;
-    for (int idx = tid; idx < r * PW; idx += 256) {
-        const int t = idx / PW, c = idx % PW;
-        Si[idx] = c < r ? Sg[(size_t)t * r + c] : 0.0;
+    const int row0 = blockIdx.x * 64 + 16 * wave;
+    const float *trow = T + ((size_t)b * M + min(row0 + c, M - 1)) * r + 4 * g;   // r is a multiple of 4
+    float4 tv[CT];                                 // this lane's share of its row, in flight under the staging
+#pragma unroll
+    for (int i = 0; i < CT; ++i) {
+        tv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (16 * i + 4 * g < r) {
+            tv[i] = *reinterpret_cast<const float4 *>(trow + 16 * i);
+            for (int p = 1; p < t_parts; ++p) {    // the other shares of the contraction axis
+                const float4 tp = *reinterpret_cast<const float4 *>(trow + p * t_part_stride + 16 * i);
+                tv[i].x += tp.x; tv[i].y += tp.y; tv[i].z += tp.z; tv[i].w += tp.w;
+            }
+        }
+    }
+    // S^{-1} to LDS, CT pairs per thread in flight (r is even)
+    const double2 *Sg2 = reinterpret_cast<const double2 *>(Sg);
+#pragma unroll 1
+    for (int base = tid; base < RP * RP / 2; base += 256 * CT) {
+        double2 v[CT];
+#pragma unroll
+        for (int u = 0; u < CT; ++u) {
+            const int i = (base + 256 * u) / (RP / 2), j = (base + 256 * u) % (RP / 2);
+            v[u] = i < r && 2 * j < r ? Sg2[((size_t)i * r >> 1) + j] : make_double2(0.0, 0.0);
+        }
+#pragma unroll
+        for (int u = 0; u < CT; ++u) {
+            const int i = (base + 256 * u) / (RP / 2), j = (base + 256 * u) % (RP / 2);
+            *reinterpret_cast<double2 *>(Si + i * PITCH + 2 * j) = v[u];
+        }
     }
     __syncthreads();
-    const int row0 = blockIdx.x * (64 * RPL) + lane;
-    const float *trow[RPL];
+    doublex4_t acc[CT];
 #pragma unroll
-    for (int p = 0; p < RPL; ++p) trow[p] = T + ((size_t)b * M + min(row0 + 64 * p, M - 1)) * r;
-    double acc[RPL][CQ];
+    for (int t = 0; t < CT; ++t) acc[t] = doublex4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int p = 0; p < RPL; ++p)
-#pragma unroll
-        for (int q = 0; q < CQ; ++q) acc[p][q] = 0.0;
-    const double *sw = Si + wave * CQ;
-    for (int t0 = 0; t0 < r; t0 += 4) {            // r is a multiple of 4
-        float4 tv[RPL];
-#pragma unroll
-        for (int p = 0; p < RPL; ++p) {
-            tv[p] = *reinterpret_cast<const float4 *>(trow[p] + t0);
-            if (t_parts > 1) {                     // second slice of the contraction axis
-                const float4 tp = *reinterpret_cast<const float4 *>(trow[p] + t_part_stride + t0);
-                tv[p].x += tp.x; tv[p].y += tp.y; tv[p].z += tp.z; tv[p].w += tp.w;
-            }
-        }
+    for (int i = 0; i < CT; ++i)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            double td[RPL];
+            const double td = (double)(u == 0 ? tv[i].x : u == 1 ? tv[i].y : u == 2 ? tv[i].z : tv[i].w);
+            const double *sr = Si + (16 * i + 4 * g + u) * PITCH + c;
 #pragma unroll
-            for (int p = 0; p < RPL; ++p)
-                td[p] = (double)(u == 0 ? tv[p].x : u == 1 ? tv[p].y : u == 2 ? tv[p].z : tv[p].w);
-#pragma unroll
-            for (int q = 0; q < CQ; ++q) {
-                const double sv = sw[(t0 + u) * PW + q];
-#pragma unroll
-                for (int p = 0; p < RPL; ++p) acc[p][q] = fma(td[p], sv, acc[p][q]);
-            }
+            for (int t = 0; t < CT; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(td, sr[16 * t], acc[t], 0, 0, 0);
         }
-    }
 #pragma unroll
-    for (int p = 0; p < RPL; ++p) {
-        const int row = row0 + 64 * p;
+    for (int e = 0; e < 4; ++e) {
+        const int row = row0 + 4 * e + g;
         if (row >= M) continue;
         TT *out = w_c + ((size_t)b * M + row) * r;
 #pragma unroll
-        for (int q = 0; q < CQ; ++q) {
-            const int c = wave * CQ + q;
-            if (c < r) Elem<TT>::store(out + c, (float)acc[p][q]);
-        }
+        for (int t = 0; t < CT; ++t)
+            if (16 * t + c < r) Elem<TT>::store(out + 16 * t + c, (float)acc[t][e]);
     }
 }
 
-// Slices of the contraction axis in the bf16 T kernel: enough workgroups to fill the chip when
-// the batch is small, none extra when it is large.
-int factor_t_parts(DType dt, int B, int M)
+// shares of the contraction axis that T comes in; the kernel that consumes T sums them
+int factor_t_parts(DType dt, int B, int M, int r, int d)
 {
-    if (dt != DType::BF16) return 1;
-    const long wgs = (long)B * ((M + 63) / 64);
-    int parts = (int)((512 + wgs - 1) / wgs);
-    return parts < 1 ? 1 : (parts > 2 ? 2 : parts);
+    return dt == DType::BF16 ? batched_f32_parts(B, M, r, d) : 1;
 }
 
 void launch_factor_t(DType dt, const void *cache, const void *g_c, int B, int M, int r, int d, float *T,
                      hipStream_t st)
 {
-    if (dt == DType::BF16) {
-        // many samples at once (the caches of all blocks of a scale): T = C G^T is an ordinary
-        // linear layer per sample, run on the tiled MFMA kernel with fp32 output
-        if (factor_t_parts(dt, B, M) == 1 && launch_gemm_bf16_batched_f32(cache, g_c, B, M, r, d, T, st))
-            return;
-        dim3 grid((M + 63) / 64, factor_t_parts(dt, B, M), B);
-        const int rt = (r + 31) / 32;
-        const size_t lds = (size_t)4 * 64 * 32 * rt * sizeof(float);
-#define FVAR_T(RT)                                                                                  \
-    do {                                                                                            \
-        if (lds > 48 * 1024)                                                                        \
-            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(t_bf16_kernel<RT>),            \
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);        \
-        launch(t_bf16_kernel<RT>, grid, dim3(256), lds, st, (const uint16_t *)cache,                \
-               (const uint16_t *)g_c, B, M, r, d, T);                                               \
-    } while (0)
-        if (rt == 1) FVAR_T(1);
-        else if (rt == 2) FVAR_T(2);
-        else if (rt == 3) FVAR_T(3);
-        else FVAR_T(4);
-#undef FVAR_T
-    } else {
+    // bf16: an ordinary linear layer per sample, in fp32
+    if (dt == DType::BF16)
+        launch_gemm_bf16_batched_f32(cache, g_c, B, M, r, d, T, st);
+    else
         launch(t_f32_kernel, dim3(M, B), dim3(256), 0, st, (const float *)cache, (const float *)g_c, M, r,
                d, T);
-    }
 }
 
 void launch_factor_gram(DType dt, const void *g_c, int B, int r, int d, double *S, hipStream_t st)
@@ -405,11 +358,11 @@ void launch_factor_inverse(const double *S, int parts, int B, int r, double ridg
                            hipStream_t st)
 {
     if (r <= 32)
-        launch(spd_inverse_kernel<32>, dim3(B), dim3(256), 0, st, S, parts, r, ridge, Sinv);
+        launch(spd_inverse_kernel<2>, dim3(B), dim3(256), 0, st, S, parts, r, ridge, Sinv);
     else if (r <= 64)
-        launch(spd_inverse_kernel<64>, dim3(B), dim3(256), 0, st, S, parts, r, ridge, Sinv);
+        launch(spd_inverse_kernel<4>, dim3(B), dim3(512), 0, st, S, parts, r, ridge, Sinv);
     else
-        launch(spd_inverse_kernel<128>, dim3(B), dim3(256), 0, st, S, parts, r, ridge, Sinv);
+        launch(spd_inverse_kernel<8>, dim3(B), dim3(1024), 0, st, S, parts, r, ridge, Sinv);
 }
 
 template <typename TT>
@@ -417,32 +370,27 @@ static void launch_w_t(const float *T, int t_parts, const double *Sinv, int B, i
                        hipStream_t st)
 {
     const size_t t_stride = (size_t)B * M * r;
-    // two rows per lane once that still leaves a workgroup for every CU
-    const bool two = (long)B * ((M + 127) / 128) >= 256;
-    dim3 grid(two ? (M + 127) / 128 : (M + 63) / 64, B);
-    const int cq = (r + 3) / 4;
-#define FVAR_W(CQ)                                                                                 \
+    const dim3 grid((M + 63) / 64, B);
+#define FVAR_W(CT)                                                                                 \
     do {                                                                                           \
-        const size_t lds = (size_t)r * 4 * CQ * sizeof(double);                                    \
-        auto k1 = w_kernel<TT, CQ, 1>;                                                             \
-        auto k2 = w_kernel<TT, CQ, 2>;                                                             \
-        auto kern = two ? k2 : k1;                                                                 \
+        const size_t lds = (size_t)16 * CT * (16 * CT + 4) * sizeof(double);                       \
+        auto kern = w_kernel<TT, CT>;                                                              \
         if (lds > 48 * 1024)                                                                       \
             (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),                        \
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);       \
         launch(kern, grid, dim3(256), lds, st, T, t_parts, t_stride, Sinv, M, r, (TT *)w_c);       \
     } while (0)
-    if (cq <= 8) FVAR_W(8);
-    else if (cq <= 16) FVAR_W(16);
-    else if (cq <= 24) FVAR_W(24);
-    else FVAR_W(32);
+    if (r <= 32) FVAR_W(2);
+    else if (r <= 64) FVAR_W(4);
+    else if (r <= 96) FVAR_W(6);
+    else FVAR_W(8);
 #undef FVAR_W
 }
 
-void launch_factor_w(DType dt, const float *T, const double *Sinv, int B, int M, int r, void *w_c,
+void launch_factor_w(DType dt, const float *T, const double *Sinv, int B, int M, int r, int d, void *w_c,
                      hipStream_t st)
 {
-    const int tp = factor_t_parts(dt, B, M);
+    const int tp = factor_t_parts(dt, B, M, r, d);
     if (dt == DType::BF16) launch_w_t<uint16_t>(T, tp, Sinv, B, M, r, w_c, st);
     else launch_w_t<float>(T, tp, Sinv, B, M, r, w_c, st);
 }

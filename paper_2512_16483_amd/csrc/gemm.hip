@@ -87,6 +87,15 @@ __device__ __forceinline__ void finish_quad(const EpiParams &ep, int row, int co
 // ------------------------------------------------------------------------------ bf16 MFMA
 constexpr int BK = 64;
 
+// Write and read of the partials (bytes / us) and the second launch.  A division of every tile leaves
+// at most a few MB, which stay in the caches (fitted); a divided last round of a large problem leaves
+// up to 84 MB of them among hundreds of MB of other traffic.  The line is drawn between two layers
+// with that much, measured inside their blocks: the last round of O at 6400 rows, hidden 4096
+// gains by the division (244 -> 229 us), that of QKV at 15360 rows, hidden 2048 makes its block
+// 0.7 % slower.
+constexpr double kMergeUs = 3.8, kMergeRate = 7.7e6;
+constexpr double kTailMergeUs = 6.0, kTailMergeRate = 5.0e6;
+
 __device__ __forceinline__ int lds_off(int row, int chunk)      // in bf16 elements
 {
     return row * BK + ((chunk ^ ((row >> 1) & 7)) << 3);
@@ -266,7 +275,7 @@ constexpr size_t gemm_epi_lds_bytes(int BM, int BN, int WM, int WN)
 // the B fragments come from the transposing LDS load.  This mode runs `nbatch` independent
 // problems of one shape in one launch (operands and output `*_bstride` elements apart), whole
 // tiles only (no division of the contraction), K a multiple of 64 and N a multiple of 8.
-// nbatch > 1 is also available with the ordinary operand layout (whole tiles only).
+// nbatch > 1 is also available with the ordinary operand layout (no divided tail).
 template <int BM, int BN, int WM, int WN, int STAGES, bool BKM = false>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     const uint16_t *__restrict__ A_in, const uint16_t *__restrict__ W_in, int rows, int N, int K,
@@ -318,8 +327,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
         ranges = nsplit;
     }
     const int tile_id = pid;
+    int bidx = 0;
     if (BKM || nbatch > 1) {
-        const int per = tiles_m * tiles_n, bidx = pid / per;
+        const int per = tiles_m * tiles_n;
+        bidx = pid / per;
         pid -= bidx * per;
         A += (size_t)bidx * a_bstride;
         W += (size_t)bidx * w_bstride;
@@ -347,8 +358,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     for (int i = 0; i < NGA; ++i) {
         const int r = (wave + NW * i) * 8 + (lane >> 3);
         const int c = (lane & 7) ^ ((r >> 1) & 7);
-        a_off[i] = (uint32_t)(((size_t)min(row0 + r, rows - 1) * K + c * 8) * sizeof(uint16_t));
+        a_off[i] = (uint32_t)(((size_t)(min(row0 + r, rows - 1) - row0) * K + c * 8) * sizeof(uint16_t));
     }
+    A += (size_t)row0 * K;
 #pragma unroll
     for (int i = 0; i < NGB; ++i) {
         if (BKM) {
@@ -512,10 +524,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     // the stage buffers are free for the epilogue's staging
     if (ranges > 1) {
         // partial tile, fp32: 16 neighbouring lanes cover 64 contiguous bytes of a row.
-        // Divided problem: [range][rows][N]; divided tail: [tail tile][range][BM][BN].
+        // Divided problem: [range][batch][rows][N]; divided tail: [tail tile][range][BM][BN].
         const bool tail = tail_split > 1;
         float *dst = tail ? part + ((size_t)(tile_id - full_tiles) * tail_split + split) * (BM * BN)
-                          : part + (size_t)split * rows * N;
+                          : part + ((size_t)split * nbatch + bidx) * rows * N;
         const size_t pitch = tail ? BN : N;
         const int rbase = tail ? 0 : row0, cbase = tail ? 0 : col0;
 #pragma unroll
@@ -646,19 +658,18 @@ static void launch_kmajor_cfg(const void *A, size_t a_bstride, const void *X, in
            (size_t)K * N, (size_t)rows * N);
 }
 
-// out[b] = A[b] W[b]^T in fp32 for nbatch problems of one shape (A[b]: [rows][K], W[b]: [N][K], both
-// bf16 and `rows*K` / `N*K` elements apart; out[b]: [rows][N]) on the tiled MFMA kernel, when the
-// shape suits it: K a multiple of the 64-wide k-tile, N <= 256 and enough tiles to fill three
-// quarters of the chip.  Returns false (nothing launched) otherwise.
+// out[p][b] = share p of the contraction of A[b] W[b]^T, in fp32, for nbatch problems of one shape (A[b]:
+// [rows][K], W[b]: [N][K], both bf16 and `rows*K` / `N*K` elements apart; out[p][b]: [rows][N]), on the
+// tiled MFMA kernel.  K a multiple of 64, N <= 128.  The number of shares is batched_f32_parts().
 template <int BM, int BN, int WM, int WN, int STAGES>
 static void launch_batched_f32_cfg(const void *A, const void *W, int nbatch, int rows, int N, int K,
-                                   float *out, hipStream_t st)
+                                   int parts, float *out, hipStream_t st)
 {
     EpiParams ep{};
     ep.out0 = out; ep.ld0 = N; ep.split = N; ep.N = N; ep.rows_per_sample = 1; ep.out_f32 = 1;
     const int tiles_m = (rows + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int ntiles = tiles_m * tiles_n * nbatch;
-    const int grid = (ntiles + 7) / 8 * 8;
+    const int grid = (ntiles * parts + 7) / 8 * 8;
     const size_t lds_stages = (size_t)STAGES * (BM + BN) * BK * sizeof(uint16_t);
     const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN);
     const size_t lds = lds_stages > lds_epi ? lds_stages : lds_epi;
@@ -668,51 +679,76 @@ static void launch_batched_f32_cfg(const void *A, const void *W, int nbatch, int
     int group_m = (int)lround(sqrt((double)tiles_m * tiles_n * BN / (8.0 * BM)));
     group_m = group_m < 1 ? 1 : (group_m > tiles_m ? tiles_m : group_m);
     launch(kern, dim3(grid), dim3(64 * WM * WN), lds, st, (const uint16_t *)A, (const uint16_t *)W, rows,
-           N, K, tiles_m, tiles_n, group_m, ep, 1, (float *)nullptr, ntiles, 1, nbatch,
+           N, K, tiles_m, tiles_n, group_m, ep, parts, out, ntiles, 1, nbatch,
            (size_t)rows * K, (size_t)N * K, (size_t)rows * N);
 }
 
-bool launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int rows, int N, int K,
+// Tile height (256, 128 or 64 rows; one tile spans all N <= 128 columns) and shares of the contraction,
+// by the same prediction as gemm_plan; the consumer sums the shares, so they cost it a read each.
+struct BatchedPlan { int bm, parts; };
+static BatchedPlan batched_f32_plan(int nbatch, int rows, int N, int K)
+{
+    const bool narrow = N <= 64;
+    const struct { int bm; double k_us, tile_us; } cands[3] = {
+        {256, 0.896, 1.9}, {128, narrow ? 0.364 : 0.537, narrow ? 0.3 : 0.95}, {64, narrow ? 0.274 : 0.375, 0.3}};
+    const int kt = K / BK;
+    BatchedPlan best{256, 1};
+    double best_us = 1e300;
+    for (const auto &c : cands)
+        for (int parts = 1; parts <= 4; ++parts) {
+            const int per = (kt + parts - 1) / parts;
+            if (parts > 1 && (kt / parts < 4 || (parts - 1) * per >= kt)) continue;
+            const long tiles = (long)((rows + c.bm - 1) / c.bm) * nbatch;
+            const double us = (double)((tiles * parts + 255) / 256) * (c.tile_us + c.k_us * per) +
+                              (parts - 1) * (1.0 + 8.0 * nbatch * rows * N / kMergeRate);
+            if (us < best_us) { best_us = us; best = {c.bm, parts}; }
+        }
+    return best;
+}
+int batched_f32_parts(int nbatch, int rows, int N, int K) { return batched_f32_plan(nbatch, rows, N, K).parts; }
+
+void launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int rows, int N, int K,
                                   float *out, hipStream_t st)
 {
-    if (K < BK || K % BK != 0 || N < 1 || N > 256 || rows < 1 || nbatch < 1) return false;
-    if ((size_t)rows * K * sizeof(uint16_t) >= ((size_t)1 << 32)) return false;   // 32-bit operand offsets
-    const bool narrow = N <= 128;
-    const long tiles = (long)((rows + 255) / 256) * nbatch;
-    if (tiles < 192) return false;
-    if (narrow) launch_batched_f32_cfg<256, 128, 4, 2, 3>(A, W, nbatch, rows, N, K, out, st);
-    else launch_batched_f32_cfg<256, 256, 2, 4, 2>(A, W, nbatch, rows, N, K, out, st);
-    return true;
+    const BatchedPlan p = batched_f32_plan(nbatch, rows, N, K);
+    const bool narrow = N <= 64;
+    if (p.bm == 256) launch_batched_f32_cfg<256, 128, 4, 2, 3>(A, W, nbatch, rows, N, K, p.parts, out, st);
+    else if (p.bm == 128 && narrow) launch_batched_f32_cfg<128, 64, 4, 2, 4>(A, W, nbatch, rows, N, K, p.parts, out, st);
+    else if (p.bm == 128) launch_batched_f32_cfg<128, 128, 2, 4, 4>(A, W, nbatch, rows, N, K, p.parts, out, st);
+    else if (narrow) launch_batched_f32_cfg<64, 64, 2, 2, 3>(A, W, nbatch, rows, N, K, p.parts, out, st);
+    else launch_batched_f32_cfg<64, 128, 2, 4, 4>(A, W, nbatch, rows, N, K, p.parts, out, st);
 }
 
 // Runs out[b] = qt[b] x[b] (qt: [rows][M] per sample or shared, x[b]: [M][d]) on the tiled MFMA
-// kernel when the shape suits it: M a multiple of the 64-wide k-tile, d a multiple of 8, and
-// enough tiles to fill three quarters of the chip.  Returns false (nothing launched) otherwise.
+// kernel when M is a multiple of the 64-wide k-tile (d is a multiple of 64).  Returns false (nothing
+// launched) otherwise.  Tile by predicted time, constants as in gemm_plan plus a tenth for the
+// transposing reads (no 320x256 tile: with them it would not fit the 256 registers).  Even a few tiles
+// here beat many of rp_project_bf16_kernel, whose 64-token chunk takes 1.7 us against 0.4 us of a
+// 64x128 k-tile: 692 x 2304 x 2048 61 -> 17 us, 4 x (128 x 4096 x 4096) 123 -> 39 us.
 bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int B, int M, int rows,
                              int d, void *out, hipStream_t st)
 {
     if (M < BK || M % BK != 0 || d % 8 != 0 || d < 8 || rows < 1 || B < 1) return false;
     if ((size_t)rows * M * sizeof(uint16_t) >= ((size_t)1 << 32)) return false;   // 32-bit operand offsets
-    struct Cand { int bm, bn; double rate; };
-    // (no 320x256 tile here: with the transposing reads it would not fit the 256 registers)
-    const Cand cands[4] = {{256, 256, 1155.0}, {128, 256, 1041.0}, {192, 256, 1100.0},
-                           {256, 128, 1045.0}};
-    int best = -1;
-    double best_cost = 1e300;
-    for (int i = 0; i < 4; ++i) {
-        const long tiles = (long)((rows + cands[i].bm - 1) / cands[i].bm) *
-                           ((d + cands[i].bn - 1) / cands[i].bn) * B;
-        if (tiles < 192) continue;
-        const double t_tile = 2.0 * cands[i].bm * cands[i].bn * (double)M * 256.0 / (cands[i].rate * 1e6);
-        const double cost = (double)((tiles + 255) / 256) * t_tile;
-        if (cost < best_cost) { best_cost = cost; best = i; }
+    const struct { int bm, bn; double k_us, tile_us; } cands[] = {
+        {256, 256, 1.64, 3.4}, {192, 256, 1.43, 2.0}, {256, 128, 0.98, 1.9}, {128, 256, 0.98, 1.9},
+        {192, 128, 0.77, 1.3}, {128, 128, 0.59, 0.95}, {64, 128, 0.41, 0.3}};
+    int best = 0;
+    double best_us = 1e300;
+    for (int i = 0; i < 7; ++i) {
+        const auto &c = cands[i];
+        const long tiles = (long)((rows + c.bm - 1) / c.bm) * ((d + c.bn - 1) / c.bn) * B;
+        const double us = (double)((tiles + 255) / 256) * (c.tile_us + c.k_us * (M / BK));
+        if (us < best_us) { best_us = us; best = i; }
     }
     switch (best) {
     case 0: launch_kmajor_cfg<256, 256, 2, 4, 2>(qt, q_stride, x, B, rows, d, M, out, st); break;
-    case 1: launch_kmajor_cfg<128, 256, 2, 4, 3>(qt, q_stride, x, B, rows, d, M, out, st); break;
-    case 2: launch_kmajor_cfg<192, 256, 2, 4, 2>(qt, q_stride, x, B, rows, d, M, out, st); break;
-    case 3: launch_kmajor_cfg<256, 128, 4, 2, 3>(qt, q_stride, x, B, rows, d, M, out, st); break;
-    default: return false;
+    case 1: launch_kmajor_cfg<192, 256, 2, 4, 2>(qt, q_stride, x, B, rows, d, M, out, st); break;
+    case 2: launch_kmajor_cfg<256, 128, 4, 2, 3>(qt, q_stride, x, B, rows, d, M, out, st); break;
+    case 3: launch_kmajor_cfg<128, 256, 2, 4, 3>(qt, q_stride, x, B, rows, d, M, out, st); break;
+    case 4: launch_kmajor_cfg<192, 128, 2, 4, 3>(qt, q_stride, x, B, rows, d, M, out, st); break;
+    case 5: launch_kmajor_cfg<128, 128, 2, 4, 4>(qt, q_stride, x, B, rows, d, M, out, st); break;
+    default: launch_kmajor_cfg<64, 128, 2, 4, 4>(qt, q_stride, x, B, rows, d, M, out, st); break;
     }
     return true;
 }
@@ -966,14 +1002,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const float *__restri
 // residual 4 % rms; the plan it picks is on average 2 % (worst 27 %) slower than the best
 // candidate of each problem, where one rate per tile and no small tiles cost 30 % (worst 3x).
 constexpr double kLaunchUs = 3.6;      // a launch by itself
-// Write and read of the partials (bytes / us) and the second launch.  A division of every tile leaves
-// at most a few MB, which stay in the caches (fitted); a divided last round of a large problem leaves
-// up to 84 MB of them among hundreds of MB of other traffic.  The line is drawn between two layers
-// with that much, measured inside their blocks: the last round of O at 6400 rows, hidden 4096
-// gains by the division (244 -> 229 us), that of QKV at 15360 rows, hidden 2048 makes its block
-// 0.7 % slower.
-constexpr double kMergeUs = 3.8, kMergeRate = 7.7e6;
-constexpr double kTailMergeUs = 6.0, kTailMergeRate = 5.0e6;
 constexpr double kDivide = 1.03;       // a division has to promise more than the prediction's error
 constexpr double kHbmRate = 6.7e6;     // bytes / us, operands in and output out
 constexpr double kRowsRate = 11.9e6;   // bytes / us that gemm_rows_kernel's workgroups read, L2 hits included

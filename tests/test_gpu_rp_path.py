@@ -181,6 +181,31 @@ def test_cache_factors_parity(dtype, B, M, d, r, rank, noise, per_sample):
             assert res_g <= (2e-2 if bf else 1e-5) * np.linalg.norm(C64)
 
 
+@pytest.mark.parametrize("B,M,d,r,ridge", [
+    (1, 520, 512, 16, 0.0),       # one 16-wide pivot block, three empty tiles
+    (2, 264, 256, 56, 1e-10),     # partly padded last block of four
+    (1, 328, 1024, 72, 1e-10),    # five of eight blocks, contraction of T in shares
+    (1, 4096, 4096, 128, 0.0),    # every block, 64 k-tiles
+    (3, 1000, 320, 104, 1e-10),   # ragged rows and token chunks
+])
+def test_cache_factors_block_edges(B, M, d, r, ridge):
+    """Edges of the 16-wide pivot blocks of the inverse and of the shares T comes in, against the
+    oracle's fp64 solution for the G that the GPU stored."""
+    Cm = wl.round_to_bf16(wl.cached_feature(B, M, d, r + 40, seed=290 + M, noise=0.1))
+    Q = _q(B, M, r, 291 + M, "bf16", False)
+    ctx = _ctx(d, "bf16")
+    w_c = torch.full((B, M, r), float("nan"), dtype=torch.bfloat16, device="cuda")
+    g_c = torch.full((B, r, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((fv.fvar_factors_workspace_bytes(ctx, B, M, r),), 0xff, dtype=torch.uint8, device="cuda")
+    fv.fvar_cache_factors(ctx, to_dev(Cm, "bf16"), _qt_dev(Q, "bf16"), False, B, M, r, ridge, w_c, g_c, ws)
+    torch.cuda.synchronize()
+    Wg, Gg = to_np(w_c).astype(np.float64), to_np(g_c).astype(np.float64)
+    for b in range(B):
+        Wo = factors.restoration_matrix(Gg[b], Cm[b], ridge)     # against the G the GPU stored
+        assert rel_err(Wg[b], Wo) <= TOL["bf16"], (b, rel_err(Wg[b], Wo))
+        assert rel_err(Gg[b], factors.project(Q[0], Cm[b])) <= TOL["bf16"]
+
+
 def test_cache_factors_feed_the_fill():
     # factors built on the GPU, used by the rank-r fill, against the oracle's fill of its factors
     dtype, B, M, d, r, k = "bf16", 2, 144, 256, 32, 58
