@@ -180,9 +180,10 @@ void launch_rp_project(DType dt, const void *qt, size_t q_stride, const void *x,
 void launch_upsample(DType dt, const void *src, int B, int hs, int ws, int hd, int wd, int c,
                      void *dst, hipStream_t st);
 
-// restoration matrix W_c = (C G_c^T)(G_c G_c^T)^{-1} in four steps; T:[factor_t_parts,B,M,r] fp32,
+// restoration matrix W_c = (C G_c^T)(G_c G_c^T)^{-1} in four steps; T:[factor_t_room (factor_t_parts of them used),B,M,r] fp32,
 // S:[B,gram_parts(dt),r,r] and Sinv:[B,r,r] fp64 are scratch.  r <= 128.
 int factor_t_parts(DType dt, int B, int M, int r, int d);
+int factor_t_room(DType dt, int B, int M, int r, int d);
 void launch_factor_t(DType dt, const void *cache, const void *g_c, int B, int M, int r, int d, float *T,
                      hipStream_t st);
 void launch_factor_gram(DType dt, const void *g_c, int B, int r, int d, double *S, hipStream_t st);

@@ -1002,7 +1002,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const float *__restri
 // residual 4 % rms; the plan it picks is on average 2 % (worst 27 %) slower than the best
 // candidate of each problem, where one rate per tile and no small tiles cost 30 % (worst 3x).
 constexpr double kLaunchUs = 3.6;      // a launch by itself
-constexpr double kDivide = 1.03;       // a division has to promise more than the prediction's error
+constexpr double kDivide = 1.008;      // a division that promises less is not worth its scratch
 constexpr double kHbmRate = 6.7e6;     // bytes / us, operands in and output out
 constexpr double kRowsRate = 11.9e6;   // bytes / us that gemm_rows_kernel's workgroups read, L2 hits included
 
