@@ -113,41 +113,72 @@ template <int P> __device__ __forceinline__ double row_bcast(double v)
 {
     const int2 w = __builtin_bit_cast(int2, v);
     int2 o;
-    o.x = __builtin_amdgcn_update_dpp(0, w.x, 0x150 + P, 0xf, 0xf, false);
-    o.y = __builtin_amdgcn_update_dpp(0, w.y, 0x150 + P, 0xf, 0xf, false);
+    o.x = __builtin_amdgcn_mov_dpp(w.x, 0x150 + P, 0xf, 0xf, true);
+    o.y = __builtin_amdgcn_mov_dpp(w.y, 0x150 + P, 0xf, 0xf, true);
     return __builtin_bit_cast(double, o);
 }
 
-// In-place Gauss-Jordan step P of a 16x16 matrix held by one wavefront in the fp64 MFMA's output layout:
-// entry e of lane (c, g) = (lane % 16, lane / 16) is row 4e + g, column c.
-template <int P> __device__ __forceinline__ void gauss_jordan_step(doublex4_t &a, int c, int g)
+// value of the lane of 16-lane row R with the same lane % 16, in every lane: two exchanges in
+// registers (a shuffle is an LDS round trip in the serial chain of the elimination)
+template <int R> __device__ __forceinline__ double col_bcast(double v)
 {
-    const double row = __shfl(a[P >> 2], 16 * (P & 3) + c);          // pivot row at this lane's column
+    const uint2 w = __builtin_bit_cast(uint2, v);
+    const auto bcast = [](unsigned x) {
+        const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);    // {rows 0 1 0 1}, {rows 2 3 2 3}
+        const unsigned y = h[R >> 1];
+        const auto q = __builtin_amdgcn_permlane16_swap(y, y, false, false);    // {even row}, {odd row}
+        return q[R & 1];
+    };
+    return __builtin_bit_cast(double, make_uint2(bcast(w.x), bcast(w.y)));
+}
+
+// Sweep step P of the symmetric 16x16 pivot block `a` and the same row operations on 16 further columns
+// `b` of its rows, both held by one wavefront in the fp64 MFMA's output layout: entry e of lane
+// (c, g) = (lane % 16, lane / 16) is row 4e + g, column c.  With d the pivot and u its row of a,
+//     a_ik -> a_ik - u_i u_k / d,   a_iP, a_Pi -> u_i / d,   a_PP -> -1 / d,
+//     b_i -> b_i - u_i b_P / d,     b_P -> b_P / d.
+// The two triangles of a stay equal to the bit (the product u_i u_k is rounded first): where they drift
+// apart, T S^-1 loses four digits at condition 4e6.  b_P as it was goes to y[P] of this lane's column,
+// divided by d to ys[P] (from the four lanes that hold it alike).
+template <int P>
+__device__ __forceinline__ void sweep_step(doublex4_t &a, doublex4_t &b, double *y, double *ys, int c, int g)
+{
+    const double row = col_bcast<(P & 3)>(a[P >> 2]);                // u at this lane's column
+    const double brow = col_bcast<(P & 3)>(b[P >> 2]);
     const double piv = row_bcast<P>(row);
     double inv = __builtin_amdgcn_rcp(piv);                          // ~1e-8, two Newton steps to full precision
     inv = fma(inv, fma(-piv, inv, 1.0), inv);
     inv = fma(inv, fma(-piv, inv, 1.0), inv);
-    const double prow = c == P ? inv : row * inv;
+    const double x = c == P ? -1.0 : row, xs = x * inv, bs = brow * inv;
+    y[P] = brow;
+    ys[P] = bs;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const double col = row_bcast<P>(a[e]);                       // pivot column at this entry's row
-        const double v = fma(-col, prow, c == P ? 0.0 : a[e]);
-        a[e] = (e == (P >> 2) && g == (P & 3)) ? prow : v;
+        const double col = row_bcast<P>(a[e]);                       // u at this entry's row
+        const double v = fma(-(col * x), inv, c == P ? 0.0 : a[e]), w = fma(-col, bs, b[e]);
+        const bool pivot = e == (P >> 2) && g == (P & 3);
+        a[e] = pivot ? xs : v;
+        b[e] = pivot ? bs : w;
+        // computed here: put off to the branch that stores them, they keep col and bs of all steps in registers
+        asm volatile("" : "+v"(b[e]));
     }
 }
 
 // One workgroup per sample inverts the symmetric positive definite Gram matrix (the sum of the
-// `parts` partial matrices, plus ridge * trace / r on the diagonal) in fp64, without pivoting: the
-// symmetric sweep, in blocks of 16.  Sweeping block j with P = A_jj, U = A_:j (so A_j: = U^T) and
-// V = U P^-1 turns
-//     A_ik -> A_ik - V_i U_k^T,   A_ij -> V_i,   A_jk -> V_k^T,   A_jj -> -P^-1     (i, k != j);
-// after every block has been swept the matrix is -S^-1.  The matrix is padded to 16*NB with an
-// identity block and stays in registers as 16x16 tiles in the fp64 MFMA's output layout, NB/2 tiles
-// of one tile row per wavefront; only U (one tile column) and P^-1 go through LDS, two barriers per
-// block.  That layout makes V^T = P^-1 U^T come out as the A operand of the update.
-// Bound by the serial chain: sixteen pivot steps of one wavefront per block, then 20 MFMAs per
-// wavefront of 64 clk each.  Rank 128, 4 samples: 71 us; one thread per half row, a barrier per
-// pivot and 64 unrolled steps of code that do not fit the instruction cache took 767.
+// `parts` partial matrices, plus ridge * trace / r on the diagonal) in fp64, without pivoting, by the
+// symmetric sweep (see sweep_step), which leaves -S^-1 after all pivots.  They are taken 16 at a time
+// (block j): sixteen steps are applied one by one to the pivot block and to its tile row
+// A_jk = U_k^T, and the rank-16 update of all the other tiles, A_ik -= sum_p (u_ip / d_p) u_kp, is made
+// from the u and d that the steps met.  Those are the scalar sweep's own operations in another order.
+// U P^-1 U^T from an explicit inverse of the pivot block is not the same: it loses the square of the
+// condition number where the sweep loses it once (condition 4e6: the inverse off by 4e-6 instead of
+// 5e-11, T S^-1 of a rank-8 cache with ridge 1e-6 wrong altogether).
+// The matrix is padded to 16*NB with an identity block and stays in registers as 16x16 tiles in the fp64
+// MFMA's output layout, NB/2 tiles of one tile row per wavefront.  The first NB wavefronts apply the
+// steps, each to its own tile of the row and all to a copy of the pivot block; only the tile
+// column, u and u / d go through LDS, three barriers per block.
+// Bound by the serial chain of pivot steps.  Rank 128, 4 samples: 90 us; one thread per half row, a barrier
+// per pivot and 64 unrolled steps of code that do not fit the instruction cache took 767.
 // A singular matrix yields non-finite output.
 template <int NB>
 __global__ __launch_bounds__(128 * NB) void spd_inverse_kernel(const double *__restrict__ S, int parts,
@@ -155,7 +186,8 @@ __global__ __launch_bounds__(128 * NB) void spd_inverse_kernel(const double *__r
                                                                double *__restrict__ Sinv)
 {
     constexpr int TPW = NB / 2, NW = 2 * NB;
-    __shared__ double U[2][16 * NB][17];
+    // U: the tile column (then, tile by tile, the swept one); Y, Ys: u and u / d
+    __shared__ double U[16 * NB][17], Y[16 * NB][17], Ys[16 * NB][17];
     __shared__ double Pi[16][17], red[NW];
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, g = lane >> 4, b = blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -192,55 +224,59 @@ __global__ __launch_bounds__(128 * NB) void spd_inverse_kernel(const double *__r
             }
     }
     for (int j = 0; 16 * j < r; ++j) {
-        double (*Uj)[17] = U[j & 1];
 #pragma unroll
         for (int t = 0; t < TPW; ++t)
             if (tk0 + t == j) {                                      // uniform
 #pragma unroll
-                for (int e = 0; e < 4; ++e) Uj[16 * ti + 4 * e + g][c] = a[t][e];
+                for (int e = 0; e < 4; ++e) U[16 * ti + 4 * e + g][c] = a[t][e];
             }
         __syncthreads();
-        if (wave == 0) {
-            doublex4_t p;
+        if (wave < NB) {
+            doublex4_t p, u;                                         // u: the transposed tile, A_jw
+            double *y = Y[16 * wave + c], *ys = Ys[16 * wave + c];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) p[e] = Uj[16 * j + 4 * e + g][c];
-            gauss_jordan_step<0>(p, c, g); gauss_jordan_step<1>(p, c, g); gauss_jordan_step<2>(p, c, g);
-            gauss_jordan_step<3>(p, c, g); gauss_jordan_step<4>(p, c, g); gauss_jordan_step<5>(p, c, g);
-            gauss_jordan_step<6>(p, c, g); gauss_jordan_step<7>(p, c, g); gauss_jordan_step<8>(p, c, g);
-            gauss_jordan_step<9>(p, c, g); gauss_jordan_step<10>(p, c, g); gauss_jordan_step<11>(p, c, g);
-            gauss_jordan_step<12>(p, c, g); gauss_jordan_step<13>(p, c, g); gauss_jordan_step<14>(p, c, g);
-            gauss_jordan_step<15>(p, c, g);
+            for (int e = 0; e < 4; ++e) {
+                // the lower triangle for both
+                p[e] = U[16 * j + max(4 * e + g, c)][min(4 * e + g, c)];
+                u[e] = U[16 * wave + c][4 * e + g];
+            }
+#define FVAR_SWEEP(P) sweep_step<P>(p, u, y, ys, c, g)
+            FVAR_SWEEP(0); FVAR_SWEEP(1); FVAR_SWEEP(2); FVAR_SWEEP(3);
+            FVAR_SWEEP(4); FVAR_SWEEP(5); FVAR_SWEEP(6); FVAR_SWEEP(7);
+            FVAR_SWEEP(8); FVAR_SWEEP(9); FVAR_SWEEP(10); FVAR_SWEEP(11);
+            FVAR_SWEEP(12); FVAR_SWEEP(13); FVAR_SWEEP(14); FVAR_SWEEP(15);
+#undef FVAR_SWEEP
+            if (wave == j) {                                         // rows 16j .. of U stay as the others read them
 #pragma unroll
-            for (int e = 0; e < 4; ++e) Pi[4 * e + g][c] = p[e];
+                for (int e = 0; e < 4; ++e) Pi[4 * e + g][c] = p[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) U[16 * wave + c][4 * e + g] = u[e];
+            }
         }
         __syncthreads();
-        double pv[4], ui[4];
+        double ui[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) { pv[s] = Pi[c][4 * s + g]; ui[s] = Uj[16 * ti + c][4 * s + g]; }
-        doublex4_t vt = {0.0, 0.0, 0.0, 0.0};                        // vt[e] = V_i[c][4e + g]
-#pragma unroll
-        for (int s = 0; s < 4; ++s) vt = __builtin_amdgcn_mfma_f64_16x16x4f64(pv[s], ui[s], vt, 0, 0, 0);
+        for (int s = 0; s < 4; ++s) ui[s] = ti == j ? 0.0 : -Ys[16 * ti + c][4 * s + g];
 #pragma unroll
         for (int t = 0; t < TPW; ++t) {
             const int tk = tk0 + t;
-            double uk[4];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) uk[s] = Uj[16 * tk + c][4 * s + g];
             if (ti == j && tk == j) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) a[t][e] = -Pi[4 * e + g][c];
-            } else if (ti == j || tk == j) {
-                a[t] = doublex4_t{0.0, 0.0, 0.0, 0.0};
+                for (int e = 0; e < 4; ++e) a[t][e] = Pi[4 * e + g][c];
+            } else if (ti == j) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s)
-                    a[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(ti == j ? pv[s] : ui[s], ti == j ? uk[s] : pv[s],
-                                                                a[t], 0, 0, 0);
+                for (int e = 0; e < 4; ++e) a[t][e] = U[16 * tk + c][4 * e + g];
+            } else if (tk == j) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[t][e] = U[16 * ti + 4 * e + g][c];
             } else {
 #pragma unroll
                 for (int s = 0; s < 4; ++s)
-                    a[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-vt[s], uk[s], a[t], 0, 0, 0);
+                    a[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(ui[s], Y[16 * tk + c][4 * s + g], a[t], 0, 0, 0);
             }
         }
+        __syncthreads();                                             // U is rewritten by the next block
     }
 #pragma unroll
     for (int t = 0; t < TPW; ++t)

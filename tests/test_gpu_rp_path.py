@@ -206,6 +206,47 @@ def test_cache_factors_block_edges(B, M, d, r, ridge):
         assert rel_err(Gg[b], factors.project(Q[0], Cm[b])) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("r", [8, 16, 24, 32, 56, 64, 72, 104, 128])
+@pytest.mark.parametrize("kind", ["rank8+ridge", "positive", "diagonal"])
+def test_gram_inverse_keeps_ill_conditioned_digits(r, kind):
+    """The inverse kernel by itself on badly conditioned matrices, in two partial sums.  Elimination in
+    fp64 without pivoting is backward stable here, X = (S + E)^-1 with |E| <= r eps |S|, which bounds the
+    inverse, |X - S^-1| <= r eps cond |S^-1|, and, far below |T| |X - S^-1|, the product T X with a T whose
+    rows lie in the range of the large eigenvalues, as those of C G^T do: |T X - T S^-1| <= r eps cond
+    |T S^-1|.  A block step by an explicit inverse breaks the first, an elimination whose triangles drift
+    apart the second.  'diagonal' has a scaled identity: exact up to the division."""
+    import ctypes as C
+    rng = np.random.default_rng(r)
+    B, ridge = 2, 0.0
+    if kind == "rank8+ridge":
+        G, ridge = rng.standard_normal((B, r, min(r, 8))) @ rng.standard_normal((B, min(r, 8), 1024)), 1e-6
+    elif kind == "positive":
+        G = np.abs(rng.standard_normal((B, r, 400))) @ np.abs(rng.standard_normal((B, 400, 2048)))
+    S = np.stack([np.diag(10.0 ** rng.uniform(-6, 6, r)) for _ in range(B)]) if kind == "diagonal" else G @ G.transpose(0, 2, 1)
+    parts = np.stack([0.25 * S, 0.75 * S], axis=1)
+    Sd = torch.from_numpy(np.ascontiguousarray(parts)).cuda()
+    X = torch.full((B, r, r), float("nan"), dtype=torch.float64, device="cuda")
+    launch = fv.load_library()["_ZN4fvar21launch_factor_inverseEPKdiiidPdP12ihipStream_t"]
+    launch.restype, launch.argtypes = None, [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_double, C.c_void_p, C.c_void_p]
+    torch.cuda.synchronize()
+    launch(Sd.data_ptr(), 2, B, r, ridge, X.data_ptr(), None)
+    torch.cuda.synchronize()
+    for b in range(B):
+        A = parts[b].sum(0)
+        A = A + np.eye(r) * (ridge * np.trace(A) / r)
+        ref, cond = np.linalg.inv(A), np.linalg.cond(A)
+        got = X[b].cpu().numpy()
+        err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+        bound = 1e-15 if kind == "diagonal" else r * 2.0 ** -52 * cond
+        assert err <= bound, (b, f"cond {cond:.1e}: {err:.1e} > {bound:.1e}")
+        if kind != "diagonal":
+            # T = Z S has T A^-1 = Z - Z (A - S) A^-1, without cancellation
+            Z, S0 = rng.standard_normal((40, r)), parts[b].sum(0)
+            W = Z - Z @ (A - S0) @ ref
+            werr = np.linalg.norm(Z @ S0 @ got - W) / np.linalg.norm(W)
+            assert werr <= bound, (b, f"cond {cond:.1e}: T X off by {werr:.1e} > {bound:.1e}")
+
+
 def test_cache_factors_feed_the_fill():
     # factors built on the GPU, used by the rank-r fill, against the oracle's fill of its factors
     dtype, B, M, d, r, k = "bf16", 2, 144, 256, 32, 58
