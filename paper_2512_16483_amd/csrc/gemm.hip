@@ -116,9 +116,10 @@ __device__ __forceinline__ int bkm_swz(int row)
 // and GELU, packs to bf16 (adjacent lanes swap one value per row pair so that a lane owns two
 // neighbouring columns)
 // and parks its sub-tile row-major in a private LDS region; it then reads the sub-tile back as
-// 16-byte row chunks, adds the residual (16-byte loads) and stores 16 bytes per lane, so a store
-// instruction covers whole 128-byte row segments.  The destination row pointers (plain output,
-// or the K / V cache rows of the sample the row belongs to) are computed once per chunk.
+// 16-byte row chunks and stores 16 bytes per lane, so a store instruction covers whole 128-byte row
+// segments (with a residual, or fp32 output, the sub-tile is parked in fp32).  The destination row
+// pointers (plain output, or the K / V cache rows of the sample the row belongs to) are computed once
+// per chunk.
 template <int FM, int FN, bool F32_STAGED>
 __device__ __forceinline__ void store_tile_epilogue(const floatx4_t (*acc)[FN][2][2], const EpiParams &ep,
                                                     int rows, int N, int wrow0, int wcol0, int lane,
@@ -128,10 +129,10 @@ __device__ __forceinline__ void store_tile_epilogue(const floatx4_t (*acc)[FN][2
     const int c16 = lane & 15, q16 = lane >> 4;
     const uint16_t *bias = reinterpret_cast<const uint16_t *>(ep.bias);
     if constexpr (F32_STAGED) {
-        // fp32 output (never routed, never GELU-ed; the residual operand is bf16): same two-phase
-        // scheme with an fp32 staging tile, 16-byte (4 float) row chunks out
-        const uint16_t *res = reinterpret_cast<const uint16_t *>(ep.residual);
-        float *out = reinterpret_cast<float *>(ep.out0);
+        // fp32 output or a residual (never routed, never GELU-ed): same two-phase scheme with an fp32
+        // staging tile, 4 columns per lane out, so that product and residual meet in fp32 and are rounded
+        // once, as in finish_quad.  (The kinds are told apart per chunk: with a copy of this code for
+        // each, the 320x256 tile spills, -8 %.)
         constexpr int P32 = TN + 4;
         float *w32 = reinterpret_cast<float *>(wlds);
 #pragma unroll
@@ -153,11 +154,22 @@ __device__ __forceinline__ void store_tile_epilogue(const floatx4_t (*acc)[FN][2
             const int lc = (it * 64 + lane) % CPR * 4, col = wcol0 + lc;
             float4 v = *reinterpret_cast<const float4 *>(w32 + lrow * P32 + lc);
             if (row >= rows || col >= N) continue;
-            if (res) {
-                const uint2 rv = *reinterpret_cast<const uint2 *>(res + (size_t)row * N + col);
-                v.x += bf16_lo(rv.x); v.y += bf16_hi(rv.x); v.z += bf16_lo(rv.y); v.w += bf16_hi(rv.y);
+            if (ep.residual) {
+                const size_t off = (size_t)row * N + col;
+                if (ep.res_f32) {
+                    const float4 r = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(ep.residual) + off);
+                    v.x += r.x; v.y += r.y; v.z += r.z; v.w += r.w;
+                } else {
+                    const uint2 r = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(ep.residual) + off);
+                    v.x += bf16_lo(r.x); v.y += bf16_hi(r.x); v.z += bf16_lo(r.y); v.w += bf16_hi(r.y);
+                }
             }
-            *reinterpret_cast<float4 *>(out + (size_t)row * ep.ld0 + col) = v;
+            const size_t off = (size_t)row * ep.ld0 + col;
+            if (ep.out_f32)
+                *reinterpret_cast<float4 *>(reinterpret_cast<float *>(ep.out0) + off) = v;
+            else
+                *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(ep.out0) + off) =
+                    make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
         }
         asm volatile("" ::: "memory");
         return;
@@ -188,7 +200,6 @@ __device__ __forceinline__ void store_tile_epilogue(const floatx4_t (*acc)[FN][2
     // accesses across this point: the stores and loads use different vector types)
     asm volatile("" ::: "memory");
     constexpr int CPR = TN / 8;                             // chunks per row
-    const uint16_t *res = reinterpret_cast<const uint16_t *>(ep.residual);
     const bool routed = ep.split < N;                       // K/V columns go to the cache
     const float inv_rps = 1.0f / (float)ep.rows_per_sample;
 #pragma unroll
@@ -197,20 +208,6 @@ __device__ __forceinline__ void store_tile_epilogue(const floatx4_t (*acc)[FN][2
         const int lc = (it * 64 + lane) % CPR * 8, col = wcol0 + lc;
         uint4 v = *reinterpret_cast<const uint4 *>(wlds + lrow * PITCH + lc);
         if (row >= rows || col >= N) continue;
-        if (res) {
-            float a[8], r[8];
-            Elem<uint16_t>::unpack(v, a);
-            if (ep.res_f32) {
-                const float *rf = reinterpret_cast<const float *>(ep.residual) + (size_t)row * N + col;
-                Elem<float>::unpack(*reinterpret_cast<const uint4 *>(rf), r);
-                Elem<float>::unpack(*reinterpret_cast<const uint4 *>(rf + 4), r + 4);
-            } else {
-                Elem<uint16_t>::unpack(*reinterpret_cast<const uint4 *>(res + (size_t)row * N + col), r);
-            }
-#pragma unroll
-            for (int t = 0; t < 8; ++t) a[t] += r[t];
-            v = Elem<uint16_t>::pack(a);
-        }
         uint16_t *dst;
         const int c = col - ep.split;
         if (!routed || c < 0) {
@@ -550,7 +547,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     constexpr int FE = epi_frags(FM), FE32 = epi_frags_f32(BM, BN, WM, WN);
     static_assert(epi_bytes_f32(BN, WM, WN, FE32) <= kLdsLimit, "fp32 staging");
     char *stage_base = reinterpret_cast<char *>(lds_raw);
-    if (ep.out_f32) {
+    if (ep.out_f32 || ep.residual) {
         uint16_t *wlds = reinterpret_cast<uint16_t *>(stage_base + wave * (FE32 * 32 * (TN + 4) * 4));
 #pragma unroll
         for (int f0 = 0; f0 < FM; f0 += FE32) {

@@ -45,3 +45,33 @@ def test_linear_layers_across_plans(dtype, B, M, d, H, F):
     assert rel_err(to_np(y), yo) <= tol
     assert np.array_equal(to_np(blk.K[:, :Lp]), Kp) and bool((blk.K[:, Lp + M:] == 7.0).all())
     assert np.array_equal(to_np(blk.V[:, :Lp]), Vp) and bool((blk.V[:, Lp + M:] == 7.0).all())
+
+
+@pytest.mark.parametrize("d,rows", [
+    (256, 5), (256, 200),                 # the kernel without staging; small tiles
+    (1024, 40), (1024, 969), (1024, 970), (1024, 1152), (1024, 1153), (1024, 1537), (1024, 2048),
+    (1024, 12289), (1920, 6145), (2048, 2050),
+])
+def test_second_mlp_layer_rounds_once(d, rows):
+    """y = residual + product, both fp32 until the one rounding to bf16, whichever tile, division or
+    merge the plan picks.  Constructed so that nothing before that rounding is inexact: attention and
+    its projection are 0 (h = x), the hidden layer is gelu(16) = 16 everywhere, and a row of W_fc2
+    holds two entries whose products are a value of 8 bits and one 2^-9 .. 2^-14 of it, so the fp32
+    product is exact in every order of summation but does not fit bf16.  Exact equality: the expected
+    value is one fp32 addition, rounded once."""
+    F, H = 4 * d, d // 64
+    rng = np.random.default_rng(rows)
+    x = wl.round_to_bf16(rng.standard_normal((1, rows, d)).astype(np.float32) * 2)
+    hi = wl.round_to_bf16(rng.standard_normal(d).astype(np.float32))
+    lo = wl.round_to_bf16(hi * rng.uniform(2.0 ** -14, 2.0 ** -9, d).astype(np.float32))
+    w = {"w_qkv": np.zeros((3 * d, d)), "w_o": np.zeros((d, d)), "w_fc1": np.zeros((F, d)),
+         "b_fc1": np.full(F, 16.0), "w_fc2": np.zeros((d, F))}
+    w = {n: v.astype(np.float32) for n, v in w.items()}
+    w["w_fc2"][np.arange(d), rng.integers(0, F // 2, d)] = hi / 16
+    w["w_fc2"][np.arange(d), rng.integers(F // 2, F, d)] = lo / 16
+    Kp = np.zeros((1, 3, H, 64), np.float32)
+    blk = GpuBlock(d, H, F, "bf16", w, Kp, Kp, 3 + rows)
+    y = blk.dense(to_dev(x, "bf16")).cpu()
+    expect = (torch.from_numpy(x) + torch.from_numpy(hi + lo)).to(torch.bfloat16)
+    assert np.array_equal((hi.astype(np.float64) + lo).astype(np.float32), hi + lo)
+    assert torch.equal(y, expect), f"{(y != expect).sum().item()} of {y.numel()} differ"
