@@ -273,7 +273,11 @@ constexpr size_t gemm_epi_lds_bytes(int BM, int BN, int WM, int WN)
 // problems of one shape in one launch (operands and output `*_bstride` elements apart), whole
 // tiles only (no division of the contraction), K a multiple of 64 and N a multiple of 8.
 // nbatch > 1 is also available with the ordinary operand layout (no divided tail).
-template <int BM, int BN, int WM, int WN, int STAGES, bool BKM = false>
+//
+// CHAINS: no fp32 accumulation runs over more than a few k-tiles; the results of these chains are added
+// up, with compensation, in a second set of registers.  For a result that meets the inverse of a Gram
+// matrix, which magnifies its rounding when it is badly conditioned.
+template <int BM, int BN, int WM, int WN, int STAGES, bool BKM = false, bool CHAINS = false>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     const uint16_t *__restrict__ A_in, const uint16_t *__restrict__ W_in, int rows, int N, int K,
     int tiles_m, int tiles_n, int group_m, EpiParams ep, int nsplit, float *__restrict__ part,
@@ -400,6 +404,23 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
 #pragma unroll
             for (int b = 0; b < 4; ++b) acc[i][j][b >> 1][b & 1] = floatx4_t{0};
 
+    floatx4_t sum[CHAINS ? FM : 1][CHAINS ? FN : 1][2][2] = {};
+    const int chain = ktiles > 16 ? 4 : 2;               // longer ones where there are many: their errors average out
+    auto fold = [&] {                   // the accumulators into the sums; the next chain starts from what that rounded off
+        if constexpr (CHAINS)
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        floatx4_t &s = sum[i][j][b >> 1][b & 1], &a = acc[i][j][b >> 1][b & 1];
+                        const floatx4_t t = s + a;
+                        a -= t - s;
+                        s = t;
+                    }
+    };
+
     const uint16_t *lds = reinterpret_cast<const uint16_t *>(lds_raw);
     // Operand fragments (16x16x32 MFMA: lane l holds row l%16, k-values 8*(l/16) .. +7 of a 32-wide
     // k-step).  The MFMAs of a k-tile are walked as ROWS = steps x (TM/16) "rows": one A fragment
@@ -512,7 +533,16 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
                     ring[row & 3], bb[q & 1][j], acc[i >> 1][j >> 1][i & 1][j & 1], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
+        if (CHAINS && ((kt + 1) & (chain - 1)) == 0 && more) fold();
         stage = nstage;
+    }
+    if constexpr (CHAINS) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) acc[i][j][b >> 1][b & 1] += sum[i][j][b >> 1][b & 1];
     }
     // the stage buffers are reused below: every wavefront must be past its last operand read
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -658,6 +688,9 @@ static void launch_kmajor_cfg(const void *A, size_t a_bstride, const void *X, in
 // out[p][b] = share p of the contraction of A[b] W[b]^T, in fp32, for nbatch problems of one shape (A[b]:
 // [rows][K], W[b]: [N][K], both bf16 and `rows*K` / `N*K` elements apart; out[p][b]: [rows][N]), on the
 // tiled MFMA kernel.  K a multiple of 64, N <= 128.  The number of shares is batched_f32_parts().
+// Error against 64 bits of positive values at K = 1024, 2048, 4096 (two shares, at 2048 three) and
+// 4096 (one share): 4.3, 4.2, 4.0 and 3.2e-8, with one chain per share 9.2, 9.2, 17 and 34e-8; 25.6 -> 28.3 us at
+// 4 x (4096 x 4096 x 128).
 template <int BM, int BN, int WM, int WN, int STAGES>
 static void launch_batched_f32_cfg(const void *A, const void *W, int nbatch, int rows, int N, int K,
                                    int parts, float *out, hipStream_t st)
@@ -670,7 +703,7 @@ static void launch_batched_f32_cfg(const void *A, const void *W, int nbatch, int
     const size_t lds_stages = (size_t)STAGES * (BM + BN) * BK * sizeof(uint16_t);
     const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN);
     const size_t lds = lds_stages > lds_epi ? lds_stages : lds_epi;
-    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, false>;
+    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, false, true>;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     int group_m = (int)lround(sqrt((double)tiles_m * tiles_n * BN / (8.0 * BM)));

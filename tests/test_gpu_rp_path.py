@@ -247,6 +247,38 @@ def test_gram_inverse_keeps_ill_conditioned_digits(r, kind):
             assert werr <= bound, (b, f"cond {cond:.1e}: T X off by {werr:.1e} > {bound:.1e}")
 
 
+@pytest.mark.parametrize("B,M,d,r", [(1, 1024, 1024, 64), (4, 4096, 4096, 128), (8, 4096, 4096, 128),
+                                     (16, 4096, 4096, 64), (2, 1000, 1920, 24), (1, 72, 320, 8), (3, 520, 512, 128)])
+def test_factor_t_rounding(B, M, d, r):
+    """T = C G_c^T, which lies in the workspace as shares to be added up, against 64 bits, on positive values (every
+    rounding counts).  A chain of n MFMAs is rounded at partial sums that have grown to i/n of its result, an
+    rms of at most sqrt(n/3) 2^-24 of it; the d/(32 n) chains of a row are independent and their sum is
+    compensated, so it and each addition of a share are one rounding more, at most 2^-24/sqrt(3) each.
+    n is 8, or 4 where a share has no more than 16 k-tiles.  One chain per share
+    breaks the bound at all of these, six-fold at d = 4096."""
+    import ctypes as C
+    rng = np.random.default_rng(M + r)
+    cache = torch.from_numpy(np.abs(rng.standard_normal((M, 32)) @ rng.standard_normal((32, d))).astype(np.float32))
+    cache = (cache * (1 + 0.1 * torch.arange(B)[:, None, None])).to(torch.bfloat16).cuda()
+    qt = torch.from_numpy(np.abs(rng.standard_normal((r, M))).astype(np.float32) / r ** 0.5).to(torch.bfloat16).cuda()
+    ctx = _ctx(d, "bf16")
+    w_c = torch.empty((B, M, r), dtype=torch.bfloat16, device="cuda")
+    g_c = torch.empty((B, r, d), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((fv.fvar_factors_workspace_bytes(ctx, B, M, r),), 0xff, dtype=torch.uint8, device="cuda")
+    fv.fvar_cache_factors(ctx, cache, qt, False, B, M, r, 1e-6, w_c, g_c, ws)
+    parts = fv.load_library()["_ZN4fvar14factor_t_partsENS_5DTypeEiiii"](C.c_int(1), B, M, r, d)
+    shares = ws[:parts * B * M * r * 4].view(torch.float32).view(parts, B, M, r)
+    T = shares[0].clone()
+    for p in range(1, parts):
+        T += shares[p]
+    n = 8 if d / 64 / parts > 16 else 4
+    bound = 2.0 ** -24 / 3 ** 0.5 * (n / max(1.0, d / (32 * n)) + parts) ** 0.5
+    for b in range(B):
+        ref = cache[b].double() @ g_c[b].double().t()
+        err = ((T[b].double() - ref).norm() / ref.norm()).item()
+        assert err <= bound, (b, parts, err, bound)
+
+
 def test_cache_factors_feed_the_fill():
     # factors built on the GPU, used by the rank-r fill, against the oracle's fill of its factors
     dtype, B, M, d, r, k = "bf16", 2, 144, 256, 32, 58
