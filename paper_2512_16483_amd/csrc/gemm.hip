@@ -94,6 +94,7 @@ constexpr int BK = 64;
 // gains by the division (244 -> 229 us), that of QKV at 15360 rows, hidden 2048 makes its block
 // 0.7 % slower.
 constexpr double kMergeUs = 3.8, kMergeRate = 7.7e6;
+constexpr double kHbmRate = 6.7e6;     // bytes / us, operands in and output out (fitted)
 constexpr double kTailMergeUs = 6.0, kTailMergeRate = 5.0e6;
 
 __device__ __forceinline__ int lds_off(int row, int chunk)      // in bf16 elements
@@ -722,6 +723,11 @@ static BatchedPlan batched_f32_plan(int nbatch, int rows, int N, int K)
     const struct { int bm; double k_us, tile_us; } cands[3] = {
         {256, 0.896, 1.9}, {128, narrow ? 0.364 : 0.537, narrow ? 0.3 : 0.95}, {64, narrow ? 0.274 : 0.375, 0.3}};
     const int kt = K / BK;
+    // operands beyond the 256 MB of last-level cache (the caller has just read them) take the time they
+    // need from HBM at 5.5 TB/s; among equals the largest tile, which is then the fastest (40 x
+    // (4096 x 4096 x 128): 280 us with 256 rows, 306 with 128; with 64 columns of G 87 and 92)
+    const double bytes = nbatch * (2.0 * ((double)rows + N) * K + 4.0 * rows * N);
+    const double hbm_us = bytes > 256e6 ? bytes / 5.5e6 : 0.0;
     BatchedPlan best{256, 1};
     double best_us = 1e300;
     for (const auto &c : cands)
@@ -729,7 +735,7 @@ static BatchedPlan batched_f32_plan(int nbatch, int rows, int N, int K)
             const int per = (kt + parts - 1) / parts;
             if (parts > 1 && (kt / parts < 4 || (parts - 1) * per >= kt)) continue;
             const long tiles = (long)((rows + c.bm - 1) / c.bm) * nbatch;
-            const double us = (double)((tiles * parts + 255) / 256) * (c.tile_us + c.k_us * per) +
+            const double us = fmax(hbm_us, (double)((tiles * parts + 255) / 256) * (c.tile_us + c.k_us * per)) +
                               (parts - 1) * (1.0 + 8.0 * nbatch * rows * N / kMergeRate);
             if (us < best_us) { best_us = us; best = {c.bm, parts}; }
         }
@@ -765,10 +771,15 @@ bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int
         {192, 128, 0.77, 1.3}, {128, 128, 0.59, 0.95}, {64, 128, 0.41, 0.3}};
     int best = 0;
     double best_us = 1e300;
+    const double bytes = 2.0 * B * ((double)M * d + (double)rows * d + (q_stride ? (double)rows * M : 0));
     for (int i = 0; i < 7; ++i) {
         const auto &c = cands[i];
         const long tiles = (long)((rows + c.bm - 1) / c.bm) * ((d + c.bn - 1) / c.bn) * B;
-        const double us = (double)((tiles + 255) / 256) * (c.tile_us + c.k_us * (M / BK));
+        // what the operands' way from HBM adds: 0.040 us/MB in rows of 512 bytes, 0.058 in rows of 256 (40
+        // samples of 4096 x 4096 to 128 rows: 247 us with 128x256 tiles, 271 with 128x128, of which the
+        // tiles' own time is 194 each; 24 samples 153 and 163)
+        const double us = (double)((tiles + 255) / 256) * (c.tile_us + c.k_us * (M / BK)) +
+                          bytes * (c.bn >= 256 ? 4.0e-8 : 5.8e-8);
         if (us < best_us) { best_us = us; best = i; }
     }
     switch (best) {
@@ -1033,7 +1044,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const float *__restri
 // candidate of each problem, where one rate per tile and no small tiles cost 30 % (worst 3x).
 constexpr double kLaunchUs = 3.6;      // a launch by itself
 constexpr double kDivide = 1.008;      // a division that promises less is not worth its scratch
-constexpr double kHbmRate = 6.7e6;     // bytes / us, operands in and output out
 constexpr double kRowsRate = 11.9e6;   // bytes / us that gemm_rows_kernel's workgroups read, L2 hits included
 
 struct TileCfg { int bm, bn; double k_us, tile_us; };   // us per k-tile and per tile with all CUs at work
