@@ -68,8 +68,10 @@ class Chain:
         maxM = max(s["M"] for s in self.scale.values())
         self.sel_ws = torch.empty(fv.fvar_select_workspace_bytes(self.ctx, B, maxM),
                                   dtype=torch.uint8, device="cuda")
-        self.ws = torch.empty(fv.fvar_block_workspace_bytes(self.ctx, B, maxM), dtype=torch.uint8,
-                              device="cuda")
+        # the largest of the sizes of all calls: they do not grow steadily with the rows
+        self.ws = torch.empty(max(fv.fvar_block_workspace_bytes(self.ctx, B, n)
+                                  for s in self.scale.values() for n in (s["M"], s["k"], W.rank)),
+                              dtype=torch.uint8, device="cuda")
 
     def pruned_scale(self, side):
         fv, W, s = self.fv, self.W, self.scale[side]

@@ -129,7 +129,11 @@ int32_t fvar_scale_tokens(const fvar_ctx *ctx, int32_t scale_index);
 int32_t fvar_scale_prev_len(const fvar_ctx *ctx, int32_t scale_index);
 
 /* Workspace sizes in bytes (multiples of 256).  `rows` is the number of rows per sample that
- * pass through the block: k for the pruned call, M for the dense call. */
+ * pass through the block: k for the pruned call, M for the dense call.  Besides the activations the
+ * bf16 block needs room for partial results wherever its kernels divide an axis between workgroups, which
+ * they do at some row counts and not at others: the size can be smaller for more rows.  A workspace
+ * that serves calls of several sizes has to have the largest of THEIR sizes, not the size of the largest call
+ * (fp32: the two are the same). */
 size_t fvar_select_workspace_bytes(const fvar_ctx *ctx, int32_t B, int32_t M);
 size_t fvar_block_workspace_bytes(const fvar_ctx *ctx, int32_t B, int32_t rows);
 

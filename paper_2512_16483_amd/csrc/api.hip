@@ -147,8 +147,8 @@ fvar_status validate_indices(fvar_ctx *c, hipStream_t st, const int32_t *idx_kee
 }
 
 struct BlockWs {
-    char *x_keep, *u, *q, *att, *h1, *hid, *att_part;
-    float *gemm_part;
+    char *x_keep, *u, *q, *att, *h1, *hid;
+    float *part;                              // partial results of the attention and of each linear layer in turn
     fvar::GemmPlan qkv, o, fc1, fc2;          // how each linear layer runs at this row count
     size_t total;
 };
@@ -166,18 +166,19 @@ BlockWs carve(const fvar_ctx *c, void *ws, int B, int rows)
     w.att = take(R * d * es);
     w.h1 = take(R * d * sizeof(float));       // intermediate residual stream, always fp32
     w.hid = take(R * F * es);
-    // partial attention results when the key axis is split between workgroups (small batches)
-    const size_t part = fvar::attention_scratch_floats(dtype(c), B, rows, c->cfg.heads, c->cfg.head_dim);
-    w.att_part = part ? take(part * sizeof(float)) : nullptr;
-    // partial tiles of the linear layers whose contraction axis is divided between workgroups
     const DType dt = dtype(c);
     w.qkv = fvar::gemm_plan(dt, (int)R, (int)(3 * d), (int)d);
     w.o = fvar::gemm_plan(dt, (int)R, (int)d, (int)d);
     w.fc1 = fvar::gemm_plan(dt, (int)R, (int)F, (int)d);
     w.fc2 = fvar::gemm_plan(dt, (int)R, (int)d, (int)F);
-    const size_t gp = std::max(std::max(w.qkv.scratch_floats, w.o.scratch_floats),
-                               std::max(w.fc1.scratch_floats, w.fc2.scratch_floats));
-    w.gemm_part = gp ? reinterpret_cast<float *>(take(gp * sizeof(float))) : nullptr;
+    // partial results where the key axis or the contraction axis is divided between workgroups
+    size_t part = std::max(std::max(w.qkv.scratch_floats, w.o.scratch_floats),
+                           std::max(w.fc1.scratch_floats, w.fc2.scratch_floats));
+    part = std::max(part, fvar::attention_scratch_floats(dt, B, rows, c->cfg.heads, c->cfg.head_dim));
+    // fp32: what the plans take falls as the rows become more; their bound does not, so that a
+    // workspace sized for the largest call serves every smaller one (bf16 never had that: see fvar.h)
+    if (dt != DType::BF16) part = std::max(part, fvar::gemm_f32_scratch_bound((int)R, (int)std::max(3 * d, F)));
+    w.part = part ? reinterpret_cast<float *>(take(part * sizeof(float))) : nullptr;
     w.total = off;
     return w;
 }
@@ -250,17 +251,17 @@ fvar_status block_forward(fvar_ctx *c, hipStream_t st, const fvar_block_weights 
         e.bias = w->b_qkv; e.out0 = s.q; e.ld0 = d; e.split = d;
         e.kcache = kv->k; e.vcache = kv->v; e.hd = d; e.cap = kv->capacity; e.len = kv->len;
         e.rows_per_sample = rows;
-        fvar::launch_gemm(dt, s.u, w->w_qkv, R, 3 * d, d, e, s.qkv, s.gemm_part, st);
+        fvar::launch_gemm(dt, s.u, w->w_qkv, R, 3 * d, d, e, s.qkv, s.part, st);
     });
     timed(c, st, "attention", [&] {
         fvar::launch_attention(dt, s.q, kv->k, kv->v, B, rows, L, kv->capacity, H, Dh, c->scale, s.att,
-                               reinterpret_cast<float *>(s.att_part), st);
+                               s.part, st);
     });
     timed(c, st, "gemm_o", [&] {
         fvar::GemmEpilogue e;
         e.bias = w->b_o; e.residual = resid; e.out0 = s.h1; e.ld0 = d; e.split = d;
         e.out_f32 = 1;
-        fvar::launch_gemm(dt, s.att, w->w_o, R, d, d, e, s.o, s.gemm_part, st);
+        fvar::launch_gemm(dt, s.att, w->w_o, R, d, d, e, s.o, s.part, st);
     });
     timed(c, st, "ln2", [&] {
         if (dt == DType::BF16)
@@ -272,12 +273,12 @@ fvar_status block_forward(fvar_ctx *c, hipStream_t st, const fvar_block_weights 
     timed(c, st, "gemm_fc1", [&] {
         fvar::GemmEpilogue e;
         e.bias = w->b_fc1; e.gelu = 1; e.out0 = s.hid; e.ld0 = F; e.split = F;
-        fvar::launch_gemm(dt, s.u, w->w_fc1, R, F, d, e, s.fc1, s.gemm_part, st);
+        fvar::launch_gemm(dt, s.u, w->w_fc1, R, F, d, e, s.fc1, s.part, st);
     });
     timed(c, st, "gemm_fc2", [&] {
         fvar::GemmEpilogue e;
         e.bias = w->b_fc2; e.residual = s.h1; e.res_f32 = 1; e.out0 = y; e.ld0 = d; e.split = d;
-        fvar::launch_gemm(dt, s.hid, w->w_fc2, R, d, F, e, s.fc2, s.gemm_part, st);
+        fvar::launch_gemm(dt, s.hid, w->w_fc2, R, d, F, e, s.fc2, s.part, st);
     });
     const fvar_status ls = launch_status(c, who);
     if (ls != FVAR_OK || !c->debug_checks) return ls;

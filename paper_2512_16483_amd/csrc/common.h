@@ -139,6 +139,8 @@ struct GemmEpilogue {
 // (tail), and the floats of scratch that their partial tiles take.  A function of the shape alone.
 struct GemmPlan { int cfg, nsplit, tail; size_t scratch_floats; };
 GemmPlan gemm_plan(DType dt, int rows, int N, int K);
+// floats that no fp32 plan of up to `rows` rows and N columns exceeds; never falls as rows grow
+size_t gemm_f32_scratch_bound(int rows, int N);
 // `part`: plan.scratch_floats floats (unused when 0)
 void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
                  const GemmEpilogue &ep, const GemmPlan &plan, float *part, hipStream_t st);

@@ -1057,13 +1057,21 @@ constexpr RowsCfg kRows[] = {{1, 1, 0.174, 3.0}, {2, 1, 0.261, 3.3}, {2, 2, 0.28
 constexpr int kNumRows = sizeof(kRows) / sizeof(kRows[0]);
 constexpr int kRowsWaves = 8, kRowsMax = 256;           // gemm_rows_kernel is not measured beyond 256 rows
 
+// fp32: at most 8 shares, and not more than 256 workgroups of 32 features x 16 rows per tile
+static int f32_row_tiles(int rows) { return rows <= 16 ? 1 : rows <= 32 ? 2 : 4; }
+size_t gemm_f32_scratch_bound(int rows, int N)
+{
+    const size_t every = (size_t)8 * rows * N, full = (size_t)256 * 32 * 16 * f32_row_tiles(rows);
+    return every < full ? every : full;
+}
+
 GemmPlan gemm_plan(DType dt, int rows, int N, int K)
 {
     GemmPlan best{0, 1, 1, 0};
     if (dt != DType::BF16) {
         // rows per workgroup: the fewest 16-row tiles that cover the problem, at most four; then divide
         // the contraction axis up to one workgroup per CU, every wavefront at least two k-steps
-        best.cfg = rows <= 16 ? 1 : rows <= 32 ? 2 : 4;
+        best.cfg = f32_row_tiles(rows);
         const long units = (long)((rows + 16 * best.cfg - 1) / (16 * best.cfg)) * (N / 32);
         while (best.nsplit < 8 && units * best.nsplit * 2 <= 256 && K / 16 >= best.nsplit * 4 * kRowsWaves) best.nsplit *= 2;
         if (best.nsplit > 1) best.scratch_floats = (size_t)best.nsplit * rows * N;

@@ -161,3 +161,43 @@ def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(fv, "LIB_PATH", "/nonexistent/libfvar.so")
     with pytest.raises(ImportError):
         fv.load_library()
+
+
+class _Plan(C.Structure):
+    _fields_ = [("cfg", C.c_int), ("nsplit", C.c_int), ("tail", C.c_int), ("scratch_floats", C.c_size_t)]
+
+
+def gemm_plan(dtype, rows, N, K):
+    """The plan of a linear layer (an internal function of the library; pure host code)."""
+    f = fv.load_library()["_ZN4fvar9gemm_planENS_5DTypeEiii"]
+    f.restype, f.argtypes = _Plan, [C.c_int, C.c_int, C.c_int, C.c_int]
+    return f(1 if dtype == "bf16" else 0, rows, N, K)
+
+
+@pytest.mark.parametrize("d,H,F", [(1024, 16, 4096), (512, 8, 5440), (64, 1, 64), (4096, 32, 4096)])
+def test_f32_block_workspace_grows_with_the_call(d, H, F):
+    """fp32 callers may size one workspace for their largest scale: the size never falls as the rows or
+    the batch grow."""
+    c = fv.Context(hidden=d, heads=H, head_dim=d // H, ffn_hidden=F, dtype="f32")
+    for B in (1, 2, 3, 8):
+        last = 0
+        for n in list(range(1, 700)) + list(range(700, 5000, 37)):
+            need = fv.fvar_block_workspace_bytes(c, B, n)
+            assert last <= need <= fv.fvar_block_workspace_bytes(c, B + 1, n), (B, n, last, need)
+            last = need
+
+
+@pytest.mark.parametrize("dtype,d,H", [("f32", 1024, 16), ("bf16", 1024, 16), ("bf16", 1920, 30), ("bf16", 4096, 32)])
+def test_block_workspace_holds_the_partial_results(dtype, d, H):
+    """What the workspace has besides the activations is enough for the plan of every linear layer and
+    for the attention, which use it in turn."""
+    F, es, al = 4 * d, 2 if dtype == "bf16" else 4, lambda n: -(-n // 256) * 256
+    c = fv.Context(hidden=d, heads=H, head_dim=d // H, ffn_hidden=F, dtype=dtype)
+    att = fv.load_library()["_ZN4fvar24attention_scratch_floatsENS_5DTypeEiiii"]
+    att.restype = C.c_size_t
+    for B in (1, 3, 32):
+        for n in list(range(1, 260, 3)) + [363, 640, 1021, 1537, 1600, 2048, 3122]:
+            R = B * n
+            part = fv.fvar_block_workspace_bytes(c, B, n) - 4 * al(R * d * es) - al(R * d * 4) - al(R * F * es)
+            plans = [gemm_plan(dtype, R, N, K).scratch_floats for N, K in ((3 * d, d), (d, d), (F, d), (d, F))]
+            assert part >= 4 * max(plans + [att(1 if dtype == "bf16" else 0, B, n, H, d // H)]), (B, n)
