@@ -243,7 +243,7 @@ fvar_status fvar_cache_fill(fvar_ctx *ctx, fvar_stream stream, const void *y_kee
  * positive definite) and the final product run in fp64.  A singular Gram matrix (r above the
  * rank of the cache with ridge == 0) gives non-finite w_c; pass a small ridge (e.g. 1e-10) then.  qt, q_per_sample as in fvar_rp_project.
  * 1 <= r <= min(M,128), r a multiple of 8 for bf16 (of 4 for fp32); M as in fvar_rp_project.
- * ws: at least fvar_factors_workspace_bytes(ctx,B,M,r). */
+ * ws: at least fvar_factors_workspace_bytes(ctx,B,M,r), which never falls as B, M or r grow. */
 size_t fvar_factors_workspace_bytes(const fvar_ctx *ctx, int32_t B, int32_t M, int32_t r);
 fvar_status fvar_cache_factors(fvar_ctx *ctx, fvar_stream stream, const void *cache, const void *qt,
                                int32_t q_per_sample, int32_t B, int32_t M, int32_t r, double ridge,

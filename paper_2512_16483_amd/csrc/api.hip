@@ -601,7 +601,7 @@ size_t fvar_factors_workspace_bytes(const fvar_ctx *c, int32_t B, int32_t M, int
 {
     if (!c || B < 1 || M < 1 || r < 1) return 0;
     const size_t rr = (size_t)B * r * r * sizeof(double);
-    return align256((size_t)B * M * r * sizeof(float) * fvar::factor_t_room(dtype(c), B, M, r, c->cfg.hidden)) +
+    return align256(fvar::factor_t_room(dtype(c), B, M, c->cfg.hidden) * r * sizeof(float)) +
            align256(rr * fvar::gram_parts(dtype(c))) + align256(rr);
 }
 
@@ -631,7 +631,7 @@ fvar_status fvar_cache_factors(fvar_ctx *c, fvar_stream stream, const void *cach
                     ws_bytes);
     char *p = static_cast<char *>(ws);
     float *T = reinterpret_cast<float *>(p);
-    p += align256((size_t)B * M * r * sizeof(float) * fvar::factor_t_room(dtype(c), B, M, r, c->cfg.hidden));
+    p += align256(fvar::factor_t_room(dtype(c), B, M, c->cfg.hidden) * r * sizeof(float));
     double *S = reinterpret_cast<double *>(p);
     p += align256((size_t)B * r * r * sizeof(double) * fvar::gram_parts(dtype(c)));
     double *Sinv = reinterpret_cast<double *>(p);

@@ -170,6 +170,7 @@ void launch_cache_fill(DType dt, const void *y_keep, const int32_t *idx_keep, co
 // out[b] = qt[b] x[b]:  qt:[rows,M] (sample stride q_stride elements, 0 = shared), x:[B,M,d],
 // out:[B,rows,d].  M must be a multiple of the 16-byte chunk (8 bf16 / 4 fp32 elements).
 int batched_f32_parts(int nbatch, int rows, int N, int K);
+size_t batched_f32_room(int nbatch, int rows, int K);
 void launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int rows, int N, int K,
                                   float *out, hipStream_t st);
 bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int B, int M, int rows,
@@ -182,10 +183,10 @@ void launch_rp_project(DType dt, const void *qt, size_t q_stride, const void *x,
 void launch_upsample(DType dt, const void *src, int B, int hs, int ws, int hd, int wd, int c,
                      void *dst, hipStream_t st);
 
-// restoration matrix W_c = (C G_c^T)(G_c G_c^T)^{-1} in four steps; T:[factor_t_room (factor_t_parts of them used),B,M,r] fp32,
+// restoration matrix W_c = (C G_c^T)(G_c G_c^T)^{-1} in four steps; T:[factor_t_parts,B,M,r] fp32 (factor_t_room rows),
 // S:[B,gram_parts(dt),r,r] and Sinv:[B,r,r] fp64 are scratch.  r <= 128.
 int factor_t_parts(DType dt, int B, int M, int r, int d);
-int factor_t_room(DType dt, int B, int M, int r, int d);
+size_t factor_t_room(DType dt, int B, int M, int d);
 void launch_factor_t(DType dt, const void *cache, const void *g_c, int B, int M, int r, int d, float *T,
                      hipStream_t st);
 void launch_factor_gram(DType dt, const void *g_c, int B, int r, int d, double *S, hipStream_t st);

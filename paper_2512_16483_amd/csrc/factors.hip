@@ -365,13 +365,10 @@ int factor_t_parts(DType dt, int B, int M, int r, int d)
     return dt == DType::BF16 ? batched_f32_parts(B, M, r, d) : 1;
 }
 
-// shares the workspace has room for: never fewer than the two (one from 512 64-row blocks of C on) that
-// callers have been told to provide, whatever the plan needs
-int factor_t_room(DType dt, int B, int M, int r, int d)
+// rows of T, over all shares, that the workspace has room for
+size_t factor_t_room(DType dt, int B, int M, int d)
 {
-    const int parts = factor_t_parts(dt, B, M, r, d);
-    const int least = dt == DType::BF16 && (long)B * ((M + 63) / 64) < 512 ? 2 : 1;
-    return parts > least ? parts : least;
+    return dt == DType::BF16 ? batched_f32_room(B, M, d) : (size_t)B * M;
 }
 
 void launch_factor_t(DType dt, const void *cache, const void *g_c, int B, int M, int r, int d, float *T,

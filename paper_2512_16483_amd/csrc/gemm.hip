@@ -714,6 +714,16 @@ static void launch_batched_f32_cfg(const void *A, const void *W, int nbatch, int
            (size_t)rows * K, (size_t)N * K, (size_t)rows * N);
 }
 
+// Output rows, over all shares and problems, that a plan never exceeds: the shares it may take (each at
+// least 4 k-tiles; two are always counted, the least this has ever been), as long as their partial
+// results stay below 96K rows.  Never falls as the problem grows, which the shares themselves do.
+size_t batched_f32_room(int nbatch, int rows, int K)
+{
+    const size_t R = (size_t)nbatch * rows, kt = K / BK, shares = kt < 8 ? 2 : kt < 16 ? kt / 4 : 4;
+    const size_t divided = shares * R < (96u << 10) ? shares * R : (96u << 10);
+    return R > divided ? R : divided;
+}
+
 // Tile height (256, 128 or 64 rows; one tile spans all N <= 128 columns) and shares of the contraction,
 // by the same prediction as gemm_plan; the consumer sums the shares, so they cost it a read each.
 struct BatchedPlan { int bm, parts; };
@@ -733,7 +743,9 @@ static BatchedPlan batched_f32_plan(int nbatch, int rows, int N, int K)
     for (const auto &c : cands)
         for (int parts = 1; parts <= 4; ++parts) {
             const int per = (kt + parts - 1) / parts;
-            if (parts > 1 && (kt / parts < 4 || (parts - 1) * per >= kt)) continue;
+            if (parts > 1 && (kt / parts < 4 || (parts - 1) * per >= kt ||
+                              (size_t)parts * nbatch * rows > batched_f32_room(nbatch, rows, K)))
+                continue;
             const long tiles = (long)((rows + c.bm - 1) / c.bm) * nbatch;
             const double us = fmax(hbm_us, (double)((tiles * parts + 255) / 256) * (c.tile_us + c.k_us * per)) +
                               (parts - 1) * (1.0 + 8.0 * nbatch * rows * N / kMergeRate);

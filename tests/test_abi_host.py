@@ -201,3 +201,22 @@ def test_block_workspace_holds_the_partial_results(dtype, d, H):
             part = fv.fvar_block_workspace_bytes(c, B, n) - 4 * al(R * d * es) - al(R * d * 4) - al(R * F * es)
             plans = [gemm_plan(dtype, R, N, K).scratch_floats for N, K in ((3 * d, d), (d, d), (F, d), (d, F))]
             assert part >= 4 * max(plans + [att(1 if dtype == "bf16" else 0, B, n, H, d // H)]), (B, n)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 512), ("bf16", 128), ("bf16", 1024), ("bf16", 1920), ("bf16", 4096)])
+def test_factors_workspace_grows_with_the_call(dtype, d):
+    """The workspace of fvar_cache_factors never shrinks as rows, samples or rank grow, and holds every share
+    that T comes in."""
+    c = fv.Context(hidden=d, heads=d // 64, head_dim=64, ffn_hidden=d, dtype=dtype)
+    parts = fv.load_library()["_ZN4fvar14factor_t_partsENS_5DTypeEiiii"]
+    size = fv.fvar_factors_workspace_bytes
+    for B in (1, 2, 4, 8, 16, 40):
+        for r in (8, 64, 128):
+            last, gram = 0, 9 * (-(-8 * B * r * r // 256) * 256) if dtype == "bf16" else 2 * (-(-8 * B * r * r // 256) * 256)
+            for M in list(range(128, 4300, 56)) + [4096, 4104] + list(range(4304, 30000, 808)):
+                if M == 4096:
+                    last = 0
+                need = size(c, B, M, r)
+                assert last <= need <= min(size(c, B + 1, M, r), size(c, B, M, r + 8)), (B, M, r, last, need)
+                assert need - gram >= 4 * parts(C.c_int(1 if dtype == "bf16" else 0), B, M, r, d) * B * M * r
+                last = need
