@@ -87,15 +87,17 @@ __device__ __forceinline__ void finish_quad(const EpiParams &ep, int row, int co
 // ------------------------------------------------------------------------------ bf16 MFMA
 constexpr int BK = 64;
 
-// Write and read of the partials (bytes / us) and the second launch.  A division of every tile leaves
-// at most a few MB, which stay in the caches (fitted); a divided last round of a large problem leaves
-// up to 84 MB of them among hundreds of MB of other traffic.  The line is drawn between two layers
-// with that much, measured inside their blocks: the last round of O at 6400 rows, hidden 4096
-// gains by the division (244 -> 229 us), that of QKV at 15360 rows, hidden 2048 makes its block
-// 0.7 % slower.
-constexpr double kMergeUs = 3.8, kMergeRate = 7.7e6;
+// Second launch (us), and write and read of the partials (bytes / us), of a division of every tile and of a
+// divided last round.  Chosen on the linear layers of 600 blocks (hidden 1024 .. 4096, rows drawn from 17 ..
+// 16000, weights from HBM), each layer timed inside its block undivided, divided and with a divided last
+// round: the constants by which picking the lower prediction costs least in sum.  On 360 other blocks the picks
+// come to 50297 us where a division was possible and 86490 where a last round was (never 55913 and 87783, best
+// 50108 and 86171).  A last round is divided only where that promises 3 %, less than the prediction is
+// off by there (5 % rms): a third fewer of them, hence second launches and scratch, for 0.02 to 0.06 % of the
+// time (86442 without).  A division of every tile needs no such margin (50352 with it).
+constexpr double kMergeUs = 3.0, kMergeRate = 7.7e6;
+constexpr double kTailMergeUs = 7.0, kTailMergeRate = 10.0e6, kTailMargin = 1.03;
 constexpr double kHbmRate = 6.7e6;     // bytes / us, operands in and output out (fitted)
-constexpr double kTailMergeUs = 6.0, kTailMergeRate = 5.0e6;
 
 __device__ __forceinline__ int lds_off(int row, int chunk)      // in bf16 elements
 {
@@ -1055,7 +1057,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const float *__restri
 // residual 4 % rms; the plan it picks is on average 2 % (worst 27 %) slower than the best
 // candidate of each problem, where one rate per tile and no small tiles cost 30 % (worst 3x).
 constexpr double kLaunchUs = 3.6;      // a launch by itself
-constexpr double kDivide = 1.008;      // a division that promises less is not worth its scratch
 constexpr double kRowsRate = 11.9e6;   // bytes / us that gemm_rows_kernel's workgroups read, L2 hits included
 
 struct TileCfg { int bm, bn; double k_us, tile_us; };   // us per k-tile and per tile with all CUs at work
@@ -1107,7 +1108,7 @@ GemmPlan gemm_plan(DType dt, int rows, int N, int K)
             const double rounds = i == kSmallTile ? (units > 1.0 ? units : 1.0) : ceil(units);
             double us = rounds * (c.tile_us + c.k_us * per);
             us = kLaunchUs + (us > hbm_us ? us : hbm_us);
-            if (ns > 1) us = (us + part_us((double)ns * rows * N)) * kDivide;
+            if (ns > 1) us += part_us((double)ns * rows * N);
             if (us < best_us) { best_us = us; best = {i, ns, 1, ns > 1 ? (size_t)ns * rows * N : 0}; }
         }
         // whole rounds undivided, the tiles beyond them divided
@@ -1118,7 +1119,7 @@ GemmPlan gemm_plan(DType dt, int rows, int N, int K)
             if (rem * t > 256 || kt / t < 4) break;
             if ((t - 1) * per >= kt) continue;
             double us = full * (c.tile_us + c.k_us * kt) + c.tile_us + c.k_us * per;
-            us = (kLaunchUs + (us > hbm_us ? us : hbm_us) + tail_us((double)rem * t * area)) * kDivide;
+            us = (kLaunchUs + (us > hbm_us ? us : hbm_us) + tail_us((double)rem * t * area)) * kTailMargin;
             if (us < best_us) { best_us = us; best = {i, 1, t, (size_t)rem * t * (size_t)area}; }
         }
     }
@@ -1132,7 +1133,7 @@ GemmPlan gemm_plan(DType dt, int rows, int N, int K)
             const int steps = (K / 32 + ns * kRowsWaves - 1) / (ns * kRowsWaves);
             const double l2_us = (double)tiles * (bm + bn) * K * 2.0 / kRowsRate, w_us = 2.0 * N * K / kHbmRate;
             double us = c.fixed_us + c.step_us * steps + (l2_us > w_us ? l2_us : w_us);
-            if (ns > 1) us = (us + part_us((double)ns * rows * N)) * kDivide;
+            if (ns > 1) us += part_us((double)ns * rows * N);
             if (us < best_us) { best_us = us; best = {kNumTiles + i, ns, 1, ns > 1 ? (size_t)ns * rows * N : 0}; }
         }
     }
