@@ -174,6 +174,38 @@ def gemm_plan(dtype, rows, N, K):
     return f(1 if dtype == "bf16" else 0, rows, N, K)
 
 
+TILES = ("320x256", "256x256", "192x256", "256x192", "256x128", "128x256", "192x128", "128x128", "64x128", "128x64",
+         "64x64", "rows 16x16", "rows 32x16", "rows 32x32")
+
+
+@pytest.mark.parametrize("rows,d,F,layer,tile,shares,last_round", [
+    (7, 1024, 4096, "qkv", "rows 16x16", 1, 1),
+    (18, 1024, 4096, "fc1", "rows 32x32", 1, 1),
+    (33, 960, 1984, "qkv", "rows 32x16", 1, 1),
+    (64, 512, 5440, "fc2", "rows 32x32", 8, 1),
+    (64, 2048, 8192, "fc2", "64x64", 7, 1),
+    (130, 1024, 4096, "fc1", "64x64", 1, 1),
+    (130, 1024, 4096, "fc2", "128x64", 8, 1),
+    (257, 1024, 4096, "fc2", "64x128", 6, 1),
+    (700, 1024, 4096, "fc1", "128x128", 1, 1),
+    (700, 1024, 4096, "fc2", "128x128", 5, 1),
+    (900, 1920, 7680, "qkv", "192x128", 1, 1),
+    (900, 1920, 7680, "fc1", "128x256", 1, 1),
+    (1848, 1920, 7680, "qkv", "256x192", 1, 1),
+    (1848, 1920, 7680, "fc1", "256x256", 1, 1),
+    (36, 2048, 8192, "qkv", "64x64", 3, 1),
+    (144, 4096, 1024, "qkv", "192x128", 2, 1),
+    (642, 4096, 64, "qkv", "128x256", 1, 8),
+    (1610, 4096, 64, "qkv", "256x256", 1, 3),
+])
+def test_plans_that_the_gpu_tests_are_there_for(rows, d, F, layer, tile, shares, last_round):
+    """tests/test_gpu_linear_plans.py runs the block at these row counts: another choice of constants must not
+    take a kernel, a tile or a division out of its reach unseen."""
+    N, K = {"qkv": (3 * d, d), "o": (d, d), "fc1": (F, d), "fc2": (d, F)}[layer]
+    p = gemm_plan("bf16", rows, N, K)
+    assert (TILES[p.cfg], p.nsplit, p.tail) == (tile, shares, last_round)
+
+
 @pytest.mark.parametrize("d,H,F", [(1024, 16, 4096), (512, 8, 5440), (64, 1, 64), (4096, 32, 4096)])
 def test_f32_block_workspace_grows_with_the_call(d, H, F):
     """fp32 callers may size one workspace for their largest scale: the size never falls as the rows or

@@ -1,6 +1,7 @@
 """Linear layers (and the fp32 attention) at the row counts where their plan changes kernel, tile or
 division of the contraction axis: the dense block (QKV routed into the cache, O with fp32 output, FC1 with GELU, FC2)
-against the oracle."""
+against the oracle.  That the rows below get the plans they are here for is checked without a GPU, in
+test_abi_host.py."""
 import numpy as np
 import pytest
 import torch
@@ -29,6 +30,11 @@ from gpu_util import TOL, GpuBlock, oracle_dense, rel_err, to_dev, to_np  # noqa
     ("bf16", 4, 225, 1920, 30, 7680),     # 192x128 tiles, K/V rows routed across samples inside a tile
     ("bf16", 2, 924, 1920, 15, 7680),     # 256x192 tiles, ragged rows and columns
     ("bf16", 2, 1300, 64, 1, 6144),       # many tiles, a single k-tile
+    ("bf16", 3, 12, 2048, 16, 8192),      # QKV divided three ways, 36 rows of three samples in one tile; every layer divided
+    ("bf16", 4, 36, 4096, 32, 1024),      # QKV divided in two: 192x128 tiles over four samples
+    ("bf16", 3, 214, 4096, 32, 64),       # QKV with a last round divided eight ways, tiles across samples
+    ("bf16", 2, 805, 4096, 32, 64),       # the same in three, 256x256 tiles
+    ("bf16", 1, 64, 512, 8, 5440),        # FC2 divided eight ways without staging
 ])
 def test_linear_layers_across_plans(dtype, B, M, d, H, F):
     Lp, bf, tol = 5, dtype == "bf16", TOL[dtype]
