@@ -573,10 +573,10 @@ static void launch_attn_bf16(const void *q, const void *K, const void *V, int B,
 
 // ------------------------------------------------------------------------------ fp32
 // Flash attention on the fp32 MFMA (16x16x4), for 16 queries per workgroup whose NW wavefronts take
-// NW contiguous shares of the key tiles and meet in LDS at the end.  Bound by the MFMA rate (no
-// faster than the vector units in fp32, but one operand register per MFMA instead of an LDS read per
-// few FMAs) and, at the sizes of the fp32 configuration, by filling the chip: 128 rows x 16 heads
-// are 128 workgroups of 8 wavefronts.  Nothing is staged: S^T = K Q^T takes its operands as float4 of
+// NW contiguous shares of the key tiles and meet in LDS at the end.  The MFMA is no faster than the
+// vector units in fp32, but takes one operand register where they take an LDS read per few FMAs.  At the
+// sizes of the fp32 configuration the chip is not filled: 128 rows x 16 heads are 128 workgroups of 8
+// wavefronts, each with four or five key tiles in sequence (pipes busy 0.09 of the clocks).  Nothing is staged: S^T = K Q^T takes its operands as float4 of
 // four consecutive head-dim values (the k-slots of four MFMAs), P stays in the registers S^T left
 // it in, and V rows are read as float4 across the head dim, which only permutes the rows of O^T.
 // 128 rows x 552 keys x 16 heads of 64: 109 us (one query row per 8 lanes, K / V through LDS) -> 11.9 us.

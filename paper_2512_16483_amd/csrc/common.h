@@ -134,9 +134,10 @@ struct GemmEpilogue {
     // fp32 between the two halves of the block so that it is not rounded twice.
     int out_f32 = 0, res_f32 = 0;
 };
-// How a bf16 linear layer is run: kernel and tile (index into the tables of gemm.hip), workgroups that
-// share the contraction axis of every tile (nsplit) or of the tiles beyond the last whole round
-// (tail), and the floats of scratch that their partial tiles take.  A function of the shape alone.
+// How a linear layer is run: kernel and tile (bf16: index into the tables of gemm.hip; fp32: 16-row tiles
+// per workgroup), workgroups that share the contraction axis of every tile (nsplit) or, in bf16, of the
+// tiles beyond the last whole round (tail), and the floats of scratch that their partial tiles take.  A
+// function of the shape alone.
 struct GemmPlan { int cfg, nsplit, tail; size_t scratch_floats; };
 GemmPlan gemm_plan(DType dt, int rows, int N, int K);
 // floats that no fp32 plan of up to `rows` rows and N columns exceeds; never falls as rows grow

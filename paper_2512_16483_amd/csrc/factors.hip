@@ -290,9 +290,9 @@ __global__ __launch_bounds__(128 * NB) void spd_inverse_kernel(const double *__r
 // ------------------------------------------------------------------ W = T S^{-1}
 // On the fp64 MFMA (16x16x4).  Workgroup = 64 rows of T, 16 per wavefront; S^{-1} is staged in LDS, zero
 // padded to 16*CT in both directions, its pitch such that the rows of the four k-slots fall on
-// different banks.  A lane takes 4 consecutive entries of its row of T (the sum of its one or two
-// slices) as the k-slots of four MFMAs.  Bound by the MFMA rate: 4*CT*CT MFMAs of 64 clk per
-// wavefront.  Rank 128, 4 x 4096 rows: 76 us with fp64 FMAs fed by LDS broadcasts -> 17 us.
+// different banks.  A lane takes 4 consecutive entries of its row of T (the sum of its up to four
+// shares) as the k-slots of four MFMAs.  4*CT*CT MFMAs of 64 clk per wavefront are 7 of the 17 us below
+// (pipes busy 0.27 of the clocks; the wavefronts wait 0.41 of their time, 0.19 of the LDS cycles are conflicts).  Rank 128, 4 x 4096 rows: 76 us with fp64 FMAs fed by LDS broadcasts -> 17 us.
 template <typename TT, int CT>
 __global__ __launch_bounds__(256) void w_kernel(const float *__restrict__ T, int t_parts,
                                                 size_t t_part_stride,

@@ -602,7 +602,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
 }
 
 // Sum of the partial tiles of the divided tail + the epilogue (bias, GELU, residual, bf16 or fp32
-// output; never the K/V routing).  One thread per 4 consecutive columns of one tile row.
+// output, K and V columns to the cache).  One thread per 4 consecutive columns of one tile row.
 __global__ __launch_bounds__(256) void gemm_tail_epilogue_kernel(const float *__restrict__ part,
                                                                  int ranges, int full_tiles,
                                                                  int tiles_m, int tiles_n, int group_m,
@@ -809,7 +809,7 @@ bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int
 }
 
 // Sum of the partial tiles of a split contraction + the epilogue (bias, GELU, residual, bf16 or
-// fp32 output; never the K/V routing).  One thread per 4 consecutive columns.
+// fp32 output, K and V columns to the cache).  One thread per 4 consecutive columns.
 __global__ __launch_bounds__(256) void gemm_splitk_epilogue_kernel(const float *__restrict__ part,
                                                                    int nsplit, int rows, int N,
                                                                    EpiParams ep)
@@ -967,9 +967,11 @@ __global__ __launch_bounds__(256) void gemm_f32_merge_kernel(const float *__rest
 // fp32 linear layer on the fp32 MFMA (16x16x4), laid out as gemm_rows_kernel: a workgroup owns 32
 // output features and 16*TT rows, its wavefronts share the contraction axis, operands go from global
 // memory to registers as float4 of four consecutive k (the k-slots of four MFMAs) and the partial
-// tiles meet in LDS.  Bound by the MFMA rate (157 TFLOP/s, as the vector units; six 1 KiB loads feed
-// 32 MFMAs of 32 clk), so the only point of the layout is to keep every CU at it: the launcher
-// divides the contraction axis until there is a workgroup for every CU.  128 rows, hidden 1024,
+// tiles meet in LDS.  The limit is the MFMA rate (157 TFLOP/s, as the vector units; six 1 KiB loads feed
+// 32 MFMAs of 32 clk), so the point of the layout is to keep every CU at it: the launcher divides the
+// contraction axis until there is a workgroup for every CU.  At 128 rows it is far from that limit: the
+// MFMA pipes are busy 0.23 of the clocks (25 TFLOP/s for O to 59 for FC1) and the wavefronts, one
+// k-step of loads ahead, wait half of their time.  128 rows, hidden 1024,
 // against 64x64 tiles of FMAs through LDS: QKV 62.8 -> 17.7, O 61.9 -> 10.6, FC1 63.5 -> 18.3,
 // FC2 232.8 -> 21.1 us (24.0, 12.1, 24.7, 23.8 with two workgroups per CU); 2048 rows: the block
 // 1499 -> 1085 us.  The error against 64 bits falls from 5.8e-7 to 1.7e-7 (shorter sums).
@@ -1055,7 +1057,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const float *__restri
 // output cross HBM.  Its constants are a least-squares fit to 8200 timings of every tile with every
 // division on 344 problems (rows 7 .. 15360, hidden 1024 .. 4096, the four layers of a block):
 // residual 4 % rms; the plan it picks is on average 2 % (worst 27 %) slower than the best
-// candidate of each problem, where one rate per tile and no small tiles cost 30 % (worst 3x).
+// candidate of each problem, where one rate per tile and no small tiles cost 30 % (worst 3x).  The
+// undivided timings are in profiles/linear_layer_tile_times.txt, divisions in linear_layer_divisions.txt.
 constexpr double kLaunchUs = 3.6;      // a launch by itself
 constexpr double kRowsRate = 11.9e6;   // bytes / us that gemm_rows_kernel's workgroups read, L2 hits included
 

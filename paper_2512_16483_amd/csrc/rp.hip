@@ -198,7 +198,7 @@ void launch_rp_project(DType dt, const void *qt, size_t q_stride, const void *x,
                        int rows, int d, void *out, hipStream_t st)
 {
     if (dt == DType::BF16) {
-        // large problems on whole k-tiles go to the tiled MFMA kernel of the linear layers
+        // whole 64-token k-tiles go to the tiled MFMA kernel of the linear layers
         if (launch_gemm_bf16_kmajor(qt, q_stride, x, B, M, rows, d, out, st)) return;
         if (rows <= 64 || (rows > 128 && rows <= 192)) {
             dim3 grid((d + kRpBN - 1) / kRpBN, (rows + 63) / 64, B);
