@@ -111,56 +111,47 @@ typedef double doublex4_t __attribute__((ext_vector_type(4)));
 // value of lane P of each 16-lane row, in every lane of the row
 template <int P> __device__ __forceinline__ double row_bcast(double v)
 {
-    const int2 w = __builtin_bit_cast(int2, v);
-    int2 o;
-    o.x = __builtin_amdgcn_mov_dpp(w.x, 0x150 + P, 0xf, 0xf, true);
-    o.y = __builtin_amdgcn_mov_dpp(w.y, 0x150 + P, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, o);
+    const long w = __builtin_amdgcn_mov_dpp(__builtin_bit_cast(long, v), 0x150 + P, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, w);
 }
 
-// value of the lane of 16-lane row R with the same lane % 16, in every lane: two exchanges in
-// registers (a shuffle is an LDS round trip in the serial chain of the elimination)
-template <int R> __device__ __forceinline__ double col_bcast(double v)
-{
-    const uint2 w = __builtin_bit_cast(uint2, v);
-    const auto bcast = [](unsigned x) {
-        const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);    // {rows 0 1 0 1}, {rows 2 3 2 3}
-        const unsigned y = h[R >> 1];
-        const auto q = __builtin_amdgcn_permlane16_swap(y, y, false, false);    // {even row}, {odd row}
-        return q[R & 1];
-    };
-    return __builtin_bit_cast(double, make_uint2(bcast(w.x), bcast(w.y)));
-}
-
-// Sweep step P of the symmetric 16x16 pivot block `a` and the same row operations on 16 further columns
-// `b` of its rows, both held by one wavefront in the fp64 MFMA's output layout: entry e of lane
+// Sweep step P of the symmetric 16x16 pivot block `a` and the same row operations on NT further 16-column
+// tiles `b` of its rows, all held by one wavefront in the fp64 MFMA's output layout: entry e of lane
 // (c, g) = (lane % 16, lane / 16) is row 4e + g, column c.  With d the pivot and u its row of a,
 //     a_ik -> a_ik - u_i u_k / d,   a_iP, a_Pi -> u_i / d,   a_PP -> -1 / d,
 //     b_i -> b_i - u_i b_P / d,     b_P -> b_P / d.
 // The two triangles of a stay equal to the bit (the product u_i u_k is rounded first): where they drift
-// apart, T S^-1 loses four digits at condition 4e6.  b_P as it was goes to y[P] of this lane's column,
-// divided by d to ys[P] (from the four lanes that hold it alike).
-template <int P>
-__device__ __forceinline__ void sweep_step(doublex4_t &a, doublex4_t &b, double *y, double *ys, int c, int g)
+// apart, T S^-1 loses four digits at condition 4e6.  b_P as it was goes to y[.][P] of its column, divided
+// by d to ys[.][P] (from the four lanes that hold it alike).
+template <int P, int NT>
+__device__ __forceinline__ void sweep_step(doublex4_t &a, doublex4_t (&b)[NT], double (*y)[17],
+                                           double (*ys)[17], int c, int g)
 {
-    const double row = col_bcast<(P & 3)>(a[P >> 2]);                // u at this lane's column
-    const double brow = col_bcast<(P & 3)>(b[P >> 2]);
+    const double row = __shfl(a[P >> 2], 16 * (P & 3) + c);          // u at this lane's column
+    double brow[NT], bs[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) brow[t] = __shfl(b[t][P >> 2], 16 * (P & 3) + c);
     const double piv = row_bcast<P>(row);
     double inv = __builtin_amdgcn_rcp(piv);                          // ~1e-8, two Newton steps to full precision
     inv = fma(inv, fma(-piv, inv, 1.0), inv);
     inv = fma(inv, fma(-piv, inv, 1.0), inv);
-    const double x = c == P ? -1.0 : row, xs = x * inv, bs = brow * inv;
-    y[P] = brow;
-    ys[P] = bs;
+    const double x = c == P ? -1.0 : row, xs = x * inv;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) { bs[t] = brow[t] * inv; y[16 * t + c][P] = brow[t]; ys[16 * t + c][P] = bs[t]; }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const double col = row_bcast<P>(a[e]);                       // u at this entry's row
-        const double v = fma(-(col * x), inv, c == P ? 0.0 : a[e]), w = fma(-col, bs, b[e]);
+        const double v = fma(-(col * x), inv, c == P ? 0.0 : a[e]);
         const bool pivot = e == (P >> 2) && g == (P & 3);
         a[e] = pivot ? xs : v;
-        b[e] = pivot ? bs : w;
-        // computed here: put off to the branch that stores them, they keep col and bs of all steps in registers
-        asm volatile("" : "+v"(b[e]));
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const double w = fma(-col, bs[t], b[t][e]);
+            b[t][e] = pivot ? bs[t] : w;
+            // computed here: put off to the branch that stores them, they keep col and bs of all steps in
+            // registers
+            asm volatile("" : "+v"(b[t][e]));
+        }
     }
 }
 
@@ -174,11 +165,13 @@ __device__ __forceinline__ void sweep_step(doublex4_t &a, doublex4_t &b, double 
 // condition number where the sweep loses it once (condition 4e6: the inverse off by 4e-6 instead of
 // 5e-11, T S^-1 of a rank-8 cache with ridge 1e-6 wrong altogether).
 // The matrix is padded to 16*NB with an identity block and stays in registers as 16x16 tiles in the fp64
-// MFMA's output layout, NB/2 tiles of one tile row per wavefront.  The first NB wavefronts apply the
-// steps, each to its own tile of the row and all to a copy of the pivot block; only the tile
-// column, u and u / d go through LDS, three barriers per block.
-// Bound by the serial chain of pivot steps.  Rank 128, 4 samples: 90 us; one thread per half row, a barrier
-// per pivot and 64 unrolled steps of code that do not fit the instruction cache took 767.
+// MFMA's output layout, NB/2 tiles of one tile row per wavefront.  The first wavefronts apply the steps,
+// each to one or two tiles of the row and all to a copy of the pivot block; only the tile column, u and
+// u / d go through LDS, three barriers per block.  Steps of the padding are left out.
+// Bound by the chain of steps, 0.5 us each.  Rank 128, 4 samples: 64 us (eight wavefronts with one tile each 68,
+// with exchanges by permlane swaps instead of shuffles 73); one thread per half row, a barrier per pivot
+// and 64 unrolled steps of code that do not fit the instruction cache took 759.  Ranks 8, 16, 24 and 32: 5.5,
+// 8.3, 10.4 and 11.3 us, before 6.3, 8.3, 11.4 and 13.6.
 // A singular matrix yields non-finite output.
 template <int NB>
 __global__ __launch_bounds__(128 * NB) void spd_inverse_kernel(const double *__restrict__ S, int parts,
@@ -231,28 +224,36 @@ __global__ __launch_bounds__(128 * NB) void spd_inverse_kernel(const double *__r
                 for (int e = 0; e < 4; ++e) U[16 * ti + 4 * e + g][c] = a[t][e];
             }
         __syncthreads();
-        if (wave < NB) {
-            doublex4_t p, u;                                         // u: the transposed tile, A_jw
-            double *y = Y[16 * wave + c], *ys = Ys[16 * wave + c];
+        constexpr int NT = NB == 8 ? 2 : 1;                          // tiles of the row per stepping wavefront
+        if (wave < NB / NT) {
+            doublex4_t p, u[NT];                                     // u: the transposed tiles, A_jk
+            double (*y)[17] = Y + 16 * NT * wave, (*ys)[17] = Ys + 16 * NT * wave;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 // the lower triangle for both
                 p[e] = U[16 * j + max(4 * e + g, c)][min(4 * e + g, c)];
-                u[e] = U[16 * wave + c][4 * e + g];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) u[t][e] = U[16 * (NT * wave + t) + c][4 * e + g];
             }
-#define FVAR_SWEEP(P) sweep_step<P>(p, u, y, ys, c, g)
+#define FVAR_SWEEP(P)                                                                              \
+    if (16 * j + P < r)                                                                            \
+        sweep_step<P, NT>(p, u, y, ys, c, g);                                                      \
+    else                                                                                           \
+        for (int t = 0; t < NT; ++t) y[16 * t + c][P] = ys[16 * t + c][P] = 0.0
             FVAR_SWEEP(0); FVAR_SWEEP(1); FVAR_SWEEP(2); FVAR_SWEEP(3);
             FVAR_SWEEP(4); FVAR_SWEEP(5); FVAR_SWEEP(6); FVAR_SWEEP(7);
             FVAR_SWEEP(8); FVAR_SWEEP(9); FVAR_SWEEP(10); FVAR_SWEEP(11);
             FVAR_SWEEP(12); FVAR_SWEEP(13); FVAR_SWEEP(14); FVAR_SWEEP(15);
 #undef FVAR_SWEEP
-            if (wave == j) {                                         // rows 16j .. of U stay as the others read them
 #pragma unroll
-                for (int e = 0; e < 4; ++e) Pi[4 * e + g][c] = p[e];
-            } else {
+            for (int t = 0; t < NT; ++t)
+                if (NT * wave + t == j) {                            // rows 16j .. of U stay as the others read them
 #pragma unroll
-                for (int e = 0; e < 4; ++e) U[16 * wave + c][4 * e + g] = u[e];
-            }
+                    for (int e = 0; e < 4; ++e) Pi[4 * e + g][c] = p[e];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) U[16 * (NT * wave + t) + c][4 * e + g] = u[t][e];
+                }
         }
         __syncthreads();
         double ui[4];
