@@ -168,10 +168,10 @@ __device__ __forceinline__ void sweep_step(doublex4_t &a, doublex4_t (&b)[NT], d
 // MFMA's output layout, NB/2 tiles of one tile row per wavefront.  The first wavefronts apply the steps,
 // each to one or two tiles of the row and all to a copy of the pivot block; only the tile column, u and
 // u / d go through LDS, three barriers per block.  Steps of the padding are left out.
-// Bound by the chain of steps, 0.5 us each.  Rank 128, 4 samples: 64 us (eight wavefronts with one tile each 68,
-// with exchanges by permlane swaps instead of shuffles 73); one thread per half row, a barrier per pivot
-// and 64 unrolled steps of code that do not fit the instruction cache took 759.  Ranks 8, 16, 24 and 32: 5.5,
-// 8.3, 10.4 and 11.3 us, before 6.3, 8.3, 11.4 and 13.6.
+// Bound by the chain of steps, 0.5 us each.  Rank 128, 4 samples, by itself: 63 us (eight wavefronts with one
+// tile each 68, with exchanges by permlane swaps instead of shuffles 73); one thread per half row, a barrier
+// per pivot and 64 unrolled steps of code that do not fit the instruction cache took 758.  Ranks 8, 16, 24 and
+// 32: 5.4, 6.3, 8.4 and 9.3 us, before 6.7, 8.3, 11.3 and 13.7.
 // A singular matrix yields non-finite output.
 template <int NB>
 __global__ __launch_bounds__(128 * NB) void spd_inverse_kernel(const double *__restrict__ S, int parts,
@@ -193,12 +193,19 @@ __global__ __launch_bounds__(128 * NB) void spd_inverse_kernel(const double *__r
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int row = 16 * ti + 4 * e + g, col = 16 * (tk0 + t) + c;
-            double v = row == col ? 1.0 : 0.0;                       // identity padding
-            if (row < r && col < r) {
-                v = 0.0;
-                for (int p = 0; p < parts; ++p) v += Sb[((size_t)p * r + row) * r + col];
-                if (row == col) tr += v;
+            // the parts' loads travel together (inside a call, where another kernel has just written them, rank 16
+            // 12.2 -> 6.8 us, rank 128 84 -> 71); rows and columns are clamped, the padding is an identity block
+            const double *src = Sb + (size_t)min(row, r - 1) * r + min(col, r - 1);
+            double v = 0.0;
+            for (int p = 0; p < parts; p += 8) {
+                double part[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) part[q] = src[(size_t)min(p + q, parts - 1) * r * r];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v += p + q < parts ? part[q] : 0.0;
             }
+            if (row >= r || col >= r) v = row == col ? 1.0 : 0.0;
+            else if (row == col) tr += v;
             a[t][e] = v;
         }
     if (ridge != 0.0) {
