@@ -241,6 +241,14 @@ __device__ __forceinline__ void dma_b128(const void *base, uint32_t byte_off, ui
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(lds_addr), "v"(byte_off), "s"(base) : "memory", "m0");
 }
+// the same from an address of its own per lane
+__device__ __forceinline__ void dma_b128(const void *addr, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :: "s"(lds_addr), "v"(addr) : "memory", "m0");
+}
+// what the chunks past the end of the contraction axis are fetched from
+__device__ const uint4 kZeroChunk = {0, 0, 0, 0};
 
 // LDS needed after the main loop: one staging tile per wavefront.
 // A wavefront sends its sub-tile through the epilogue in passes of a few 32-row fragments:
@@ -274,13 +282,15 @@ constexpr size_t gemm_epi_lds_bytes(int BM, int BN, int WM, int WN)
 // Feature", Q^T X) instead of W[N][K].  Its tiles travel to LDS in their own row-major layout and
 // the B fragments come from the transposing LDS load.  This mode runs `nbatch` independent
 // problems of one shape in one launch (operands and output `*_bstride` elements apart), whole
-// tiles only (no division of the contraction), K a multiple of 64 and N a multiple of 8.
+// tiles only (no division of the contraction), N a multiple of 8, K of 64 or (RAGGED) of 8: the lanes whose
+// chunk of the last k-tile lies past its end then fetch zeros for both operands (a copy of the kernel,
+// because the test for it in every k-tile costs the whole ones 4 %: 17.4 -> 18.1 us at 692 x 2304 x 2048).
 // nbatch > 1 is also available with the ordinary operand layout (no divided tail).
 //
 // CHAINS: no fp32 accumulation runs over more than a few k-tiles; the results of these chains are added
 // up, with compensation, in a second set of registers.  For a result that meets the inverse of a Gram
 // matrix, which magnifies its rounding when it is badly conditioned.
-template <int BM, int BN, int WM, int WN, int STAGES, bool BKM = false, bool CHAINS = false>
+template <int BM, int BN, int WM, int WN, int STAGES, bool BKM = false, bool CHAINS = false, bool RAGGED = false>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     const uint16_t *__restrict__ A_in, const uint16_t *__restrict__ W_in, int rows, int N, int K,
     int tiles_m, int tiles_n, int group_m, EpiParams ep, int nsplit, float *__restrict__ part,
@@ -380,13 +390,33 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
             b_off[i] = (uint32_t)(((size_t)min(col0 + r, N - 1) * K + c * 8) * sizeof(uint16_t));
         }
     }
-    const int ktiles_all = K / BK, kper = (ktiles_all + ranges - 1) / ranges;
+    const int ktiles_all = RAGGED ? (K + BK - 1) / BK : K / BK, kper = (ktiles_all + ranges - 1) / ranges;
     const int kt0 = split * kper;
     const int ktiles = min(ktiles_all, kt0 + kper) - kt0;   // k-tiles of this workgroup (>= 1)
     // DMA instructions i0 .. i1-1 (of the NG that make up a k-tile) of k-tile kt into `stage`
     auto issue_part = [&](int kt, int stage, int i0, int i1) {
         const int koff = (kt0 + kt) * BK;
         const uint32_t sbase = lds_base + stage * STAGE_BYTES + wave * 1024;
+        if (RAGGED && koff + BK > K) {                   // the last k-tile; uniform
+#pragma unroll
+            for (int i = 0; i < NGA; ++i) {
+                const int r = (wave + NW * i) * 8 + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+                if (i >= i0 && i < i1)
+                    dma_b128(koff + c * 8 < K ? reinterpret_cast<const char *>(A + koff) + a_off[i]
+                                              : reinterpret_cast<const char *>(&kZeroChunk),
+                             sbase + i * (NW * 1024));
+            }
+#pragma unroll
+            for (int i = 0; i < NGB; ++i) {
+                constexpr int CPR = BN / 8, RPI = 64 / CPR;
+                const int r = (wave + NW * i) * RPI + lane / CPR;
+                if (NGA + i >= i0 && NGA + i < i1)
+                    dma_b128(koff + r < K ? reinterpret_cast<const char *>(W + (size_t)koff * N) + b_off[i]
+                                          : reinterpret_cast<const char *>(&kZeroChunk),
+                             sbase + BM * BK * 2 + i * (NW * 1024));
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < NGA; ++i)
             if (i >= i0 && i < i1) dma_b128(A + koff, a_off[i], sbase + i * (NW * 1024));
@@ -678,7 +708,8 @@ static void launch_kmajor_cfg(const void *A, size_t a_bstride, const void *X, in
     const size_t lds_stages = (size_t)STAGES * (BM + BN) * BK * sizeof(uint16_t);
     const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN);
     const size_t lds = lds_stages > lds_epi ? lds_stages : lds_epi;
-    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, true>;
+    auto kern = K % BK ? gemm_bf16_kernel<BM, BN, WM, WN, STAGES, true, false, true>
+                       : gemm_bf16_kernel<BM, BN, WM, WN, STAGES, true>;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     int group_m = (int)lround(sqrt((double)tiles_m * tiles_n * BN / (8.0 * BM)));
@@ -770,29 +801,31 @@ void launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int 
 }
 
 // Runs out[b] = qt[b] x[b] (qt: [rows][M] per sample or shared, x[b]: [M][d]) on the tiled MFMA
-// kernel when M is a multiple of the 64-wide k-tile (d is a multiple of 64).  Returns false (nothing
-// launched) otherwise.  Tile by predicted time, constants as in gemm_plan plus a tenth for the
-// transposing reads (no 320x256 tile: with them it would not fit the 256 registers).  Even a few tiles
-// here beat many of rp_project_bf16_kernel, whose 64-token chunk takes 1.7 us against 0.4 us of a
-// 64x128 k-tile: 692 x 2304 x 2048 61 -> 17 us, 4 x (128 x 4096 x 4096) 123 -> 39 us.
+// kernel (M a multiple of 8, d of 64).  Returns false, with nothing launched, where a row tile of qt does
+// not fit 32-bit byte offsets (M of 2^25 and more).  Tile by predicted time, constants as in gemm_plan plus
+// a tenth for the transposing reads (no 320x256 tile: with them it would not fit the 256 registers).  Even a
+// few tiles here beat many of a kernel that turns X around through registers, whose 64-token chunk takes
+// 1.7 us against 0.4 us of a 64x128 k-tile: 692 x 2304 x 2048 61 -> 17 us, 4 x (128 x 4096 x 4096)
+// 123 -> 39 us; ragged, 692 x 2312 x 2048 51.5 -> 18.6, 4 x (2000 x 6392 x 4096) 720 -> 368 us.
 bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int B, int M, int rows,
                              int d, void *out, hipStream_t st)
 {
-    if (M < BK || M % BK != 0 || d % 8 != 0 || d < 8 || rows < 1 || B < 1) return false;
-    if ((size_t)rows * M * sizeof(uint16_t) >= ((size_t)1 << 32)) return false;   // 32-bit operand offsets
+    if (M % 8 != 0 || d % 8 != 0 || M < 8 || d < 8 || rows < 1 || B < 1) return false;
     const struct { int bm, bn; double k_us, tile_us; } cands[] = {
         {256, 256, 1.64, 3.4}, {192, 256, 1.43, 2.0}, {256, 128, 0.98, 1.9}, {128, 256, 0.98, 1.9},
         {192, 128, 0.77, 1.3}, {128, 128, 0.59, 0.95}, {64, 128, 0.41, 0.3}};
-    int best = 0;
+    int best = -1;
     double best_us = 1e300;
+    const int kt = (M + BK - 1) / BK;
     const double bytes = 2.0 * B * ((double)M * d + (double)rows * d + (q_stride ? (double)rows * M : 0));
     for (int i = 0; i < 7; ++i) {
         const auto &c = cands[i];
+        if ((size_t)c.bm * M * sizeof(uint16_t) >= ((size_t)1 << 32)) continue;   // 32-bit operand offsets
         const long tiles = (long)((rows + c.bm - 1) / c.bm) * ((d + c.bn - 1) / c.bn) * B;
         // what the operands' way from HBM adds: 0.040 us/MB in rows of 512 bytes, 0.058 in rows of 256 (40
         // samples of 4096 x 4096 to 128 rows: 247 us with 128x256 tiles, 271 with 128x128, of which the
         // tiles' own time is 194 each; 24 samples 153 and 163)
-        const double us = (double)((tiles + 255) / 256) * (c.tile_us + c.k_us * (M / BK)) +
+        const double us = (double)((tiles + 255) / 256) * (c.tile_us + c.k_us * kt) +
                           bytes * (c.bn >= 256 ? 4.0e-8 : 5.8e-8);
         if (us < best_us) { best_us = us; best = i; }
     }
@@ -803,7 +836,8 @@ bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int
     case 3: launch_kmajor_cfg<128, 256, 2, 4, 3>(qt, q_stride, x, B, rows, d, M, out, st); break;
     case 4: launch_kmajor_cfg<192, 128, 2, 4, 3>(qt, q_stride, x, B, rows, d, M, out, st); break;
     case 5: launch_kmajor_cfg<128, 128, 2, 4, 4>(qt, q_stride, x, B, rows, d, M, out, st); break;
-    default: launch_kmajor_cfg<64, 128, 2, 4, 4>(qt, q_stride, x, B, rows, d, M, out, st); break;
+    case 6: launch_kmajor_cfg<64, 128, 2, 4, 4>(qt, q_stride, x, B, rows, d, M, out, st); break;
+    default: return false;
     }
     return true;
 }

@@ -82,6 +82,36 @@ def test_rp_project_tiled_path(B, M, rows, d, per_sample):
         assert rel_err(got[b], ref) <= TOL["bf16"], (b, rel_err(got[b], ref))
 
 
+@pytest.mark.parametrize("B,M,rows,d,per_sample", [
+    (2, 56, 50, 192, True),          # less than one k-tile
+    (1, 2312, 692, 2048, False),     # 64x128 tiles, one chunk past the last whole k-tile
+    (5, 136, 130, 1024, False),      # the samples share Q: its rows end inside the last k-tile
+    (4, 440, 190, 4096, True),       # 128x128 tiles, seven of the eight chunks
+    (4, 840, 330, 4096, True),       # 192x128
+    (3, 1000, 700, 4096, True),      # 192x256
+    (16, 264, 250, 3136, False),     # 256x256
+    (32, 520, 500, 384, False),      # 128x256
+])
+def test_rp_project_ragged_token_counts(B, M, rows, d, per_sample):
+    """Token counts that are no multiple of the 64-token k-tile.  What lies behind a sample's map and
+    behind Q must not matter, not even as NaN: each sample is run among neighbours of NaN."""
+    x = wl.activations_lowrank(B, M, d, seed=250 + M + rows, bf16=True)
+    Q = _q(B, M, rows, 260 + M + rows, "bf16", per_sample)
+    ctx = _ctx(d, "bf16")
+    xd, qd, nan = to_dev(x, "bf16"), _qt_dev(Q, "bf16"), float("nan")
+    q_room = torch.full((qd.numel() + 64 * M,), nan, dtype=torch.bfloat16, device="cuda")
+    q_room[:qd.numel()] = qd.flatten()
+    for b in range(B) if B < 8 else (0, B // 2, B - 1):
+        room = torch.full((B + 1, M, d), nan, dtype=torch.bfloat16, device="cuda")
+        room[b] = xd[b]
+        out = torch.zeros((B, rows, d), dtype=torch.bfloat16, device="cuda")
+        fv.fvar_rp_project(ctx, q_room, per_sample, room, B, M, rows, out)
+        torch.cuda.synchronize()
+        ref = rp_path.rp_input(Q[b if per_sample else 0], x[b], bf16=True)
+        assert rel_err(to_np(out[b]), ref) <= TOL["bf16"], b
+        assert bool(torch.isnan(out[:b]).all()) and bool(torch.isnan(out[b + 1:]).all())
+
+
 def test_rp_project_tiled_path_selection_matrix_bitexact():
     # products with 1 and 0 are exact: a column-selection Q reproduces the rows bit for bit
     B, M, rows, d = 12, 128, 128, 4096
