@@ -393,25 +393,27 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     const int ktiles_all = RAGGED ? (K + BK - 1) / BK : K / BK, kper = (ktiles_all + ranges - 1) / ranges;
     const int kt0 = split * kper;
     const int ktiles = min(ktiles_all, kt0 + kper) - kt0;   // k-tiles of this workgroup (>= 1)
+    const int rlane = lane, rK = K;      // for the ragged copy alone: lane and K themselves captured below cost
+                                         // the 320x256 tile two spilled registers
     // DMA instructions i0 .. i1-1 (of the NG that make up a k-tile) of k-tile kt into `stage`
     auto issue_part = [&](int kt, int stage, int i0, int i1) {
         const int koff = (kt0 + kt) * BK;
         const uint32_t sbase = lds_base + stage * STAGE_BYTES + wave * 1024;
-        if (RAGGED && koff + BK > K) {                   // the last k-tile; uniform
+        if (RAGGED && koff + BK > rK) {                   // the last k-tile; uniform
 #pragma unroll
             for (int i = 0; i < NGA; ++i) {
-                const int r = (wave + NW * i) * 8 + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+                const int r = (wave + NW * i) * 8 + (rlane >> 3), c = (rlane & 7) ^ ((r >> 1) & 7);
                 if (i >= i0 && i < i1)
-                    dma_b128(koff + c * 8 < K ? reinterpret_cast<const char *>(A + koff) + a_off[i]
+                    dma_b128(koff + c * 8 < rK ? reinterpret_cast<const char *>(A + koff) + a_off[i]
                                               : reinterpret_cast<const char *>(&kZeroChunk),
                              sbase + i * (NW * 1024));
             }
 #pragma unroll
             for (int i = 0; i < NGB; ++i) {
                 constexpr int CPR = BN / 8, RPI = 64 / CPR;
-                const int r = (wave + NW * i) * RPI + lane / CPR;
+                const int r = (wave + NW * i) * RPI + rlane / CPR;
                 if (NGA + i >= i0 && NGA + i < i1)
-                    dma_b128(koff + r < K ? reinterpret_cast<const char *>(W + (size_t)koff * N) + b_off[i]
+                    dma_b128(koff + r < rK ? reinterpret_cast<const char *>(W + (size_t)koff * N) + b_off[i]
                                           : reinterpret_cast<const char *>(&kZeroChunk),
                              sbase + BM * BK * 2 + i * (NW * 1024));
             }
