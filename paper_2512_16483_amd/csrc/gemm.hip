@@ -270,11 +270,17 @@ constexpr int epi_frags_f32(int BM, int BN, int WM, int WN)
     while (fe > 1 && epi_bytes_f32(BN, WM, WN, fe) > kLdsLimit) --fe;
     return fe;
 }
-constexpr size_t gemm_epi_lds_bytes(int BM, int BN, int WM, int WN)
+// LDS of a launch: the groups' rings, then their exchange, then the staging (in pieces, see the kernel)
+constexpr size_t gemm_lds_bytes(int BM, int BN, int WM, int WN, int STAGES, int KG)
 {
-    const size_t a = epi_bytes_bf16(BM, BN, WM, WN);
-    const size_t b = epi_bytes_f32(BN, WM, WN, epi_frags_f32(BM, BN, WM, WN));
-    return a > b ? a : b;
+    const int FM = BM / WM / 32, KGM = FM % KG == 0 ? KG : FM % 2 == 0 && KG % 2 == 0 ? 2 : 1;
+    const int EWM = WM * KGM, EWN = WN * (KG / KGM);
+    const size_t need[4] = {(size_t)STAGES * KG * (BM + BN) * 64 * 2, (size_t)(KG - 1) * BM * BN * 4,
+                            epi_bytes_bf16(BM, BN, EWM, EWN),
+                            epi_bytes_f32(BN, EWM, EWN, epi_frags_f32(BM, BN, EWM, EWN))};
+    size_t most = 0;
+    for (size_t n : need) most = n > most ? n : most;
+    return most;
 }
 
 // BKM ("B k-major"): the second operand is given as X[K][N] (row = contraction index, as a token
@@ -287,25 +293,35 @@ constexpr size_t gemm_epi_lds_bytes(int BM, int BN, int WM, int WN)
 // because the test for it in every k-tile costs the whole ones 4 %: 17.4 -> 18.1 us at 692 x 2304 x 2048).
 // nbatch > 1 is also available with the ordinary operand layout (no divided tail).
 //
+// KG > 1: that many groups of WM x WN wavefronts, each with a whole output tile in its accumulators, a ring of
+// its own and every KG-th k-tile; the groups' results meet in LDS at the end.  For the small tiles, whose loop
+// is bound neither by the DMA (2/3 of its time by itself), nor the LDS reads (1/2 to 2/3) nor the MFMAs (1/3 to
+// 1/2), but by how badly these overlap between two barriers: KG k-tiles per barrier, and fewer fragment reads,
+// since a group of half the wavefronts has sub-tiles of twice the area.  Us per k-tile with all CUs at work,
+// one group -> KG: 64x64 0.32 -> 0.25, 64x128 0.34 -> 0.30, 128x64 0.34 -> 0.28.  128x128 and 192x128 gain a
+// tenth there too (0.51 -> 0.45, 0.69 -> 0.61) but lose it to the longer first fill and the exchange at the 30
+// to 130 k-tiles that they get, and keep one group.
+//
 // CHAINS: no fp32 accumulation runs over more than a few k-tiles; the results of these chains are added
 // up, with compensation, in a second set of registers.  For a result that meets the inverse of a Gram
 // matrix, which magnifies its rounding when it is badly conditioned.
-template <int BM, int BN, int WM, int WN, int STAGES, bool BKM = false, bool CHAINS = false, bool RAGGED = false>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
+template <int BM, int BN, int WM, int WN, int STAGES, int KG = 1, bool BKM = false, bool CHAINS = false,
+          bool RAGGED = false>
+__global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(
     const uint16_t *__restrict__ A_in, const uint16_t *__restrict__ W_in, int rows, int N, int K,
     int tiles_m, int tiles_n, int group_m, EpiParams ep, int nsplit, float *__restrict__ part,
     int full_tiles, int tail_split, int nbatch, size_t a_bstride, size_t w_bstride,
     size_t o_bstride)
 {
     const uint16_t *A = A_in, *W = W_in;
-    constexpr int NW = WM * WN;                        // wavefronts per workgroup
+    constexpr int NW = WM * WN;                        // wavefronts per group
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int FM = TM / 32, FN = TN / 32;
     constexpr int NGA = BM / 8 / NW, NGB = BN / 8 / NW; // 1 KiB groups (8 rows) per wavefront
     constexpr int NG = NGA + NGB;                      // DMA instructions per lane per k-tile
     constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
     extern __shared__ uint4 lds_raw[];
-    const uint32_t lds_base = (uint32_t)(uintptr_t)lds_raw;
+    uint32_t lds_base = (uint32_t)(uintptr_t)lds_raw;
 
     // Work decomposition.  Workgroups are dealt to the 8 XCDs round-robin; XCD x takes the x-th
     // eighth of the work in ascending order.  Three modes:
@@ -360,7 +376,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     const int row0 = tm * BM, col0 = tn * BN;
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int all_wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = KG > 1 ? all_wave / NW : 0, wave = KG > 1 ? all_wave % NW : all_wave;   // group, wavefront in it
+    lds_base += kg * (STAGES * STAGE_BYTES);           // every group has a ring of its own
     const int c16 = lane & 15, q16 = lane >> 4;
     const int wm = wave % NW / WN, wn = wave % NW % WN;     // the modulus saves the 320x256 tile a spill
 
@@ -393,11 +411,13 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     const int ktiles_all = RAGGED ? (K + BK - 1) / BK : K / BK, kper = (ktiles_all + ranges - 1) / ranges;
     const int kt0 = split * kper;
     const int ktiles = min(ktiles_all, kt0 + kper) - kt0;   // k-tiles of this workgroup (>= 1)
+    const int steps = (ktiles + KG - 1) / KG;               // trips of its loop
+    const int nk = (ktiles - kg + KG - 1) / KG;             // k-tiles of this group: kg, kg + KG, ... (steps or one less)
     const int rlane = lane, rK = K;      // for the ragged copy alone: lane and K themselves captured below cost
                                          // the 320x256 tile two spilled registers
     // DMA instructions i0 .. i1-1 (of the NG that make up a k-tile) of k-tile kt into `stage`
     auto issue_part = [&](int kt, int stage, int i0, int i1) {
-        const int koff = (kt0 + kt) * BK;
+        const int koff = (kt0 + kg + KG * kt) * BK;
         const uint32_t sbase = lds_base + stage * STAGE_BYTES + wave * 1024;
         if (RAGGED && koff + BK > rK) {                   // the last k-tile; uniform
 #pragma unroll
@@ -440,7 +460,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
             for (int b = 0; b < 4; ++b) acc[i][j][b >> 1][b & 1] = floatx4_t{0};
 
     floatx4_t sum[CHAINS ? FM : 1][CHAINS ? FN : 1][2][2] = {};
-    const int chain = ktiles > 16 ? 4 : 2;               // longer ones where there are many: their errors average out
+    const int chain = nk > 16 ? 4 : 2;               // longer ones where there are many: their errors average out
     auto fold = [&] {                   // the accumulators into the sums; the next chain starts from what that rounded off
         if constexpr (CHAINS)
 #pragma unroll
@@ -456,7 +476,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
                     }
     };
 
-    const uint16_t *lds = reinterpret_cast<const uint16_t *>(lds_raw);
+    const uint16_t *lds = reinterpret_cast<const uint16_t *>(lds_raw) + kg * (STAGES * STAGE_BYTES / 2);
     // Operand fragments (16x16x32 MFMA: lane l holds row l%16, k-values 8*(l/16) .. +7 of a 32-wide
     // k-step).  The MFMAs of a k-tile are walked as ROWS = steps x (TM/16) "rows": one A fragment
     // (16 tile rows) against the FN16 B fragments of its k-step.  A fragments go through a ring of
@@ -473,7 +493,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     constexpr int SPW = BK / 32;                         // k-steps per k-tile
     constexpr int ROWS = SPW * FM16;
     static_assert(ROWS % 4 == 0 && ROWS >= 4, "ring of four A fragments");
-    constexpr int SPREAD = ROWS >= 12 ? 6 : 1;           // rows over which a k-tile's DMA is issued
+    constexpr int SPREAD = ROWS >= 12 ? 6 : KG > 1 && ROWS >= 8 ? 4 : 1;   // rows over which a k-tile's DMA is issued
     static_assert(STAGES >= 2 && STAGES <= 4, "wait counts below are written for 2 to 4 stages");
     // rows at which the B fragments of the next k-step / of the next k-tile are fetched: after the
     // last use of the buffer they go to, and (for this tile's) before the hand-over point
@@ -510,13 +530,13 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
         }
     };
 
-    issue(0, 0);
-    if (ktiles > 1) issue(1, 1);
-    if (STAGES >= 3 && ktiles > 2) issue(2, 2);
-    if (STAGES >= 4 && ktiles > 3) issue(3, 3);
-    if (ktiles == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else if (STAGES >= 4 && ktiles > 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NG) : "memory");
-    else if (STAGES >= 3 && ktiles > 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NG) : "memory");
+    if (KG == 1 || nk > 0) issue(0, 0);
+    if (nk > 1) issue(1, 1);
+    if (STAGES >= 3 && nk > 2) issue(2, 2);
+    if (STAGES >= 4 && nk > 3) issue(3, 3);
+    if (KG == 1 ? nk == 1 : nk <= 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else if (STAGES >= 4 && nk > 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NG) : "memory");
+    else if (STAGES >= 3 && nk > 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NG) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NG) : "memory");
     __syncthreads();
 
@@ -525,11 +545,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
 #pragma unroll
     for (int t = 0; t < 3; ++t) ring[t] = load_a(lds, t);
     int stage = 0;                                       // stage holding k-tile kt
-    for (int kt = 0; kt < ktiles; ++kt) {
+    for (int kt = 0; kt < steps; ++kt) {
+        if (KG > 1 && kt >= nk) break;                   // the last trip has no k-tile for this group
         const uint16_t *cur = lds + stage * (STAGE_BYTES / 2);
         const int nstage = stage + 1 == STAGES ? 0 : stage + 1;
         const uint16_t *nxt = lds + nstage * (STAGE_BYTES / 2);
-        const bool more = kt + 1 < ktiles;               // uniform
+        const bool more = kt + 1 < steps;                // uniform
 #pragma unroll
         for (int row = 0; row < ROWS; ++row) {
             const int q = row / FM16, i = row % FM16;
@@ -537,8 +558,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
                 // own reads of this stage are complete before the barrier says so
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 // k-tile kt+1 has landed once only the requests of the tiles after it are outstanding
-                if (STAGES >= 4 && kt + 3 < ktiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NG) : "memory");
-                else if (STAGES >= 3 && kt + 2 < ktiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NG) : "memory");
+                if (STAGES >= 4 && kt + 3 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NG) : "memory");
+                else if (STAGES >= 3 && kt + 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NG) : "memory");
                 else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __syncthreads();
             }
@@ -549,11 +570,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
             // the CU's vector-memory queue and holds up the MFMAs queued behind them.
             if (row >= ROWS - 3) {
                 const int w = row - (ROWS - 3);
-                if (w < SPREAD && more && kt + STAGES < ktiles)
+                if (w < SPREAD && more && kt + STAGES < nk)
                     issue_part(kt + STAGES, stage, w * NG / SPREAD, (w + 1) * NG / SPREAD);
             } else if (row + 3 < SPREAD) {
                 const int w = row + 3;
-                if (kt >= 1 && kt - 1 + STAGES < ktiles)
+                if (kt >= 1 && kt - 1 + STAGES < nk)
                     issue_part(kt - 1 + STAGES, stage == 0 ? STAGES - 1 : stage - 1, w * NG / SPREAD,
                                (w + 1) * NG / SPREAD);
             }
@@ -583,7 +604,38 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();
     // every request has landed and every wavefront is past its last operand read (barrier above):
-    // the stage buffers are free for the epilogue's staging
+    // the stage buffers are free for the groups' exchange and the epilogue's staging.
+    // Each group takes a KG-th of every wavefront's sub-tile to the end: KGM x KGN pieces of EM x EN fragments.
+    constexpr int KGM = FM % KG == 0 ? KG : FM % 2 == 0 && KG % 2 == 0 ? 2 : 1, KGN = KG / KGM;
+    constexpr int EM = FM / KGM, EN = FN / KGN, EWM = WM * KGM, EWN = WN * KGN;
+    static_assert(FM % KGM == 0 && FN % KGN == 0, "pieces of whole fragments");
+    floatx4_t own[KG > 1 ? EM : 1][KG > 1 ? EN : 1][2][2];
+    if constexpr (KG > 1) {
+        floatx4_t *xch = reinterpret_cast<floatx4_t *>(lds_raw);
+        auto slot = [&](int to, int from, int q) {           // quad q of a piece on its way between groups
+            return (((to * (KG - 1) + from) * NW + wave) * (EM * EN * 4) + q) * 64 + lane;
+        };
+#pragma unroll
+        for (int o = 0; o < KG; ++o)
+#pragma unroll
+            for (int q = 0; q < EM * EN * 4; ++q) {
+                const floatx4_t v = acc[o / KGN * EM + q / 4 / EN][o % KGN * EN + q / 4 % EN][(q >> 1) & 1][q & 1];
+                if (kg == o) own[q / 4 / EN][q / 4 % EN][(q >> 1) & 1][q & 1] = v;      // uniform
+                else xch[slot(o, kg < o ? kg : kg - 1, q)] = v;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+            for (int q = 0; q < EM * EN * 4; ++q) own[q / 4 / EN][q / 4 % EN][(q >> 1) & 1][q & 1] += xch[slot(kg, g, q)];
+        __syncthreads();
+    }
+    auto &res = [&]() -> auto & { if constexpr (KG > 1) return own; else return acc; }();
+    // row and column of the piece in the tile (not variables: with one group that changes the addressing of the
+    // whole epilogue, 1 % of a block; with several these expressions in place of them cost 3 % of a projection)
+    const int piece_row = wm * TM + kg / KGN * (EM * 32), piece_col = wn * TN + kg % KGN * (EN * 32);
+    auto prow = [&] { if constexpr (KG > 1) return piece_row; else return wm * TM; };
+    auto pcol = [&] { if constexpr (KG > 1) return piece_col; else return wn * TN; };
     if (ranges > 1) {
         // partial tile, fp32: 16 neighbouring lanes cover 64 contiguous bytes of a row.
         // Divided problem: [range][batch][rows][N]; divided tail: [tail tile][range][BM][BN].
@@ -593,44 +645,43 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(
         const size_t pitch = tail ? BN : N;
         const int rbase = tail ? 0 : row0, cbase = tail ? 0 : col0;
 #pragma unroll
-        for (int jj = 0; jj < 2 * FN; ++jj) {
-            const int lcol = wn * TN + jj * 16 + c16;
+        for (int jj = 0; jj < 2 * EN; ++jj) {
+            const int lcol = pcol() + jj * 16 + c16;
             if (col0 + lcol >= N) continue;
 #pragma unroll
-            for (int ii = 0; ii < 2 * FM; ++ii)
+            for (int ii = 0; ii < 2 * EM; ++ii)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int lrow = wm * TM + ii * 16 + 4 * q16 + e;
+                    const int lrow = prow() + ii * 16 + 4 * q16 + e;
                     if (row0 + lrow < rows)
-                        dst[(size_t)(rbase + lrow) * pitch + cbase + lcol] = acc[ii >> 1][jj >> 1][ii & 1][jj & 1][e];
+                        dst[(size_t)(rbase + lrow) * pitch + cbase + lcol] = res[ii >> 1][jj >> 1][ii & 1][jj & 1][e];
                 }
         }
         return;
     }
-    // per-wavefront staging region; the sub-tile passes through it a few
-    // fragments at a time (fewer per pass when the output is fp32)
-    constexpr int FE = epi_frags(FM), FE32 = epi_frags_f32(BM, BN, WM, WN);
-    static_assert(epi_bytes_f32(BN, WM, WN, FE32) <= kLdsLimit, "fp32 staging");
+    // per-wavefront staging region; the piece passes through it a few fragments at a time (fewer per pass
+    // when the output is fp32)
+    constexpr int FE = epi_frags(EM), FE32 = epi_frags_f32(BM, BN, EWM, EWN);
+    static_assert(epi_bytes_f32(BN, EWM, EWN, FE32) <= kLdsLimit, "fp32 staging");
     char *stage_base = reinterpret_cast<char *>(lds_raw);
     if (ep.out_f32 || ep.residual) {
-        uint16_t *wlds = reinterpret_cast<uint16_t *>(stage_base + wave * (FE32 * 32 * (TN + 4) * 4));
+        uint16_t *wlds = reinterpret_cast<uint16_t *>(stage_base + all_wave * (FE32 * 32 * (EN * 32 + 4) * 4));
 #pragma unroll
-        for (int f0 = 0; f0 < FM; f0 += FE32) {
-            constexpr int dummy = 0; (void)dummy;
-            if (f0 + FE32 <= FM)
-                store_tile_epilogue<FE32, FN, true>(acc + f0, ep, rows, N, row0 + wm * TM + f0 * 32,
-                                                    col0 + wn * TN, lane, wlds);
+        for (int f0 = 0; f0 < EM; f0 += FE32) {
+            if (f0 + FE32 <= EM)
+                store_tile_epilogue<FE32, EN, true>(res + f0, ep, rows, N, row0 + prow() + f0 * 32, col0 + pcol(),
+                                                    lane, wlds);
             else
-                store_tile_epilogue<(FM % FE32 ? FM % FE32 : FE32), FN, true>(
-                    acc + f0, ep, rows, N, row0 + wm * TM + f0 * 32, col0 + wn * TN, lane, wlds);
+                store_tile_epilogue<(EM % FE32 ? EM % FE32 : FE32), EN, true>(
+                    res + f0, ep, rows, N, row0 + prow() + f0 * 32, col0 + pcol(), lane, wlds);
         }
         return;
     }
-    uint16_t *wlds = reinterpret_cast<uint16_t *>(stage_base + wave * (FE * 32 * (TN + 8) * 2));
-    store_tile_epilogue<FE, FN, false>(acc, ep, rows, N, row0 + wm * TM, col0 + wn * TN, lane, wlds);
-    if constexpr (FE < FM)
-        store_tile_epilogue<FM - FE, FN, false>(acc + FE, ep, rows, N, row0 + wm * TM + FE * 32,
-                                                col0 + wn * TN, lane, wlds);
+    uint16_t *wlds = reinterpret_cast<uint16_t *>(stage_base + all_wave * (FE * 32 * (EN * 32 + 8) * 2));
+    store_tile_epilogue<FE, EN, false>(res, ep, rows, N, row0 + prow(), col0 + pcol(), lane, wlds);
+    if constexpr (FE < EM)
+        store_tile_epilogue<EM - FE, EN, false>(res + FE, ep, rows, N, row0 + prow() + FE * 32, col0 + pcol(), lane,
+                                                wlds);
 }
 
 // Sum of the partial tiles of the divided tail + the epilogue (bias, GELU, residual, bf16 or fp32
@@ -665,7 +716,7 @@ __global__ __launch_bounds__(256) void gemm_tail_epilogue_kernel(const float *__
 
 // tail > 1: the tiles beyond the last full round of 256 are divided into `tail` ranges of the
 // contraction axis each (nsplit must be 1 then)
-template <int BM, int BN, int WM, int WN, int STAGES>
+template <int BM, int BN, int WM, int WN, int STAGES, int KG = 1>
 static void launch_gemm_bf16_cfg(const void *A, const void *W, int rows, int N, int K,
                                  const EpiParams &ep, hipStream_t st, int nsplit = 1,
                                  float *part = nullptr, int tail = 1)
@@ -675,10 +726,9 @@ static void launch_gemm_bf16_cfg(const void *A, const void *W, int rows, int N, 
     const int full_tiles = tail > 1 ? ntiles / 256 * 256 : ntiles;
     const int tail_units = (ntiles - full_tiles) * tail;
     const int grid = tail > 1 ? full_tiles + (tail_units + 7) / 8 * 8 : (ntiles * nsplit + 7) / 8 * 8;
-    const size_t lds_stages = (size_t)STAGES * (BM + BN) * BK * sizeof(uint16_t);
-    const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN);
-    const size_t lds = lds_stages > lds_epi ? lds_stages : lds_epi;
-    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES>;
+    constexpr size_t lds = gemm_lds_bytes(BM, BN, WM, WN, STAGES, KG);
+    static_assert(lds <= kLdsLimit, "LDS of a CU");
+    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, KG>;
     // set on every launch: the attribute belongs to the current device's copy of the kernel
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -686,7 +736,7 @@ static void launch_gemm_bf16_cfg(const void *A, const void *W, int rows, int N, 
     // tiles reads g row strips (BM x K) and c column strips (BN x K), with g * c = tiles / 8
     int group_m = (int)lround(sqrt((double)ntiles * BN / (8.0 * BM)));
     group_m = group_m < 1 ? 1 : (group_m > tiles_m ? tiles_m : group_m);
-    launch(kern, dim3(grid), dim3(64 * WM * WN), lds, st, (const uint16_t *)A,
+    launch(kern, dim3(grid), dim3(64 * WM * WN * KG), lds, st, (const uint16_t *)A,
                        (const uint16_t *)W, rows, N, K, tiles_m, tiles_n, group_m, ep, nsplit, part,
                        full_tiles, tail, 1, (size_t)0, (size_t)0, (size_t)0);
     if (tail > 1) {
@@ -698,7 +748,7 @@ static void launch_gemm_bf16_cfg(const void *A, const void *W, int rows, int N, 
 
 // out[b] = A[b] X[b] for nbatch problems with the second operand k-major (X[b]: [K][N], A[b]:
 // [rows][K], `a_bstride` elements apart or shared when 0), bf16 output, no epilogue terms.
-template <int BM, int BN, int WM, int WN, int STAGES>
+template <int BM, int BN, int WM, int WN, int STAGES, int KG = 1>
 static void launch_kmajor_cfg(const void *A, size_t a_bstride, const void *X, int nbatch, int rows,
                               int N, int K, void *out, hipStream_t st)
 {
@@ -707,16 +757,15 @@ static void launch_kmajor_cfg(const void *A, size_t a_bstride, const void *X, in
     const int tiles_m = (rows + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int ntiles = tiles_m * tiles_n * nbatch;
     const int grid = (ntiles + 7) / 8 * 8;
-    const size_t lds_stages = (size_t)STAGES * (BM + BN) * BK * sizeof(uint16_t);
-    const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN);
-    const size_t lds = lds_stages > lds_epi ? lds_stages : lds_epi;
-    auto kern = K % BK ? gemm_bf16_kernel<BM, BN, WM, WN, STAGES, true, false, true>
-                       : gemm_bf16_kernel<BM, BN, WM, WN, STAGES, true>;
+    constexpr size_t lds = gemm_lds_bytes(BM, BN, WM, WN, STAGES, KG);
+    static_assert(lds <= kLdsLimit, "LDS of a CU");
+    auto kern = K % BK ? gemm_bf16_kernel<BM, BN, WM, WN, STAGES, KG, true, false, true>
+                       : gemm_bf16_kernel<BM, BN, WM, WN, STAGES, KG, true>;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     int group_m = (int)lround(sqrt((double)tiles_m * tiles_n * BN / (8.0 * BM)));
     group_m = group_m < 1 ? 1 : (group_m > tiles_m ? tiles_m : group_m);
-    launch(kern, dim3(grid), dim3(64 * WM * WN), lds, st, (const uint16_t *)A, (const uint16_t *)X, rows,
+    launch(kern, dim3(grid), dim3(64 * WM * WN * KG), lds, st, (const uint16_t *)A, (const uint16_t *)X, rows,
            N, K, tiles_m, tiles_n, group_m, ep, 1, (float *)nullptr, ntiles, 1, nbatch, a_bstride,
            (size_t)K * N, (size_t)rows * N);
 }
@@ -727,7 +776,7 @@ static void launch_kmajor_cfg(const void *A, size_t a_bstride, const void *X, in
 // Error against 64 bits of positive values at K = 1024, 2048, 4096 (two shares, at 2048 three) and
 // 4096 (one share): 4.3, 4.2, 4.0 and 3.2e-8, with one chain per share 9.2, 9.2, 17 and 34e-8; 25.6 -> 28.3 us at
 // 4 x (4096 x 4096 x 128).
-template <int BM, int BN, int WM, int WN, int STAGES>
+template <int BM, int BN, int WM, int WN, int STAGES, int KG = 1>
 static void launch_batched_f32_cfg(const void *A, const void *W, int nbatch, int rows, int N, int K,
                                    int parts, float *out, hipStream_t st)
 {
@@ -736,15 +785,14 @@ static void launch_batched_f32_cfg(const void *A, const void *W, int nbatch, int
     const int tiles_m = (rows + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int ntiles = tiles_m * tiles_n * nbatch;
     const int grid = (ntiles * parts + 7) / 8 * 8;
-    const size_t lds_stages = (size_t)STAGES * (BM + BN) * BK * sizeof(uint16_t);
-    const size_t lds_epi = gemm_epi_lds_bytes(BM, BN, WM, WN);
-    const size_t lds = lds_stages > lds_epi ? lds_stages : lds_epi;
-    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, false, true>;
+    constexpr size_t lds = gemm_lds_bytes(BM, BN, WM, WN, STAGES, KG);
+    static_assert(lds <= kLdsLimit, "LDS of a CU");
+    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, KG, false, true>;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     int group_m = (int)lround(sqrt((double)tiles_m * tiles_n * BN / (8.0 * BM)));
     group_m = group_m < 1 ? 1 : (group_m > tiles_m ? tiles_m : group_m);
-    launch(kern, dim3(grid), dim3(64 * WM * WN), lds, st, (const uint16_t *)A, (const uint16_t *)W, rows,
+    launch(kern, dim3(grid), dim3(64 * WM * WN * KG), lds, st, (const uint16_t *)A, (const uint16_t *)W, rows,
            N, K, tiles_m, tiles_n, group_m, ep, parts, out, ntiles, 1, nbatch,
            (size_t)rows * K, (size_t)N * K, (size_t)rows * N);
 }
@@ -798,7 +846,7 @@ void launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int 
     if (p.bm == 256) launch_batched_f32_cfg<256, 128, 4, 2, 3>(A, W, nbatch, rows, N, K, p.parts, out, st);
     else if (p.bm == 128 && narrow) launch_batched_f32_cfg<128, 64, 4, 2, 4>(A, W, nbatch, rows, N, K, p.parts, out, st);
     else if (p.bm == 128) launch_batched_f32_cfg<128, 128, 2, 4, 4>(A, W, nbatch, rows, N, K, p.parts, out, st);
-    else if (narrow) launch_batched_f32_cfg<64, 64, 2, 2, 3>(A, W, nbatch, rows, N, K, p.parts, out, st);
+    else if (narrow) launch_batched_f32_cfg<64, 64, 1, 1, 2, 4>(A, W, nbatch, rows, N, K, p.parts, out, st);
     else launch_batched_f32_cfg<64, 128, 2, 4, 4>(A, W, nbatch, rows, N, K, p.parts, out, st);
 }
 
@@ -838,7 +886,7 @@ bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int
     case 3: launch_kmajor_cfg<128, 256, 2, 4, 3>(qt, q_stride, x, B, rows, d, M, out, st); break;
     case 4: launch_kmajor_cfg<192, 128, 2, 4, 3>(qt, q_stride, x, B, rows, d, M, out, st); break;
     case 5: launch_kmajor_cfg<128, 128, 2, 4, 4>(qt, q_stride, x, B, rows, d, M, out, st); break;
-    case 6: launch_kmajor_cfg<64, 128, 2, 4, 4>(qt, q_stride, x, B, rows, d, M, out, st); break;
+    case 6: launch_kmajor_cfg<64, 128, 2, 2, 3, 2>(qt, q_stride, x, B, rows, d, M, out, st); break;
     default: return false;
     }
     return true;
@@ -1095,6 +1143,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const float *__restri
 // residual 4 % rms; the plan it picks is on average 2 % (worst 27 %) slower than the best
 // candidate of each problem, where one rate per tile and no small tiles cost 30 % (worst 3x).  The
 // undivided timings are in profiles/linear_layer_tile_times.txt, divisions in linear_layer_divisions.txt.
+// The last three tiles' constants were chosen anew, with the others held, on 26800 timings of the same problems
+// when those tiles got wavefront groups: the picks take 26.41 us in geometric mean where the one-group
+// kernels took 26.83 (best candidates 25.8 and 26.3).  The 64x128 and 128x64 constants are 8 and 3 % above the
+// best fit: inside blocks a second layer of 250 to 500 rows lost 1 to 2 % by going over to them.
 constexpr double kLaunchUs = 3.6;      // a launch by itself
 constexpr double kRowsRate = 11.9e6;   // bytes / us that gemm_rows_kernel's workgroups read, L2 hits included
 
@@ -1102,7 +1154,7 @@ struct TileCfg { int bm, bn; double k_us, tile_us; };   // us per k-tile and per
 constexpr TileCfg kTiles[] = {
     {320, 256, 1.745, 4.9}, {256, 256, 1.491, 3.4}, {192, 256, 1.304, 2.0}, {256, 192, 1.289, 2.0},
     {256, 128, 0.896, 1.9}, {128, 256, 0.891, 1.9}, {192, 128, 0.704, 1.3}, {128, 128, 0.537, 0.95},
-    {64, 128, 0.375, 0.3},  {128, 64, 0.364, 0.3},  {64, 64, 0.274, 0.1}};
+    {64, 128, 0.365, 0.3},  {128, 64, 0.315, 0.53}, {64, 64, 0.237, 0.46}};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]), kSmallTile = kNumTiles - 1;
 struct RowsCfg { int ft, tt; double step_us, fixed_us; };   // us per k-step of a wavefront, and once
 constexpr RowsCfg kRows[] = {{1, 1, 0.174, 3.0}, {2, 1, 0.261, 3.3}, {2, 2, 0.281, 3.7}};
@@ -1202,7 +1254,7 @@ void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
     ep.out_f32 = e.out_f32;
     ep.res_f32 = e.res_f32;
     if (dt == DType::BF16) {
-        const int ns = plan.nsplit, tail = plan.tail;
+        const int ns = plan.nsplit, tail = plan.tail, per = (K / BK + ns - 1) / ns;   // k-tiles of a workgroup
         switch (plan.cfg) {
         case 0: launch_gemm_bf16_cfg<320, 256, 2, 4, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
         case 1: launch_gemm_bf16_cfg<256, 256, 2, 4, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
@@ -1212,9 +1264,24 @@ void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
         case 5: launch_gemm_bf16_cfg<128, 256, 2, 4, 3>(A, W, rows, N, K, ep, st, ns, part, tail); break;
         case 6: launch_gemm_bf16_cfg<192, 128, 2, 4, 3>(A, W, rows, N, K, ep, st, ns, part, tail); break;
         case 7: launch_gemm_bf16_cfg<128, 128, 2, 4, 4>(A, W, rows, N, K, ep, st, ns, part, tail); break;
-        case 8: launch_gemm_bf16_cfg<64, 128, 2, 4, 4>(A, W, rows, N, K, ep, st, ns, part, tail); break;
-        case 9: launch_gemm_bf16_cfg<128, 64, 4, 2, 4>(A, W, rows, N, K, ep, st, ns, part, tail); break;
-        case 10: launch_gemm_bf16_cfg<64, 64, 2, 2, 3>(A, W, rows, N, K, ep, st, ns, part, tail); break;
+        // wavefront groups from 16 (64x128: 32) k-tiles per workgroup on; 64x64 only up to one workgroup per CU,
+        // beyond which three workgroups of the one-group kernel share a CU.  Time of one group over time of
+        // several at 2-7, 8-15, 16-31, 32-63 and 64-127 k-tiles: 64x64 0.95, 1.00, 1.06, 1.10, 1.15 (0.75 with
+        // more workgroups than CUs), 64x128 0.96, 0.98, 1.00, 1.01, 1.03, 128x64 0.97, 1.00, 1.06, 1.08, 1.12.
+        case 8:
+            if (per >= 32) launch_gemm_bf16_cfg<64, 128, 2, 2, 3, 2>(A, W, rows, N, K, ep, st, ns, part, tail);
+            else launch_gemm_bf16_cfg<64, 128, 2, 4, 4>(A, W, rows, N, K, ep, st, ns, part, tail);
+            break;
+        case 9:
+            if (per >= 16) launch_gemm_bf16_cfg<128, 64, 2, 2, 3, 2>(A, W, rows, N, K, ep, st, ns, part, tail);
+            else launch_gemm_bf16_cfg<128, 64, 4, 2, 4>(A, W, rows, N, K, ep, st, ns, part, tail);
+            break;
+        case 10:
+            if (per >= 16 && (long)ns * ((rows + 63) / 64) * ((N + 63) / 64) <= 256)
+                launch_gemm_bf16_cfg<64, 64, 1, 1, 2, 4>(A, W, rows, N, K, ep, st, ns, part, tail);
+            else
+                launch_gemm_bf16_cfg<64, 64, 2, 2, 3>(A, W, rows, N, K, ep, st, ns, part, tail);
+            break;
         case kNumTiles + 0: launch_gemm_rows<1, 1>(A, W, rows, N, K, ep, st, ns, part); break;
         case kNumTiles + 1: launch_gemm_rows<2, 1>(A, W, rows, N, K, ep, st, ns, part); break;
         default: launch_gemm_rows<2, 2>(A, W, rows, N, K, ep, st, ns, part); break;

@@ -53,6 +53,19 @@ def test_linear_layers_across_plans(dtype, B, M, d, H, F):
     assert np.array_equal(to_np(blk.V[:, :Lp]), Vp) and bool((blk.V[:, Lp + M:] == 7.0).all())
 
 
+@pytest.mark.parametrize("B,M,d,H,F", [
+    (1, 65, 1088, 17, 1088),      # 64x64 by four groups, 17 k-tiles: the last trip is one group's alone
+    (1, 520, 960, 15, 2240),      # FC2: 64x64 by four groups, 35 k-tiles: one group has none in the last trip
+    (1, 257, 512, 8, 1088),       # FC2: row remainder 1
+    (1, 330, 1088, 17, 4096),     # FC1 (GELU): 128x64 by two groups, 17 k-tiles
+    (1, 400, 960, 15, 4160),      # FC2: the same divided four ways, 17 and 14 k-tiles a workgroup
+    (3, 100, 2048, 16, 2112),     # QKV: 64x128 by two groups, K/V rows routed across samples inside a tile
+])
+def test_linear_layers_by_wavefront_groups(B, M, d, H, F):
+    """The tiles whose k-tiles are dealt to groups of wavefronts: counts that do not divide evenly."""
+    test_linear_layers_across_plans("bf16", B, M, d, H, F)
+
+
 @pytest.mark.parametrize("d,rows", [
     (256, 5), (256, 200),                 # the kernel without staging; small tiles
     (1024, 40), (1024, 969), (1024, 970), (1024, 1152), (1024, 1153), (1024, 1537), (1024, 2048),
