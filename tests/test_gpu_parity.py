@@ -91,6 +91,33 @@ def test_select_on_given_scores(M):
             assert np.array_equal(drop[b].cpu().numpy(), do), (M, k, b)
 
 
+@pytest.mark.parametrize("M", [65, 1024, 2049, 4097, 8193, 12288])
+def test_select_divides_crowded_bins(M):
+    """Score vectors whose first histogram puts nearly everything into one bin, also on the next level,
+    and vectors with infinities; more than 64, exactly 64 and 65 keys in the decisive bin."""
+    rng = np.random.default_rng(M)
+    blk = GpuBlock(64, 1, 64, "f32", {}, np.zeros((1, 0, 1, 64), np.float32),
+                   np.zeros((1, 0, 1, 64), np.float32), 1)
+    near = (1.0 + rng.integers(0, 5000, M) * 2.0 ** -23).astype(np.float32)     # 5000 neighbouring keys
+    outliers = near.copy()
+    outliers[0], outliers[M // 2], outliers[M - 1] = 3e38, -3e38, 1.5
+    nested = np.where(rng.random(M) < 0.5, near, rng.random(M).astype(np.float32) * 1e-3).astype(np.float32)
+    nested[M // 3] = 1e30
+    infinite = outliers.copy()
+    infinite[::5], infinite[1::7] = np.inf, -np.inf
+    groups = np.concatenate([np.full(64, 1.0), np.full(M - 64, 2.0)]).astype(np.float32)
+    groups65 = np.concatenate([np.full(min(65, M), 1.0), np.full(max(M - 65, 0), 1.0 + 2.0 ** -23)]).astype(np.float32)
+    S = np.stack([near, outliers, nested, infinite, groups, groups65, -outliers])
+    sd = torch.from_numpy(S).cuda()
+    for k in sorted({1, 2, 63, 64, 65, M // 4, M // 2, M - 65, M - 64, M - 1, M} & set(range(1, M + 1))):
+        _, keep, drop = blk.score_select(torch.empty((len(S), M, 64), device="cuda"), k, scores_in=sd)
+        torch.cuda.synchronize()
+        for b in range(len(S)):
+            ko, do = oracle.topk(S[b], k)
+            assert np.array_equal(keep[b].cpu().numpy(), ko), (M, k, b)
+            assert np.array_equal(drop[b].cpu().numpy(), do), (M, k, b)
+
+
 # ----------------------------------------------------------------------------- fill
 @pytest.mark.parametrize("dtype,r", [("bf16", 8), ("bf16", 64), ("bf16", 72), ("bf16", 128),
                                      ("bf16", 256), ("f32", 4), ("f32", 32), ("f32", 100)])
