@@ -57,14 +57,6 @@ template <int DH> __device__ __forceinline__ int v_swz(int row)
     return DH == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2);
 }
 
-// Position of workgroup `id` of `count` in a numbering that gives XCD x (= id % 8) the x-th
-// contiguous share of [0, count): a bijection for any count.
-__device__ __forceinline__ int xcd_contiguous(int id, int count)
-{
-    const int x = id & 7, pos = id >> 3, q = count >> 3, r = count & 7;
-    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + pos;
-}
-
 template <int DH, int NQ>
 __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t *__restrict__ q,
                                                         const uint16_t *__restrict__ Kc,

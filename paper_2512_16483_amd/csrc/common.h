@@ -76,6 +76,15 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+// ---------------------------------------------------------------- workgroup numbering
+// Position of workgroup `id` of `count` in a numbering that gives XCD x (= id % 8) the x-th
+// contiguous share of [0, count): a bijection for any count.
+__device__ __forceinline__ int xcd_contiguous(int id, int count)
+{
+    const int x = id & 7, pos = id >> 3, q = count >> 3, r = count & 7;
+    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + pos;
+}
+
 // ---------------------------------------------------------------- launcher interface
 // Every launcher only enqueues kernels on `st`; shapes are validated by the callers in api.hip.
 namespace fvar {

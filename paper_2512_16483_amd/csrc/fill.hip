@@ -30,6 +30,17 @@ __device__ __forceinline__ double group_sum(double v, int width)
     return v;
 }
 
+// 16 bytes of the restored map, past the caches (nontemporal), in which y_keep, w_c and the dirty lines of
+// whatever ran before stay: 67.7 us with ordinary stores, 53.4 with these, where fills follow each other (shape
+// below).  A score pass over the map right after it pays for that if the map fits the 256 MB of last-level cache
+// and gains if it does not: fill + score in a chain of blocks 91 -> 102 us with 210 MB, 29.3 -> 30.9 with 67 MB,
+// 157 -> 148 with 210 to 537 MB, 10.2 -> 9.3 with 7 to 17 MB (100.9, 32.1, 164.6 and 10.3 before either change).
+__device__ __forceinline__ void store_stream(void *dst, const uint4 &v)
+{
+    typedef uint32_t uintx4_t __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store(uintx4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<uintx4_t *>(dst));
+}
+
 // sum of squares of the 8 bf16 (4 fp32) elements of a 16-byte chunk, in fp64
 template <typename T> __device__ __forceinline__ double chunk_energy(const uint4 &c)
 {
@@ -60,9 +71,20 @@ __device__ __forceinline__ void scatter_rows(int blk, const T *__restrict__ y_ke
     uint4 *dst = reinterpret_cast<uint4 *>(y + ((size_t)b * M + dst_row) * d);
     const int nchunk = d / E;
     double e = 0.0;
-    for (int c = lane; c < nchunk; c += 64) {
+    int c = lane;
+    for (; c + 192 < nchunk; c += 256) {            // four chunks in flight per lane
+        uint4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = src[c + 64 * u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            store_stream(dst + c + 64 * u, v[u]);
+            if (parts) e += chunk_energy<T>(v[u]);
+        }
+    }
+    for (; c < nchunk; c += 64) {
         const uint4 v = src[c];
-        dst[c] = v;
+        store_stream(dst + c, v);
         if (parts) e += chunk_energy<T>(v);
     }
     if (parts) {
@@ -74,7 +96,7 @@ __device__ __forceinline__ void scatter_rows(int blk, const T *__restrict__ y_ke
 
 // ------------------------------------------------------------------ pruned rows, bf16 MFMA
 constexpr int kFillCols = 128;              // column slab per workgroup (16 chunks of 16 B per row)
-constexpr int kFillStage = 64 + 8;          // row pitch (elements) of the per-wavefront output staging
+constexpr int kFillStage = 64;              // row pitch (elements) of the per-wavefront output staging
 
 typedef short fill_shortx4_t __attribute__((ext_vector_type(4)));
 
@@ -84,11 +106,21 @@ __device__ __forceinline__ void fill_dma_b128(const void *base, uint32_t byte_of
                  :: "s"(lds_addr), "v"(byte_off), "s"(base) : "memory", "m0");
 }
 
+// Bound by the output's way to memory, as long as every wavefront keeps stores in flight: 4 x 6400 rows of 4096,
+// keep 1/4, rank 128: 76.9 -> 53.4 us (5.0 TB/s; a plain fill of the same map takes 33 and its kept rows' copy
+// 20), 32 x 1600 of 2048, keep 0.3, rank 64: 64.9 -> 50.4.  Before, a group's stores waited for indices that
+// queued behind the stores of the group before it, every MFMA for its own LDS read, and 30 % of the LDS cycles
+// were bank conflicts of the staging tile.
+// Workgroups are numbered so that an XCD gets all slabs of its rows: it then writes whole rows (slabs dealt
+// round robin put every eighth slab of all rows on one XCD: 13.6 -> 12.0 us with scores, 4096 rows of 2048).
 // One launch does both parts: workgroups [0, fill_blocks) restore pruned rows (slab, row share and
 // sample decoded from the block id), the workgroups after them copy kept rows.
-// KSTEPS = ceil(r / 16): 16-wide steps of the contraction.
+// KSTEPS >= ceil(r / 16): 16-wide steps of the contraction, of which the first kFillWholeSteps are whole at
+// every rank that gets this KSTEPS.
 template <int KSTEPS>
-__global__ __launch_bounds__(256) void fill_bf16_kernel(const uint16_t *__restrict__ y_keep,
+constexpr int kFillWholeSteps = KSTEPS <= 4 ? KSTEPS - 1 : KSTEPS == 6 ? 4 : KSTEPS == 8 ? 6 : KSTEPS == 12 ? 8 : 12;
+template <int KSTEPS, bool SCORED>
+__global__ __launch_bounds__(256, KSTEPS + SCORED <= 8 ? 3 : 2) void fill_bf16_kernel(const uint16_t *__restrict__ y_keep,
                                                         const int32_t *__restrict__ idx_keep,
                                                         const int32_t *__restrict__ idx_drop, int M,
                                                         int k, int B, int r, int d,
@@ -104,8 +136,9 @@ __global__ __launch_bounds__(256) void fill_bf16_kernel(const uint16_t *__restri
     }
     constexpr int RP = KSTEPS * 16;                           // slab rows in LDS (k extent, padded)
     const int nd = M - k;
-    const int slab = blockIdx.x % slabs, share = (blockIdx.x / slabs) % row_split;
-    const int b = blockIdx.x / (slabs * row_split);
+    const int unit = xcd_contiguous(blockIdx.x, fill_blocks);
+    const int slab = unit % slabs, share = (unit / slabs) % row_split;
+    const int b = unit / (slabs * row_split);
     extern __shared__ uint4 lds_raw[];
     uint16_t *gs = reinterpret_cast<uint16_t *>(lds_raw);     // [RP][kFillCols], chunks swizzled
     const uint32_t lds_base = (uint32_t)(uintptr_t)lds_raw;
@@ -141,10 +174,14 @@ __global__ __launch_bounds__(256) void fill_bf16_kernel(const uint16_t *__restri
     const int gstep = row_split * 4;
     int grp_row = share * 4 + wave;                             // this wavefront's current group
 
-    // other operand: lane (row rl, half g) holds w_c[row][16s + 8g .. +8)
+    // other operand: lane (row rl, half g) holds w_c[row][16s + 8g .. +8), zeros past r.
     // The token row of a slot comes from idx_drop: that index is fetched two groups ahead of the
     // MFMAs (one group ahead of the w_c fragments it addresses), so neither the fragment loads nor
     // the stores wait for an index at the moment they are issued.
+    // Loads and stores of a wavefront complete in one order, so a load that is waited for in the group that
+    // issues it, or whose place among the stores the compiler does not know, waits for all stores before it
+    // to reach memory.  Hence no branch around a load or a store: slots past the last row repeat that row,
+    // result and all.
     uint4 afrag[2][KSTEPS];
     auto load_row = [&](int grpi) { return drop[min(grpi * 32 + rl, nd - 1)]; };
     auto load_a = [&](int row, uint4 *dst) {
@@ -152,47 +189,60 @@ __global__ __launch_bounds__(256) void fill_bf16_kernel(const uint16_t *__restri
 #pragma unroll
         for (int s = 0; s < KSTEPS; ++s) {
             const int t = 16 * s + 8 * g;
-            dst[s] = t < r ? *reinterpret_cast<const uint4 *>(wrow + t) : make_uint4(0, 0, 0, 0);
+            dst[s] = *reinterpret_cast<const uint4 *>(wrow + (s < kFillWholeSteps<KSTEPS> ? t : min(t, r - 8)));
         }
     };
-    int row_next = 0;                                          // token row of this lane in the next group
-    if (grp_row < groups) load_a(load_row(grp_row), afrag[0]);
-    if (grp_row + gstep < groups) row_next = load_row(grp_row + gstep);
+    int row_cur = load_row(grp_row), row_next = load_row(grp_row + gstep);   // token row of this lane
+    load_a(row_cur, afrag[0]);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
     // one 32-row group: af holds its w_c fragments, af_next receives those of the next group
     auto group = [&](int grp_row, const uint4 *af, uint4 *af_next) {
-        const int j0 = grp_row * 32;
         // destination rows of the 4 row-chunks this lane stores per half (rows it*8 + lane/8)
         int orow[4];
 #pragma unroll
-        for (int it = 0; it < 4; ++it) orow[it] = drop[min(j0 + it * 8 + (lane >> 3), nd - 1)];
-        if (grp_row + gstep < groups) load_a(row_next, af_next);
-        if (grp_row + 2 * gstep < groups) row_next = load_row(grp_row + 2 * gstep);
+        for (int it = 0; it < 4; ++it) orow[it] = __shfl(row_cur, it * 8 + (lane >> 3));
+        row_cur = row_next;
+        load_a(row_next, af_next);
+        row_next = load_row(grp_row + 2 * gstep);
         double erow[4] = {0.0, 0.0, 0.0, 0.0};
-        // two halves of 64 columns: 2 x 32-column accumulator tiles each
-#pragma unroll 1
-        for (int half = 0; half < 2; ++half) {
-            floatx16_t acc[2] = {floatx16_t{0}, floatx16_t{0}};
+        // two halves of 64 columns (one, where the row ends in between): 2 x 32-column accumulator tiles each
 #pragma unroll
-            for (int s = 0; s < KSTEPS; ++s) {
+        for (int half = 0; half < 2; ++half) {
+            if (half == 1 && col0 + 64 >= d) break;            // uniform
+            typedef __attribute__((address_space(3))) fill_shortx4_t lds_shortx4_t;
+            // slab fragments, one step ahead of the MFMAs that use them
+            bf16x8_t gf[2][2];
+            auto load_g = [&](int s, bf16x8_t *dst) {
 #pragma unroll
                 for (int c2 = 0; c2 < 2; ++c2) {
-                    typedef __attribute__((address_space(3))) fill_shortx4_t lds_shortx4_t;
                     const int cb = half * 2 + c2;
                     const uint16_t *src = gs + g_lane + 16 * s * kFillCols + ((cb ^ tj) << 5);
                     const fill_shortx4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4_t *)src);
                     const fill_shortx4_t hi =
                         __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4_t *)(src + 4 * kFillCols));
-                    const bf16x8_t gf = __builtin_bit_cast(
-                        bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                    acc[c2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        gf, __builtin_bit_cast(bf16x8_t, af[s]), acc[c2], 0, 0, 0);
+                    dst[c2] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
                 }
+            };
+            floatx16_t acc[2] = {floatx16_t{0}, floatx16_t{0}};
+            load_g(0, gf[0]);
+#pragma unroll
+            for (int s = 0; s < KSTEPS; ++s) {
+                if (s + 1 < KSTEPS) load_g(s + 1, gf[(s + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                const uint4 av = s < kFillWholeSteps<KSTEPS> || 16 * s + 8 * g < r ? af[s] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+                for (int c2 = 0; c2 < 2; ++c2)
+                    acc[c2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        gf[s & 1][c2], __builtin_bit_cast(bf16x8_t, av), acc[c2], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
             // accumulator entry e of tile c2: token row rl, slab column 32*cb + 8*(e/4) + 4*g + e%4.
-            // Pack 4 consecutive columns and park them row-major in this wavefront's staging tile.
+            // Pack 4 consecutive columns and park them row-major in this wavefront's staging tile, whose
+            // 16-byte chunks are swizzled (chunk ^ (row / 2) % 8) and, from row 16 on, have their halves
+            // swapped: the 32 lanes that write at once (8 bytes of 32 rows) and the 16 that read (two rows)
+            // then cover all 64 banks once.
 #pragma unroll
             for (int c2 = 0; c2 < 2; ++c2)
 #pragma unroll
@@ -200,37 +250,38 @@ __global__ __launch_bounds__(256) void fill_bf16_kernel(const uint16_t *__restri
                     uint2 pk;
                     pk.x = pack_bf16x2(acc[c2][4 * q], acc[c2][4 * q + 1]);
                     pk.y = pack_bf16x2(acc[c2][4 * q + 2], acc[c2][4 * q + 3]);
-                    *reinterpret_cast<uint2 *>(wl + rl * kFillStage + c2 * 32 + 8 * q + 4 * g) = pk;
+                    *reinterpret_cast<uint2 *>(wl + rl * kFillStage + (((c2 * 4 + q) ^ ((rl >> 1) & 7)) << 3) +
+                                               4 * (g ^ (rl >> 4))) = pk;
                 }
             // same wavefront wrote and reads the region: LDS operations of a wavefront stay in order
             // in hardware; the compiler is told not to move them across these points (the stores
             // and loads use different vector types).
             // 8 lanes cover the 128 bytes of one row half: 8 rows per store instruction.
             asm volatile("" ::: "memory");
-            const int c = (lane & 7) * 8;
+            uint4 v[4];
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
-                const int lrow = it * 8 + (lane >> 3), rr = j0 + lrow;
-                const uint4 v = *reinterpret_cast<const uint4 *>(wl + lrow * kFillStage + c);
-                const int col = col0 + half * 64 + c;
-                const bool ok = rr < nd && col < d;
-                if (ok) *reinterpret_cast<uint4 *>(Y + (size_t)orow[it] * d + col) = v;
-                if (parts && ok) erow[it] += chunk_energy<uint16_t>(v);
+                const int lrow = it * 8 + (lane >> 3);
+                v[it] = *reinterpret_cast<const uint4 *>(wl + lrow * kFillStage +
+                                                         (((lane & 7) ^ ((lrow >> 1) & 7)) << 3));
+                if (it >= 2) v[it] = make_uint4(v[it].z, v[it].w, v[it].x, v[it].y);
+            }
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                store_stream(Y + (size_t)orow[it] * d + col0 + half * 64 + (lane & 7) * 8, v[it]);
+                if (SCORED) erow[it] += chunk_energy<uint16_t>(v[it]);
             }
             asm volatile("" ::: "memory");
         }
         // the 8 lanes of a group hold the pieces of one row; the lane at their head owns rows
         // it*8 + lane/8 of the group
-        double e8[4];
-        if (parts) {
+        if constexpr (SCORED) {
+            double e8[4];
 #pragma unroll
             for (int it = 0; it < 4; ++it) e8[it] = group_sum(erow[it], 8);
-        }
-        if (parts && (lane & 7) == 0) {
+            if ((lane & 7) == 0) {
 #pragma unroll
-            for (int it = 0; it < 4; ++it) {
-                const int rr = j0 + it * 8 + (lane >> 3);
-                if (rr < nd) parts[((size_t)b * M + orow[it]) * slabs + slab] = e8[it];
+                for (int it = 0; it < 4; ++it) parts[((size_t)b * M + orow[it]) * slabs + slab] = e8[it];
             }
         }
     };
@@ -286,17 +337,20 @@ __global__ __launch_bounds__(256) void fill_f32_kernel(const float *__restrict__
 }
 
 // Row energies of the restored map from the per-slab parts: scores[row] = fl32(sum of the row's
-// parts in slab order), one thread per row.
+// parts).  `width` neighbouring lanes (a power of two, at most 16) share a row: with one thread per row the
+// 4096 rows of a single image are 16 workgroups, each a chain of 16 loads 128 bytes apart.
 __global__ __launch_bounds__(256) void scores_from_parts_kernel(const double *__restrict__ parts,
-                                                                int nparts, long rows,
+                                                                int nparts, int width, long rows,
                                                                 float *__restrict__ scores)
 {
-    const long row = (long)blockIdx.x * 256 + threadIdx.x;
-    if (row >= rows) return;
+    const long t = (long)blockIdx.x * 256 + threadIdx.x, row = t / width;
+    const int l = (int)(t % width);
+    if (row >= rows) return;                               // the lanes of a row together
     const double *p = parts + (size_t)row * nparts;
     double acc = 0.0;
-    for (int i = 0; i < nparts; ++i) acc += p[i];
-    scores[row] = (float)acc;
+    for (int i = l; i < nparts; i += width) acc += p[i];
+    acc = group_sum(acc, width);
+    if (l == 0) scores[row] = (float)acc;
 }
 
 // ------------------------------------------------------------------ raw cached rows
@@ -359,13 +413,14 @@ static void launch_fill_bf16(const void *y_keep, const int32_t *idx_keep, const 
     const int scatter_blocks = (B * k + 3) / 4;
     const int slabs = (d + kFillCols - 1) / kFillCols;
     const int groups = (nd + 31) / 32;                      // 32-row groups, one wavefront each
-    // enough workgroups to cover the chip a few times while the slab staging stays amortised
-    int row_split = nd > 0 ? (1536 + slabs * B - 1) / (slabs * B) : 0;
+    // one round of the three workgroups that a CU holds: each stages its slab once (with two rounds 71.2 us
+    // where one takes 67.7 at 4 x 6400 rows of 4096, rank 128, 62.5 and 60.6 at 32 x 1600 of 2048, rank 64)
+    int row_split = nd > 0 ? (768 + slabs * B - 1) / (slabs * B) : 0;
     const int max_split = (groups + 3) / 4;
     if (row_split > max_split) row_split = max_split;
     const int fill_blocks = slabs * row_split * B;
     const size_t lds = nd > 0 ? ((size_t)KSTEPS * 16 * kFillCols + 4 * 32 * kFillStage) * sizeof(uint16_t) : 0;
-    auto kern = fill_bf16_kernel<KSTEPS>;
+    auto kern = parts ? fill_bf16_kernel<KSTEPS, true> : fill_bf16_kernel<KSTEPS, false>;
     if (lds > 48 * 1024)
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -404,8 +459,11 @@ void launch_fill(DType dt, const void *y_keep, const int32_t *idx_keep, const in
     }
     if (parts && scores_out) {
         const long rows = (long)B * M;
-        launch(scores_from_parts_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st,
-               (const double *)parts, fill_score_parts(dt, d), rows, scores_out);
+        const int nparts = fill_score_parts(dt, d);
+        int width = 1;
+        while (2 * width <= nparts && width < 16) width *= 2;
+        launch(scores_from_parts_kernel, dim3((unsigned)((rows * width + 255) / 256)), dim3(256), 0, st,
+               (const double *)parts, nparts, width, rows, scores_out);
     }
 }
 
