@@ -602,7 +602,7 @@ size_t fvar_factors_workspace_bytes(const fvar_ctx *c, int32_t B, int32_t M, int
     if (!c || B < 1 || M < 1 || r < 1) return 0;
     const size_t rr = (size_t)B * r * r * sizeof(double);
     return align256(fvar::factor_t_room(dtype(c), B, M, c->cfg.hidden) * r * sizeof(float)) +
-           align256(rr * fvar::gram_parts(dtype(c))) + align256(rr);
+           align256(rr * fvar::gram_room(dtype(c))) + align256(rr);
 }
 
 fvar_status fvar_cache_factors(fvar_ctx *c, fvar_stream stream, const void *cache, const void *qt,
@@ -633,7 +633,7 @@ fvar_status fvar_cache_factors(fvar_ctx *c, fvar_stream stream, const void *cach
     float *T = reinterpret_cast<float *>(p);
     p += align256(fvar::factor_t_room(dtype(c), B, M, c->cfg.hidden) * r * sizeof(float));
     double *S = reinterpret_cast<double *>(p);
-    p += align256((size_t)B * r * r * sizeof(double) * fvar::gram_parts(dtype(c)));
+    p += align256((size_t)B * r * r * sizeof(double) * fvar::gram_room(dtype(c)));
     double *Sinv = reinterpret_cast<double *>(p);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const DType dt = dtype(c);
@@ -641,9 +641,10 @@ fvar_status fvar_cache_factors(fvar_ctx *c, fvar_stream stream, const void *cach
     timed(c, st, "factor_project", [&] {
         fvar::launch_rp_project(dt, qt, q_per_sample ? (size_t)r * M : 0, cache, B, M, r, d, g_c, st);
     });
-    timed(c, st, "factor_t", [&] { fvar::launch_factor_t(dt, cache, g_c, B, M, r, d, T, st); });
     timed(c, st, "factor_gram", [&] { fvar::launch_factor_gram(dt, g_c, B, r, d, S, st); });
-    timed(c, st, "factor_inverse", [&] { fvar::launch_factor_inverse(S, fvar::gram_parts(dt), B, r, ridge, Sinv, st); });
+    timed(c, st, "factor_t_inverse", [&] {
+        fvar::launch_factor_t_inverse(dt, cache, g_c, B, M, r, d, T, S, ridge, Sinv, st);
+    });
     timed(c, st, "factor_w", [&] { fvar::launch_factor_w(dt, T, Sinv, B, M, r, d, w_c, st); });
     return launch_status(c, who);
 }

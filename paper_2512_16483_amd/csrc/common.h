@@ -181,8 +181,11 @@ void launch_cache_fill(DType dt, const void *y_keep, const int32_t *idx_keep, co
 // out:[B,rows,d].  M must be a multiple of the 16-byte chunk (8 bf16 / 4 fp32 elements).
 int batched_f32_parts(int nbatch, int rows, int N, int K);
 size_t batched_f32_room(int nbatch, int rows, int K);
+// ... and in the same launch the inverse of each problem's N x N matrix, the sum of kGramParts (see spd_inverse)
+constexpr int kGramParts = 4;              // partial matrices that the bf16 Gram matrix comes in
+struct InverseJob { const double *S; double ridge; double *Sinv; int r; };
 void launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int rows, int N, int K,
-                                  float *out, hipStream_t st);
+                                  float *out, const InverseJob &inv, hipStream_t st);
 bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int B, int M, int rows,
                              int d, void *out, hipStream_t st);
 void launch_rp_project(DType dt, const void *qt, size_t q_stride, const void *x, int B, int M,
@@ -193,16 +196,16 @@ void launch_rp_project(DType dt, const void *qt, size_t q_stride, const void *x,
 void launch_upsample(DType dt, const void *src, int B, int hs, int ws, int hd, int wd, int c,
                      void *dst, hipStream_t st);
 
-// restoration matrix W_c = (C G_c^T)(G_c G_c^T)^{-1} in four steps; T:[factor_t_parts,B,M,r] fp32 (factor_t_room rows),
-// S:[B,gram_parts(dt),r,r] and Sinv:[B,r,r] fp64 are scratch.  r <= 128.
+// restoration matrix W_c = (C G_c^T)(G_c G_c^T)^{-1}; T:[factor_t_parts,B,M,r] fp32 (factor_t_room rows),
+// S and Sinv:[B,r,r] fp64 are scratch, S with room for gram_room matrices.  r <= 128.
 int factor_t_parts(DType dt, int B, int M, int r, int d);
 size_t factor_t_room(DType dt, int B, int M, int d);
-void launch_factor_t(DType dt, const void *cache, const void *g_c, int B, int M, int r, int d, float *T,
-                     hipStream_t st);
+int gram_room(DType dt);
 void launch_factor_gram(DType dt, const void *g_c, int B, int r, int d, double *S, hipStream_t st);
-int gram_parts(DType dt);
 void launch_factor_inverse(const double *S, int parts, int B, int r, double ridge, double *Sinv,
                            hipStream_t st);
+void launch_factor_t_inverse(DType dt, const void *cache, const void *g_c, int B, int M, int r, int d, float *T,
+                             const double *S, double ridge, double *Sinv, hipStream_t st);
 void launch_factor_w(DType dt, const float *T, const double *Sinv, int B, int M, int r, int d, void *w_c,
                      hipStream_t st);
 

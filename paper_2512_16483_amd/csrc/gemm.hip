@@ -21,9 +21,11 @@
 #include <type_traits>
 
 #include "common.h"
+#include "spd_inverse.h"
 
 namespace fvar {
 
+struct NoJob {};
 struct EpiParams {
     const void *bias;
     const void *residual;
@@ -304,14 +306,16 @@ constexpr size_t gemm_lds_bytes(int BM, int BN, int WM, int WN, int STAGES, int 
 //
 // CHAINS: no fp32 accumulation runs over more than a few k-tiles; the results of these chains are added
 // up, with compensation, in a second set of registers.  For a result that meets the inverse of a Gram
-// matrix, which magnifies its rounding when it is badly conditioned.
+// matrix, which magnifies its rounding when it is badly conditioned.  The first workgroups of such a launch, one
+// per problem in whole rounds of the XCDs, invert that matrix, which takes as long as the product or longer and
+// a CU each.
 template <int BM, int BN, int WM, int WN, int STAGES, int KG = 1, bool BKM = false, bool CHAINS = false,
           bool RAGGED = false>
 __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(
     const uint16_t *__restrict__ A_in, const uint16_t *__restrict__ W_in, int rows, int N, int K,
     int tiles_m, int tiles_n, int group_m, EpiParams ep, int nsplit, float *__restrict__ part,
     int full_tiles, int tail_split, int nbatch, size_t a_bstride, size_t w_bstride,
-    size_t o_bstride)
+    size_t o_bstride, std::conditional_t<CHAINS, InverseJob, NoJob> inv)
 {
     const uint16_t *A = A_in, *W = W_in;
     constexpr int NW = WM * WN;                        // wavefronts per group
@@ -321,6 +325,24 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(
     constexpr int NG = NGA + NGB;                      // DMA instructions per lane per k-tile
     constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
     extern __shared__ uint4 lds_raw[];
+    int wg = blockIdx.x, nwg = gridDim.x;
+    if constexpr (CHAINS) {
+        const int ahead = (nbatch + 7) & ~7;
+        if (wg < ahead) {
+            constexpr int NW_ALL = WM * WN * KG;
+            double *mat = reinterpret_cast<double *>(lds_raw);
+            if (wg >= nbatch) return;
+            const int r = inv.r;
+            const double *S = inv.S + (size_t)wg * kGramParts * r * r;
+            double *Sinv = inv.Sinv + (size_t)wg * r * r;
+            if (r <= 32) spd_inverse<2, NW_ALL>(S, kGramParts, r, inv.ridge, Sinv, mat);
+            else if (BN == 64 || r <= 64) spd_inverse<4, NW_ALL>(S, kGramParts, r, inv.ridge, Sinv, mat);
+            else if constexpr (BN > 64) spd_inverse<8, NW_ALL>(S, kGramParts, r, inv.ridge, Sinv, mat);
+            return;
+        }
+        wg -= ahead;
+        nwg -= ahead;
+    }
     uint32_t lds_base = (uint32_t)(uintptr_t)lds_raw;
 
     // Work decomposition.  Workgroups are dealt to the 8 XCDs round-robin; XCD x takes the x-th
@@ -334,7 +356,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(
     //    the whole tiles first and an eighth of the divided ones after them.
     // Partial tiles are summed and finished by a second kernel.
     const int ntiles = tiles_m * tiles_n * nbatch;
-    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+    const int xcd = wg % 8, slot = wg / 8;
     int pid, split = 0, ranges = 1;
     if (tail_split > 1) {
         const int nf = full_tiles / 8, tail_units = (ntiles - full_tiles) * tail_split;
@@ -349,7 +371,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(
             ranges = tail_split;
         }
     } else {
-        const int per_xcd = (gridDim.x + 7) / 8;
+        const int per_xcd = (nwg + 7) / 8;
         pid = xcd * per_xcd + slot;
         if (pid >= ntiles * nsplit) return;
         split = pid % nsplit;
@@ -738,7 +760,7 @@ static void launch_gemm_bf16_cfg(const void *A, const void *W, int rows, int N, 
     group_m = group_m < 1 ? 1 : (group_m > tiles_m ? tiles_m : group_m);
     launch(kern, dim3(grid), dim3(64 * WM * WN * KG), lds, st, (const uint16_t *)A,
                        (const uint16_t *)W, rows, N, K, tiles_m, tiles_n, group_m, ep, nsplit, part,
-                       full_tiles, tail, 1, (size_t)0, (size_t)0, (size_t)0);
+                       full_tiles, tail, 1, (size_t)0, (size_t)0, (size_t)0, NoJob{});
     if (tail > 1) {
         const long total = (long)(ntiles - full_tiles) * BM * (BN / 4);
         launch(gemm_tail_epilogue_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
@@ -767,7 +789,7 @@ static void launch_kmajor_cfg(const void *A, size_t a_bstride, const void *X, in
     group_m = group_m < 1 ? 1 : (group_m > tiles_m ? tiles_m : group_m);
     launch(kern, dim3(grid), dim3(64 * WM * WN * KG), lds, st, (const uint16_t *)A, (const uint16_t *)X, rows,
            N, K, tiles_m, tiles_n, group_m, ep, 1, (float *)nullptr, ntiles, 1, nbatch, a_bstride,
-           (size_t)K * N, (size_t)rows * N);
+           (size_t)K * N, (size_t)rows * N, NoJob{});
 }
 
 // out[p][b] = share p of the contraction of A[b] W[b]^T, in fp32, for nbatch problems of one shape (A[b]:
@@ -778,14 +800,15 @@ static void launch_kmajor_cfg(const void *A, size_t a_bstride, const void *X, in
 // 4 x (4096 x 4096 x 128).
 template <int BM, int BN, int WM, int WN, int STAGES, int KG = 1>
 static void launch_batched_f32_cfg(const void *A, const void *W, int nbatch, int rows, int N, int K,
-                                   int parts, float *out, hipStream_t st)
+                                   int parts, float *out, const InverseJob &inv, hipStream_t st)
 {
     EpiParams ep{};
     ep.out0 = out; ep.ld0 = N; ep.split = N; ep.N = N; ep.rows_per_sample = 1; ep.out_f32 = 1;
     const int tiles_m = (rows + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const int ntiles = tiles_m * tiles_n * nbatch;
-    const int grid = (ntiles * parts + 7) / 8 * 8;
+    const int grid = (nbatch + 7) / 8 * 8 + (ntiles * parts + 7) / 8 * 8;
     constexpr size_t lds = gemm_lds_bytes(BM, BN, WM, WN, STAGES, KG);
+    static_assert(lds >= spd_inverse_lds(BN > 64 ? 8 : 4), "the inverse's tables fit the rings");
     static_assert(lds <= kLdsLimit, "LDS of a CU");
     auto kern = gemm_bf16_kernel<BM, BN, WM, WN, STAGES, KG, false, true>;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -794,7 +817,7 @@ static void launch_batched_f32_cfg(const void *A, const void *W, int nbatch, int
     group_m = group_m < 1 ? 1 : (group_m > tiles_m ? tiles_m : group_m);
     launch(kern, dim3(grid), dim3(64 * WM * WN * KG), lds, st, (const uint16_t *)A, (const uint16_t *)W, rows,
            N, K, tiles_m, tiles_n, group_m, ep, parts, out, ntiles, 1, nbatch,
-           (size_t)rows * K, (size_t)N * K, (size_t)rows * N);
+           (size_t)rows * K, (size_t)N * K, (size_t)rows * N, inv);
 }
 
 // Output rows, over all shares and problems, that a plan never exceeds: the shares it may take (each at
@@ -821,6 +844,10 @@ static BatchedPlan batched_f32_plan(int nbatch, int rows, int N, int K)
     // (4096 x 4096 x 128): 280 us with 256 rows, 306 with 128; with 64 columns of G 87 and 92)
     const double bytes = nbatch * (2.0 * ((double)rows + N) * K + 4.0 * rows * N);
     const double hbm_us = bytes > 256e6 ? bytes / 5.5e6 : 0.0;
+    // the inverse of the same launch takes that long in any case, and a CU per problem (4 samples at rank 128:
+    // one share instead of two for the kernel that reads them, 132.8 -> 128.1 us in all)
+    const double inverse_us = (N <= 64 ? 0.22 : 0.39) * N;
+    const int cus = nbatch <= 32 ? 256 - nbatch : 256;
     BatchedPlan best{256, 1};
     double best_us = 1e300;
     for (const auto &c : cands)
@@ -830,7 +857,8 @@ static BatchedPlan batched_f32_plan(int nbatch, int rows, int N, int K)
                               (size_t)parts * nbatch * rows > batched_f32_room(nbatch, rows, K)))
                 continue;
             const long tiles = (long)((rows + c.bm - 1) / c.bm) * nbatch;
-            const double us = fmax(hbm_us, (double)((tiles * parts + 255) / 256) * (c.tile_us + c.k_us * per)) +
+            const double rounds = (double)((tiles * parts + cus - 1) / cus);
+            const double us = fmax(fmax(hbm_us, inverse_us), rounds * (c.tile_us + c.k_us * per)) +
                               (parts - 1) * (1.0 + 8.0 * nbatch * rows * N / kMergeRate);
             if (us < best_us) { best_us = us; best = {c.bm, parts}; }
         }
@@ -839,15 +867,15 @@ static BatchedPlan batched_f32_plan(int nbatch, int rows, int N, int K)
 int batched_f32_parts(int nbatch, int rows, int N, int K) { return batched_f32_plan(nbatch, rows, N, K).parts; }
 
 void launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int rows, int N, int K,
-                                  float *out, hipStream_t st)
+                                  float *out, const InverseJob &inv, hipStream_t st)
 {
     const BatchedPlan p = batched_f32_plan(nbatch, rows, N, K);
     const bool narrow = N <= 64;
-    if (p.bm == 256) launch_batched_f32_cfg<256, 128, 4, 2, 3>(A, W, nbatch, rows, N, K, p.parts, out, st);
-    else if (p.bm == 128 && narrow) launch_batched_f32_cfg<128, 64, 4, 2, 4>(A, W, nbatch, rows, N, K, p.parts, out, st);
-    else if (p.bm == 128) launch_batched_f32_cfg<128, 128, 2, 4, 4>(A, W, nbatch, rows, N, K, p.parts, out, st);
-    else if (narrow) launch_batched_f32_cfg<64, 64, 1, 1, 2, 4>(A, W, nbatch, rows, N, K, p.parts, out, st);
-    else launch_batched_f32_cfg<64, 128, 2, 4, 4>(A, W, nbatch, rows, N, K, p.parts, out, st);
+    if (p.bm == 256) launch_batched_f32_cfg<256, 128, 4, 2, 3>(A, W, nbatch, rows, N, K, p.parts, out, inv, st);
+    else if (p.bm == 128 && narrow) launch_batched_f32_cfg<128, 64, 4, 2, 4>(A, W, nbatch, rows, N, K, p.parts, out, inv, st);
+    else if (p.bm == 128) launch_batched_f32_cfg<128, 128, 2, 4, 4>(A, W, nbatch, rows, N, K, p.parts, out, inv, st);
+    else if (narrow) launch_batched_f32_cfg<64, 64, 1, 1, 2, 4>(A, W, nbatch, rows, N, K, p.parts, out, inv, st);
+    else launch_batched_f32_cfg<64, 128, 2, 4, 4>(A, W, nbatch, rows, N, K, p.parts, out, inv, st);
 }
 
 // Runs out[b] = qt[b] x[b] (qt: [rows][M] per sample or shared, x[b]: [M][d]) on the tiled MFMA
