@@ -8,6 +8,7 @@ import torch
 
 import oracle
 from oracle import factors
+import paper_2512_16483_amd as fv
 import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -426,3 +427,46 @@ def test_pruned_path_random_geometry(seed):
     for b in range(B):
         check_map(f"b{b}", to_np(y[b]), to_np(y_keep[b]), ref["idx_keep"][b], ref["idx_drop"][b],
                   ref["y"][b], tol)
+
+
+# ----------------------------------------------------------------------------- LayerNorm affine
+@pytest.mark.parametrize("d", [64, 320, 1088, 2112, 4160, 8192])
+@pytest.mark.parametrize("which", ["gb", "g", "b"])
+def test_layernorm_affine_batches(which, d):
+    """Both LayerNorms of a block with gamma, beta or both, at widths whose chunks end inside, at and past a
+    batch of affine loads.  With identity weights and no attention output the appended keys are LN1(x), rounded
+    once, and y = x + gelu(LN2(x)), rounded at LN2, at the GELU (slope at most 1.13) and at y: each at most
+    2^-8 of its value (bf16 stores 7 bits of the fraction: half a unit in the last), and 1e-4 for the fp32
+    statistics."""
+    rng = np.random.default_rng(d)
+    M = 7
+    x = torch.from_numpy(rng.standard_normal((1, M, d)).astype(np.float32)).to(torch.bfloat16).cuda()
+    eye = torch.eye(d, dtype=torch.bfloat16, device="cuda")
+    w = {"w_qkv": torch.cat([eye, eye, eye]), "w_o": torch.zeros_like(eye), "w_fc1": eye, "w_fc2": eye}
+    for n in ("ln1", "ln2"):
+        if "g" in which:
+            w[n + "_g"] = torch.from_numpy(1 + 0.3 * rng.standard_normal(d).astype(np.float32)).to(torch.bfloat16).cuda()
+        if "b" in which:
+            w[n + "_b"] = torch.from_numpy(rng.standard_normal(d).astype(np.float32)).to(torch.bfloat16).cuda()
+    ctx = fv.Context(hidden=d, heads=d // 64, head_dim=64, ffn_hidden=d, dtype="bf16")
+    K = torch.zeros((1, M, d // 64, 64), dtype=torch.bfloat16, device="cuda")
+    V, y = torch.zeros_like(K), torch.empty_like(x)
+    ws = torch.empty(fv.fvar_block_workspace_bytes(ctx, 1, M), dtype=torch.uint8, device="cuda")
+    fv.fvar_block_forward_dense(ctx, w, x, 1, M, K, V, M, 0, y, ws)
+    torch.cuda.synchronize()
+
+    def ln(n):
+        v = x.double()
+        v = v - v.mean(-1, keepdim=True)
+        v = v / torch.sqrt((v * v).mean(-1, keepdim=True) + 1e-6)
+        v = v * w[n + "_g"].double() if "g" in which else v
+        return v + w[n + "_b"].double() if "b" in which else v
+
+    u1, u2 = ln("ln1"), ln("ln2")
+    err = (K.reshape(1, M, d).double() - u1).abs()
+    assert torch.equal(K, V) and bool((err <= 2.0 ** -8 * u1.abs() + 1e-4).all()), float(err.max())
+    g = torch.nn.functional.gelu(u2, approximate="tanh")
+    ref = x.double() + g
+    err = (y.double() - ref).abs()
+    bound = 2.0 ** -8 * (1.13 * u2.abs() + g.abs() + ref.abs()) * 1.01 + 1e-4
+    assert bool((err <= bound).all()), float((err - bound).max())
