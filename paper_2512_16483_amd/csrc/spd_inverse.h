@@ -70,8 +70,9 @@ constexpr size_t spd_inverse_lds(int NB) { return ((size_t)3 * 16 * NB * 17 + 16
 // u / d go through LDS, three barriers per block.  Steps of the padding are left out.
 // Bound by the chain of steps, 500 clk each, and at rank 128 by the rank-16 updates, 5000 clk per block.  (Columns
 // held one per lane, with the pivot column as scalar operands by readlane, take 500 to 560 clk per step too:
-// 32 readlanes and 32 fp64 operations, with nothing else to issue from.)  Inside a call, rank 128: 65 -> 50 us
-// with half the matrices to read and their loads in flight together, where one element waited for the last.
+// 32 readlanes and 32 fp64 operations, with nothing else to issue from.)  Inside a call, 4 samples at
+// rank 128: 65 us in a launch of its own -> 58 in T's launch (which took 28), reading half the matrices with their
+// loads in flight together, where one element waited for the last.
 // A singular matrix yields non-finite output.
 template <int NB, int NW>
 __device__ __forceinline__ void spd_inverse(const double *__restrict__ Sb, int parts, int r, double ridge,
