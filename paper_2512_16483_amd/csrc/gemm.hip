@@ -1171,10 +1171,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const float *__restri
 // residual 4 % rms; the plan it picks is on average 2 % (worst 27 %) slower than the best
 // candidate of each problem, where one rate per tile and no small tiles cost 30 % (worst 3x).  The
 // undivided timings are in profiles/linear_layer_tile_times.txt, divisions in linear_layer_divisions.txt.
-// The last three tiles' constants were chosen anew, with the others held, on 26800 timings of the same problems
-// when those tiles got wavefront groups: the picks take 26.41 us in geometric mean where the one-group
-// kernels took 26.83 (best candidates 25.8 and 26.3).  The 64x128 and 128x64 constants are 8 and 3 % above the
-// best fit: inside blocks a second layer of 250 to 500 rows lost 1 to 2 % by going over to them.
+// With wavefront groups the last three tiles have constants of their own (kGroupedTiles), used exactly where the
+// launch takes them.  With these for the kernels without groups too, 320 workgroups of 64x64 looked 10 % cheaper than
+// they are: on 139 problems where the picks differ 16.6 us in geometric mean instead of 15.8, at worst 1536 x 6144
+// with 703 rows 40.5 instead of 28.1, and 128x64 divided eight ways took more workspace than 64x64 in five.
 constexpr double kLaunchUs = 3.6;      // a launch by itself
 constexpr double kRowsRate = 11.9e6;   // bytes / us that gemm_rows_kernel's workgroups read, L2 hits included
 
@@ -1182,10 +1182,21 @@ struct TileCfg { int bm, bn; double k_us, tile_us; };   // us per k-tile and per
 constexpr TileCfg kTiles[] = {
     {320, 256, 1.745, 4.9}, {256, 256, 1.491, 3.4}, {192, 256, 1.304, 2.0}, {256, 192, 1.289, 2.0},
     {256, 128, 0.896, 1.9}, {128, 256, 0.891, 1.9}, {192, 128, 0.704, 1.3}, {128, 128, 0.537, 0.95},
-    {64, 128, 0.365, 0.3},  {128, 64, 0.315, 0.53}, {64, 64, 0.237, 0.46}};
+    {64, 128, 0.375, 0.3},  {128, 64, 0.364, 0.3},  {64, 64, 0.274, 0.1}};
+constexpr TileCfg kGroupedTiles[] = {{64, 128, 0.365, 0.3}, {128, 64, 0.315, 0.53}, {64, 64, 0.237, 0.46}};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]), kSmallTile = kNumTiles - 1;
-struct RowsCfg { int ft, tt; double step_us, fixed_us; };   // us per k-step of a wavefront, and once
-constexpr RowsCfg kRows[] = {{1, 1, 0.174, 3.0}, {2, 1, 0.261, 3.3}, {2, 2, 0.281, 3.7}};
+// Whether `workgroups` workgroups of `per` k-tiles each run with wavefront groups: from 16 (64x128: 32) k-tiles on,
+// 64x64 only up to one workgroup per CU, beyond which three workgroups of the one-group kernel share a CU.  Time of
+// one group over time of several at 2-7, 8-15, 16-31, 32-63 and 64-127 k-tiles: 64x64 0.95, 1.00, 1.06, 1.10, 1.15
+// (0.75 with more workgroups than CUs), 64x128 0.96, 0.98, 1.00, 1.01, 1.03, 128x64 0.97, 1.00, 1.06, 1.08, 1.12.
+static bool in_groups(int cfg, int per, long workgroups)
+{
+    return cfg == 8 ? per >= 32 : cfg == 9 ? per >= 16 : cfg == kSmallTile && per >= 16 && workgroups <= 256;
+}
+// us per k-step of a wavefront, once, and for every further round of workgroups over the CUs (only the largest fills
+// a CU with one: 192 workgroups 9.0 us, 288 12.2 at 3072 x 768)
+struct RowsCfg { int ft, tt; double step_us, fixed_us, round_us; };
+constexpr RowsCfg kRows[] = {{1, 1, 0.174, 3.0, 0.0}, {2, 1, 0.261, 3.3, 0.0}, {2, 2, 0.281, 3.7, 3.0}};
 constexpr int kNumRows = sizeof(kRows) / sizeof(kRows[0]);
 constexpr int kRowsWaves = 8, kRowsMax = 256;           // gemm_rows_kernel is not measured beyond 256 rows
 
@@ -1195,6 +1206,67 @@ size_t gemm_f32_scratch_bound(int rows, int N)
 {
     const size_t every = (size_t)8 * rows * N, full = (size_t)256 * 32 * 16 * f32_row_tiles(rows);
     return every < full ? every : full;
+}
+
+// bf16; `groups`: with the kernels that use wavefront groups, as they are launched.  Candidates with more than
+// `most` floats of scratch are left out.
+static GemmPlan gemm_bf16_plan(int rows, int N, int K, bool groups, size_t most)
+{
+    GemmPlan best{0, 1, 1, 0};
+    double best_us = 1e300;
+    const int kt = K / BK;
+    const double hbm_us = 2.0 * ((double)rows * K + (double)N * K + (double)rows * N) / kHbmRate;
+    const auto part_us = [](double floats) { return kMergeUs + floats * 8.0 / kMergeRate; };
+    const auto tail_us = [](double floats) { return kTailMergeUs + floats * 8.0 / kTailMergeRate; };
+    for (int i = 0; i < kNumTiles; ++i) {
+        const int bm = kTiles[i].bm, bn = kTiles[i].bn;
+        const long tiles = (long)((rows + bm - 1) / bm) * ((N + bn - 1) / bn);
+        const double area = (double)bm * bn;
+        for (int ns = 1; ns <= 8; ++ns) {
+            // every workgroup at least two k-tiles, none without any; one division beyond a full chip
+            const int per = (kt + ns - 1) / ns;
+            if (ns > 1 && (tiles * ns > 512 || kt / ns < 2 || (ns - 1) * per >= kt)) continue;
+            const TileCfg &c = groups && in_groups(i, per, tiles * ns) ? kGroupedTiles[i - 8] : kTiles[i];
+            const size_t scratch = ns > 1 ? (size_t)ns * rows * N : 0;
+            const double units = (double)tiles * ns / 256.0;
+            // three workgroups of the smallest tile share a CU, so its rounds are not whole
+            const double rounds = i == kSmallTile ? (units > 1.0 ? units : 1.0) : ceil(units);
+            double us = rounds * (c.tile_us + c.k_us * per);
+            us = kLaunchUs + (us > hbm_us ? us : hbm_us);
+            if (ns > 1) us += part_us((double)ns * rows * N);
+            if (us < best_us && scratch <= most) { best_us = us; best = {i, ns, 1, scratch}; }
+        }
+        // whole rounds undivided, the tiles beyond them divided
+        const long full = tiles / 256, rem = tiles - full * 256;
+        if (full == 0 || rem == 0) continue;
+        const TileCfg &c = groups && in_groups(i, kt, tiles) ? kGroupedTiles[i - 8] : kTiles[i];
+        for (int t = 2; t <= 8; ++t) {
+            const int per = (kt + t - 1) / t;
+            if (rem * t > 256 || kt / t < 4) break;
+            if ((t - 1) * per >= kt) continue;
+            double us = full * (c.tile_us + c.k_us * kt) + c.tile_us + c.k_us * per;
+            us = (kLaunchUs + (us > hbm_us ? us : hbm_us) + tail_us((double)rem * t * area)) * kTailMargin;
+            const size_t scratch = (size_t)rem * t * (size_t)area;
+            if (us < best_us && scratch <= most) { best_us = us; best = {i, 1, t, scratch}; }
+        }
+    }
+    if (rows > kRowsMax) return best;
+    for (int i = 0; i < kNumRows; ++i) {
+        const RowsCfg &c = kRows[i];
+        const int bm = 16 * c.tt, bn = 16 * c.ft;
+        const long tiles = (long)((rows + bm - 1) / bm) * (N / bn);
+        for (int ns = 1; ns <= 8; ns *= 2) {
+            if (ns > 1 && (tiles * ns > 1024 || K / 32 < ns * kRowsWaves)) break;
+            const int steps = (K / 32 + ns * kRowsWaves - 1) / (ns * kRowsWaves);
+            const double l2_us = (double)tiles * (bm + bn) * K * 2.0 / kRowsRate, w_us = 2.0 * N * K / kHbmRate;
+            double us = c.fixed_us + c.step_us * steps + (l2_us > w_us ? l2_us : w_us) +
+                        (groups ? (tiles * ns - 1) / 256 * c.round_us : 0.0);
+            if (ns > 1) us += part_us((double)ns * rows * N);
+            const size_t scratch = ns > 1 ? (size_t)ns * rows * N : 0;
+            if (us < best_us && scratch <= most) { best_us = us; best = {kNumTiles + i, ns, 1, scratch}; }
+        }
+    }
+    return best;
 }
 
 GemmPlan gemm_plan(DType dt, int rows, int N, int K)
@@ -1209,54 +1281,11 @@ GemmPlan gemm_plan(DType dt, int rows, int N, int K)
         if (best.nsplit > 1) best.scratch_floats = (size_t)best.nsplit * rows * N;
         return best;
     }
-    double best_us = 1e300;
-    const int kt = K / BK;
-    const double hbm_us = 2.0 * ((double)rows * K + (double)N * K + (double)rows * N) / kHbmRate;
-    const auto part_us = [](double floats) { return kMergeUs + floats * 8.0 / kMergeRate; };
-    const auto tail_us = [](double floats) { return kTailMergeUs + floats * 8.0 / kTailMergeRate; };
-    for (int i = 0; i < kNumTiles; ++i) {
-        const TileCfg &c = kTiles[i];
-        const long tiles = (long)((rows + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-        const double area = (double)c.bm * c.bn;
-        for (int ns = 1; ns <= 8; ++ns) {
-            // every workgroup at least two k-tiles, none without any; one division beyond a full chip
-            const int per = (kt + ns - 1) / ns;
-            if (ns > 1 && (tiles * ns > 512 || kt / ns < 2 || (ns - 1) * per >= kt)) continue;
-            const double units = (double)tiles * ns / 256.0;
-            // three workgroups of the smallest tile share a CU, so its rounds are not whole
-            const double rounds = i == kSmallTile ? (units > 1.0 ? units : 1.0) : ceil(units);
-            double us = rounds * (c.tile_us + c.k_us * per);
-            us = kLaunchUs + (us > hbm_us ? us : hbm_us);
-            if (ns > 1) us += part_us((double)ns * rows * N);
-            if (us < best_us) { best_us = us; best = {i, ns, 1, ns > 1 ? (size_t)ns * rows * N : 0}; }
-        }
-        // whole rounds undivided, the tiles beyond them divided
-        const long full = tiles / 256, rem = tiles - full * 256;
-        if (full == 0 || rem == 0) continue;
-        for (int t = 2; t <= 8; ++t) {
-            const int per = (kt + t - 1) / t;
-            if (rem * t > 256 || kt / t < 4) break;
-            if ((t - 1) * per >= kt) continue;
-            double us = full * (c.tile_us + c.k_us * kt) + c.tile_us + c.k_us * per;
-            us = (kLaunchUs + (us > hbm_us ? us : hbm_us) + tail_us((double)rem * t * area)) * kTailMargin;
-            if (us < best_us) { best_us = us; best = {i, 1, t, (size_t)rem * t * (size_t)area}; }
-        }
-    }
-    if (rows > kRowsMax) return best;
-    for (int i = 0; i < kNumRows; ++i) {
-        const RowsCfg &c = kRows[i];
-        const int bm = 16 * c.tt, bn = 16 * c.ft;
-        const long tiles = (long)((rows + bm - 1) / bm) * (N / bn);
-        for (int ns = 1; ns <= 8; ns *= 2) {
-            if (ns > 1 && (tiles * ns > 1024 || K / 32 < ns * kRowsWaves)) break;
-            const int steps = (K / 32 + ns * kRowsWaves - 1) / (ns * kRowsWaves);
-            const double l2_us = (double)tiles * (bm + bn) * K * 2.0 / kRowsRate, w_us = 2.0 * N * K / kHbmRate;
-            double us = c.fixed_us + c.step_us * steps + (l2_us > w_us ? l2_us : w_us);
-            if (ns > 1) us += part_us((double)ns * rows * N);
-            if (us < best_us) { best_us = us; best = {kNumTiles + i, ns, 1, ns > 1 ? (size_t)ns * rows * N : 0}; }
-        }
-    }
-    return best;
+    best = gemm_bf16_plan(rows, N, K, true, SIZE_MAX);
+    if (best.scratch_floats == 0) return best;
+    // never more scratch than without the groups, which is what callers have been told the workspace takes
+    const size_t told = gemm_bf16_plan(rows, N, K, false, SIZE_MAX).scratch_floats;
+    return best.scratch_floats <= told ? best : gemm_bf16_plan(rows, N, K, true, told);
 }
 
 template <int FT, int TT>
@@ -1282,7 +1311,10 @@ void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
     ep.out_f32 = e.out_f32;
     ep.res_f32 = e.res_f32;
     if (dt == DType::BF16) {
-        const int ns = plan.nsplit, tail = plan.tail, per = (K / BK + ns - 1) / ns;   // k-tiles of a workgroup
+        const int ns = plan.nsplit, tail = plan.tail, tile = plan.cfg < kNumTiles ? plan.cfg : kSmallTile;
+        const bool groups = in_groups(plan.cfg, (K / BK + ns - 1) / ns,
+                                      (long)ns * ((rows + kTiles[tile].bm - 1) / kTiles[tile].bm) *
+                                          ((N + kTiles[tile].bn - 1) / kTiles[tile].bn));
         switch (plan.cfg) {
         case 0: launch_gemm_bf16_cfg<320, 256, 2, 4, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
         case 1: launch_gemm_bf16_cfg<256, 256, 2, 4, 2>(A, W, rows, N, K, ep, st, ns, part, tail); break;
@@ -1292,20 +1324,16 @@ void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
         case 5: launch_gemm_bf16_cfg<128, 256, 2, 4, 3>(A, W, rows, N, K, ep, st, ns, part, tail); break;
         case 6: launch_gemm_bf16_cfg<192, 128, 2, 4, 3>(A, W, rows, N, K, ep, st, ns, part, tail); break;
         case 7: launch_gemm_bf16_cfg<128, 128, 2, 4, 4>(A, W, rows, N, K, ep, st, ns, part, tail); break;
-        // wavefront groups from 16 (64x128: 32) k-tiles per workgroup on; 64x64 only up to one workgroup per CU,
-        // beyond which three workgroups of the one-group kernel share a CU.  Time of one group over time of
-        // several at 2-7, 8-15, 16-31, 32-63 and 64-127 k-tiles: 64x64 0.95, 1.00, 1.06, 1.10, 1.15 (0.75 with
-        // more workgroups than CUs), 64x128 0.96, 0.98, 1.00, 1.01, 1.03, 128x64 0.97, 1.00, 1.06, 1.08, 1.12.
         case 8:
-            if (per >= 32) launch_gemm_bf16_cfg<64, 128, 2, 2, 3, 2>(A, W, rows, N, K, ep, st, ns, part, tail);
+            if (groups) launch_gemm_bf16_cfg<64, 128, 2, 2, 3, 2>(A, W, rows, N, K, ep, st, ns, part, tail);
             else launch_gemm_bf16_cfg<64, 128, 2, 4, 4>(A, W, rows, N, K, ep, st, ns, part, tail);
             break;
         case 9:
-            if (per >= 16) launch_gemm_bf16_cfg<128, 64, 2, 2, 3, 2>(A, W, rows, N, K, ep, st, ns, part, tail);
+            if (groups) launch_gemm_bf16_cfg<128, 64, 2, 2, 3, 2>(A, W, rows, N, K, ep, st, ns, part, tail);
             else launch_gemm_bf16_cfg<128, 64, 4, 2, 4>(A, W, rows, N, K, ep, st, ns, part, tail);
             break;
         case 10:
-            if (per >= 16 && (long)ns * ((rows + 63) / 64) * ((N + 63) / 64) <= 256)
+            if (groups)
                 launch_gemm_bf16_cfg<64, 64, 1, 1, 2, 4>(A, W, rows, N, K, ep, st, ns, part, tail);
             else
                 launch_gemm_bf16_cfg<64, 64, 2, 2, 3>(A, W, rows, N, K, ep, st, ns, part, tail);
