@@ -513,7 +513,8 @@ static fvar_status lowrank_fill(fvar_ctx *c, fvar_stream stream, const void *y_k
     }
     timed(c, st, "fill", [&] {
         fvar::launch_fill(dtype(c), y_keep, idx_keep, idx_drop, B, M, k, r, c->cfg.hidden, w_c, g_c, y,
-                          parts, scores_out, st);
+                          parts, scores_out,
+                          fvar::map_past_caches((size_t)B * M * c->cfg.hidden * esize(c), scores_out != nullptr), st);
     });
     return launch_status(c, who);
 }

@@ -19,6 +19,8 @@
 // stored (exact products of the stored elements, fp64 sum): the row energies of the map, i.e. the
 // selection scores of the NEXT block (paper, Sec. "Representative Token Restoration"), so that
 // the next block does not have to read the map again.
+#include <type_traits>
+
 #include "common.h"
 
 namespace fvar {
@@ -30,15 +32,26 @@ __device__ __forceinline__ double group_sum(double v, int width)
     return v;
 }
 
-// 16 bytes of the restored map, past the caches (nontemporal), in which y_keep, w_c and the dirty lines of
-// whatever ran before stay: 67.7 us with ordinary stores, 53.4 with these, where fills follow each other (shape
-// below).  A score pass over the map right after it pays for that if the map fits the 256 MB of last-level cache
-// and gains if it does not: fill + score in a chain of blocks 91 -> 102 us with 210 MB, 29.3 -> 30.9 with 67 MB,
-// 157 -> 148 with 210 to 537 MB, 10.2 -> 9.3 with 7 to 17 MB (100.9, 32.1, 164.6 and 10.3 before either change).
-__device__ __forceinline__ void store_stream(void *dst, const uint4 &v)
+// 16 bytes of the restored map; PAST: past the caches (nontemporal), see map_past_caches
+template <bool PAST> __device__ __forceinline__ void store_map(void *dst, const uint4 &v)
 {
     typedef uint32_t uintx4_t __attribute__((ext_vector_type(4)));
-    __builtin_nontemporal_store(uintx4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<uintx4_t *>(dst));
+    if constexpr (PAST) __builtin_nontemporal_store(uintx4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<uintx4_t *>(dst));
+    else *reinterpret_cast<uint4 *>(dst) = v;
+}
+
+// Whether a restored map of that many bytes is written past the caches.  What counts is the map's next reader, the
+// score pass (scored fills: the gather) of the next block: from 20 % more than the 256 MB of last-level cache on
+// next to nothing of the map is still there when it comes, and stores past the caches spare y_keep, w_c and the
+// weights; a small map's dirty lines leave the L2s sooner that way.  In between, the reader finds the map in
+// the cache.  Score + LayerNorm gather + fill in a chain of blocks, ordinary -> past the caches, us: 9 MB 13.6 -> 13.1,
+// 19 16.4 -> 15.5, 38 27.0 -> 28.2, 105 60.0 -> 61.1, 164 95.1 -> 103.6, 210 115.5 -> 126.7, 268 146.8 -> 151.2,
+// 302 173.8 -> 179.3, 333 211 -> 204, 380 233 -> 215, 537 342 -> 294; with scores (no score pass) 9 MB 13.6 -> 13.0,
+// 38 26.2 -> 24.9 and 31.3 -> 31.7, 75 37.4 -> 41.4, 210 89.0 -> 98.1, 268 115.2 -> 115.9, 333 156.5 -> 157.4,
+// 419 183.6 -> 174.0.  Fills that follow each other without a reader see it otherwise (210 MB 63.6 -> 48.0).
+bool map_past_caches(size_t bytes, bool scored)
+{
+    return bytes <= (scored ? 40u : 24u) * 1000000 || bytes > (size_t)256 * 1024 * 1024 / 5 * 6;
 }
 
 // sum of squares of the 8 bf16 (4 fp32) elements of a 16-byte chunk, in fp64
@@ -55,7 +68,7 @@ template <typename T> __device__ __forceinline__ double chunk_energy(const uint4
 // ------------------------------------------------------------------ kept rows: scatter
 // Workgroup `blk` of the scatter part: four rows, one per wavefront.  With `parts` the row's
 // energy goes to part 0 of the row and zeros to its other parts.
-template <typename T>
+template <typename T, bool PAST>
 __device__ __forceinline__ void scatter_rows(int blk, const T *__restrict__ y_keep,
                                              const int32_t *__restrict__ idx_keep, int M, int k,
                                              int total_rows, int d, T *__restrict__ y,
@@ -78,13 +91,13 @@ __device__ __forceinline__ void scatter_rows(int blk, const T *__restrict__ y_ke
         for (int u = 0; u < 4; ++u) v[u] = src[c + 64 * u];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            store_stream(dst + c + 64 * u, v[u]);
+            store_map<PAST>(dst + c + 64 * u, v[u]);
             if (parts) e += chunk_energy<T>(v[u]);
         }
     }
     for (; c < nchunk; c += 64) {
         const uint4 v = src[c];
-        store_stream(dst + c, v);
+        store_map<PAST>(dst + c, v);
         if (parts) e += chunk_energy<T>(v);
     }
     if (parts) {
@@ -107,8 +120,9 @@ __device__ __forceinline__ void fill_dma_b128(const void *base, uint32_t byte_of
 }
 
 // Bound by the output's way to memory, as long as every wavefront keeps stores in flight: 4 x 6400 rows of 4096,
-// keep 1/4, rank 128: 76.9 -> 53.4 us (5.0 TB/s; a plain fill of the same map takes 33 and its kept rows' copy
-// 20), 32 x 1600 of 2048, keep 0.3, rank 64: 64.9 -> 50.4.  Before, a group's stores waited for indices that
+// keep 1/4, rank 128: 68.4 -> 57.9 us in a chain of blocks, 73.3 -> 63.6 one after the other (a plain fill of the
+// same map takes 33 and its kept rows' copy 20), 32 x 1600 of 2048, keep 0.3, rank 64: 56.7 -> 52.0 and
+// 63.1 -> 58.2.  Before, a group's stores waited for indices that
 // queued behind the stores of the group before it, every MFMA for its own LDS read, and 30 % of the LDS cycles
 // were bank conflicts (21 % with the staging tile swizzled).
 // Workgroups are numbered so that an XCD gets all slabs of its rows: it then writes whole rows (slabs dealt
@@ -119,7 +133,7 @@ __device__ __forceinline__ void fill_dma_b128(const void *base, uint32_t byte_of
 // every rank that gets this KSTEPS.
 template <int KSTEPS>
 constexpr int kFillWholeSteps = KSTEPS <= 4 ? KSTEPS - 1 : KSTEPS == 6 ? 4 : KSTEPS == 8 ? 6 : KSTEPS == 12 ? 8 : 12;
-template <int KSTEPS, bool SCORED>
+template <int KSTEPS, bool SCORED, bool PAST>
 __global__ __launch_bounds__(256, KSTEPS + SCORED <= 8 ? 3 : 2) void fill_bf16_kernel(const uint16_t *__restrict__ y_keep,
                                                         const int32_t *__restrict__ idx_keep,
                                                         const int32_t *__restrict__ idx_drop, int M,
@@ -131,7 +145,7 @@ __global__ __launch_bounds__(256, KSTEPS + SCORED <= 8 ? 3 : 2) void fill_bf16_k
                                                         double *__restrict__ parts)
 {
     if ((int)blockIdx.x >= fill_blocks) {
-        scatter_rows<uint16_t>(blockIdx.x - fill_blocks, y_keep, idx_keep, M, k, B * k, d, y, parts, slabs);
+        scatter_rows<uint16_t, PAST>(blockIdx.x - fill_blocks, y_keep, idx_keep, M, k, B * k, d, y, parts, slabs);
         return;
     }
     constexpr int RP = KSTEPS * 16;                           // slab rows in LDS (k extent, padded)
@@ -268,7 +282,7 @@ __global__ __launch_bounds__(256, KSTEPS + SCORED <= 8 ? 3 : 2) void fill_bf16_k
             }
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
-                store_stream(Y + (size_t)orow[it] * d + col0 + half * 64 + (lane & 7) * 8, v[it]);
+                store_map<PAST>(Y + (size_t)orow[it] * d + col0 + half * 64 + (lane & 7) * 8, v[it]);
                 if (SCORED) erow[it] += chunk_energy<uint16_t>(v[it]);
             }
             asm volatile("" ::: "memory");
@@ -304,7 +318,7 @@ __global__ __launch_bounds__(256) void fill_f32_kernel(const float *__restrict__
     __shared__ float wrow[256];
     __shared__ double esum[4];
     if ((int)blockIdx.x >= fill_blocks) {
-        scatter_rows<float>(blockIdx.x - fill_blocks, y_keep, idx_keep, M, k, B * k, d, y, parts, 1);
+        scatter_rows<float, false>(blockIdx.x - fill_blocks, y_keep, idx_keep, M, k, B * k, d, y, parts, 1);
         return;
     }
     const int nd = M - k;
@@ -357,7 +371,10 @@ __global__ __launch_bounds__(256) void scores_from_parts_kernel(const double *__
 // Eq. "redefine" as printed: kept rows come from the block output, every other row is the cached
 // counterpart row itself.  One wavefront per output row: the first B*k rows of the launch scatter
 // y_keep, the remaining B*(M-k) copy row idx_drop[b,j] of the cache to the same position of y.
-template <typename T>
+// PAST: the kept rows are stored past the caches, where the map does not fit the last-level cache of 256 MB
+// (score + fill in a chain, ordinary -> past, us: 16 MB 10.8 -> 11.5, 63 35.2 -> 36.5, 210 98.8 -> 98.5,
+// 262 133.4 -> 129.6, 302 170.6 -> 165.1, 537 302.5 -> 293.0).
+template <typename T, bool PAST>
 __global__ __launch_bounds__(256) void cache_fill_kernel(const T *__restrict__ y_keep,
                                                          const int32_t *__restrict__ idx_keep,
                                                          const int32_t *__restrict__ idx_drop, int M,
@@ -368,7 +385,7 @@ __global__ __launch_bounds__(256) void cache_fill_kernel(const T *__restrict__ y
     constexpr int E = Elem<T>::kPerChunk;
     const int kept_blocks = (B * k + 3) / 4;
     if ((int)blockIdx.x < kept_blocks) {
-        scatter_rows<T>(blockIdx.x, y_keep, idx_keep, M, k, B * k, d, y, nullptr, 0);
+        scatter_rows<T, PAST>(blockIdx.x, y_keep, idx_keep, M, k, B * k, d, y, nullptr, 0);
         return;
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -390,12 +407,15 @@ void launch_cache_fill(DType dt, const void *y_keep, const int32_t *idx_keep, co
     const int copy_rows = cache == y ? 0 : B * (M - k);
     const int blocks = (B * k + 3) / 4 + (copy_rows + 3) / 4;
     if (blocks == 0) return;
-    if (dt == DType::BF16)
-        launch(cache_fill_kernel<uint16_t>, dim3(blocks), dim3(256), 0, st, (const uint16_t *)y_keep,
-               idx_keep, idx_drop, M, k, B, d, (const uint16_t *)cache, (uint16_t *)y);
-    else
-        launch(cache_fill_kernel<float>, dim3(blocks), dim3(256), 0, st, (const float *)y_keep, idx_keep,
-               idx_drop, M, k, B, d, (const float *)cache, (float *)y);
+    const bool past = dt == DType::BF16 && (size_t)B * M * d * sizeof(uint16_t) > 256u * 1000000;
+    auto run = [&](auto kern, auto *t) {
+        typedef std::remove_pointer_t<decltype(t)> T;
+        launch(kern, dim3(blocks), dim3(256), 0, st, (const T *)y_keep, idx_keep, idx_drop, M, k, B, d, (const T *)cache,
+               (T *)y);
+    };
+    if (dt != DType::BF16) run(cache_fill_kernel<float, false>, (float *)nullptr);
+    else if (past) run(cache_fill_kernel<uint16_t, true>, (uint16_t *)nullptr);
+    else run(cache_fill_kernel<uint16_t, false>, (uint16_t *)nullptr);
 }
 
 // parts per output row that launch_fill leaves when row energies are requested
@@ -407,7 +427,7 @@ int fill_score_parts(DType dt, int d)
 template <int KSTEPS>
 static void launch_fill_bf16(const void *y_keep, const int32_t *idx_keep, const int32_t *idx_drop, int B,
                              int M, int k, int r, int d, const void *w_c, const void *g_c, void *y,
-                             double *parts, hipStream_t st)
+                             double *parts, bool past, hipStream_t st)
 {
     const int nd = M - k;
     const int scatter_blocks = (B * k + 3) / 4;
@@ -420,7 +440,8 @@ static void launch_fill_bf16(const void *y_keep, const int32_t *idx_keep, const 
     if (row_split > max_split) row_split = max_split;
     const int fill_blocks = slabs * row_split * B;
     const size_t lds = nd > 0 ? ((size_t)KSTEPS * 16 * kFillCols + 4 * 32 * kFillStage) * sizeof(uint16_t) : 0;
-    auto kern = parts ? fill_bf16_kernel<KSTEPS, true> : fill_bf16_kernel<KSTEPS, false>;
+    auto kern = parts ? past ? fill_bf16_kernel<KSTEPS, true, true> : fill_bf16_kernel<KSTEPS, true, false>
+                      : past ? fill_bf16_kernel<KSTEPS, false, true> : fill_bf16_kernel<KSTEPS, false, false>;
     if (lds > 48 * 1024)
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -431,16 +452,17 @@ static void launch_fill_bf16(const void *y_keep, const int32_t *idx_keep, const 
 }
 
 // parts: null, or B*M*fill_score_parts() doubles that receive the energy of every output row in
-// parts; scores_out (with parts): [B*M] fp32 row energies, summed from the parts by a second kernel
+// parts; scores_out (with parts): [B*M] fp32 row energies, summed from the parts by a second kernel.  past: bf16
+// maps are written past the caches
 void launch_fill(DType dt, const void *y_keep, const int32_t *idx_keep, const int32_t *idx_drop,
                  int B, int M, int k, int r, int d, const void *w_c, const void *g_c, void *y,
-                 double *parts, float *scores_out, hipStream_t st)
+                 double *parts, float *scores_out, bool past, hipStream_t st)
 {
     const int nd = M - k;
     const int scatter_blocks = (B * k + 3) / 4;
     if (dt == DType::BF16) {
         const int ks = nd > 0 ? (r + 15) / 16 : 1;
-#define FVAR_FILL(KS) launch_fill_bf16<KS>(y_keep, idx_keep, idx_drop, B, M, k, r, d, w_c, g_c, y, parts, st)
+#define FVAR_FILL(KS) launch_fill_bf16<KS>(y_keep, idx_keep, idx_drop, B, M, k, r, d, w_c, g_c, y, parts, past, st)
         if (ks <= 1) FVAR_FILL(1);
         else if (ks <= 2) FVAR_FILL(2);
         else if (ks <= 3) FVAR_FILL(3);

@@ -230,6 +230,16 @@ def test_bf16_block_workspace_stays_within_what_callers_were_told(B, rows, d, H,
     assert fv.fvar_block_workspace_bytes(c, B, rows) <= most
 
 
+def test_fill_keeps_maps_in_cache_that_the_next_block_reads_there():
+    """A restored map is read again by the next block's score pass: it goes past the caches only where it is small
+    or does not fit the 256 MB of last-level cache."""
+    past = fv.load_library()["_ZN4fvar15map_past_cachesEmb"]
+    past.restype, past.argtypes = C.c_bool, [C.c_size_t, C.c_bool]
+    for mb, plain, scored in ((1, True, True), (19, True, True), (31, False, True), (52, False, False),
+                              (105, False, False), (210, False, False), (302, False, False), (420, True, True), (5000, True, True)):
+        assert (past(mb * 10 ** 6, False), past(mb * 10 ** 6, True)) == (plain, scored), mb
+
+
 @pytest.mark.parametrize("rows,d,F,layer,tile,shares", [
     (65, 1088, 1088, "qkv", "64x64", 1), (520, 960, 2240, "fc2", "64x64", 1), (257, 512, 1088, "fc2", "64x64", 1),
     (330, 1088, 4096, "fc1", "128x64", 1), (400, 960, 4160, "fc2", "128x64", 4), (300, 2048, 2112, "qkv", "64x128", 1),

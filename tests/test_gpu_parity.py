@@ -194,6 +194,47 @@ def test_lowrank_fill_scored(dtype, r, M, d, k):
         assert torch.equal(keep2, keep3) and torch.equal(drop2, drop3)
 
 
+@pytest.mark.parametrize("r", [8, 24, 40, 64, 72, 104, 136, 200, 256])
+def test_fill_many_groups_both_stores(r):
+    """Every instance of the bf16 fill, by rank, with and without scores, written past the caches and through
+    them: three 32-row groups per wavefront, the last one ragged, and a width that ends inside a 128-column slab.
+    All restored rows against 64 bits, all scores against the stored map; one map for all four."""
+    import ctypes as C
+    B, M, k, d = 8, 1400, 297, 4160
+    g = torch.Generator(device="cuda").manual_seed(r)
+    bf = torch.bfloat16
+    W = torch.randn((B, M, r), generator=g, device="cuda").to(bf)
+    G = (torch.randn((B, r, d), generator=g, device="cuda") / r ** 0.5).to(bf)
+    yk = torch.randn((B, k, d), generator=g, device="cuda").to(bf)
+    order = torch.argsort(torch.rand((B, M), generator=g, device="cuda"), dim=1)
+    keep, drop = (order[:, :k].sort(1)[0], order[:, k:].sort(1)[0])
+    ref = torch.matmul(W.double(), G.double())
+    rms = ref.square().mean().sqrt()
+    ref.scatter_(1, keep[:, :, None].expand(B, k, d), yk.double())
+    keep, drop = keep.to(torch.int32).contiguous(), drop.to(torch.int32).contiguous()
+    lib = fv.load_library()
+    fill = lib["_ZN4fvar11launch_fillENS_5DTypeEPKvPKiS4_iiiiiS2_S2_PvPdPfbP12ihipStream_t"]
+    fill.restype, fill.argtypes = None, [C.c_int] + 3 * [C.c_void_p] + 5 * [C.c_int] + 5 * [C.c_void_p] + [C.c_bool, C.c_void_p]
+    first = None
+    for scored in (False, True):
+        parts = torch.full((B * M * 33,), float("nan"), dtype=torch.float64, device="cuda") if scored else None
+        for past in (False, True):
+            y = torch.full((B, M, d), float("nan"), dtype=bf, device="cuda")
+            sc = torch.full((B, M), float("nan"), device="cuda")
+            torch.cuda.synchronize()
+            fill(1, yk.data_ptr(), keep.data_ptr(), drop.data_ptr(), B, M, k, r, d, W.data_ptr(), G.data_ptr(),
+                 y.data_ptr(), parts.data_ptr() if scored else None, sc.data_ptr() if scored else None, past, None)
+            torch.cuda.synchronize()
+            first = y if first is None else first
+            assert torch.equal(y, first), (scored, past)
+            if scored:
+                want = y.double().square().sum(-1).float()
+                off = (sc.view(torch.int32) - want.view(torch.int32)).abs()
+                assert int(off.max()) <= 1 and int((off > 0).sum()) <= 2, (past, int((off > 0).sum()))
+    err = (first.double() - ref).abs() / ref.abs().clamp(min=float(rms))
+    assert float(err.max()) <= TOL["bf16"]
+
+
 # ----------------------------------------------------------------------------- block, small shapes
 SMALL = [  # dtype, B, M, d, H, F, Lp, k, r
     ("bf16", 2, 96, 128, 2, 256, 37, 40, 16),
