@@ -171,6 +171,7 @@ void launch_attention(DType dt, const void *q, const void *K, const void *V, int
 // past: bf16 maps are written past the caches; map_past_caches says whether that is the better way
 int fill_score_parts(DType dt, int d);
 bool map_past_caches(size_t bytes, bool scored);
+int fill_row_split(int slabs, int nd);
 void launch_fill(DType dt, const void *y_keep, const int32_t *idx_keep, const int32_t *idx_drop,
                  int B, int M, int k, int r, int d, const void *w_c, const void *g_c, void *y,
                  double *parts, float *scores_out, bool past, hipStream_t st);

@@ -424,6 +424,18 @@ int fill_score_parts(DType dt, int d)
     return dt == DType::BF16 ? (d + kFillCols - 1) / kFillCols : 1;
 }
 
+// Workgroups that share the pruned rows of one slab: one round of the two that a CU holds at every rank, rounded
+// down, and no more than there are 32-row groups for their four wavefronts.  Each stages its slab once.  Against 768
+// in all, rounded up, which is one and a half rounds from rank 136 (with scores 104) on and a little over one where
+// 768 is no multiple of the slabs: 6400 x 4096 rank 64 15.7 -> 13.9 us, rank 256 26.6 -> 23.5, 7 x 1600 x 4096
+// rank 160 32.1 -> 27.8, 16 x 1024 x 4096 rank 128 49.6 -> 45.6, 4 x 6400 x 4096 rank 128 65.6 -> 64.6, on average
+// over 168 shapes 0.967 (0.87 to 1.05); 1024 workgroups 1.007, 1536 1.02.
+int fill_row_split(int slabs, int nd)
+{
+    const int most = ((nd + 31) / 32 + 3) / 4, round = slabs < 512 ? 512 / slabs : 1;
+    return round < most ? round : most;
+}
+
 template <int KSTEPS>
 static void launch_fill_bf16(const void *y_keep, const int32_t *idx_keep, const int32_t *idx_drop, int B,
                              int M, int k, int r, int d, const void *w_c, const void *g_c, void *y,
@@ -432,12 +444,7 @@ static void launch_fill_bf16(const void *y_keep, const int32_t *idx_keep, const 
     const int nd = M - k;
     const int scatter_blocks = (B * k + 3) / 4;
     const int slabs = (d + kFillCols - 1) / kFillCols;
-    const int groups = (nd + 31) / 32;                      // 32-row groups, one wavefront each
-    // one round of the three workgroups that a CU holds: each stages its slab once (with two rounds 71.2 us
-    // where one takes 67.7 at 4 x 6400 rows of 4096, rank 128, 62.5 and 60.6 at 32 x 1600 of 2048, rank 64)
-    int row_split = nd > 0 ? (768 + slabs * B - 1) / (slabs * B) : 0;
-    const int max_split = (groups + 3) / 4;
-    if (row_split > max_split) row_split = max_split;
+    const int row_split = fill_row_split(slabs * B, nd);
     const int fill_blocks = slabs * row_split * B;
     const size_t lds = nd > 0 ? ((size_t)KSTEPS * 16 * kFillCols + 4 * 32 * kFillStage) * sizeof(uint16_t) : 0;
     auto kern = parts ? past ? fill_bf16_kernel<KSTEPS, true, true> : fill_bf16_kernel<KSTEPS, true, false>

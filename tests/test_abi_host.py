@@ -230,6 +230,17 @@ def test_bf16_block_workspace_stays_within_what_callers_were_told(B, rows, d, H,
     assert fv.fvar_block_workspace_bytes(c, B, rows) <= most
 
 
+def test_fill_runs_in_one_round_of_workgroups():
+    """Two workgroups of the fill fit a CU at every rank: more than 512 of them are a second round, unless the slabs
+    alone are more.  Every 32-row group has a workgroup's wavefront, and no workgroup goes without."""
+    split = fv.load_library()["_ZN4fvar14fill_row_splitEii"]
+    for slabs in list(range(1, 70)) + [105, 120, 224, 256, 257, 511, 512, 513, 1024]:      # all samples' together
+        for nd in (0, 1, 32, 33, 128, 129, 700, 1120, 4800):
+            n = split(slabs, nd)
+            assert (nd == 0 and n == 0) or 1 <= n <= max(1, 512 // slabs)
+            assert (n - 1) * 128 < max(nd, 1) and (n == 512 // slabs or n * 128 >= nd or n == 1)
+
+
 def test_fill_keeps_maps_in_cache_that_the_next_block_reads_there():
     """A restored map is read again by the next block's score pass: it goes past the caches only where it is small
     or does not fit the 256 MB of last-level cache."""
