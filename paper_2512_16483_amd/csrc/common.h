@@ -189,6 +189,7 @@ constexpr int kGramParts = 4;              // partial matrices that the bf16 Gra
 struct InverseJob { const double *S; double ridge; double *Sinv; int r; };
 void launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int rows, int N, int K,
                                   float *out, const InverseJob &inv, hipStream_t st);
+bool kmajor_in_groups(int B, int M, int rows, int d);
 bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int B, int M, int rows,
                              int d, void *out, hipStream_t st);
 void launch_rp_project(DType dt, const void *qt, size_t q_stride, const void *x, int B, int M,

@@ -878,6 +878,17 @@ void launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int 
     else launch_batched_f32_cfg<64, 128, 2, 4, 4>(A, W, nbatch, rows, N, K, p.parts, out, inv, st);
 }
 
+// Whether the 64x128 tiles of a projection run with wavefront groups: from 8 k-tiles on, in one round, and as long
+// as no more than 160 column strips of x, which the tiles above each other share, are read at once.  Where every
+// CU reads a strip of its own the loop waits for memory and the groups' longer first fill comes on top.  Time of one
+// group over time of two: 16 or 128 strips, 2 k-tiles 0.95, 5 and 7 0.99 to 1.01, 14 1.04, 36 1.08, 64 1.12; 192
+// strips, 8 to 64 k-tiles 0.93 to 0.98; 512 strips and more, 1 to 8 k-tiles 0.85 to 0.92, 16 0.95, 64 0.98.
+bool kmajor_in_groups(int B, int M, int rows, int d)
+{
+    const long strips = (long)((d + 127) / 128) * B;
+    return (M + BK - 1) / BK >= 8 && strips <= 160 && (rows + 63) / 64 * strips <= 256;
+}
+
 // Runs out[b] = qt[b] x[b] (qt: [rows][M] per sample or shared, x[b]: [M][d]) on the tiled MFMA
 // kernel (M a multiple of 8, d of 64).  Returns false, with nothing launched, where a row tile of qt does
 // not fit 32-bit byte offsets (M of 2^25 and more).  Tile by predicted time, constants as in gemm_plan plus
@@ -914,7 +925,10 @@ bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int
     case 3: launch_kmajor_cfg<128, 256, 2, 4, 3>(qt, q_stride, x, B, rows, d, M, out, st); break;
     case 4: launch_kmajor_cfg<192, 128, 2, 4, 3>(qt, q_stride, x, B, rows, d, M, out, st); break;
     case 5: launch_kmajor_cfg<128, 128, 2, 4, 4>(qt, q_stride, x, B, rows, d, M, out, st); break;
-    case 6: launch_kmajor_cfg<64, 128, 2, 2, 3, 2>(qt, q_stride, x, B, rows, d, M, out, st); break;
+    case 6:
+        if (kmajor_in_groups(B, M, rows, d)) launch_kmajor_cfg<64, 128, 2, 2, 3, 2>(qt, q_stride, x, B, rows, d, M, out, st);
+        else launch_kmajor_cfg<64, 128, 2, 4, 4>(qt, q_stride, x, B, rows, d, M, out, st);
+        break;
     default: return false;
     }
     return true;

@@ -84,7 +84,9 @@ def test_rp_project_tiled_path(B, M, rows, d, per_sample):
 
 @pytest.mark.parametrize("B,M,rows,d,per_sample", [
     (2, 56, 50, 192, True),          # less than one k-tile
-    (1, 2312, 692, 2048, False),     # 64x128 tiles, one chunk past the last whole k-tile
+    (1, 2312, 692, 2048, False),     # 64x128 tiles by two groups, one chunk past the last whole k-tile
+    (1, 520, 60, 256, False),        # 64x128 by two groups, nine k-tiles: the last trip is one group's alone
+    (24, 584, 50, 1024, True),       # 64x128 by one group: every workgroup reads a strip of its own
     (5, 136, 130, 1024, False),      # the samples share Q: its rows end inside the last k-tile
     (4, 440, 190, 4096, True),       # 128x128 tiles, seven of the eight chunks
     (4, 840, 330, 4096, True),       # 192x128
