@@ -172,6 +172,12 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
                     few[atomicAdd(&sh_few, 1)] = key[j];
             __syncthreads();
             const uint32_t mine = few[min(lane, count - 1)];
+            const uint32_t one = (uint32_t)__builtin_amdgcn_readfirstlane((int)mine);
+            if (__ballot(mine == one) == ~0ull) {        // equal scores: 48 of them ranked one by one take 3 us
+                T = one;
+                need_eq = remaining;
+                break;
+            }
             int above = 0, equal = 0;
             for (int i = 0; i < count; ++i) {
                 const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, i);
