@@ -180,15 +180,18 @@ void launch_fill(DType dt, const void *y_keep, const int32_t *idx_keep, const in
 void launch_cache_fill(DType dt, const void *y_keep, const int32_t *idx_keep, const int32_t *idx_drop,
                        int B, int M, int k, int d, const void *cache, void *y, hipStream_t st);
 
-// out[b] = qt[b] x[b]:  qt:[rows,M] (sample stride q_stride elements, 0 = shared), x:[B,M,d],
-// out:[B,rows,d].  M must be a multiple of the 16-byte chunk (8 bf16 / 4 fp32 elements).
+// out[p][b] = share p of A[b] W[b]^T in fp32, bf16 operands, see gemm.hip: shares and rows per workgroup of the plan,
+// rows over all shares that no plan exceeds
 int batched_f32_parts(int nbatch, int rows, int N, int K);
+int batched_f32_tile_rows(int nbatch, int rows, int N, int K);
 size_t batched_f32_room(int nbatch, int rows, int K);
 // ... and in the same launch the inverse of each problem's N x N matrix, the sum of kGramParts (see spd_inverse)
 constexpr int kGramParts = 4;              // partial matrices that the bf16 Gram matrix comes in
 struct InverseJob { const double *S; double ridge; double *Sinv; int r; };
 void launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int rows, int N, int K,
                                   float *out, const InverseJob &inv, hipStream_t st);
+// out[b] = qt[b] x[b]:  qt:[rows,M] (sample stride q_stride elements, 0 = shared), x:[B,M,d],
+// out:[B,rows,d].  M must be a multiple of the 16-byte chunk (8 bf16 / 4 fp32 elements).
 bool kmajor_in_groups(int B, int M, int rows, int d);
 bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int B, int M, int rows,
                              int d, void *out, hipStream_t st);

@@ -865,6 +865,7 @@ static BatchedPlan batched_f32_plan(int nbatch, int rows, int N, int K)
     return best;
 }
 int batched_f32_parts(int nbatch, int rows, int N, int K) { return batched_f32_plan(nbatch, rows, N, K).parts; }
+int batched_f32_tile_rows(int nbatch, int rows, int N, int K) { return batched_f32_plan(nbatch, rows, N, K).bm; }
 
 void launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int rows, int N, int K,
                                   float *out, const InverseJob &inv, hipStream_t st)

@@ -230,6 +230,17 @@ def test_bf16_block_workspace_stays_within_what_callers_were_told(B, rows, d, H,
     assert fv.fvar_block_workspace_bytes(c, B, rows) <= most
 
 
+def test_shares_and_tiles_of_the_factor_tests():
+    """tests/test_gpu_rp_path.py covers T = C G^T in one to four shares, on 64, 128 and 256 rows per tile, with each
+    instance of the inverse: another choice of constants must not empty these cases unseen."""
+    lib = fv.load_library()
+    tile, parts = lib["_ZN4fvar21batched_f32_tile_rowsEiiii"], lib["_ZN4fvar17batched_f32_partsEiiii"]
+    for (B, M, d, r), expect in {(1, 1024, 4096, 64): (128, 2), (1, 264, 4096, 32): (64, 3), (1, 520, 4096, 8): (64, 4),
+                                 (1, 1024, 1920, 40): (64, 1), (1, 1024, 4096, 72): (64, 1), (1, 4096, 4096, 128): (128, 1),
+                                 (2, 1000, 1920, 24): (64, 2)}.items():
+        assert (tile(B, M, r, d), parts(B, M, r, d)) == expect, (B, M, d, r)
+
+
 def test_projection_groups_only_where_tiles_share_what_they_read():
     """Wavefront groups in the small projection tile gain where few column strips are read at once; many samples,
     or a few k-tiles, are faster without (512 samples of 256 x 1024: 80 us instead of 90)."""

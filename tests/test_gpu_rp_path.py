@@ -216,9 +216,14 @@ def test_cache_factors_parity(dtype, B, M, d, r, rank, noise, per_sample):
 @pytest.mark.parametrize("B,M,d,r,ridge", [
     (1, 520, 512, 16, 0.0),       # one 16-wide pivot block, three empty tiles
     (2, 264, 256, 56, 1e-10),     # partly padded last block of four
-    (1, 328, 1024, 72, 1e-10),    # five of eight blocks, contraction of T in shares
+    (1, 328, 1024, 72, 1e-10),    # five of eight blocks
     (1, 4096, 4096, 128, 0.0),    # every block, 64 k-tiles
     (3, 1000, 320, 104, 1e-10),   # ragged rows and token chunks
+    (1, 1024, 4096, 64, 0.0),     # T in two shares, 128 x 64 tiles
+    (1, 264, 4096, 32, 1e-10),    # T in three shares, 64 x 64 tiles
+    (1, 520, 4096, 8, 0.0),       # T in four
+    (1, 1024, 1920, 40, 1e-10),   # 64 x 64 tiles, the inverse on their four wavefronts
+    (1, 1024, 4096, 72, 1e-10),   # 64 x 128 tiles
 ])
 def test_cache_factors_block_edges(B, M, d, r, ridge):
     """Edges of the 16-wide pivot blocks of the inverse and of the shares T comes in, against the
@@ -236,6 +241,73 @@ def test_cache_factors_block_edges(B, M, d, r, ridge):
         Wo = factors.restoration_matrix(Gg[b], Cm[b], ridge)     # against the G the GPU stored
         assert rel_err(Wg[b], Wo) <= TOL["bf16"], (b, rel_err(Wg[b], Wo))
         assert rel_err(Gg[b], factors.project(Q[0], Cm[b])) <= TOL["bf16"]
+
+
+def _gram_matrices(kind, B, r, rng):
+    """B badly conditioned matrices and their ridge, see test_gram_inverse_keeps_ill_conditioned_digits."""
+    if kind == "diagonal":
+        return np.stack([np.diag(10.0 ** rng.uniform(-6, 6, r)) for _ in range(B)]), 0.0
+    if kind == "rank8+ridge":
+        G, ridge = rng.standard_normal((B, r, min(r, 8))) @ rng.standard_normal((B, min(r, 8), 1024)), 1e-6
+    else:
+        G, ridge = np.abs(rng.standard_normal((B, r, 400))) @ np.abs(rng.standard_normal((B, 400, 2048))), 0.0
+    return G @ G.transpose(0, 2, 1), ridge
+
+
+def _check_inverse(kind, got, A0, ridge, rng):
+    """One inverse against numpy's of A0 (the sum of the partial matrices) + ridge, with the bounds of
+    test_gram_inverse_keeps_ill_conditioned_digits."""
+    r = A0.shape[0]
+    A = A0 + np.eye(r) * (ridge * np.trace(A0) / r)
+    ref, cond = np.linalg.inv(A), np.linalg.cond(A)
+    err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    bound = 1e-15 if kind == "diagonal" else r * 2.0 ** -52 * cond
+    assert err <= bound, f"cond {cond:.1e}: {err:.1e} > {bound:.1e}"
+    if kind != "diagonal":
+        Z = rng.standard_normal((40, r))
+        W = Z - Z @ (A - A0) @ ref
+        werr = np.linalg.norm(Z @ A0 @ got - W) / np.linalg.norm(W)
+        assert werr <= bound, f"cond {cond:.1e}: T X off by {werr:.1e} > {bound:.1e}"
+
+
+# (samples, rows, width, rank) -> rows per tile of T and its shares: every tile height with every instance of the
+# inverse that its launch can hold
+T_INVERSE = [((1, 256, 512, 8), 64, 1), ((1, 256, 512, 16), 128, 1), ((64, 1024, 2048, 16), 256, 1),
+             ((1, 264, 4096, 32), 64, 3), ((3, 2304, 4096, 24), 128, 4),
+             ((1, 256, 1920, 40), 64, 1), ((3, 256, 512, 56), 256, 1), ((1, 256, 512, 40), 128, 1), ((1, 512, 4096, 64), 128, 2),
+             ((1, 256, 4096, 72), 64, 1), ((2, 256, 1920, 72), 128, 1), ((1, 256, 512, 104), 256, 1), ((4, 512, 4096, 128), 128, 1)]
+
+
+@pytest.mark.parametrize("kind", ["rank8+ridge", "positive", "diagonal"])
+@pytest.mark.parametrize("shape,tile,shares", T_INVERSE)
+def test_inverse_inside_the_launch_of_t(shape, tile, shares, kind):
+    """The bf16 path inverts inside T's launch, in the tiles' LDS and on as many wavefronts as they have: the same
+    matrices and bounds as for the inverse by itself, in four partial sums, and T = C G^T beside it."""
+    import ctypes as C
+    B, M, d, r = shape
+    rng = np.random.default_rng(M + r)
+    lib = fv.load_library()
+    assert lib["_ZN4fvar21batched_f32_tile_rowsEiiii"](B, M, r, d) == tile
+    assert lib["_ZN4fvar17batched_f32_partsEiiii"](B, M, r, d) == shares
+    n = min(B, 3)                                     # different matrices; sample b gets number b % n
+    S, ridge = _gram_matrices(kind, n, r, rng)
+    parts = np.stack([0.125 * S, 0.25 * S, 0.125 * S, 0.5 * S], axis=1)
+    Sd = torch.from_numpy(np.ascontiguousarray(parts)).cuda()[torch.arange(B) % n].contiguous()
+    g = torch.Generator(device="cuda").manual_seed(r)
+    cache = torch.randn((B, M, d), generator=g, device="cuda").to(torch.bfloat16)
+    G = torch.randn((B, r, d), generator=g, device="cuda").to(torch.bfloat16)
+    T = torch.full((shares, B, M, r), float("nan"), device="cuda")
+    X = torch.full((B, r, r), float("nan"), dtype=torch.float64, device="cuda")
+    launch = lib["_ZN4fvar23launch_factor_t_inverseENS_5DTypeEPKvS2_iiiiPfPKddPdP12ihipStream_t"]
+    launch.restype = None
+    launch.argtypes = [C.c_int, C.c_void_p, C.c_void_p] + 4 * [C.c_int] + [C.c_void_p, C.c_void_p, C.c_double, C.c_void_p, C.c_void_p]
+    torch.cuda.synchronize()
+    launch(1, cache.data_ptr(), G.data_ptr(), B, M, r, d, T.data_ptr(), Sd.data_ptr(), ridge, X.data_ptr(), None)
+    torch.cuda.synchronize()
+    for b in sorted({0, 1, 2, B - 1} & set(range(B))):
+        _check_inverse(kind, X[b].cpu().numpy(), parts[b % n].sum(0), ridge, rng)
+        ref = cache[b].double() @ G[b].double().t()
+        assert float((T[:, b].double().sum(0) - ref).norm() / ref.norm()) <= 1e-6    # fp32 sums of bf16 products
 
 
 @pytest.mark.parametrize("r", [8, 16, 24, 32, 56, 64, 72, 104, 128])
