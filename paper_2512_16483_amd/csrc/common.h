@@ -193,7 +193,7 @@ void launch_gemm_bf16_batched_f32(const void *A, const void *W, int nbatch, int 
 // out[b] = qt[b] x[b]:  qt:[rows,M] (sample stride q_stride elements, 0 = shared), x:[B,M,d],
 // out:[B,rows,d].  M must be a multiple of the 16-byte chunk (8 bf16 / 4 fp32 elements).
 bool kmajor_in_groups(int B, int M, int rows, int d);
-bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int B, int M, int rows,
+void launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int B, int M, int rows,
                              int d, void *out, hipStream_t st);
 void launch_rp_project(DType dt, const void *qt, size_t q_stride, const void *x, int B, int M,
                        int rows, int d, void *out, hipStream_t st);

@@ -891,16 +891,16 @@ bool kmajor_in_groups(int B, int M, int rows, int d)
 }
 
 // Runs out[b] = qt[b] x[b] (qt: [rows][M] per sample or shared, x[b]: [M][d]) on the tiled MFMA
-// kernel (M a multiple of 8, d of 64).  Returns false, with nothing launched, where a row tile of qt does
-// not fit 32-bit byte offsets (M of 2^25 and more).  Tile by predicted time, constants as in gemm_plan plus
+// kernel (M a multiple of 8, d of 64).  Where not even 64 rows of qt fit 32-bit byte offsets (M of 2^25 and more),
+// as many rows at a time as do, sample by sample (8 rows of 2^25 tokens, width 64: 0.20 s; 15.8 by a thread per
+// column).  Tile by predicted time, constants as in gemm_plan plus
 // a tenth for the transposing reads (no 320x256 tile: with them it would not fit the 256 registers).  Even a
 // few tiles here beat many of a kernel that turns X around through registers, whose 64-token chunk takes
 // 1.7 us against 0.4 us of a 64x128 k-tile: 692 x 2304 x 2048 61 -> 17 us, 4 x (128 x 4096 x 4096)
 // 123 -> 39 us; ragged, 692 x 2312 x 2048 51.5 -> 18.6, 4 x (2000 x 6392 x 4096) 720 -> 368 us.
-bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int B, int M, int rows,
+void launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int B, int M, int rows,
                              int d, void *out, hipStream_t st)
 {
-    if (M % 8 != 0 || d % 8 != 0 || M < 8 || d < 8 || rows < 1 || B < 1) return false;
     const struct { int bm, bn; double k_us, tile_us; } cands[] = {
         {256, 256, 1.64, 3.4}, {192, 256, 1.43, 2.0}, {256, 128, 0.98, 1.9}, {128, 256, 0.98, 1.9},
         {192, 128, 0.77, 1.3}, {128, 128, 0.59, 0.95}, {64, 128, 0.41, 0.3}};
@@ -930,9 +930,15 @@ bool launch_gemm_bf16_kmajor(const void *qt, size_t q_stride, const void *x, int
         if (kmajor_in_groups(B, M, rows, d)) launch_kmajor_cfg<64, 128, 2, 2, 3, 2>(qt, q_stride, x, B, rows, d, M, out, st);
         else launch_kmajor_cfg<64, 128, 2, 4, 4>(qt, q_stride, x, B, rows, d, M, out, st);
         break;
-    default: return false;
+    default: {
+        const int n = (int)(((1u << 31) - BK) / (unsigned)M) + 1;
+        for (int b = 0; b < B; ++b)
+            for (int t = 0; t < rows; t += n)
+                launch_kmajor_cfg<64, 128, 2, 4, 4>((const uint16_t *)qt + b * q_stride + (size_t)t * M, 0,
+                                                    (const uint16_t *)x + (size_t)b * M * d, 1, n < rows - t ? n : rows - t,
+                                                    d, M, (uint16_t *)out + ((size_t)b * rows + t) * d, st);
     }
-    return true;
+    }
 }
 
 // Sum of the partial tiles of a split contraction + the epilogue (bias, GELU, residual, bf16 or

@@ -114,6 +114,21 @@ def test_rp_project_ragged_token_counts(B, M, rows, d, per_sample):
         assert bool(torch.isnan(out[:b]).all()) and bool(torch.isnan(out[b + 1:]).all())
 
 
+def test_rp_project_rows_beyond_32bit_offsets():
+    """Token counts whose 64 rows of Q^T span 4 GiB: the rows are taken a few at a time.  A selection matrix gives
+    rows of the map bit for bit; one past the last row of a tile and the last token are among them."""
+    M, rows, d = (1 << 26) + 8, 37, 64
+    x = torch.empty((1, M, d), dtype=torch.bfloat16, device="cuda").normal_(generator=torch.Generator("cuda").manual_seed(1))
+    q = torch.zeros((rows, M), dtype=torch.bfloat16, device="cuda")
+    idx = torch.tensor([(M - 1) * (rows - 1 - t) // (rows - 1) for t in range(rows)])     # the last token first
+    assert int(idx.min()) == 0 and int(idx.max()) == M - 1
+    q[torch.arange(rows), idx] = 1.0
+    out = torch.full((1, rows, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    fv.fvar_rp_project(_ctx(d, "bf16"), q, False, x, 1, M, rows, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], x[0, idx])
+
+
 def test_rp_project_tiled_path_selection_matrix_bitexact():
     # products with 1 and 0 are exact: a column-selection Q reproduces the rows bit for bit
     B, M, rows, d = 12, 128, 128, 4096
