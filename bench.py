@@ -267,7 +267,8 @@ def kernel_work(W, side):
     out["rp_project"] = ("flop", 2.0 * B * k * M * d)
     out["cache_fill"] = ("byte", 2.0 * B * M * d * es)
     out["factor_project"] = ("flop", 2.0 * B * r * M * d)
-    out["factor_t_inverse"] = ("byte", B * (M * d * es + r * d * es + M * r * 4.0))
+    out["factor_t_inverse"] = out["factor_t"] = ("byte", B * (M * d * es + r * d * es + M * r * 4.0))
+    out["factor_inverse"] = ("flop", B * (r ** 3) * (1.0 / 3 + 1.0 / 3 + 2.0 / 3))
     out["factor_gram"] = ("flop", 2.0 * B * r * r * d)
     out["factor_w"] = ("flop", 2.0 * B * M * r * r)
     return out

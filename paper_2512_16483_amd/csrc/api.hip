@@ -643,9 +643,14 @@ fvar_status fvar_cache_factors(fvar_ctx *c, fvar_stream stream, const void *cach
         fvar::launch_rp_project(dt, qt, q_per_sample ? (size_t)r * M : 0, cache, B, M, r, d, g_c, st);
     });
     timed(c, st, "factor_gram", [&] { fvar::launch_factor_gram(dt, g_c, B, r, d, S, st); });
-    timed(c, st, "factor_t_inverse", [&] {
-        fvar::launch_factor_t_inverse(dt, cache, g_c, B, M, r, d, T, S, ridge, Sinv, st);
-    });
+    if (dt == DType::BF16) {
+        timed(c, st, "factor_t_inverse", [&] {
+            fvar::launch_factor_t_inverse(cache, g_c, B, M, r, d, T, S, ridge, Sinv, st);
+        });
+    } else {
+        timed(c, st, "factor_t", [&] { fvar::launch_factor_t_f32(cache, g_c, B, M, r, d, T, st); });
+        timed(c, st, "factor_inverse", [&] { fvar::launch_factor_inverse(S, 1, B, r, ridge, Sinv, st); });
+    }
     timed(c, st, "factor_w", [&] { fvar::launch_factor_w(dt, T, Sinv, B, M, r, d, w_c, st); });
     return launch_status(c, who);
 }

@@ -211,8 +211,9 @@ int gram_room(DType dt);
 void launch_factor_gram(DType dt, const void *g_c, int B, int r, int d, double *S, hipStream_t st);
 void launch_factor_inverse(const double *S, int parts, int B, int r, double ridge, double *Sinv,
                            hipStream_t st);
-void launch_factor_t_inverse(DType dt, const void *cache, const void *g_c, int B, int M, int r, int d, float *T,
+void launch_factor_t_inverse(const void *cache, const void *g_c, int B, int M, int r, int d, float *T,
                              const double *S, double ridge, double *Sinv, hipStream_t st);
+void launch_factor_t_f32(const void *cache, const void *g_c, int B, int M, int r, int d, float *T, hipStream_t st);
 void launch_factor_w(DType dt, const float *T, const double *Sinv, int B, int M, int r, int d, void *w_c,
                      hipStream_t st);
 

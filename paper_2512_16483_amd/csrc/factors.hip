@@ -256,16 +256,16 @@ void launch_factor_inverse(const double *S, int parts, int B, int r, double ridg
 #undef FVAR_INVERSE
 }
 
-// T, and the inverse of S, which does not need it
-void launch_factor_t_inverse(DType dt, const void *cache, const void *g_c, int B, int M, int r, int d, float *T,
+// bf16: T, an ordinary linear layer per sample in fp32, and the inverse of S, which does not need it, in one launch
+void launch_factor_t_inverse(const void *cache, const void *g_c, int B, int M, int r, int d, float *T,
                              const double *S, double ridge, double *Sinv, hipStream_t st)
 {
-    if (dt == DType::BF16) {                       // an ordinary linear layer per sample, in fp32
-        launch_gemm_bf16_batched_f32(cache, g_c, B, M, r, d, T, InverseJob{S, ridge, Sinv, r}, st);
-        return;
-    }
+    launch_gemm_bf16_batched_f32(cache, g_c, B, M, r, d, T, InverseJob{S, ridge, Sinv, r}, st);
+}
+
+void launch_factor_t_f32(const void *cache, const void *g_c, int B, int M, int r, int d, float *T, hipStream_t st)
+{
     launch(t_f32_kernel, dim3(M, B), dim3(256), 0, st, (const float *)cache, (const float *)g_c, M, r, d, T);
-    launch_factor_inverse(S, 1, B, r, ridge, Sinv, st);
 }
 
 template <typename TT>

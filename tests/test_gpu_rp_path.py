@@ -313,11 +313,11 @@ def test_inverse_inside_the_launch_of_t(shape, tile, shares, kind):
     G = torch.randn((B, r, d), generator=g, device="cuda").to(torch.bfloat16)
     T = torch.full((shares, B, M, r), float("nan"), device="cuda")
     X = torch.full((B, r, r), float("nan"), dtype=torch.float64, device="cuda")
-    launch = lib["_ZN4fvar23launch_factor_t_inverseENS_5DTypeEPKvS2_iiiiPfPKddPdP12ihipStream_t"]
+    launch = lib["_ZN4fvar23launch_factor_t_inverseEPKvS1_iiiiPfPKddPdP12ihipStream_t"]
     launch.restype = None
-    launch.argtypes = [C.c_int, C.c_void_p, C.c_void_p] + 4 * [C.c_int] + [C.c_void_p, C.c_void_p, C.c_double, C.c_void_p, C.c_void_p]
+    launch.argtypes = [C.c_void_p, C.c_void_p] + 4 * [C.c_int] + [C.c_void_p, C.c_void_p, C.c_double, C.c_void_p, C.c_void_p]
     torch.cuda.synchronize()
-    launch(1, cache.data_ptr(), G.data_ptr(), B, M, r, d, T.data_ptr(), Sd.data_ptr(), ridge, X.data_ptr(), None)
+    launch(cache.data_ptr(), G.data_ptr(), B, M, r, d, T.data_ptr(), Sd.data_ptr(), ridge, X.data_ptr(), None)
     torch.cuda.synchronize()
     for b in sorted({0, 1, 2, B - 1} & set(range(B))):
         _check_inverse(kind, X[b].cpu().numpy(), parts[b % n].sum(0), ridge, rng)
@@ -396,6 +396,22 @@ def test_factor_t_rounding(B, M, d, r):
         ref = cache[b].double() @ g_c[b].double().t()
         err = ((T[b].double() - ref).norm() / ref.norm()).item()
         assert err <= bound, (b, parts, err, bound)
+
+
+@pytest.mark.parametrize("dtype,steps", [("f32", ["project", "t", "gram", "inverse", "w"]),
+                                         ("bf16", ["project", "gram", "t_inverse", "w"])])
+def test_cache_factors_profile_names_every_step(dtype, steps):
+    """Per-kernel timing of the factors: a label for each launch (bf16: T and the inverse share one)."""
+    B, M, d, r = 1, 64, 64, 16
+    ctx = _ctx(d, dtype)
+    Cm, Q = wl.cached_feature(B, M, d, 20, seed=5, noise=0.1), _q(B, M, r, 6, dtype, False)
+    w_c, g_c = (torch.empty(s, dtype=tdtype(dtype), device="cuda") for s in ((B, M, r), (B, r, d)))
+    ws = torch.empty(fv.fvar_factors_workspace_bytes(ctx, B, M, r), dtype=torch.uint8, device="cuda")
+    fv.fvar_profile_enable(ctx, True)
+    fv.fvar_cache_factors(ctx, to_dev(Cm, dtype), _qt_dev(Q, dtype), False, B, M, r, 1e-6, w_c, g_c, ws)
+    torch.cuda.synchronize()
+    prof = fv.fvar_profile_read(ctx)
+    assert sorted(prof) == sorted("factor_" + s for s in steps) and all(n == 1 and ms > 0 for n, ms in prof.values())
 
 
 def test_cache_factors_feed_the_fill():
