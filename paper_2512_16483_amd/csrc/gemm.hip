@@ -300,9 +300,9 @@ constexpr size_t gemm_lds_bytes(int BM, int BN, int WM, int WN, int STAGES, int 
 // is bound neither by the DMA (2/3 of its time by itself), nor the LDS reads (1/2 to 2/3) nor the MFMAs (1/3 to
 // 1/2), but by how badly these overlap between two barriers: KG k-tiles per barrier, and fewer fragment reads,
 // since a group of half the wavefronts has sub-tiles of twice the area.  Us per k-tile with all CUs at work,
-// one group -> KG: 64x64 0.32 -> 0.25, 64x128 0.34 -> 0.30, 128x64 0.34 -> 0.28.  128x128 and 192x128 gain a
-// tenth there too (0.51 -> 0.45, 0.69 -> 0.61) but lose it to the longer first fill and the exchange at the 30
-// to 130 k-tiles that they get, and keep one group.
+// one group -> KG: 64x64 0.32 -> 0.25, 64x128 0.34 -> 0.30, 128x64 0.34 -> 0.28.  128x128 and 192x128 keep
+// one group: in two, whose rings then have two stages instead of four and three, they take 1.10 and 1.07 of the time
+// over 3000 timings, 1.09 and 1.05 at 16 k-tiles per workgroup, 1.12 and 1.05 at 128.
 //
 // CHAINS: no fp32 accumulation runs over more than a few k-tiles; the results of these chains are added
 // up, with compensation, in a second set of registers.  For a result that meets the inverse of a Gram
@@ -835,6 +835,8 @@ size_t batched_f32_room(int nbatch, int rows, int K)
 struct BatchedPlan { int bm, parts; };
 static BatchedPlan batched_f32_plan(int nbatch, int rows, int N, int K)
 {
+    // (64 rows of the narrow tile run in four groups, but are priced without: as linear layers are, 0.237 and 0.46,
+    // takes more shares and makes handovers of 144 sizes 0.1 % slower, at rank 32 up to 4.6)
     const bool narrow = N <= 64;
     const struct { int bm; double k_us, tile_us; } cands[3] = {
         {256, 0.896, 1.9}, {128, narrow ? 0.364 : 0.537, narrow ? 0.3 : 0.95}, {64, narrow ? 0.274 : 0.375, 0.3}};
@@ -1189,12 +1191,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const float *__restri
 // with rounds of workgroups over the 256 CUs, never below the time in which the operands and the
 // output cross HBM.  Its constants are a least-squares fit to 8200 timings of every tile with every
 // division on 344 problems (rows 7 .. 15360, hidden 1024 .. 4096, the four layers of a block):
-// residual 4 % rms; the plan it picks is on average 2 % (worst 27 %) slower than the best
-// candidate of each problem, where one rate per tile and no small tiles cost 30 % (worst 3x).  The
-// undivided timings are in profiles/linear_layer_tile_times.txt, divisions in linear_layer_divisions.txt.
+// residual 4 % rms.  Of 63000 timings of the kernels as they are now, on 1320 problems, its picks are on average
+// 2.7 % (19 in 20 at most 15 %, worst 34 %) slower than the best candidate of each; constants of the small tiles
+// refitted on half of them gain 0.2 % on the other half.  One rate per tile and no small tiles cost 30 % (worst 3x).
+// The undivided timings are in profiles/linear_layer_tile_times.txt, divisions in linear_layer_divisions.txt.
 // With wavefront groups the last three tiles have constants of their own (kGroupedTiles), used exactly where the
 // launch takes them.  With these for the kernels without groups too, 320 workgroups of 64x64 looked 10 % cheaper than
-// they are: on 139 problems where the picks differ 16.6 us in geometric mean instead of 15.8, at worst 1536 x 6144
+// they are: on 115 of 3000 problems where the picks differ 17.1 us in geometric mean instead of 15.9, at worst 1536 x 6144
 // with 703 rows 40.5 instead of 28.1, and 128x64 divided eight ways took more workspace than 64x64 in five.
 constexpr double kLaunchUs = 3.6;      // a launch by itself
 constexpr double kRowsRate = 11.9e6;   // bytes / us that gemm_rows_kernel's workgroups read, L2 hits included

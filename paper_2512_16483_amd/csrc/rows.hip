@@ -12,7 +12,8 @@ namespace fvar {
 // 11.8 -> 6.9, 300 of 4096 10.7 -> 6.4 and 16.0 -> 7.3, 6400 of 4096 39 -> 35 and 44 -> 33, 120 of 1024 4.6 -> 3.8
 // and 5.5 -> 3.5.  Four 16-byte or eight 8-byte chunks a batch: with eight of 16 bytes the registers leave two
 // wavefronts per SIMD at 4096 columns (39 us for 6400 rows), with two the last batches wait again (6.8 and 8.8
-// for 300 rows).
+// for 300 rows).  At 8192 columns the eight of 8 bytes take two registers too many for two wavefronts per SIMD; four
+// would not: whole blocks are 1 % slower with four up to 512 rows, 0.5 % faster at 1600, the same at 4096.
 constexpr int kAffineGather = 4, kAffineStream = 8;
 
 // CH = 16-byte chunks per lane (row length <= 64 * CH chunks); AFFINE: gamma or beta or both are there
