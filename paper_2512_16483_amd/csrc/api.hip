@@ -167,17 +167,15 @@ BlockWs carve(const fvar_ctx *c, void *ws, int B, int rows)
     w.h1 = take(R * d * sizeof(float));       // intermediate residual stream, always fp32
     w.hid = take(R * F * es);
     const DType dt = dtype(c);
-    w.qkv = fvar::gemm_plan(dt, (int)R, (int)(3 * d), (int)d);
-    w.o = fvar::gemm_plan(dt, (int)R, (int)d, (int)d);
-    w.fc1 = fvar::gemm_plan(dt, (int)R, (int)F, (int)d);
-    w.fc2 = fvar::gemm_plan(dt, (int)R, (int)d, (int)F);
+    const int shape[4][2] = {{(int)(3 * d), (int)d}, {(int)d, (int)d}, {(int)F, (int)d}, {(int)d, (int)F}};   // N, K
     // partial results where the key axis or the contraction axis is divided between workgroups
-    size_t part = std::max(std::max(w.qkv.scratch_floats, w.o.scratch_floats),
-                           std::max(w.fc1.scratch_floats, w.fc2.scratch_floats));
-    part = std::max(part, fvar::attention_scratch_floats(dt, B, rows, c->cfg.heads, c->cfg.head_dim));
+    size_t part = fvar::attention_scratch_floats(dt, B, rows, c->cfg.heads, c->cfg.head_dim);
+    for (const auto &l : shape) part = std::max(part, fvar::gemm_plan(dt, (int)R, l[0], l[1]).scratch_floats);
     // fp32: what the plans take falls as the rows become more; their bound does not, so that a
     // workspace sized for the largest call serves every smaller one (bf16 never had that: see fvar.h)
     if (dt != DType::BF16) part = std::max(part, fvar::gemm_f32_scratch_bound((int)R, (int)std::max(3 * d, F)));
+    fvar::GemmPlan *plan[4] = {&w.qkv, &w.o, &w.fc1, &w.fc2};
+    for (int i = 0; i < 4; ++i) *plan[i] = fvar::linear_plan(dt, (int)R, shape[i][0], shape[i][1], part);
     w.part = part ? reinterpret_cast<float *>(take(part * sizeof(float))) : nullptr;
     w.total = off;
     return w;

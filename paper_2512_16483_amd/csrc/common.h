@@ -143,12 +143,15 @@ struct GemmEpilogue {
     // fp32 between the two halves of the block so that it is not rounded twice.
     int out_f32 = 0, res_f32 = 0;
 };
-// How a linear layer is run: kernel and tile (bf16: index into the tables of gemm.hip; fp32: 16-row tiles
-// per workgroup), workgroups that share the contraction axis of every tile (nsplit) or, in bf16, of the
-// tiles beyond the last whole round (tail), and the floats of scratch that their partial tiles take.  A
-// function of the shape alone.
+// How a linear layer is run: kernel and tile (index into the tables of gemm.hip), workgroups that share the
+// contraction axis of every tile (nsplit) or, with the tiled kernel, of the tiles beyond the last whole round
+// (tail), and the floats of scratch that their partial tiles take.
+// gemm_plan is a function of the shape alone and tells what scratch a call is given (in fp32, and for cfg >= the
+// number of tiles, that is all it is for); linear_plan is what runs: gemm_plan's tile or an instance of
+// gemm_rows_kernel, whichever is predicted faster, the latter within `room` floats.
 struct GemmPlan { int cfg, nsplit, tail; size_t scratch_floats; };
 GemmPlan gemm_plan(DType dt, int rows, int N, int K);
+GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room);
 // floats that no fp32 plan of up to `rows` rows and N columns exceeds; never falls as rows grow
 size_t gemm_f32_scratch_bound(int rows, int N);
 // `part`: plan.scratch_floats floats (unused when 0)

@@ -13,10 +13,10 @@
 // grid.  Bigger tiles cut the L1/LDS traffic per flop (a 128x128 tile needs the full 64 B/clk of
 // the CU's vector L1 at peak MFMA rate, a 256x256 tile half of it) but quantise badly on the few
 // thousand rows of a pruned scale, and a few rows leave most CUs without a tile: eleven tiles from
-// 320x256 down to 64x64, a kernel without staging for a few rows, and divisions of the contraction
-// axis between workgroups, picked per problem by predicted time (gemm_plan, at the end).
+// 320x256 down to 64x64, a kernel whose wavefronts have rings of their own for a few rows, and divisions of
+// the contraction axis between workgroups, picked per problem by predicted time (linear_plan, at the end).
 //
-// fp32: the fp32 MFMA without staging (gemm_f32_kernel).
+// fp32: the same kernel on the fp32 MFMA at every size (gemm_rows_kernel).
 #include <cmath>
 #include <type_traits>
 
@@ -962,105 +962,6 @@ __global__ __launch_bounds__(256) void gemm_splitk_epilogue_kernel(const float *
     finish_quad(ep, row, col, v);
 }
 
-// Linear layer of a few rows: bound by the latency of the weights' one trip from HBM, not by MFMA.
-// No LDS staging and no barrier before the end: a workgroup owns 16*FT output features and 16*TT
-// rows, its NW wavefronts take NW contiguous shares of the contraction axis, and every operand
-// fragment goes from global memory straight to registers, two groups of U k-steps in flight (for
-// K = 2048 that is the wavefront's whole share).  Weights are the A operand of the 16x16x32 MFMA, so a
-// lane ends up with 4 consecutive features of one row; the wavefronts' partial tiles meet in LDS.
-// The rows are read again by every feature tile (L2 hits), which is what bounds the kernel from
-// about 64 rows on; there the staged tiles win.  Microseconds at 16 rows, hidden 2048, 128x128 tiles
-// (divided where that helped) -> here: QKV 20.2 -> 8.9, O 11.5 -> 6.3, FC1 15.0 -> 11.1; at 64 rows
-// O 13.5 -> 8.3 (25 MB of weights alone take 5.2 us at the rate of a large copy).
-template <int FT, int TT, int NW>
-__global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(
-    const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, int rows, int N, int K, int row_tiles,
-    int nsplit, EpiParams ep, float *__restrict__ part)
-{
-    constexpr int U = 4;                                // k-steps per load group
-    __shared__ float4 red[NW][FT * TT][64];
-    const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q16 = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // each XCD takes one contiguous share of the (feature tile, split, row tile) units
-    const int units = row_tiles * nsplit * (N / (16 * FT));
-    const int per_xcd = (units + 7) / 8;
-    int pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (pid >= units || (int)(blockIdx.x >> 3) >= per_xcd) return;
-    const int rt = pid % row_tiles; pid /= row_tiles;
-    const int split = pid % nsplit, n0 = pid / nsplit * (16 * FT), row0 = rt * (16 * TT);
-
-    const int steps = K / 32, parts = nsplit * NW, pi = split * NW + wave;
-    const int s0 = (int)((long)steps * pi / parts), s1 = (int)((long)steps * (pi + 1) / parts);
-    const uint16_t *wp[FT], *ap[TT];
-#pragma unroll
-    for (int f = 0; f < FT; ++f) wp[f] = W + (size_t)(n0 + 16 * f + c16) * K + 8 * q16;
-#pragma unroll
-    for (int t = 0; t < TT; ++t) ap[t] = A + (size_t)min(row0 + 16 * t + c16, rows - 1) * K + 8 * q16;
-    floatx4_t acc[FT][TT];
-#pragma unroll
-    for (int f = 0; f < FT; ++f)
-#pragma unroll
-        for (int t = 0; t < TT; ++t) acc[f][t] = floatx4_t{0};
-    bf16x8_t wf[2][U][FT], af[2][U][TT];
-    auto load = [&](int s, int buf) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = min(s + u, s1 - 1) * 32;
-#pragma unroll
-            for (int f = 0; f < FT; ++f) wf[buf][u][f] = *reinterpret_cast<const bf16x8_t *>(wp[f] + k);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = min(s + u, s1 - 1) * 32;
-#pragma unroll
-            for (int t = 0; t < TT; ++t) af[buf][u][t] = *reinterpret_cast<const bf16x8_t *>(ap[t] + k);
-        }
-    };
-    auto mac = [&](int s, int buf) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (s + u < s1) {
-#pragma unroll
-                for (int f = 0; f < FT; ++f)
-#pragma unroll
-                    for (int t = 0; t < TT; ++t)
-                        acc[f][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[buf][u][f], af[buf][u][t],
-                                                                            acc[f][t], 0, 0, 0);
-            }
-    };
-    if (s0 < s1) {
-        load(s0, 0);
-        for (int s = s0; s < s1; s += 2 * U) {
-            if (s + U < s1) load(s + U, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            mac(s, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            if (s + 2 * U < s1) load(s + 2 * U, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            if (s + U < s1) mac(s + U, 1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-#pragma unroll
-    for (int f = 0; f < FT; ++f)
-#pragma unroll
-        for (int t = 0; t < TT; ++t)
-            red[wave][f * TT + t][lane] = make_float4(acc[f][t][0], acc[f][t][1], acc[f][t][2], acc[f][t][3]);
-    __syncthreads();
-    for (int blk = wave; blk < FT * TT; blk += NW) {
-        float4 v = red[0][blk][lane];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) {
-            const float4 p = red[w][blk][lane];
-            v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-        }
-        const int row = row0 + (blk % TT) * 16 + c16, col = n0 + (blk / TT) * 16 + 4 * q16;
-        if (row >= rows) continue;
-        if (nsplit > 1) *reinterpret_cast<float4 *>(part + ((size_t)split * rows + row) * N + col) = v;
-        else finish_quad(ep, row, col, v);
-    }
-}
-
 // ------------------------------------------------------------------------------ fp32
 // Same epilogue for fp32 storage.
 __device__ __forceinline__ void finish_quad_f32(const EpiParams &ep, int row, int col, float4 v)
@@ -1099,87 +1000,144 @@ __global__ __launch_bounds__(256) void gemm_f32_merge_kernel(const float *__rest
     finish_quad_f32(ep, row, col, v);
 }
 
-// fp32 linear layer on the fp32 MFMA (16x16x4), laid out as gemm_rows_kernel: a workgroup owns 32
-// output features and 16*TT rows, its wavefronts share the contraction axis, operands go from global
-// memory to registers as float4 of four consecutive k (the k-slots of four MFMAs) and the partial
-// tiles meet in LDS.  The limit is the MFMA rate (157 TFLOP/s, as the vector units; six 1 KiB loads feed
-// 32 MFMAs of 32 clk), so the point of the layout is to keep every CU at it: the launcher divides the
-// contraction axis until there is a workgroup for every CU.  At 128 rows it is far from that limit: the
-// MFMA pipes are busy 0.23 of the clocks (25 TFLOP/s for O to 59 for FC1) and the wavefronts, one
-// k-step of loads ahead, wait half of their time.  128 rows, hidden 1024,
-// against 64x64 tiles of FMAs through LDS: QKV 62.8 -> 17.7, O 61.9 -> 10.6, FC1 63.5 -> 18.3,
-// FC2 232.8 -> 21.1 us (24.0, 12.1, 24.7, 23.8 with two workgroups per CU); 2048 rows: the block
-// 1499 -> 1085 us.  The error against 64 bits falls from 5.8e-7 to 1.7e-7 (shorter sums).
-template <int TT, int NW>
-__global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const float *__restrict__ A,
-                                                           const float *__restrict__ W, int rows, int N,
-                                                           int K, int row_tiles, int nsplit, EpiParams ep,
-                                                           float *__restrict__ part)
+// Linear layer of a few rows (bf16), or of any number (fp32).  A workgroup owns 16*FT output features and 16*TT rows; its
+// NW wavefronts take NW shares of the contraction axis, each with a ring of its own in LDS, so there is no
+// barrier before the end, where the partial tiles meet in LDS.  Weights are the A operand of the MFMA: a lane ends up
+// with 4 consecutive features of one row.
+// What bounds it: at few rows the operands' way through the CU's vector L1 (the rows are read again by
+// every feature tile, L2 hits), so the DMA fetches whole 128-byte lines.  Loads in the MFMA's own lane order, a row
+// per lane, would save the LDS but reach only 38 GB/s per CU where these reach 150: only neighbouring lanes'
+// addresses are taken together.  Rings of 64-byte rows are 20 to 30 % slower too, and more than two or three steps
+// in flight bring nothing.  us at 64 rows, hidden 2048, weights from HBM, against loads straight to registers or 64x64
+// tiles, whichever was faster: QKV 14.5 -> 10.3, O 11.0 -> 6.8, FC1 15.1 -> 11.1, FC2 15.9 -> 14.1 (the
+// weights alone take 7.2, 4.8, 8.9 and 8.9, an empty launch 2.4); at 16 rows QKV 10.8 -> 7.5, FC1 11.9 -> 8.6.
+// fp32, bound by the MFMA's rate (157 TFLOP/s, as the vector units) from a few hundred rows on, so what counts is
+// that every CU gets the same share: hidden 1024, 128 rows QKV 17.7 -> 11.1, O 10.6 -> 6.8, FC1 18.3 -> 13.9,
+// FC2 21.1 -> 14.9, 2048 rows FC1 227 -> 178.
+template <typename T, int FT, int TT, int NW, int STAGES>
+__global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(
+    const T *__restrict__ A, const T *__restrict__ W, int rows, int N, int K, int row_tiles,
+    int nsplit, EpiParams ep, float *__restrict__ part)
 {
-    constexpr int FT = 2;
-    __shared__ float4 red[NW][FT * TT][64];
+    constexpr int NF = FT + TT;                         // fragments of 16 rows
+    constexpr int IPF = 2, NI = NF * IPF;               // DMA instructions (8 rows x 128 bytes) per fragment and step
+    constexpr int KE = 128 / sizeof(T);                 // contraction indices per step: two MFMA k-steps
+    static_assert(FT * TT <= STAGES * NI, "a wavefront's result fits its ring");
+    extern __shared__ uint4 lds_raw[];
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q16 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int units = row_tiles * nsplit * (N / (16 * FT)), per_xcd = (units + 7) / 8;
+    // each XCD takes one contiguous share of the (feature tile, split, row tile) units
+    const int units = row_tiles * nsplit * (N / (16 * FT));
+    const int per_xcd = (units + 7) / 8;
     int pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (pid >= units) return;
+    if (pid >= units || (int)(blockIdx.x >> 3) >= per_xcd) return;
     const int rt = pid % row_tiles; pid /= row_tiles;
     const int split = pid % nsplit, n0 = pid / nsplit * (16 * FT), row0 = rt * (16 * TT);
-    const int steps = K / 16, parts = nsplit * NW, pi = split * NW + wave;
-    const int s0 = (int)((long)steps * pi / parts), s1 = (int)((long)steps * (pi + 1) / parts);
-    const float *wp[FT], *ap[TT];
+
+    // steps of this wavefront: the first `extra` of all shares take one more
+    const int steps = K / KE, parts = nsplit * NW, pi = split * NW + wave;
+    const int per = steps / parts, extra = steps - per * parts;
+    const int s0 = pi * per + min(pi, extra), n = per + (pi < extra ? 1 : 0);
+    // lane l of a DMA instruction fills physical chunk l%8 of row l/8; chunks are swizzled as in lds_off()
+    const T *Wb = W + (size_t)n0 * K + (size_t)s0 * KE, *Ab = A + (size_t)row0 * K + (size_t)s0 * KE;
+    uint32_t off[NI];
 #pragma unroll
-    for (int f = 0; f < FT; ++f) wp[f] = W + (size_t)(n0 + 16 * f + c16) * K + 4 * q16;
+    for (int i = 0; i < NI; ++i) {
+        const int r = (i % IPF) * 8 + lane / 8, f = i / IPF;
+        const int row = f < FT ? 16 * f + r : min(row0 + 16 * (f - FT) + r, rows - 1) - row0;
+        off[i] = (uint32_t)((size_t)row * K * sizeof(T)) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+    }
+    constexpr int RING = STAGES * NI * 1024;
+    const uint32_t ring = (uint32_t)(uintptr_t)lds_raw + wave * RING;
+    const uint4 *mine = lds_raw + wave * (RING / 16);
+    auto issue = [&](int s) {
+        const uint32_t dst = ring + (uint32_t)(s % STAGES) * (NI * 1024);
 #pragma unroll
-    for (int t = 0; t < TT; ++t) ap[t] = A + (size_t)min(row0 + 16 * t + c16, rows - 1) * K + 4 * q16;
+        for (int i = 0; i < NI; ++i)
+            dma_b128((i / IPF < FT ? Wb : Ab) + (size_t)s * KE, off[i], dst + i * 1024);
+    };
+    // waits until only the `after` steps requested last are outstanding
+    auto landed = [&](int after) {
+        if (STAGES > 3 && after == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STAGES > 3 ? 3 * NI : 0) : "memory");
+        else if (STAGES > 2 && after == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STAGES > 2 ? 2 * NI : 0) : "memory");
+        else if (after == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    static_assert(STAGES >= 2 && STAGES <= 4, "wait counts are written for 2 to 4 stages");
+
     floatx4_t acc[FT][TT];
 #pragma unroll
     for (int f = 0; f < FT; ++f)
 #pragma unroll
         for (int t = 0; t < TT; ++t) acc[f][t] = floatx4_t{0};
-    float4 wf[2][FT], af[2][TT];
-    auto load = [&](int s, int buf) {
+    uint4 frag[2][NF];
+    // fragments of MFMA k-step u of step s
+    auto fetch = [&](int s, int u, uint4 *dst) {
+        const uint4 *src = mine + (s % STAGES) * (NI * 64) + c16 * 8 + ((u * 4 + q16) ^ (c16 >> 1));
 #pragma unroll
-        for (int f = 0; f < FT; ++f) wf[buf][f] = *reinterpret_cast<const float4 *>(wp[f] + s * 16);
-#pragma unroll
-        for (int t = 0; t < TT; ++t) af[buf][t] = *reinterpret_cast<const float4 *>(ap[t] + s * 16);
+        for (int i = 0; i < NF; ++i) dst[i] = src[i * 128];
     };
-    auto mac = [&](int buf) {
+    auto mac = [&](const uint4 *v) {
+        if constexpr (sizeof(T) == 2) {
+#pragma unroll
+            for (int f = 0; f < FT; ++f)
+#pragma unroll
+                for (int t = 0; t < TT; ++t)
+                    acc[f][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8_t, v[f]), __builtin_bit_cast(bf16x8_t, v[FT + t]), acc[f][t], 0, 0, 0);
+        } else {
+            // a chunk holds four consecutive k of a row: the k-slots of four MFMAs
 #define FVAR_MAC(c)                                                                                       \
-        _Pragma("unroll") for (int f = 0; f < FT; ++f) _Pragma("unroll") for (int t = 0; t < TT; ++t)     \
-            acc[f][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[buf][f].c, af[buf][t].c, acc[f][t], 0, 0, 0)
-        FVAR_MAC(x); FVAR_MAC(y); FVAR_MAC(z); FVAR_MAC(w);
+            _Pragma("unroll") for (int f = 0; f < FT; ++f) _Pragma("unroll") for (int t = 0; t < TT; ++t) \
+                acc[f][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(v[f].c),                 \
+                                                                 __uint_as_float(v[FT + t].c), acc[f][t], 0, 0, 0)
+            FVAR_MAC(x); FVAR_MAC(y); FVAR_MAC(z); FVAR_MAC(w);
 #undef FVAR_MAC
-    };
-    if (s0 < s1) load(s0, 0);
-    for (int s = s0; s < s1; s += 2) {
-        if (s + 1 < s1) load(s + 1, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        mac(0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (s + 1 < s1) {
-            if (s + 2 < s1) load(s + 2, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            mac(1);
-            __builtin_amdgcn_sched_barrier(0);
         }
+    };
+#pragma unroll
+    for (int s = 0; s < STAGES; ++s)
+        if (s < n) issue(s);
+    if (n > 0) {
+        landed(min(n, STAGES) - 1);
+        fetch(0, 0, frag[0]);
     }
+    for (int s = 0; s < n; ++s) {
+        fetch(s, 1, frag[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        mac(frag[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        // the stage is free once its last fragments are in registers
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (s + STAGES < n) issue(s + STAGES);
+        if (s + 1 < n) {
+            landed(min(n - 2 - s, STAGES - 1));
+            fetch(s + 1, 0, frag[0]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        mac(frag[1]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // the wavefronts' partial tiles meet in LDS, each in its own ring
+    float4 *red = reinterpret_cast<float4 *>(lds_raw);
 #pragma unroll
     for (int f = 0; f < FT; ++f)
 #pragma unroll
         for (int t = 0; t < TT; ++t)
-            red[wave][f * TT + t][lane] = make_float4(acc[f][t][0], acc[f][t][1], acc[f][t][2], acc[f][t][3]);
+            red[wave * (RING / 16) + (f * TT + t) * 64 + lane] =
+                make_float4(acc[f][t][0], acc[f][t][1], acc[f][t][2], acc[f][t][3]);
     __syncthreads();
     for (int blk = wave; blk < FT * TT; blk += NW) {
-        float4 v = red[0][blk][lane];
+        float4 v = red[blk * 64 + lane];
 #pragma unroll
         for (int w = 1; w < NW; ++w) {
-            const float4 p = red[w][blk][lane];
+            const float4 p = red[w * (RING / 16) + blk * 64 + lane];
             v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
         }
         const int row = row0 + (blk % TT) * 16 + c16, col = n0 + (blk / TT) * 16 + 4 * q16;
         if (row >= rows) continue;
         if (nsplit > 1) *reinterpret_cast<float4 *>(part + ((size_t)split * rows + row) * N + col) = v;
+        else if constexpr (sizeof(T) == 2) finish_quad(ep, row, col, v);
         else finish_quad_f32(ep, row, col, v);
     }
 }
@@ -1200,7 +1158,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const float *__restri
 // they are: on 115 of 3000 problems where the picks differ 17.1 us in geometric mean instead of 15.9, at worst 1536 x 6144
 // with 703 rows 40.5 instead of 28.1, and 128x64 divided eight ways took more workspace than 64x64 in five.
 constexpr double kLaunchUs = 3.6;      // a launch by itself
-constexpr double kRowsRate = 11.9e6;   // bytes / us that gemm_rows_kernel's workgroups read, L2 hits included
+constexpr double kRowsRate = 11.9e6;   // bytes / us of the kernel that kRows once described, see linear_plan
 
 struct TileCfg { int bm, bn; double k_us, tile_us; };   // us per k-tile and per tile with all CUs at work
 constexpr TileCfg kTiles[] = {
@@ -1219,10 +1177,26 @@ static bool in_groups(int cfg, int per, long workgroups)
 }
 // us per k-step of a wavefront, once, and for every further round of workgroups over the CUs (only the largest fills
 // a CU with one: 192 workgroups 9.0 us, 288 12.2 at 3072 x 768)
+// These are the times of a kernel without LDS, which gemm_rows_kernel has replaced: what gemm_plan picks with them
+// still sizes the workspace, so that it stays what callers were told, and never runs.
 struct RowsCfg { int ft, tt; double step_us, fixed_us, round_us; };
 constexpr RowsCfg kRows[] = {{1, 1, 0.174, 3.0, 0.0}, {2, 1, 0.261, 3.3, 0.0}, {2, 2, 0.281, 3.7, 3.0}};
 constexpr int kNumRows = sizeof(kRows) / sizeof(kRows[0]);
-constexpr int kRowsWaves = 8, kRowsMax = 256;           // gemm_rows_kernel is not measured beyond 256 rows
+constexpr int kRowsWaves = 8, kRowsMax = 256;           // bf16: gemm_rows_kernel is not used beyond 256 rows
+
+// Instances of gemm_rows_kernel (features / 16, rows / 16, wavefronts), with us once, per round of workgroups over
+// the CUs (the rings fill a CU's LDS) and per step of a wavefront.  Never below the operands' way into the CUs at
+// kRingRate bytes / us and the weights' from HBM.  Fitted per type to timings of every instance and division on 200
+// problems (bf16: 7 .. 320 rows, hidden 1024 .. 4096; fp32: 4 .. 2048 rows, hidden 512 .. 1920), weights from
+// HBM: the picks are 3.2 and 1.5 % off the best on average.
+struct RingCfg { int ft, tt, nw; double fixed_us, round_us, step_us; };
+constexpr int kNumRings = 8;
+constexpr RingCfg kRings[2][kNumRings] = {
+    {{1, 1, 8, 3.86, 0.94, 0.406}, {2, 1, 8, 3.47, 1.25, 0.620}, {1, 2, 8, 3.55, 1.37, 0.510}, {2, 2, 8, 2.40, 2.02, 0.998},
+     {3, 2, 8, 2.40, 2.23, 1.529}, {2, 4, 4, 2.40, 1.84, 1.140}, {4, 4, 4, 2.40, 2.55, 2.208}, {3, 4, 4, 2.40, 2.43, 1.697}},
+    {{1, 1, 8, 4.23, 0.78, 0.376}, {2, 1, 8, 4.14, 0.80, 0.562}, {1, 2, 8, 3.95, 0.99, 0.470}, {2, 2, 8, 3.65, 1.10, 0.710},
+     {3, 2, 8, 3.52, 1.21, 0.982}, {2, 4, 4, 2.84, 1.80, 0.530}, {4, 4, 4, 2.40, 2.69, 0.825}, {3, 4, 4, 2.40, 2.27, 0.699}}};
+constexpr double kRingRate[2] = {11.0e6, 15.0e6};
 
 // fp32: at most 8 shares, and not more than 256 workgroups of 32 features x 16 rows per tile
 static int f32_row_tiles(int rows) { return rows <= 16 ? 1 : rows <= 32 ? 2 : 4; }
@@ -1234,10 +1208,11 @@ size_t gemm_f32_scratch_bound(int rows, int N)
 
 // bf16; `groups`: with the kernels that use wavefront groups, as they are launched.  Candidates with more than
 // `most` floats of scratch are left out.
-static GemmPlan gemm_bf16_plan(int rows, int N, int K, bool groups, size_t most)
+static GemmPlan gemm_bf16_plan(int rows, int N, int K, bool groups, size_t most, double *us_out = nullptr)
 {
     GemmPlan best{0, 1, 1, 0};
-    double best_us = 1e300;
+    double none, &best_us = us_out ? *us_out : none;
+    best_us = 1e300;
     const int kt = K / BK;
     const double hbm_us = 2.0 * ((double)rows * K + (double)N * K + (double)rows * N) / kHbmRate;
     const auto part_us = [](double floats) { return kMergeUs + floats * 8.0 / kMergeRate; };
@@ -1293,7 +1268,7 @@ static GemmPlan gemm_bf16_plan(int rows, int N, int K, bool groups, size_t most)
     return best;
 }
 
-GemmPlan gemm_plan(DType dt, int rows, int N, int K)
+static GemmPlan gemm_plan_us(DType dt, int rows, int N, int K, double *us)
 {
     GemmPlan best{0, 1, 1, 0};
     if (dt != DType::BF16) {
@@ -1305,21 +1280,72 @@ GemmPlan gemm_plan(DType dt, int rows, int N, int K)
         if (best.nsplit > 1) best.scratch_floats = (size_t)best.nsplit * rows * N;
         return best;
     }
-    best = gemm_bf16_plan(rows, N, K, true, SIZE_MAX);
+    best = gemm_bf16_plan(rows, N, K, true, SIZE_MAX, us);
     if (best.scratch_floats == 0) return best;
     // never more scratch than without the groups, which is what callers have been told the workspace takes
     const size_t told = gemm_bf16_plan(rows, N, K, false, SIZE_MAX).scratch_floats;
-    return best.scratch_floats <= told ? best : gemm_bf16_plan(rows, N, K, true, told);
+    return best.scratch_floats <= told ? best : gemm_bf16_plan(rows, N, K, true, told, us);
+}
+GemmPlan gemm_plan(DType dt, int rows, int N, int K) { return gemm_plan_us(dt, rows, N, K, nullptr); }
+
+GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room)
+{
+    const bool bf16 = dt == DType::BF16;
+    const int step = bf16 ? 64 : 32;
+    double best_us = 1e300;
+    GemmPlan best = gemm_plan_us(dt, rows, N, K, &best_us);
+    if (bf16 && best.cfg < kNumTiles && rows > kRowsMax) return best;
+    if (!bf16 || best.cfg >= kNumTiles) best_us = 1e300;       // priced as the instance it is, below
+    const double es = bf16 ? 2.0 : 4.0, hbm_us = 3.4 + es * ((double)rows * K + (double)N * K + (double)rows * N) / 6.0e6;
+    for (int i = 0; i < kNumRings; ++i) {
+        const RingCfg &c = kRings[bf16][i];
+        if (N % (16 * c.ft)) continue;
+        const long tiles = (long)((rows + 16 * c.tt - 1) / (16 * c.tt)) * (N / (16 * c.ft));
+        const double l2_us = 2.8 + (double)tiles * 16 * (c.ft + c.tt) * K * es / kRingRate[bf16];
+        for (int ns = 1; ns <= 8; ns *= 2) {
+            const size_t scratch = ns > 1 ? (size_t)ns * rows * N : 0;
+            if (ns > 1 && (K / step < ns * c.nw || scratch > room)) break;
+            const int steps = (K / step + ns * c.nw - 1) / (ns * c.nw);
+            double us = c.fixed_us + (double)((tiles * ns + 255) / 256) * (c.round_us + c.step_us * steps);
+            us = us > l2_us ? us : l2_us;
+            us = us > hbm_us ? us : hbm_us;
+            if (ns > 1) us += kMergeUs + scratch * 8.0 / kMergeRate;
+            if (us < best_us) { best_us = us; best = {kNumTiles + kNumRows + i, ns, 1, scratch}; }
+        }
+    }
+    return best;
 }
 
-template <int FT, int TT>
+template <typename T, int FT, int TT, int NW, int STAGES>
 static void launch_gemm_rows(const void *A, const void *W, int rows, int N, int K, const EpiParams &ep,
                              hipStream_t st, int nsplit, float *part)
 {
     const int row_tiles = (rows + 16 * TT - 1) / (16 * TT);
     const int units = row_tiles * nsplit * (N / (16 * FT));
-    launch(gemm_rows_kernel<FT, TT, kRowsWaves>, dim3((units + 7) / 8 * 8), dim3(64 * kRowsWaves), 0, st,
-           (const uint16_t *)A, (const uint16_t *)W, rows, N, K, row_tiles, nsplit, ep, part);
+    constexpr size_t lds = (size_t)NW * STAGES * (FT + TT) * 2048;
+    static_assert(lds <= kLdsLimit, "LDS of a CU");
+    auto kern = gemm_rows_kernel<T, FT, TT, NW, STAGES>;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    launch(kern, dim3((units + 7) / 8 * 8), dim3(64 * NW), lds, st, (const T *)A, (const T *)W, rows, N, K,
+           row_tiles, nsplit, ep, part);
+}
+
+// instance i of kRings
+template <typename T>
+static void launch_gemm_ring(int i, const void *A, const void *W, int rows, int N, int K, const EpiParams &ep,
+                             hipStream_t st, int nsplit, float *part)
+{
+    switch (i) {
+    case 0: launch_gemm_rows<T, 1, 1, 8, 4>(A, W, rows, N, K, ep, st, nsplit, part); break;
+    case 1: launch_gemm_rows<T, 2, 1, 8, 3>(A, W, rows, N, K, ep, st, nsplit, part); break;
+    case 2: launch_gemm_rows<T, 1, 2, 8, 3>(A, W, rows, N, K, ep, st, nsplit, part); break;
+    case 3: launch_gemm_rows<T, 2, 2, 8, 2>(A, W, rows, N, K, ep, st, nsplit, part); break;
+    case 4: launch_gemm_rows<T, 3, 2, 8, 2>(A, W, rows, N, K, ep, st, nsplit, part); break;
+    case 5: launch_gemm_rows<T, 2, 4, 4, 2>(A, W, rows, N, K, ep, st, nsplit, part); break;
+    case 6: launch_gemm_rows<T, 4, 4, 4, 2>(A, W, rows, N, K, ep, st, nsplit, part); break;
+    default: launch_gemm_rows<T, 3, 4, 4, 2>(A, W, rows, N, K, ep, st, nsplit, part); break;
+    }
 }
 
 void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
@@ -1362,9 +1388,7 @@ void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
             else
                 launch_gemm_bf16_cfg<64, 64, 2, 2, 3>(A, W, rows, N, K, ep, st, ns, part, tail);
             break;
-        case kNumTiles + 0: launch_gemm_rows<1, 1>(A, W, rows, N, K, ep, st, ns, part); break;
-        case kNumTiles + 1: launch_gemm_rows<2, 1>(A, W, rows, N, K, ep, st, ns, part); break;
-        default: launch_gemm_rows<2, 2>(A, W, rows, N, K, ep, st, ns, part); break;
+        default: launch_gemm_ring<uint16_t>(plan.cfg - kNumTiles - kNumRows, A, W, rows, N, K, ep, st, ns, part); break;
         }
         if (ns > 1) {
             const long total = (long)rows * (N / 4);
@@ -1372,14 +1396,7 @@ void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
                    (const float *)part, ns, rows, N, ep);
         }
     } else {
-        const int row_tiles = (rows + 16 * plan.cfg - 1) / (16 * plan.cfg);
-        const long units = (long)row_tiles * plan.nsplit * (N / 32);
-        const dim3 grid((unsigned)((units + 7) / 8 * 8)), block(64 * kRowsWaves);
-        auto k1 = gemm_f32_kernel<1, kRowsWaves>;
-        auto k2 = gemm_f32_kernel<2, kRowsWaves>;
-        auto k4 = gemm_f32_kernel<4, kRowsWaves>;
-        launch(plan.cfg == 1 ? k1 : plan.cfg == 2 ? k2 : k4, grid, block, 0, st, (const float *)A,
-               (const float *)W, rows, N, K, row_tiles, plan.nsplit, ep, part);
+        launch_gemm_ring<float>(plan.cfg - kNumTiles - kNumRows, A, W, rows, N, K, ep, st, plan.nsplit, part);
         if (plan.nsplit > 1) {
             const long total = (long)rows * (N / 4);
             launch(gemm_f32_merge_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,

@@ -334,3 +334,51 @@ def test_factors_workspace_grows_with_the_call(dtype, d):
                 assert last <= need <= min(size(c, B + 1, M, r), size(c, B, M, r + 8)), (B, M, r, last, need)
                 assert need - gram >= 4 * parts(C.c_int(1 if dtype == "bf16" else 0), B, M, r, d) * B * M * r
                 last = need
+
+
+RINGS = ("16x16", "32x16", "16x32", "32x32", "48x32", "32x64", "64x64", "48x64")     # features x rows of a workgroup
+
+
+def linear_plans(dtype, B, n, d, H, F):
+    """(tile or ring instance, shares) of the four layers of a block as they run."""
+    lib, b, R = fv.load_library(), 1 if dtype == "bf16" else 0, B * n
+    run = lib["_ZN4fvar11linear_planENS_5DTypeEiiim"]
+    run.restype, run.argtypes = _Plan, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t]
+    att, bound = lib["_ZN4fvar24attention_scratch_floatsENS_5DTypeEiiii"], lib["_ZN4fvar22gemm_f32_scratch_boundEii"]
+    att.restype = bound.restype = C.c_size_t
+    shapes = ((3 * d, d), (d, d), (F, d), (d, F))
+    room = max([gemm_plan(dtype, R, N, K).scratch_floats for N, K in shapes] + [att(b, B, n, H, d // H)] +
+               ([] if b else [bound(R, max(3 * d, F))]))
+    out = []
+    for N, K in shapes:
+        p = run(b, R, N, K, room)
+        assert p.scratch_floats <= room and p.scratch_floats >= (p.nsplit * R * N if p.nsplit > 1 else 0)
+        out.append((TILES[p.cfg] if p.cfg < len(TILES) else "ring " + RINGS[p.cfg - len(TILES)], p.nsplit))
+    return out
+
+
+@pytest.mark.parametrize("dtype,B,n,d,H,F,expect", [
+    ("f32", 3, 6, 1024, 8, 4096, [("16x32", 1), ("16x16", 1), ("32x16", 1), ("32x32", 8)]),
+    ("f32", 5, 50, 320, 5, 1280, [("32x32", 1), ("16x32", 1), ("32x64", 1), ("16x32", 1)]),
+    ("f32", 1, 85, 960, 15, 3840, [None, None, None, ("48x32", 4)]),
+    ("f32", 1, 200, 1024, 16, 4096, [("48x64", 1), None, ("64x64", 1), None]),
+    ("bf16", 1, 43, 1536, 24, 6144, [None, None, None, ("48x64", 8)]),
+    ("bf16", 1, 99, 1536, 24, 6144, [None, None, None, ("48x64", 4)]),
+    ("bf16", 1, 141, 4096, 32, 1024, [None, ("64x64", 1), None, None]),
+    ("bf16", 7, 14, 1024, 16, 4096, [None, None, None, ("32x16", 1)]),
+    ("bf16", 1, 48, 1920, 30, 7680, [("48x32", 1), ("16x32", 1), ("32x64", 1), None]),
+    ("bf16", 1, 15, 2048, 16, 8192, [("32x16", 1), ("16x16", 1), ("16x16", 1), ("16x16", 1)]),
+    ("bf16", 2, 65, 1024, 16, 4096, [("48x64", 1), ("32x32", 1), None, ("32x32", 1)]),
+])
+def test_instances_of_the_ring_kernel(dtype, B, n, d, H, F, expect):
+    """tests/test_gpu_linear_plans.py is there for these."""
+    got = linear_plans(dtype, B, n, d, H, F)
+    assert all(e is None or g == ("ring " + e[0], e[1]) for g, e in zip(got, expect)), got
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_plans_that_run_stay_within_the_workspace(dtype):
+    """Every call gets a plan within the scratch that its workspace holds (asserted in linear_plans)."""
+    for d, H, F in ((64, 1, 64), (192, 3, 256), (1024, 16, 4096), (1920, 30, 7680), (4096, 32, 1024)):
+        for B, n in ((1, 1), (1, 15), (3, 11), (1, 100), (2, 128), (1, 257), (4, 700), (32, 1600)):
+            linear_plans(dtype, B, n, d, H, F)

@@ -94,3 +94,19 @@ def test_second_mlp_layer_rounds_once(d, rows):
     expect = (torch.from_numpy(x) + torch.from_numpy(hi + lo)).to(torch.bfloat16)
     assert np.array_equal((hi.astype(np.float64) + lo).astype(np.float32), hi + lo)
     assert torch.equal(y, expect), f"{(y != expect).sum().item()} of {y.numel()} differ"
+
+
+@pytest.mark.parametrize("dtype,B,M,d,H,F", [
+    ("f32", 3, 6, 1024, 8, 4096),         # 32x16, 16x16, 16x32 and 32x32 in eight shares; 18 rows of three samples
+    ("f32", 5, 50, 320, 5, 1280),         # 250 rows: remainder 10; ten contraction steps for eight wavefronts
+    ("f32", 1, 85, 960, 15, 3840),        # 48x32 in four shares; row remainder 5
+    ("f32", 1, 200, 1024, 16, 4096),      # 48x64 (QKV), 64x64, 32x64 in shares
+    ("bf16", 1, 43, 1536, 24, 6144),      # FC2: 48x64 in eight shares, row remainder 11
+    ("bf16", 1, 99, 1536, 24, 6144),      # FC2: 48x64 in four shares, second row tile of 35 rows
+    ("bf16", 1, 141, 4096, 32, 1024),     # O: 64x64
+    ("bf16", 7, 14, 1024, 16, 4096),      # 98 rows of seven samples: K/V rows routed across samples; 32x16
+    ("bf16", 1, 48, 1920, 30, 7680),      # 48x32, 16x32, 32x64
+])
+def test_linear_layers_with_a_ring_per_wavefront(dtype, B, M, d, H, F):
+    """The kernel of a few rows (fp32: of all), each of its instances, with row remainders and shares."""
+    test_linear_layers_across_plans(dtype, B, M, d, H, F)
