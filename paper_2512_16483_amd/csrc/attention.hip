@@ -57,8 +57,10 @@ template <int DH> __device__ __forceinline__ int v_swz(int row)
     return DH == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2);
 }
 
-template <int DH, int NQ>
-__global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t *__restrict__ q,
+// KG = 2: two groups of four wavefronts work on the same queries, each with half of the workgroup's key tiles and
+// double buffers of its own, and meet in LDS at the end.
+template <int DH, int NQ, int KG>
+__global__ __launch_bounds__(256 * KG, 2) void attn_bf16_kernel(const uint16_t *__restrict__ q,
                                                         const uint16_t *__restrict__ Kc,
                                                         const uint16_t *__restrict__ Vc, int n, int L,
                                                         int cap, int H, float c_log2,
@@ -77,10 +79,12 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t *__res
 
     extern __shared__ uint4 lds_raw[];
     uint16_t *lds = reinterpret_cast<uint16_t *>(lds_raw);   // [stage][K tile | V tile]
-    const uint32_t lds_base = (uint32_t)(uintptr_t)lds_raw;
+    uint32_t lds_base = (uint32_t)(uintptr_t)lds_raw;
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int all_wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = KG > 1 ? all_wave >> 2 : 0, wave = KG > 1 ? all_wave & 3 : all_wave;    // group, wavefront in it
+    if (KG > 1) { lds += kg * 2 * STAGE; lds_base += kg * 4 * STAGE; }
     const int rl = lane & 31, g = lane >> 5;
     // Work decomposition.  A unit is one (query block, head, sample) triple, numbered with the
     // query block fastest.  Two ways of dividing the key axis between workgroups exist:
@@ -195,10 +199,17 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t *__res
     for (int j = 0; j < NQ; ++j) { m_run[j] = -INFINITY; l_run[j] = 0.f; }
 
     const int ntiles_all = (L + BT - 1) / BT;
-    const int tile0 = ranges > 1 ? split * tiles_per_split : 0;
+    int tile0 = ranges > 1 ? split * tiles_per_split : 0;
     const int tile1 = ranges > 1 ? min(ntiles_all, tile0 + tiles_per_split) : ntiles_all;
-    const int nloc = tile1 - tile0;
-    issue_tile(tile0 * BT, 0);
+    int nloc = tile1 - tile0;                                // tiles of this group
+    const int trips = KG > 1 ? (nloc + 1) / 2 : nloc;
+    if (KG > 1) {
+        // the second group, which has the cache's ragged tail, takes the odd tile: it comes in the last trip
+        const int first = nloc - trips;
+        if (kg == 0) nloc = first;
+        else { tile0 += first; nloc = trips; }
+    }
+    if (KG == 1 || nloc > 0) issue_tile(tile0 * BT, 0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // the Q fragments are consumed here once so that the compiler's own wait for their loads
     // sits in front of the loop instead of inside it (where it would also wait for the prefetch)
@@ -221,7 +232,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t *__res
         __builtin_amdgcn_sched_barrier(0);
 
         // a wavefront whose queries all lie past the end only helps with the staging
-        if (wave_active) {
+        if (wave_active && (KG == 1 || lt < nloc)) {
         // ---- S^T = K Q^T : [64 keys] x [32*NQ queries]
         floatx16_t sacc[2][NQ];
 #pragma unroll
@@ -293,9 +304,9 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t *__res
             // 1600 rows x 12121 keys x 32 heads of 128, batch 4, 28.5 -> 27.0 us at head_dim 64)
             const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
             mx = fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
-            const float m_new = fmaxf(m_run[j], mx);
-            const float alpha = __builtin_amdgcn_exp2f((m_run[j] - m_new) * c_log2);
-            const float mc = m_new * c_log2;
+            const float m_new = fmaxf(m_run[j], mx), m_fin = fmaxf(m_new, -1e30f);   // nothing finite yet: weights of 0
+            const float alpha = __builtin_amdgcn_exp2f((m_run[j] - m_fin) * c_log2);
+            const float mc = m_fin * c_log2;
             m_run[j] = m_new;
             float psum = 0.f;
 #pragma unroll
@@ -341,9 +352,61 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t *__res
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     };
-    for (int lt = 0; lt + 1 < nloc; ++lt) tile(lt, std::false_type{});
-    tile(nloc - 1, std::true_type{});
+    for (int lt = 0; lt + 1 < trips; ++lt) tile(lt, std::false_type{});
+    tile(trips - 1, std::true_type{});
 
+    if constexpr (KG > 1) {
+        // Each group takes half of the head-dim blocks to the end: it parks the other half, its running max and sum
+        // where the other group finds them (the stages are free: the last tile ended with a barrier).
+        constexpr int HB = DB / 2;
+        float4 *xo = reinterpret_cast<float4 *>(lds_raw);                        // [group][wave][j][block, quad][lane]
+        float2 *xm = reinterpret_cast<float2 *>(xo + 8 * NQ * HB * 4 * 64);      // [group][wave][j][lane]
+        float m_own[NQ], l_own[NQ];
+        auto slot = [&](int grp, int j, int q) { return (((grp * 4 + wave) * NQ + j) * (HB * 4) + q) * 64 + lane; };
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            m_own[j] = m_run[j];
+            l_own[j] = l_run[j] + __shfl_xor(l_run[j], 32);
+            xm[((kg * 4 + wave) * NQ + j) * 64 + lane] = make_float2(m_own[j], l_own[j]);
+#pragma unroll
+            for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+                for (int e = 0; e < 16; e += 4) {
+                    const floatx16_t &v = kg ? oacc[hb][j] : oacc[HB + hb][j];
+                    xo[slot(kg, j, hb * 4 + e / 4)] = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            const float2 other = xm[(((1 - kg) * 4 + wave) * NQ + j) * 64 + lane];
+            const float m = fmaxf(m_own[j], other.x);        // the second group always has a tile: finite
+            const float wo = __builtin_amdgcn_exp2f((m_own[j] - m) * c_log2);
+            const float wx = __builtin_amdgcn_exp2f((other.x - m) * c_log2);
+            const float l = l_own[j] * wo + other.y * wx;
+            const int row = q0 + j * 32 + rl;
+            if (row >= n) continue;
+            const float inv = 1.0f / l;
+            const size_t prow = prow_base + (size_t)row * prow_stride;
+#pragma unroll
+            for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+                for (int e = 0; e < 16; e += 4) {
+                    const floatx16_t &v = kg ? oacc[HB + hb][j] : oacc[hb][j];
+                    const float4 x = xo[slot(1 - kg, j, hb * 4 + e / 4)];
+                    const float4 r = make_float4(fmaf(x.x, wx, v[e] * wo), fmaf(x.y, wx, v[e + 1] * wo),
+                                                 fmaf(x.z, wx, v[e + 2] * wo), fmaf(x.w, wx, v[e + 3] * wo));
+                    const int dh = (kg * HB + hb) * 32 + 8 * (e >> 2) + 4 * g;
+                    if (ranges > 1)
+                        *reinterpret_cast<float4 *>(part_o + prow * DH + dh) = r;
+                    else
+                        *reinterpret_cast<uint2 *>(o + ((size_t)b * n + row) * rowpitch + (size_t)h * DH + dh) =
+                            make_uint2(pack_bf16x2(r.x * inv, r.y * inv), pack_bf16x2(r.z * inv, r.w * inv));
+                }
+            if (ranges > 1 && kg == 0 && g == 0) *reinterpret_cast<float2 *>(part_ml + prow * 2) = make_float2(m, l);
+        }
+        return;
+    }
     if (ranges > 1) {
         // partial result of this key range: unnormalised O (fp32), running max and sum
 #pragma unroll
@@ -516,26 +579,85 @@ size_t attention_scratch_floats(DType dt, int B, int n, int H, int Dh)
     return 0;
 }
 
-template <int DH, int NQ>
+// How an attention is run: wavefront groups per workgroup, key ranges of every unit, key ranges of the units beyond
+// the last whole round.
+struct AttnRun { int kg, nsplit, tail; };
+
+// Predicted time: rounds of workgroups over the places that a CU has for them, each with a fixed part and a pace per
+// key tile that depends on how many share the CU; a last round with less than a workgroup per CU runs a little faster;
+// the partial results and their merge.  One row per variant (head_dim 128, 64 with 256 and with 128 queries),
+// fitted to 1194 timings of 150 problems (1 to 20 samples, 10 to 2500 queries, 70 to 11000 keys): 6 to 10 % rms.
+struct AttnTimes { double once, round, merge, merge_mb, light, pace[2][4]; };
+constexpr AttnTimes kAttnTimes[3] = {{0.4, 4.1, 4.8, 0.120, 0.29, {{1.42, 2.16, 0, 0}, {2.40, 0, 0, 0}}},
+                                     {2.7, 4.2, 4.2, 0.125, 0.24, {{1.40, 2.14, 0, 0}, {2.40, 0, 0, 0}}},
+                                     {3.25, 0.72, 4.4, 0.160, 0.07, {{0.76, 1.19, 1.74, 2.14}, {1.20, 2.25, 0, 0}}}};
+static double attention_us(int B, int n, int L, int H, int Dh, const AttnPlan &p, const AttnRun &run)
+{
+    const AttnTimes &c = kAttnTimes[Dh == 128 ? 0 : p.bq == 256 ? 1 : 2];
+    const int ntiles = (L + BT - 1) / BT, tps = (ntiles + run.nsplit - 1) / run.nsplit, ns = (ntiles + tps - 1) / tps;
+    const int trips = (tps + run.kg - 1) / run.kg, per = p.slots / 256 / run.kg;
+    const long wgs = (long)p.units * ns, full = wgs / (256 * per), rem = wgs % (256 * per);
+    const double *pace = c.pace[run.kg - 1];
+    double us = c.once + full * (c.round + trips * pace[per - 1]) + (run.kg > 1 ? 0.8 : 0.0);
+    if (rem && run.tail > 1) {
+        us += c.round + (double)((trips + run.tail - 1) / run.tail) * pace[per - 1] + c.merge;
+    } else if (rem) {
+        const int k = (int)((rem + 255) / 256);
+        us += c.round + trips * pace[k - 1] * (k == 1 ? 1.0 - c.light * (1.0 - rem / 256.0) : 1.0);
+    }
+    return ns > 1 ? us + c.merge + c.merge_mb * (2.0e-6 * ns * B * n * H * (Dh + 2) * sizeof(float)) : us;
+}
+
+// The division by key ranges that the workspace is sized for, unless fewer ranges, or two wavefront groups per
+// workgroup with at most as many, promise 3 % less: two groups fill a CU as two workgroups do, without partial results
+// in memory.  us, one group and the ranges above -> here: 2 x 1024 queries, 2521 keys, 16 heads of 128 65.4 -> 50.6,
+// 2000 x 6000 122.8 -> 105.8, 3 x 400 x 1500 42.8 -> 29.7, 2 x 576 x 1216, 30 heads of 64 33.5 -> 26.0; over the
+// 150 problems 5.9 % on average, at worst 4 % more.
+static AttnRun attention_run(int B, int n, int L, int H, int Dh, bool scratch)
+{
+    const AttnPlan p = attention_plan(B, n, H, Dh);
+    const int ntiles = (L + BT - 1) / BT, longest = ntiles / 4 > 0 ? ntiles / 4 : 1;   // ranges of at least 4 tiles
+    AttnRun run{1, scratch ? attention_max_splits(DType::BF16, B, n, H, Dh) : 1, 1};
+    if (run.nsplit > longest) run.nsplit = longest;
+    if (scratch && run.nsplit == 1) run.tail = p.tail_ranges;
+    if (run.tail > longest) run.tail = longest;
+    const int most = run.nsplit;
+    double best = 0.97 * attention_us(B, n, L, H, Dh, p, run);
+    for (int kg = 1; kg <= 2; ++kg)
+        for (int ns = 1; ns <= most; ++ns) {
+            if (kg == 1 ? ns == most : ntiles < 6 * ns) continue;
+            const AttnRun other{kg, ns, 1};
+            const double us = attention_us(B, n, L, H, Dh, p, other);
+            if (us < best) { best = us; run = other; }
+        }
+    return run;
+}
+
+int attention_ways(int B, int n, int L, int H, int Dh)
+{
+    const AttnRun run = attention_run(B, n, L, H, Dh, true);
+    return 100 * run.kg + run.nsplit;
+}
+
+template <int DH, int NQ, int KG>
 static void launch_attn_bf16(const void *q, const void *K, const void *V, int B, int n, int L,
-                             int cap, int H, float scale, void *o, float *part, hipStream_t st)
+                             int cap, int H, float scale, void *o, float *part, const AttnRun &run, hipStream_t st)
 {
     constexpr int BQ = 128 * NQ;
-    const size_t lds = (size_t)2 * 2 * BT * DH * sizeof(uint16_t);
-    auto kern = attn_bf16_kernel<DH, NQ>;
+    constexpr size_t stages = (size_t)KG * 2 * 2 * BT * DH * sizeof(uint16_t);
+    constexpr size_t meet = KG > 1 ? (size_t)8 * NQ * 64 * (DH / 64 * 4 * sizeof(float4) + sizeof(float2)) : 0;
+    constexpr size_t lds = stages > meet ? stages : meet;
+    auto kern = attn_bf16_kernel<DH, NQ, KG>;
     if (lds > 48 * 1024)
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    // key ranges: every range at least 4 tiles long, none empty
+    // no range is empty
     const int ntiles = (L + BT - 1) / BT;
-    int nsplit = part ? attention_max_splits(DType::BF16, B, n, H, DH) : 1;
-    if (nsplit > ntiles / 4) nsplit = ntiles / 4 > 0 ? ntiles / 4 : 1;
-    int tps = (ntiles + nsplit - 1) / nsplit;
+    int nsplit = run.nsplit, tps = (ntiles + nsplit - 1) / nsplit;
     nsplit = (ntiles + tps - 1) / tps;
     const float c_log2 = scale * 1.4426950408889634f;
     AttnPlan plan = attention_plan(B, n, H, DH);
-    int tail = (part && nsplit == 1) ? plan.tail_ranges : 1;
-    if (tail > ntiles / 4) tail = ntiles / 4 > 0 ? ntiles / 4 : 1;
+    int tail = nsplit == 1 ? run.tail : 1;
     if (tail > 1) {
         tps = (ntiles + tail - 1) / tail;
         tail = (ntiles + tps - 1) / tps;
@@ -547,7 +669,7 @@ static void launch_attn_bf16(const void *q, const void *K, const void *V, int B,
     else if (tail > 1) part_ml = part + (size_t)tail_units * tail * BQ * DH;
     const unsigned nwg = nsplit > 1 ? (unsigned)plan.units * nsplit
                                     : (unsigned)(plan.full_units + tail_units * tail);
-    launch(kern, dim3(nwg), dim3(256), lds, st, (const uint16_t *)q, (const uint16_t *)K,
+    launch(kern, dim3(nwg), dim3(256 * KG), lds, st, (const uint16_t *)q, (const uint16_t *)K,
            (const uint16_t *)V, n, L, cap, H, c_log2, (uint16_t *)o, nsplit, tps, part_o, part_ml,
            plan.nqb, plan.full_units, tail);
     if (nsplit > 1) {
@@ -698,15 +820,20 @@ void launch_attention(DType dt, const void *q, const void *K, const void *V, int
         // two 32-query blocks per wavefront halve the LDS operand traffic per MFMA; use the
         // single-block variant when that would leave most of a 256-query tile empty
         const bool wide = (n % 256 == 0) || (n % 256 > 128);
+        const AttnRun run = attention_run(B, n, L, H, Dh, part != nullptr);
+#define FVAR_ATTN(DH, NQ)                                                                                        \
+    (run.kg == 2 ? launch_attn_bf16<DH, NQ, 2>(q, K, V, B, n, L, cap, H, scale, o, part, run, st)                \
+                 : launch_attn_bf16<DH, NQ, 1>(q, K, V, B, n, L, cap, H, scale, o, part, run, st))
         if (Dh == 64) {
-            if (wide) launch_attn_bf16<64, 2>(q, K, V, B, n, L, cap, H, scale, o, part, st);
-            else launch_attn_bf16<64, 1>(q, K, V, B, n, L, cap, H, scale, o, part, st);
+            if (wide) FVAR_ATTN(64, 2);
+            else FVAR_ATTN(64, 1);
         } else {
             // head_dim 128 with two query blocks per wavefront does not fit the register budget of
             // two wavefronts per SIMD, which is what lets one wavefront's softmax overlap the
             // other's MFMAs
-            launch_attn_bf16<128, 1>(q, K, V, B, n, L, cap, H, scale, o, part, st);
+            FVAR_ATTN(128, 1);
         }
+#undef FVAR_ATTN
     } else {
         const int nqb = (n + 15) / 16;
         const dim3 grid((unsigned)nqb * H * B), block(512);

@@ -165,6 +165,7 @@ void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
 // only the units of the last, mostly empty round of workgroups of a large problem), or null
 // (never divide).  With more than one key range a second kernel merges the partial results.
 size_t attention_scratch_floats(DType dt, int B, int n, int H, int Dh);
+int attention_ways(int B, int n, int L, int H, int Dh);   // bf16: 100 * wavefront groups per workgroup + key ranges
 void launch_attention(DType dt, const void *q, const void *K, const void *V, int B, int n, int L,
                       int cap, int H, int Dh, float scale, void *o, float *part, hipStream_t st);
 
