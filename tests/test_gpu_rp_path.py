@@ -658,3 +658,11 @@ def test_cache_factors_many_samples(B, M, d, r):
         Wo, Go = factors.stored_factors(Cm[b], Q[0], bf16=True)
         assert rel_err(to_np(g_c[b]), Go) <= TOL["bf16"], (b, rel_err(to_np(g_c[b]), Go))
         assert rel_err(to_np(w_c[b]), Wo) <= TOL["bf16"], (b, rel_err(to_np(w_c[b]), Wo))
+
+
+@pytest.mark.parametrize("r", [4, 12, 20, 36, 60, 68, 92, 100, 124])
+@pytest.mark.parametrize("kind", ["rank8+ridge", "positive"])
+def test_gram_inverse_at_ranks_of_four(r, kind):
+    """Ranks that fp32 storage allows: the last group of four pivots ends a quarter, half or three quarters into its
+    block of sixteen, in an odd or even number of tiles."""
+    test_gram_inverse_keeps_ill_conditioned_digits(r, kind)
