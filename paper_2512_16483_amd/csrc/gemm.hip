@@ -48,6 +48,13 @@ __device__ __forceinline__ float gelu_tanh(float v)
     return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
 }
 
+// value of the other lane of each pair of lanes, in registers (a shuffle is an LDS operation, one per pair of
+// outputs: 2048 rows of 2048, FC1 62.9 -> 61.2 us, QKV 53.4 -> 51.9)
+__device__ __forceinline__ float neighbour(float v)
+{
+    return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0xb1, 0xf, 0xf, true));   // quad_perm 1,0,3,2
+}
+
 // destination of element (row, col) in elements from the base pointer it returns
 template <typename T>
 __device__ __forceinline__ T *epi_dst(const EpiParams &ep, int row, int col)
@@ -260,7 +267,7 @@ __device__ __forceinline__ void store_tile_epilogue(const floatx4_t (*acc)[FN][2
                 float v0 = acc[ii >> 1][j][ii & 1][bj][e] + bv, v1 = acc[ii >> 1][j][ii & 1][bj][e + 1] + bv;
                 if (ep.gelu) { v0 = gelu_tanh(v0); v1 = gelu_tanh(v1); }
                 const float send = odd ? v0 : v1;
-                const float recv = __shfl_xor(send, 1);
+                const float recv = neighbour(send);
                 const int lrow = ii * 16 + 4 * q16 + e + odd;
                 *reinterpret_cast<uint32_t *>(wlds + lrow * PITCH + lcol) =
                     odd ? pack_bf16x2(recv, v1) : pack_bf16x2(v0, recv);
