@@ -63,10 +63,19 @@ template <> struct Elem<uint16_t> {                     // bf16 stored as raw 16
 };
 
 // ---------------------------------------------------------------- wavefront reductions
+// Butterfly over lane distances 32, 16, 8, 4, 2, 1, in registers: a shuffle is a trip through LDS, twelve of them in
+// a LayerNorm.  (Rotating a 16-lane row by 8 and then by 4 meets the lanes at these distances, since lanes 8 apart
+// are equal by then.)
 __device__ __forceinline__ float wave_sum(float v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x128, 0xf, 0xf, true));   // row_ror:8
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x124, 0xf, 0xf, true));   // row_ror:4
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x4e, 0xf, 0xf, true));    // quad_perm 2,3,0,1
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0xb1, 0xf, 0xf, true));    // quad_perm 1,0,3,2
     return v;
 }
 __device__ __forceinline__ double wave_sum(double v)
