@@ -170,12 +170,17 @@ BlockWs carve(const fvar_ctx *c, void *ws, int B, int rows)
     const int shape[4][2] = {{(int)(3 * d), (int)d}, {(int)d, (int)d}, {(int)F, (int)d}, {(int)d, (int)F}};   // N, K
     // partial results where the key axis or the contraction axis is divided between workgroups
     size_t part = fvar::attention_scratch_floats(dt, B, rows, c->cfg.heads, c->cfg.head_dim);
-    for (const auto &l : shape) part = std::max(part, fvar::gemm_plan(dt, (int)R, l[0], l[1]).scratch_floats);
+    fvar::GemmPlan *plan[4] = {&w.qkv, &w.o, &w.fc1, &w.fc2};
+    double us[4] = {};                        // predicted times, not used in fp32
+    for (int i = 0; i < 4; ++i) {
+        *plan[i] = fvar::gemm_plan_us(dt, (int)R, shape[i][0], shape[i][1], &us[i]);
+        part = std::max(part, plan[i]->scratch_floats);
+    }
     // fp32: what the plans take falls as the rows become more; their bound does not, so that a
     // workspace sized for the largest call serves every smaller one (bf16 never had that: see fvar.h)
     if (dt != DType::BF16) part = std::max(part, fvar::gemm_f32_scratch_bound((int)R, (int)std::max(3 * d, F)));
-    fvar::GemmPlan *plan[4] = {&w.qkv, &w.o, &w.fc1, &w.fc2};
-    for (int i = 0; i < 4; ++i) *plan[i] = fvar::linear_plan(dt, (int)R, shape[i][0], shape[i][1], part);
+    for (int i = 0; i < 4; ++i)
+        *plan[i] = fvar::linear_plan(dt, (int)R, shape[i][0], shape[i][1], part, *plan[i], us[i]);
     w.part = part ? reinterpret_cast<float *>(take(part * sizeof(float))) : nullptr;
     w.total = off;
     return w;

@@ -161,6 +161,9 @@ struct GemmEpilogue {
 struct GemmPlan { int cfg, nsplit, tail; size_t scratch_floats; };
 GemmPlan gemm_plan(DType dt, int rows, int N, int K);
 GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room);
+// the same in two steps, for callers that need both: gemm_plan with its predicted time, then what runs
+GemmPlan gemm_plan_us(DType dt, int rows, int N, int K, double *us);
+GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room, GemmPlan best, double best_us);
 // floats that no fp32 plan of up to `rows` rows and N columns exceeds; never falls as rows grow
 size_t gemm_f32_scratch_bound(int rows, int N);
 // `part`: plan.scratch_floats floats (unused when 0)

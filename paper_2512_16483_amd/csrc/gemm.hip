@@ -1358,7 +1358,7 @@ static GemmPlan gemm_bf16_plan(int rows, int N, int K, bool groups, size_t most,
     return best;
 }
 
-static GemmPlan gemm_plan_us(DType dt, int rows, int N, int K, double *us)
+GemmPlan gemm_plan_us(DType dt, int rows, int N, int K, double *us)
 {
     GemmPlan best{0, 1, 1, 0};
     if (dt != DType::BF16) {
@@ -1380,10 +1380,15 @@ GemmPlan gemm_plan(DType dt, int rows, int N, int K) { return gemm_plan_us(dt, r
 
 GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room)
 {
+    double us = 1e300;
+    const GemmPlan p = gemm_plan_us(dt, rows, N, K, &us);
+    return linear_plan(dt, rows, N, K, room, p, us);
+}
+
+GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room, GemmPlan best, double best_us)
+{
     const bool bf16 = dt == DType::BF16;
     const int step = bf16 ? 64 : 32;
-    double best_us = 1e300;
-    GemmPlan best = gemm_plan_us(dt, rows, N, K, &best_us);
     if (bf16 && best.cfg < kNumTiles && rows > kRowsMax) return best;
     if (!bf16 || best.cfg >= kNumTiles) best_us = 1e300;       // priced as the instance it is, below
     const double es = bf16 ? 2.0 : 4.0, hbm_us = 3.4 + es * ((double)rows * K + (double)N * K + (double)rows * N) / 6.0e6;
