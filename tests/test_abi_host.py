@@ -382,3 +382,12 @@ def test_plans_that_run_stay_within_the_workspace(dtype):
     for d, H, F in ((64, 1, 64), (192, 3, 256), (1024, 16, 4096), (1920, 30, 7680), (4096, 32, 1024)):
         for B, n in ((1, 1), (1, 15), (3, 11), (1, 100), (2, 128), (1, 257), (4, 700), (32, 1600)):
             linear_plans(dtype, B, n, d, H, F)
+
+
+@pytest.mark.parametrize("B,n,d,H,F,expect", [
+    (1, 436, 768, 12, 3072, ("64x64", 3)), (4, 100, 512, 8, 2048, ("64x64", 4)),
+    (1, 72, 1920, 30, 7680, ("128x64", 8)), (1, 137, 1536, 24, 6144, ("64x128", 7)),
+])
+def test_small_tiles_in_shares_stay_in_reach(B, n, d, H, F, expect):
+    """tests/test_gpu_linear_plans.py runs these for the division of small tiles (their FC2)."""
+    assert linear_plans("bf16", B, n, d, H, F)[3] == expect

@@ -110,3 +110,14 @@ def test_second_mlp_layer_rounds_once(d, rows):
 def test_linear_layers_with_a_ring_per_wavefront(dtype, B, M, d, H, F):
     """The kernel of a few rows (fp32: of all), each of its instances, with row remainders and shares."""
     test_linear_layers_across_plans(dtype, B, M, d, H, F)
+
+
+@pytest.mark.parametrize("B,M,d,H,F", [
+    (1, 436, 768, 12, 3072),      # FC2: 64x64 in three shares
+    (4, 100, 512, 8, 2048),       # FC2: 64x64 in four shares, tiles over four samples
+    (1, 72, 1920, 30, 7680),      # FC2: 128x64 in eight shares, row remainder 72
+    (1, 137, 1536, 24, 6144),     # FC2: 64x128 in seven shares, row remainder 9
+])
+def test_small_tiles_that_still_divide_the_contraction(B, M, d, H, F):
+    """Where the kernel of a few rows is not the faster one, small tiles in shares run as before."""
+    test_linear_layers_across_plans("bf16", B, M, d, H, F)
