@@ -59,17 +59,19 @@ __global__ __launch_bounds__(kGramThreads) void gram_f32_kernel(const float *__r
 
 // bf16 storage, on MFMA.  A workgroup owns one 32x32 tile (ti >= tj) of S for one slice of the
 // contraction axis: the 64-element chunks c = part, part + parts, ... are dealt round-robin to its
-// four wavefronts, two in flight.  Within a chunk the products (exact in fp32) are summed in fp32; chunk results
+// four wavefronts.  Within a chunk the products (exact in fp32) are summed in fp32; chunk results
 // are added in fp64.  The slices' partial matrices are written to Spart[b][part] (both triangles)
 // and summed by the inverse, so the result does not depend on scheduling.  The inverse reads them through one
 // CU, so fewer is better there (128 KB each at rank 128): this and the inverse, with T beside it, take
 // 68.7 us at rank 128, 4 samples with four slices, 69.4 with two of eight wavefronts and 75 with one of sixteen.
+// The chunks come by DMA in whole 128-byte lines, two in flight per wavefront (a row per lane is a quarter of the
+// vector L1's rate, see gemm_rows_kernel): rank 128, 4 samples of width 4096 6.5 -> 4.9 us, 40 of them 35.4 -> 28.5.
 // Chunks past the end are not fetched: where a wavefront has one, as with d = 1024, those in their place tripled
 // its reads (512 samples, rank 32: 17.7 -> 13.6 us; 480 x 1920: 26.3 -> 18.1).
 __global__ __launch_bounds__(256) void gram_bf16_kernel(const uint16_t *__restrict__ g_c, int r, int d,
                                                         double *__restrict__ Spart)
 {
-    __shared__ double red[4][32 * 32];
+    extern __shared__ uint4 gram_lds[];              // [wavefront][stage][64 rows of 128 bytes], then the partial tiles
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rl = lane & 31, g = lane >> 5;
@@ -78,47 +80,54 @@ __global__ __launch_bounds__(256) void gram_bf16_kernel(const uint16_t *__restri
     const int tj = blockIdx.x - ti * (ti + 1) / 2;
     const int part = blockIdx.y, parts = gridDim.y, b = blockIdx.z;
     const uint16_t *G = g_c + (size_t)b * r * d;
-    const uint16_t *arow = G + (size_t)min(ti * 32 + rl, r - 1) * d;
-    const uint16_t *brow = G + (size_t)min(tj * 32 + rl, r - 1) * d;
     double acc[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.0;
-    const int nchunks = d / 64, step = parts * 4;
-    uint4 av[2][4], bv[2][4];                        // two chunks in flight
-    auto load = [&](int c, int buf) {
+    const int nchunks = d / 64, step = parts * 4, c0 = part + parts * wave;
+    const int n = c0 < nchunks ? (nchunks - 1 - c0) / step + 1 : 0;
+    const uint32_t ring = (uint32_t)(uintptr_t)gram_lds + wave * 16384;
+    const uint4 *mine = gram_lds + wave * 1024;
+    // chunk i of this wavefront, 8 rows (1 KiB) per instruction: lane l fills physical chunk l%8 of row l/8 with the
+    // logical chunk that the swizzle (chunk ^ row/2 % 8) maps there
+    auto fetch = [&](int i) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int t = c * 64 + 16 * s + 8 * g;
-            av[buf][s] = *reinterpret_cast<const uint4 *>(arow + t);
-            bv[buf][s] = *reinterpret_cast<const uint4 *>(brow + t);
+        for (int u = 0; u < 8; ++u) {
+            const int lrow = (u & 3) * 8 + lane / 8, row = min((u < 4 ? ti : tj) * 32 + lrow, r - 1);
+            const uint16_t *src = G + (size_t)row * d + (c0 + i * step) * 64 + (((lane & 7) ^ ((lrow >> 1) & 7)) << 3);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                         :: "s"(ring + (i & 1) * 8192 + u * 1024), "v"(src) : "memory", "m0");
         }
     };
-    auto add = [&](int buf) {
+    if (n > 0) fetch(0);
+    if (n > 1) fetch(1);
+    for (int i = 0; i < n; ++i) {
+        if (i + 1 < n) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        uint4 av[4], bv[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const uint4 *src = mine + (i & 1) * 512 + rl * 8 + ((2 * s + g) ^ ((rl >> 1) & 7));
+            av[s] = src[0];
+            bv[s] = src[256];
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the stage is free
+        if (i + 2 < n) fetch(i + 2);
         floatx16_t a32 = {0};
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-            a32 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av[buf][s]),
-                                                          __builtin_bit_cast(bf16x8_t, bv[buf][s]), a32, 0, 0, 0);
+            a32 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av[s]),
+                                                          __builtin_bit_cast(bf16x8_t, bv[s]), a32, 0, 0, 0);
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[e] += (double)a32[e];
-    };
-    int c = part + parts * wave;
-    if (c < nchunks) load(c, 0);
-    for (; c < nchunks; c += 2 * step) {
-        if (c + step < nchunks) load(c + step, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        add(0);
-        if (c + 2 * step < nchunks) load(c + 2 * step, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (c + step < nchunks) add(1);
     }
+    double *red = reinterpret_cast<double *>(gram_lds);              // every wavefront's tile in its own ring
 #pragma unroll
-    for (int e = 0; e < 16; ++e) red[wave][(8 * (e >> 2) + 4 * g + (e & 3)) * 32 + rl] = acc[e];
+    for (int e = 0; e < 16; ++e) red[wave * 2048 + (8 * (e >> 2) + 4 * g + (e & 3)) * 32 + rl] = acc[e];
     __syncthreads();
     double *Sb = Spart + ((size_t)b * parts + part) * r * r;
     for (int idx = tid; idx < 32 * 32; idx += 256) {
         const int i = ti * 32 + idx / 32, j = tj * 32 + idx % 32;
-        const double v = (red[0][idx] + red[1][idx]) + (red[2][idx] + red[3][idx]);
+        const double v = (red[idx] + red[2048 + idx]) + (red[4096 + idx] + red[6144 + idx]);
         if (i < r && j < r) {
             Sb[(size_t)i * r + j] = v;
             if (ti != tj) Sb[(size_t)j * r + i] = v;
@@ -225,7 +234,9 @@ void launch_factor_gram(DType dt, const void *g_c, int B, int r, int d, double *
 {
     if (dt == DType::BF16) {
         const int rt = (r + 31) / 32;
-        launch(gram_bf16_kernel, dim3(rt * (rt + 1) / 2, kGramParts, B), dim3(256), 0, st,
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(gram_bf16_kernel),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
+        launch(gram_bf16_kernel, dim3(rt * (rt + 1) / 2, kGramParts, B), dim3(256), 65536, st,
                (const uint16_t *)g_c, r, d, S);
     } else {
         launch(gram_f32_kernel, dim3(r, B), dim3(kGramThreads), (size_t)d * sizeof(float), st,
