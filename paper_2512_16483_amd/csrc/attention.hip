@@ -584,35 +584,42 @@ size_t attention_scratch_floats(DType dt, int B, int n, int H, int Dh)
 struct AttnRun { int kg, nsplit, tail; };
 
 // Predicted time: rounds of workgroups over the places that a CU has for them, each with a fixed part and a pace per
-// key tile that depends on how many share the CU; a last round with less than a workgroup per CU runs a little faster;
-// the partial results and their merge.  One row per variant (head_dim 128, 64 with 256 and with 128 queries),
-// fitted to 1194 timings of 150 problems (1 to 20 samples, 10 to 2500 queries, 70 to 11000 keys): 6 to 10 % rms.
-struct AttnTimes { double once, round, merge, merge_mb, light, pace[2][4]; };
-constexpr AttnTimes kAttnTimes[3] = {{0.4, 4.1, 4.8, 0.120, 0.29, {{1.42, 2.16, 0, 0}, {2.40, 0, 0, 0}}},
-                                     {2.7, 4.2, 4.2, 0.125, 0.24, {{1.40, 2.14, 0, 0}, {2.40, 0, 0, 0}}},
-                                     {3.25, 0.72, 4.4, 0.160, 0.07, {{0.76, 1.19, 1.74, 2.14}, {1.20, 2.25, 0, 0}}}};
+// key tile that depends on how many share the CU and, up to one per CU, on how many CUs are at work; once a part that
+// grows with the wavefronts of a workgroup that have queries (they load, merge and store); the partial results and
+// their merge.  One row per variant (head_dim 128, 64 with 256 and with 128 queries), fitted to 3000 timings of 570
+// problems (1 to 20 samples, 2 to 2500 queries, 70 to 11000 keys): 5 to 7 % rms.
+struct AttnTimes { double once, active, groups, round, merge, merge_mb, pace[2][4], crowd[2]; };
+constexpr AttnTimes kAttnTimes[3] = {
+    {3.93, 1.64, 0.75, 1.90, 3.91, 0.14, {{1.06, 2.12, 0, 0}, {1.78, 0, 0, 0}}, {0.33, 0.68}},
+    {2.89, 3.63, 0.88, 1.26, 3.62, 0.16, {{1.20, 2.16, 0, 0}, {1.90, 0, 0, 0}}, {0.22, 0.58}},
+    {3.04, 1.37, 0.77, 0.52, 3.80, 0.15, {{0.72, 1.18, 1.80, 2.22}, {1.10, 2.24, 0, 0}}, {0.17, 0.32}}};
 static double attention_us(int B, int n, int L, int H, int Dh, const AttnPlan &p, const AttnRun &run)
 {
     const AttnTimes &c = kAttnTimes[Dh == 128 ? 0 : p.bq == 256 ? 1 : 2];
     const int ntiles = (L + BT - 1) / BT, tps = (ntiles + run.nsplit - 1) / run.nsplit, ns = (ntiles + tps - 1) / tps;
     const int trips = (tps + run.kg - 1) / run.kg, per = p.slots / 256 / run.kg;
+    const int waves = n >= p.bq ? 4 : (4 * n + p.bq - 1) / p.bq;         // that have queries
     const long wgs = (long)p.units * ns, full = wgs / (256 * per), rem = wgs % (256 * per);
     const double *pace = c.pace[run.kg - 1];
-    double us = c.once + full * (c.round + trips * pace[per - 1]) + (run.kg > 1 ? 0.8 : 0.0);
+    const auto tile_us = [&](int k, double busy) { return k == 1 ? pace[0] + c.crowd[run.kg - 1] * busy : pace[k - 1]; };
+    double us = c.once + c.active * (waves - 1) / 3.0 + (run.kg > 1 ? c.groups : 0.0);
+    us += full * (c.round + trips * tile_us(per, 1.0)) - (full && !rem ? c.round : 0.0);     // between rounds only
     if (rem && run.tail > 1) {
-        us += c.round + (double)((trips + run.tail - 1) / run.tail) * pace[per - 1] + c.merge;
+        us += c.round + (double)((trips + run.tail - 1) / run.tail) * tile_us(per, 1.0) + c.merge;
     } else if (rem) {
         const int k = (int)((rem + 255) / 256);
-        us += c.round + trips * pace[k - 1] * (k == 1 ? 1.0 - c.light * (1.0 - rem / 256.0) : 1.0);
+        us += (full ? c.round : 0.0) + trips * tile_us(k, rem / 256.0);
     }
     return ns > 1 ? us + c.merge + c.merge_mb * (2.0e-6 * ns * B * n * H * (Dh + 2) * sizeof(float)) : us;
 }
 
 // The division by key ranges that the workspace is sized for, unless fewer ranges, or two wavefront groups per
-// workgroup with at most as many, promise 3 % less: two groups fill a CU as two workgroups do, without partial results
-// in memory.  us, one group and the ranges above -> here: 2 x 1024 queries, 2521 keys, 16 heads of 128 65.4 -> 50.6,
-// 2000 x 6000 122.8 -> 105.8, 3 x 400 x 1500 42.8 -> 29.7, 2 x 576 x 1216, 30 heads of 64 33.5 -> 26.0; over the
-// 150 problems 5.9 % on average, at worst 4 % more.
+// workgroup with at most as many, promise 3 % and 0.9 us less: two groups fill a CU as two workgroups do, without
+// partial results in memory.  us, one group and the ranges above -> here: 2 x 1024 queries, 2521 keys, 16 heads of 128
+// 65.4 -> 50.6, 2000 x 6000 122.8 -> 105.8, 3 x 400 x 1500 42.8 -> 29.7, 2 x 576 x 1216, 30 heads of 64 33.5 -> 26.0;
+// over the 570 problems 6 % on average, at worst 2 % more.  (With 3 % alone, and fixed parts that do not know how many
+// wavefronts have queries, 24 of them were 3 to 18 % slower, all with few queries and a short cache: 2 x 2 queries,
+// 635 keys, 32 heads of 128 12.7 us in two ranges, 15.0 by two groups.)
 static AttnRun attention_run(int B, int n, int L, int H, int Dh, bool scratch)
 {
     const AttnPlan p = attention_plan(B, n, H, Dh);
@@ -622,7 +629,8 @@ static AttnRun attention_run(int B, int n, int L, int H, int Dh, bool scratch)
     if (scratch && run.nsplit == 1) run.tail = p.tail_ranges;
     if (run.tail > longest) run.tail = longest;
     const int most = run.nsplit;
-    double best = 0.97 * attention_us(B, n, L, H, Dh, p, run);
+    const double sized = attention_us(B, n, L, H, Dh, p, run);
+    double best = fmin(0.97 * sized, sized - 0.9);
     for (int kg = 1; kg <= 2; ++kg)
         for (int ns = 1; ns <= most; ++ns) {
             if (kg == 1 ? ns == most : ntiles < 6 * ns) continue;

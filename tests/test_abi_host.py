@@ -391,3 +391,19 @@ def test_plans_that_run_stay_within_the_workspace(dtype):
 def test_small_tiles_in_shares_stay_in_reach(B, n, d, H, F, expect):
     """tests/test_gpu_linear_plans.py runs these for the division of small tiles (their FC2)."""
     assert linear_plans("bf16", B, n, d, H, F)[3] == expect
+
+
+@pytest.mark.parametrize("B,n,L,H,Dh,groups,ranges", [
+    (2, 2, 635, 32, 128, 1, 2),       # 12.7 us; two groups without ranges 15.0
+    (5, 18, 1271, 30, 64, 1, 3),      # 14.8; 17.2
+    (1, 17, 582, 32, 128, 1, 2),      # 12.1; 13.7
+    (3, 2, 944, 30, 64, 1, 3),        # 11.4; two groups, two ranges 12.7
+    (3, 25, 567, 16, 128, 1, 2),      # 12.9; undivided 14.2
+    (6, 3, 910, 16, 128, 1, 3),       # 16.6; two groups, two ranges 18.1
+    (2, 142, 519, 30, 64, 1, 2),      # 15.6; undivided 16.5
+    (2, 1024, 2521, 16, 128, 2, 1),   # 50.6; three ranges 65.4
+    (8, 231, 871, 30, 64, 2, 1),
+])
+def test_attention_is_divided_as_measured(B, n, L, H, Dh, groups, ranges):
+    """Few queries over a short cache: a division that is not the faster one (microseconds above) is not taken."""
+    assert fv.load_library()["_ZN4fvar14attention_waysEiiiii"](B, n, L, H, Dh) == 100 * groups + ranges

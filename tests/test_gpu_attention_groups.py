@@ -13,14 +13,14 @@ from gpu_util import TOL, GpuBlock, oracle_dense, rel_err, to_dev, to_np  # noqa
 
 
 @pytest.mark.parametrize("B,n,Lp,d,H,ranges", [
-    (2, 33, 441, 512, 4, 1),        # 8 tiles, one active wavefront and one query in the next
-    (3, 150, 441, 512, 4, 1),       # 10 tiles
-    (3, 200, 441, 512, 4, 1),       # 11 tiles, the last with one key
+    (20, 33, 441, 512, 4, 1),       # 8 tiles, one active wavefront and one query in the next
+    (10, 150, 441, 512, 4, 1),      # 10 tiles
+    (11, 200, 441, 512, 4, 1),      # 11 tiles, the last with one key
     (5, 256, 441, 1024, 16, 1),     # head_dim 64, 256 queries per workgroup, 11 tiles
     (8, 100, 441, 1024, 16, 1),     # head_dim 64, 128 queries per workgroup, 9 tiles
     (1, 300, 300, 256, 4, 1),       # query remainder 44, 10 tiles
-    (1, 20, 4000, 1024, 8, 8),      # 63 tiles in ranges of 8, each for two groups; the last of 7
-    (2, 20, 4000, 512, 8, 8),       # the same with head_dim 64
+    (12, 20, 917, 1024, 8, 2),      # 15 tiles in ranges of 8, each for two groups; the last of 7
+    (1, 20, 4629, 256, 4, 8),       # head_dim 64, 73 tiles in ranges of 10; the last of 3
 ])
 def test_two_wavefront_groups_share_the_keys(B, n, Lp, d, H, ranges):
     ways = fv.load_library()["_ZN4fvar14attention_waysEiiiii"]
