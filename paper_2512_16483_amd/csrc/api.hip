@@ -1,6 +1,5 @@
 // C ABI of the library: argument validation, workspace carving and the launch sequence of each
 // entry point.  Host code only; every arithmetic step runs in the kernels of this directory.
-#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -166,21 +165,10 @@ BlockWs carve(const fvar_ctx *c, void *ws, int B, int rows)
     w.att = take(R * d * es);
     w.h1 = take(R * d * sizeof(float));       // intermediate residual stream, always fp32
     w.hid = take(R * F * es);
-    const DType dt = dtype(c);
-    const int shape[4][2] = {{(int)(3 * d), (int)d}, {(int)d, (int)d}, {(int)F, (int)d}, {(int)d, (int)F}};   // N, K
-    // partial results where the key axis or the contraction axis is divided between workgroups
-    size_t part = fvar::attention_scratch_floats(dt, B, rows, c->cfg.heads, c->cfg.head_dim);
-    fvar::GemmPlan *plan[4] = {&w.qkv, &w.o, &w.fc1, &w.fc2};
-    double us[4] = {};                        // predicted times, not used in fp32
-    for (int i = 0; i < 4; ++i) {
-        *plan[i] = fvar::gemm_plan_us(dt, (int)R, shape[i][0], shape[i][1], &us[i]);
-        part = std::max(part, plan[i]->scratch_floats);
-    }
-    // fp32: what the plans take falls as the rows become more; their bound does not, so that a
-    // workspace sized for the largest call serves every smaller one (bf16 never had that: see fvar.h)
-    if (dt != DType::BF16) part = std::max(part, fvar::gemm_f32_scratch_bound((int)R, (int)std::max(3 * d, F)));
-    for (int i = 0; i < 4; ++i)
-        *plan[i] = fvar::linear_plan(dt, (int)R, shape[i][0], shape[i][1], part, *plan[i], us[i]);
+    const fvar::BlockPlan plan = fvar::block_plan(dtype(c), B, rows, c->cfg.hidden, c->cfg.heads, c->cfg.head_dim,
+                                                  c->cfg.ffn_hidden);
+    w.qkv = plan.layer[0]; w.o = plan.layer[1]; w.fc1 = plan.layer[2]; w.fc2 = plan.layer[3];
+    const size_t part = plan.floats;
     w.part = part ? reinterpret_cast<float *>(take(part * sizeof(float))) : nullptr;
     w.total = off;
     return w;

@@ -155,15 +155,11 @@ struct GemmEpilogue {
 // How a linear layer is run: kernel and tile (index into the tables of gemm.hip), workgroups that share the
 // contraction axis of every tile (nsplit) or, with the tiled kernel, of the tiles beyond the last whole round
 // (tail), and the floats of scratch that their partial tiles take.
-// gemm_plan is a function of the shape alone and tells what scratch a call is given (in fp32, and for cfg >= the
-// number of tiles, that is all it is for); linear_plan is what runs: gemm_plan's tile or an instance of
-// gemm_rows_kernel, whichever is predicted faster, the latter within `room` floats.
 struct GemmPlan { int cfg, nsplit, tail; size_t scratch_floats; };
-GemmPlan gemm_plan(DType dt, int rows, int N, int K);
-GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room);
-// the same in two steps, for callers that need both: gemm_plan with its predicted time, then what runs
-GemmPlan gemm_plan_us(DType dt, int rows, int N, int K, double *us);
-GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room, GemmPlan best, double best_us);
+// The four linear layers of a block (QKV, O, FC1, FC2) as they run, and the floats of scratch that its workspace has
+// for them and the attention, which use it in turn.
+struct BlockPlan { GemmPlan layer[4]; size_t floats; };
+BlockPlan block_plan(DType dt, int B, int rows, int d, int H, int Dh, int F);
 // floats that no fp32 plan of up to `rows` rows and N columns exceeds; never falls as rows grow
 size_t gemm_f32_scratch_bound(int rows, int N);
 // `part`: plan.scratch_floats floats (unused when 0)

@@ -1248,7 +1248,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(
 // they are: on 115 of 3000 problems where the picks differ 17.1 us in geometric mean instead of 15.9, at worst 1536 x 6144
 // with 703 rows 40.5 instead of 28.1, and 128x64 divided eight ways took more workspace than 64x64 in five.
 constexpr double kLaunchUs = 3.6;      // a launch by itself
-constexpr double kRowsRate = 11.9e6;   // bytes / us of the kernel that kRows once described, see linear_plan
 
 struct TileCfg { int bm, bn; double k_us, tile_us; };   // us per k-tile and per tile with all CUs at work
 constexpr TileCfg kTiles[] = {
@@ -1265,28 +1264,20 @@ static bool in_groups(int cfg, int per, long workgroups)
 {
     return cfg == 8 ? per >= 32 : cfg == 9 ? per >= 16 : cfg == kSmallTile && per >= 16 && workgroups <= 256;
 }
-// us per k-step of a wavefront, once, and for every further round of workgroups over the CUs (only the largest fills
-// a CU with one: 192 workgroups 9.0 us, 288 12.2 at 3072 x 768)
-// These are the times of a kernel without LDS, which gemm_rows_kernel has replaced: what gemm_plan picks with them
-// still sizes the workspace, so that it stays what callers were told, and never runs.
-struct RowsCfg { int ft, tt; double step_us, fixed_us, round_us; };
-constexpr RowsCfg kRows[] = {{1, 1, 0.174, 3.0, 0.0}, {2, 1, 0.261, 3.3, 0.0}, {2, 2, 0.281, 3.7, 3.0}};
-constexpr int kNumRows = sizeof(kRows) / sizeof(kRows[0]);
-constexpr int kRowsWaves = 8, kRowsMax = 256;           // bf16: gemm_rows_kernel is not used beyond 256 rows
+constexpr int kRowsMax = 256;           // bf16: gemm_rows_kernel is not used beyond 256 rows
 
-// Instances of gemm_rows_kernel (features / 16, rows / 16, wavefronts), with us once, per round of workgroups over
-// the CUs (the rings fill a CU's LDS) and per step of a wavefront.  Never below the operands' way into the CUs at
-// kRingRate bytes / us and the weights' from HBM.  Fitted per type to timings of every instance and division on 200
-// problems (bf16: 7 .. 320 rows, hidden 1024 .. 4096; fp32: 4 .. 2048 rows, hidden 512 .. 1920), weights from
-// HBM: the picks are 3.2 and 1.5 % off the best on average.
-struct RingCfg { int ft, tt, nw; double fixed_us, round_us, step_us; };
+// Instances of gemm_rows_kernel (features / 16, rows / 16, wavefronts), with us per round of workgroups over the CUs
+// (the rings fill a CU's LDS) and per step of a wavefront.  They and the constants of ring_us are fitted to 19000
+// timings of every instance and division on 1184 layers (bf16: 4 .. 256 rows, hidden 512 .. 8192; fp32: 4 .. 2048 rows,
+// hidden 512 .. 4096), weights from HBM: 8 % rms.
+struct RingCfg { int ft, tt, nw; double round_us, step_us; };
 constexpr int kNumRings = 8;
 constexpr RingCfg kRings[2][kNumRings] = {
-    {{1, 1, 8, 3.86, 0.94, 0.406}, {2, 1, 8, 3.47, 1.25, 0.620}, {1, 2, 8, 3.55, 1.37, 0.510}, {2, 2, 8, 2.40, 2.02, 0.998},
-     {3, 2, 8, 2.40, 2.23, 1.529}, {2, 4, 4, 2.40, 1.84, 1.140}, {4, 4, 4, 2.40, 2.55, 2.208}, {3, 4, 4, 2.40, 2.43, 1.697}},
-    {{1, 1, 8, 4.23, 0.78, 0.376}, {2, 1, 8, 4.14, 0.80, 0.562}, {1, 2, 8, 3.95, 0.99, 0.470}, {2, 2, 8, 3.65, 1.10, 0.710},
-     {3, 2, 8, 3.52, 1.21, 0.982}, {2, 4, 4, 2.84, 1.80, 0.530}, {4, 4, 4, 2.40, 2.69, 0.825}, {3, 4, 4, 2.40, 2.27, 0.699}}};
-constexpr double kRingRate[2] = {11.0e6, 15.0e6};
+    {{1, 1, 8, 1.51, 0.548}, {2, 1, 8, 1.85, 0.799}, {1, 2, 8, 1.87, 0.767}, {2, 2, 8, 2.60, 1.114},
+     {3, 2, 8, 2.90, 1.622}, {2, 4, 4, 2.92, 1.221}, {4, 4, 4, 4.01, 2.267}, {3, 4, 4, 3.31, 1.773}},
+    {{1, 1, 8, 1.23, 0.503}, {2, 1, 8, 1.22, 0.754}, {1, 2, 8, 1.29, 0.692}, {2, 2, 8, 1.39, 0.971},
+     {3, 2, 8, 1.41, 1.252}, {2, 4, 4, 2.08, 0.672}, {4, 4, 4, 3.12, 0.962}, {3, 4, 4, 2.59, 0.826}}};
+constexpr double kRingHbmRate = 6.5e6;  // bytes / us
 
 // fp32: at most 8 shares, and not more than 256 workgroups of 32 features x 16 rows per tile
 static int f32_row_tiles(int rows) { return rows <= 16 ? 1 : rows <= 32 ? 2 : 4; }
@@ -1296,12 +1287,11 @@ size_t gemm_f32_scratch_bound(int rows, int N)
     return every < full ? every : full;
 }
 
-// bf16; `groups`: with the kernels that use wavefront groups, as they are launched.  Candidates with more than
-// `most` floats of scratch are left out.
-static GemmPlan gemm_bf16_plan(int rows, int N, int K, bool groups, size_t most, double *us_out = nullptr)
+// bf16: the fastest tile and division, and its predicted time.  `groups`: with the kernels that use wavefront groups, as
+// they are launched.  Candidates with more than `most` floats of scratch are left out.
+static GemmPlan tile_plan(int rows, int N, int K, bool groups, size_t most, double &best_us)
 {
     GemmPlan best{0, 1, 1, 0};
-    double none, &best_us = us_out ? *us_out : none;
     best_us = 1e300;
     const int kt = K / BK;
     const double hbm_us = 2.0 * ((double)rows * K + (double)N * K + (double)rows * N) / kHbmRate;
@@ -1339,9 +1329,21 @@ static GemmPlan gemm_bf16_plan(int rows, int N, int K, bool groups, size_t most,
             if (us < best_us && scratch <= most) { best_us = us; best = {i, 1, t, scratch}; }
         }
     }
-    if (rows > kRowsMax) return best;
-    for (int i = 0; i < kNumRows; ++i) {
-        const RowsCfg &c = kRows[i];
+    return best;
+}
+
+// How much scratch callers have been told a layer takes.  It was once the plan's own, and the plan then had, for up to
+// kRowsMax rows, a kernel without LDS to choose from, described here by its us per k-step of a wavefront, once, and for
+// every further round of workgroups over the CUs.  The kernel is gone; the workspace keeps its size, since programs
+// keep it: a smaller one could not hold the shares that are the faster ones here, a larger one would refuse them.
+struct RowsCfg { int ft, tt; double step_us, fixed_us, round_us; };
+constexpr RowsCfg kRows[] = {{1, 1, 0.174, 3.0, 0.0}, {2, 1, 0.261, 3.3, 0.0}, {2, 2, 0.281, 3.7, 3.0}};
+constexpr double kRowsRate = 11.9e6;    // bytes / us
+constexpr int kRowsWaves = 8;
+static size_t rows_scratch(int rows, int N, int K, bool groups, size_t most, size_t scratch, double best_us)
+{
+    if (rows > kRowsMax) return scratch;
+    for (const RowsCfg &c : kRows) {
         const int bm = 16 * c.tt, bn = 16 * c.ft;
         const long tiles = (long)((rows + bm - 1) / bm) * (N / bn);
         for (int ns = 1; ns <= 8; ns *= 2) {
@@ -1350,69 +1352,113 @@ static GemmPlan gemm_bf16_plan(int rows, int N, int K, bool groups, size_t most,
             const double l2_us = (double)tiles * (bm + bn) * K * 2.0 / kRowsRate, w_us = 2.0 * N * K / kHbmRate;
             double us = c.fixed_us + c.step_us * steps + (l2_us > w_us ? l2_us : w_us) +
                         (groups ? (tiles * ns - 1) / 256 * c.round_us : 0.0);
-            if (ns > 1) us += part_us((double)ns * rows * N);
-            const size_t scratch = ns > 1 ? (size_t)ns * rows * N : 0;
-            if (us < best_us && scratch <= most) { best_us = us; best = {kNumTiles + i, ns, 1, scratch}; }
+            if (ns > 1) us += kMergeUs + (double)ns * rows * N * 8.0 / kMergeRate;
+            const size_t floats = ns > 1 ? (size_t)ns * rows * N : 0;
+            if (us < best_us && floats <= most) { best_us = us; scratch = floats; }
         }
     }
-    return best;
+    return scratch;
 }
 
-GemmPlan gemm_plan_us(DType dt, int rows, int N, int K, double *us)
+// bf16: the fastest tile; `floats`: the scratch that callers have been told, never more than without the groups
+struct TileChoice { GemmPlan plan; double us; size_t floats; };
+static TileChoice tile_choice(int rows, int N, int K)
 {
-    GemmPlan best{0, 1, 1, 0};
-    if (dt != DType::BF16) {
-        // rows per workgroup: the fewest 16-row tiles that cover the problem, at most four; then divide
-        // the contraction axis up to one workgroup per CU, every wavefront at least two k-steps
-        best.cfg = f32_row_tiles(rows);
-        const long units = (long)((rows + 16 * best.cfg - 1) / (16 * best.cfg)) * (N / 32);
-        while (best.nsplit < 8 && units * best.nsplit * 2 <= 256 && K / 16 >= best.nsplit * 4 * kRowsWaves) best.nsplit *= 2;
-        if (best.nsplit > 1) best.scratch_floats = (size_t)best.nsplit * rows * N;
-        return best;
+    TileChoice c;
+    const auto search = [&](bool groups, size_t most, GemmPlan &p, double &us) {
+        p = tile_plan(rows, N, K, groups, most, us);
+        return rows_scratch(rows, N, K, groups, most, p.scratch_floats, us);
+    };
+    c.floats = search(true, SIZE_MAX, c.plan, c.us);
+    if (c.floats == 0) return c;
+    GemmPlan none;
+    double us;
+    const size_t told = search(false, SIZE_MAX, none, us);
+    if (c.floats > told) c.floats = search(true, told, c.plan, c.us);
+    return c;
+}
+
+// Time of what a CU does and of what HBM gives, of which neither quite hides the other
+static double together(double cu_us, double hbm_us)
+{
+    const double x = cu_us / hbm_us, x2 = x * x, x4 = x2 * x2;
+    return hbm_us * sqrt(sqrt(sqrt(1.0 + x4 * x4)));
+}
+
+// Predicted time of an instance of gemm_rows_kernel without its merge
+static double ring_us(const RingCfg &c, int rows, int N, int K, int es, int ns)
+{
+    const int parts = ns * c.nw, steps = K * es / 128, per = (steps + parts - 1) / parts;
+    const long tiles = (long)((rows + 16 * c.tt - 1) / (16 * c.tt)) * (N / (16 * c.ft));
+    const double rounds = (double)((tiles * ns + 255) / 256);
+    // Where the shares of the contraction start whole multiples of 4 KiB apart, the wavefronts of all workgroups are on
+    // the same few HBM channels: 32 rows, 16384 to 4096, 32x32 undivided (4 KiB) 49.0 us, in two shares (2 KiB) 29.3.
+    double conflict = 1.0;
+    if (steps % parts == 0) {
+        const int apart = steps / parts * 128;
+        conflict = apart % 8192 == 0 ? 1.25 : apart % 4096 == 0 ? 1.5 : 1.0;
     }
-    best = gemm_bf16_plan(rows, N, K, true, SIZE_MAX, us);
-    if (best.scratch_floats == 0) return best;
-    // never more scratch than without the groups, which is what callers have been told the workspace takes
-    const size_t told = gemm_bf16_plan(rows, N, K, false, SIZE_MAX).scratch_floats;
-    return best.scratch_floats <= told ? best : gemm_bf16_plan(rows, N, K, true, told, us);
-}
-GemmPlan gemm_plan(DType dt, int rows, int N, int K) { return gemm_plan_us(dt, rows, N, K, nullptr); }
-
-GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room)
-{
-    double us = 1e300;
-    const GemmPlan p = gemm_plan_us(dt, rows, N, K, &us);
-    return linear_plan(dt, rows, N, K, room, p, us);
+    const double bytes = (double)es * ((double)rows * K + (double)N * K + (double)rows * N);
+    return together(1.0 + rounds * (c.round_us + c.step_us * per), 3.4 + 0.7 * (rounds - 1.0) + bytes * conflict / kRingHbmRate);
 }
 
-GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room, GemmPlan best, double best_us)
+static double merge_us(const GemmPlan &p) { return p.nsplit > 1 ? kMergeUs + p.scratch_floats * 8.0 / kMergeRate : 0.0; }
+
+// What runs, within `room` floats: an instance of gemm_rows_kernel (fp32 always; plans of kNumTiles + instance) or the
+// tile, whichever is predicted faster.  The tiles' own times leave out that the weights' way from HBM is not hidden at so few
+// rows (12 rows, 3072 to 12288: 64x64 16.2 us predicted, 21.4 measured, 15.2 by 48x32), and are a little low besides: on
+// 1296 layers of other sizes the picks take 0.7586 of the time of the plan without gemm_rows_kernel with a factor of 1.0,
+// 0.7571 with 1.03 and 0.7540 with 1.1, at worst 1 %, 3 % and 5 % more than it.
+// On the layers that kRings is fitted to, none is more than 3 % above the time of the plan without gemm_rows_kernel
+// (fp32: of a kernel that loads straight to registers); on average they take 0.78 and 0.68 of it.  The picks are
+// 1.3 and 0.5 % off the best of all candidates, at worst 42 % (another tile) and 13 %.  (Without the conflicts, with the
+// weights at 6.0e6 bytes / us beside anything, and steps fitted where they are few, FC2 of 16384 to 4096 took 39 to 49 us
+// at 4 to 32 rows, where the tiles take 33 to 34 and 32x32 in two shares 27 to 29.)
+static GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room, TileChoice tile)
 {
     const bool bf16 = dt == DType::BF16;
-    const int step = bf16 ? 64 : 32;
-    if (bf16 && best.cfg < kNumTiles && rows > kRowsMax) return best;
-    if (!bf16 || best.cfg >= kNumTiles) best_us = 1e300;       // priced as the instance it is, below
-    // The tiles' times are that much too low here, above all where they are divided (64 rows, 8192 to 2048: 12.8 us
-    // predicted, 15.9 measured, 14.0 by 32x64 in four shares).  Loss against the better of both over 132 layers of up
-    // to 256 rows: 2.3 % at 1.0, 2.0 at 1.05, 1.2 at 1.1, 1.4 at 1.15, 1.6 at 1.25.
-    best_us *= 1.1;
-    const double es = bf16 ? 2.0 : 4.0, hbm_us = 3.4 + es * ((double)rows * K + (double)N * K + (double)rows * N) / 6.0e6;
+    const int es = bf16 ? 2 : 4;
+    if (bf16 && rows > kRowsMax) return tile.plan;
+    GemmPlan best{0, 1, 1, 0};
+    double best_us = 1e300;
+    if (bf16) {
+        if (tile.plan.scratch_floats > room) tile.plan = tile_plan(rows, N, K, true, room, tile.us);
+        const double bytes = 2.0 * ((double)rows * K + (double)N * K + (double)rows * N), merge = merge_us(tile.plan);
+        best = tile.plan;
+        best_us = together(1.03 * (tile.us - merge), 3.4 + bytes / kRingHbmRate) + merge;
+    }
     for (int i = 0; i < kNumRings; ++i) {
         const RingCfg &c = kRings[bf16][i];
         if (N % (16 * c.ft)) continue;
-        const long tiles = (long)((rows + 16 * c.tt - 1) / (16 * c.tt)) * (N / (16 * c.ft));
-        const double l2_us = 2.8 + (double)tiles * 16 * (c.ft + c.tt) * K * es / kRingRate[bf16];
         for (int ns = 1; ns <= 8; ns *= 2) {
-            const size_t scratch = ns > 1 ? (size_t)ns * rows * N : 0;
-            if (ns > 1 && (K / step < ns * c.nw || scratch > room)) break;
-            const int steps = (K / step + ns * c.nw - 1) / (ns * c.nw);
-            double us = c.fixed_us + (double)((tiles * ns + 255) / 256) * (c.round_us + c.step_us * steps);
-            us = us > l2_us ? us : l2_us;
-            us = us > hbm_us ? us : hbm_us;
-            if (ns > 1) us += kMergeUs + scratch * 8.0 / kMergeRate;
-            if (us < best_us) { best_us = us; best = {kNumTiles + kNumRows + i, ns, 1, scratch}; }
+            const GemmPlan p{kNumTiles + i, ns, 1, ns > 1 ? (size_t)ns * rows * N : 0};
+            if (ns > 1 && (K * es / 128 < ns * c.nw || p.scratch_floats > room)) break;
+            const double us = ring_us(c, rows, N, K, es, ns) + merge_us(p);
+            if (us < best_us) { best_us = us; best = p; }
         }
     }
     return best;
+}
+
+BlockPlan block_plan(DType dt, int B, int rows, int d, int H, int Dh, int F)
+{
+    const int R = B * rows, shape[4][2] = {{3 * d, d}, {d, d}, {F, d}, {d, F}};   // N, K
+    BlockPlan p;
+    TileChoice tile[4] = {};
+    p.floats = attention_scratch_floats(dt, B, rows, H, Dh);
+    if (dt == DType::BF16) {
+        for (int i = 0; i < 4; ++i) {
+            tile[i] = tile_choice(R, shape[i][0], shape[i][1]);
+            if (tile[i].floats > p.floats) p.floats = tile[i].floats;
+        }
+    } else {
+        // what the plans take falls as the rows become more; their bound does not, so that a workspace sized for the
+        // largest call serves every smaller one (bf16 never had that)
+        const size_t bound = gemm_f32_scratch_bound(R, 3 * d > F ? 3 * d : F);
+        if (bound > p.floats) p.floats = bound;
+    }
+    for (int i = 0; i < 4; ++i) p.layer[i] = linear_plan(dt, R, shape[i][0], shape[i][1], p.floats, tile[i]);
+    return p;
 }
 
 template <typename T, int FT, int TT, int NW, int STAGES>
@@ -1487,7 +1533,7 @@ void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
             else
                 launch_gemm_bf16_cfg<64, 64, 2, 2, 3>(A, W, rows, N, K, ep, st, ns, part, tail);
             break;
-        default: launch_gemm_ring<uint16_t>(plan.cfg - kNumTiles - kNumRows, A, W, rows, N, K, ep, st, ns, part); break;
+        default: launch_gemm_ring<uint16_t>(plan.cfg - kNumTiles, A, W, rows, N, K, ep, st, ns, part); break;
         }
         if (ns > 1) {
             const long total = (long)rows * (N / 4);
@@ -1495,7 +1541,7 @@ void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
                    (const float *)part, ns, rows, N, ep);
         }
     } else {
-        launch_gemm_ring<float>(plan.cfg - kNumTiles - kNumRows, A, W, rows, N, K, ep, st, plan.nsplit, part);
+        launch_gemm_ring<float>(plan.cfg - kNumTiles, A, W, rows, N, K, ep, st, plan.nsplit, part);
         if (plan.nsplit > 1) {
             const long total = (long)rows * (N / 4);
             launch(gemm_f32_merge_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,

@@ -167,58 +167,87 @@ class _Plan(C.Structure):
     _fields_ = [("cfg", C.c_int), ("nsplit", C.c_int), ("tail", C.c_int), ("scratch_floats", C.c_size_t)]
 
 
-def gemm_plan(dtype, rows, N, K):
-    """The plan of a linear layer (an internal function of the library; pure host code)."""
-    f = fv.load_library()["_ZN4fvar9gemm_planENS_5DTypeEiii"]
-    f.restype, f.argtypes = _Plan, [C.c_int, C.c_int, C.c_int, C.c_int]
-    return f(1 if dtype == "bf16" else 0, rows, N, K)
+class _BlockPlan(C.Structure):
+    _fields_ = [("layer", _Plan * 4), ("floats", C.c_size_t)]
 
 
-TILES = ("320x256", "256x256", "192x256", "256x192", "256x128", "128x256", "192x128", "128x128", "64x128", "128x64",
-         "64x64", "rows 16x16", "rows 32x16", "rows 32x32")
+def block_plan(dtype, B, n, d, H, F):
+    """How a block's linear layers run (an internal function of the library; pure host code)."""
+    f = fv.load_library()["_ZN4fvar10block_planENS_5DTypeEiiiiii"]
+    f.restype, f.argtypes = _BlockPlan, [C.c_int] * 7
+    return f(1 if dtype == "bf16" else 0, B, n, d, H, d // H, F)
 
 
-@pytest.mark.parametrize("rows,d,F,layer,tile,shares,last_round", [
-    (7, 1024, 4096, "qkv", "rows 16x16", 1, 1),
-    (18, 1024, 4096, "fc1", "rows 32x32", 1, 1),
-    (33, 960, 1984, "qkv", "rows 32x16", 1, 1),
-    (64, 512, 5440, "fc2", "rows 32x32", 8, 1),
-    (64, 2048, 8192, "fc2", "64x64", 7, 1),
-    (130, 1024, 4096, "fc1", "64x64", 1, 1),
-    (130, 1024, 4096, "fc2", "128x64", 8, 1),
-    (257, 1024, 4096, "fc2", "64x128", 6, 1),
-    (700, 1024, 4096, "fc1", "128x128", 1, 1),
-    (700, 1024, 4096, "fc2", "128x128", 5, 1),
-    (900, 1920, 7680, "qkv", "192x128", 1, 1),
-    (900, 1920, 7680, "fc1", "128x256", 1, 1),
-    (1848, 1920, 7680, "qkv", "256x192", 1, 1),
-    (1848, 1920, 7680, "fc1", "256x256", 1, 1),
-    (36, 2048, 8192, "qkv", "64x64", 3, 1),
-    (144, 4096, 1024, "qkv", "192x128", 2, 1),
-    (642, 4096, 64, "qkv", "128x256", 1, 8),
-    (1610, 4096, 64, "qkv", "256x256", 1, 3),
+TILES = ("320x256", "256x256", "192x256", "256x192", "256x128", "128x256", "192x128", "128x128", "64x128", "128x64", "64x64")
+RINGS = ("16x16", "32x16", "16x32", "32x32", "48x32", "32x64", "64x64", "48x64")     # features x rows of a workgroup
+LAYERS = ("qkv", "o", "fc1", "fc2")
+
+
+def linear_plans(dtype, B, n, d, H, F):
+    """{layer: (tile or ring instance, shares, last round's shares)} of a block as it runs."""
+    return {l: (TILES[p.cfg] if p.cfg < len(TILES) else "ring " + RINGS[p.cfg - len(TILES)], p.nsplit, p.tail)
+            for l, p in zip(LAYERS, block_plan(dtype, B, n, d, H, F).layer)}
+
+
+@pytest.mark.parametrize("B,n,d,H,F,layer,tile,shares,last_round", [
+    (1, 64, 2048, 16, 8192, "qkv", "ring 48x32", 1, 1),
+    (1, 64, 2048, 16, 8192, "fc2", "ring 32x64", 4, 1),
+    (2, 65, 1024, 16, 4096, "fc1", "ring 64x64", 1, 1),
+    (1, 257, 1024, 16, 4096, "fc1", "128x64", 1, 1),
+    (1, 257, 1024, 16, 4096, "fc2", "64x128", 6, 1),
+    (1, 257, 128, 2, 256, "fc2", "64x64", 1, 1),
+    (1, 700, 1024, 16, 4096, "fc1", "128x128", 1, 1),
+    (1, 700, 1024, 16, 4096, "fc2", "128x128", 5, 1),
+    (4, 225, 1920, 30, 7680, "qkv", "192x128", 1, 1),
+    (4, 225, 1920, 30, 7680, "fc1", "128x256", 1, 1),
+    (2, 924, 1920, 15, 7680, "qkv", "256x192", 1, 1),
+    (2, 924, 1920, 15, 7680, "fc1", "256x256", 1, 1),
+    (3, 25, 3072, 48, 64, "qkv", "128x128", 3, 1),
+    (4, 36, 4096, 32, 1024, "qkv", "192x128", 2, 1),
+    (3, 214, 4096, 32, 64, "qkv", "128x256", 1, 8),
+    (3, 214, 4096, 32, 64, "fc1", "64x64", 8, 1),
+    (2, 805, 4096, 32, 64, "qkv", "256x256", 1, 3),
+    (1, 180, 1536, 24, 5440, "fc2", "64x128", 7, 1),
 ])
-def test_plans_that_the_gpu_tests_are_there_for(rows, d, F, layer, tile, shares, last_round):
+def test_plans_that_the_gpu_tests_are_there_for(B, n, d, H, F, layer, tile, shares, last_round):
     """tests/test_gpu_linear_plans.py runs the block at these row counts: another choice of constants must not
     take a kernel, a tile or a division out of its reach unseen."""
-    N, K = {"qkv": (3 * d, d), "o": (d, d), "fc1": (F, d), "fc2": (d, F)}[layer]
-    p = gemm_plan("bf16", rows, N, K)
-    assert (TILES[p.cfg], p.nsplit, p.tail) == (tile, shares, last_round)
+    assert linear_plans("bf16", B, n, d, H, F)[layer] == (tile, shares, last_round)
 
 
 @pytest.mark.parametrize("rows,d,layer,tile,shares", [
     (703, 1536, "fc2", "192x128", 5), (776, 1280, "fc2", "192x128", 5), (1229, 1024, "fc2", "128x128", 3),
     (300, 4096, "o", "192x128", 4), (421, 3072, "o", "128x64", 1),       # 64x64: more workgroups than CUs, hence no groups
-    (152, 1024, "fc2", "64x64", 5), (128, 1536, "fc2", "64x64", 5),      # 128x64 in eight shares: too few k-tiles for groups
-    (90, 768, "fc1", "64x64", 1),                                        # 32x32 without staging: a second round of workgroups
 ])
 def test_plan_prices_the_kernel_that_is_launched(rows, d, layer, tile, shares):
     """Tiles with wavefront groups have time constants of their own, which hold only where the launch uses groups.
-    The first five picks measured 22 to 31 % less time than those of a plan that prices both kernels alike, the sixth
-    and seventh the same within 2 % with less workspace, the last 27 % less than without staging."""
-    N, K = {"o": (d, d), "fc1": (4 * d, d), "fc2": (d, 4 * d)}[layer]
-    p = gemm_plan("bf16", rows, N, K)
-    assert (TILES[p.cfg], p.nsplit, p.tail) == (tile, shares, 1)
+    These picks measured 22 to 31 % less time than those of a plan that prices both kernels alike."""
+    assert linear_plans("bf16", 1, rows, d, d // 64, 4 * d)[layer] == (tile, shares, 1)
+
+
+# Microseconds of a layer of few rows, weights from HBM: by the plan that had no kernel with rings per wavefront (fp32: by
+# the kernel that loaded its operands straight to registers), and by candidates of now.
+FEW_ROWS = [
+    ("bf16", 7, 4096, 16384, "fc2", 33.2, {("ring 16x16", 1): 39.4, ("ring 32x16", 2): 27.2, ("ring 32x32", 2): 27.4}),
+    ("bf16", 16, 4096, 16384, "fc2", 33.4, {("ring 16x16", 1): 40.0, ("ring 32x16", 2): 27.6, ("ring 32x32", 2): 27.4}),
+    ("bf16", 24, 4096, 16384, "fc2", 34.4, {("ring 32x32", 1): 47.0, ("ring 32x32", 2): 28.5}),
+    ("bf16", 32, 4096, 16384, "fc2", 34.4, {("ring 32x32", 1): 49.0, ("ring 32x32", 2): 29.3, ("ring 64x64", 4): 30.5}),
+    ("bf16", 32, 4096, 16384, "fc1", 31.5, {("ring 32x32", 1): 33.2, ("ring 64x64", 1): 27.6}),
+    ("bf16", 32, 3072, 16384, "fc2", 27.7, {("ring 32x16", 1): 35.0, ("ring 48x32", 4): 24.1}),
+    ("bf16", 24, 3072, 16384, "fc2", 27.5, {("ring 32x16", 1): 33.2, ("ring 48x32", 4): 23.6}),
+    ("bf16", 12, 3072, 12288, "fc1", 21.3, {("64x64", 1): 21.5, ("ring 48x32", 1): 15.2}),
+    ("bf16", 48, 1920, 7680, "fc2", 14.1, {("ring 64x64", 8): 14.8, ("ring 32x64", 4): 13.5}),
+    ("bf16", 4, 2048, 8192, "fc1", 9.1, {("ring 16x16", 1): 9.9, ("ring 32x16", 1): 8.2, ("ring 32x32", 1): 8.3}),
+    ("f32", 4, 1024, 8192, "fc1", 10.2, {("ring 16x16", 1): 11.5, ("ring 32x16", 1): 9.8}),
+    ("f32", 16, 1024, 8192, "fc1", 10.7, {("ring 16x16", 1): 11.5, ("ring 32x16", 1): 9.5}),
+]
+
+
+@pytest.mark.parametrize("dtype,rows,d,F,layer,before,now", FEW_ROWS)
+def test_few_rows_take_no_slower_kernel(dtype, rows, d, F, layer, before, now):
+    """The kernel with a ring per wavefront is for the rows where it is the faster one."""
+    pick = linear_plans(dtype, 1, rows, d, d // (64 if d < 2048 else 128), F)[layer]
+    assert now[pick[:2]] <= before, pick
 
 
 @pytest.mark.parametrize("B,rows,d,H,most", [(4, 38, 1024, 16, 6225920), (8, 19, 1024, 16, 6225920), (3, 51, 1024, 16, 6364928),
@@ -274,17 +303,18 @@ def test_fill_keeps_maps_in_cache_that_the_next_block_reads_there():
         assert (past(mb * 10 ** 6, False), past(mb * 10 ** 6, True)) == (plain, scored), mb
 
 
-@pytest.mark.parametrize("rows,d,F,layer,tile,shares", [
-    (65, 1088, 1088, "qkv", "64x64", 1), (520, 960, 2240, "fc2", "64x64", 1), (257, 512, 1088, "fc2", "64x64", 1),
-    (330, 1088, 4096, "fc1", "128x64", 1), (400, 960, 4160, "fc2", "128x64", 4), (300, 2048, 2112, "qkv", "64x128", 1),
+@pytest.mark.parametrize("B,n,d,H,F,layer,tile,shares", [
+    (3, 90, 1088, 17, 1088, "qkv", "64x64", 1), (1, 520, 960, 15, 2240, "fc2", "64x64", 1),
+    (1, 257, 512, 8, 1088, "fc2", "64x64", 1),
+    (1, 330, 1088, 17, 4096, "fc1", "128x64", 1), (1, 400, 960, 15, 4160, "fc2", "128x64", 4),
+    (3, 100, 2048, 16, 2112, "qkv", "64x128", 1),
 ])
-def test_plans_of_the_wavefront_group_tests(rows, d, F, layer, tile, shares):
+def test_plans_of_the_wavefront_group_tests(B, n, d, H, F, layer, tile, shares):
     """tests/test_gpu_linear_plans.py runs these blocks for the tiles whose k-tiles are dealt to groups."""
     N, K = {"qkv": (3 * d, d), "fc1": (F, d), "fc2": (d, F)}[layer]
-    p = gemm_plan("bf16", rows, N, K)
-    assert (TILES[p.cfg], p.nsplit, p.tail) == (tile, shares, 1)
+    assert linear_plans("bf16", B, n, d, H, F)[layer] == (tile, shares, 1)
     bm, bn = map(int, tile.split("x"))
-    workgroups, per = -(-rows // bm) * -(-N // bn) * shares, -(-K // 64 // shares)
+    workgroups, per = -(-B * n // bm) * -(-N // bn) * shares, -(-K // 64 // shares)
     assert per >= (32 if tile == "64x128" else 16) and (tile != "64x64" or workgroups <= 256)
 
 
@@ -313,8 +343,10 @@ def test_block_workspace_holds_the_partial_results(dtype, d, H):
         for n in list(range(1, 260, 3)) + [363, 640, 1021, 1537, 1600, 2048, 3122]:
             R = B * n
             part = fv.fvar_block_workspace_bytes(c, B, n) - 4 * al(R * d * es) - al(R * d * 4) - al(R * F * es)
-            plans = [gemm_plan(dtype, R, N, K).scratch_floats for N, K in ((3 * d, d), (d, d), (F, d), (d, F))]
-            assert part >= 4 * max(plans + [att(1 if dtype == "bf16" else 0, B, n, H, d // H)]), (B, n)
+            plans = block_plan(dtype, B, n, d, H, F).layer
+            held = [p.nsplit * R * N if p.nsplit > 1 else 0 for p, N in zip(plans, (3 * d, d, F, d))]
+            held += [p.scratch_floats for p in plans] + [att(1 if dtype == "bf16" else 0, B, n, H, d // H)]
+            assert part >= 4 * max(held), (B, n)
 
 
 @pytest.mark.parametrize("dtype,d", [("f32", 512), ("bf16", 128), ("bf16", 1024), ("bf16", 1920), ("bf16", 4096)])
@@ -336,61 +368,53 @@ def test_factors_workspace_grows_with_the_call(dtype, d):
                 last = need
 
 
-RINGS = ("16x16", "32x16", "16x32", "32x32", "48x32", "32x64", "64x64", "48x64")     # features x rows of a workgroup
-
-
-def linear_plans(dtype, B, n, d, H, F):
-    """(tile or ring instance, shares) of the four layers of a block as they run."""
-    lib, b, R = fv.load_library(), 1 if dtype == "bf16" else 0, B * n
-    run = lib["_ZN4fvar11linear_planENS_5DTypeEiiim"]
-    run.restype, run.argtypes = _Plan, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t]
-    att, bound = lib["_ZN4fvar24attention_scratch_floatsENS_5DTypeEiiii"], lib["_ZN4fvar22gemm_f32_scratch_boundEii"]
-    att.restype = bound.restype = C.c_size_t
-    shapes = ((3 * d, d), (d, d), (F, d), (d, F))
-    room = max([gemm_plan(dtype, R, N, K).scratch_floats for N, K in shapes] + [att(b, B, n, H, d // H)] +
-               ([] if b else [bound(R, max(3 * d, F))]))
-    out = []
-    for N, K in shapes:
-        p = run(b, R, N, K, room)
-        assert p.scratch_floats <= room and p.scratch_floats >= (p.nsplit * R * N if p.nsplit > 1 else 0)
-        out.append((TILES[p.cfg] if p.cfg < len(TILES) else "ring " + RINGS[p.cfg - len(TILES)], p.nsplit))
-    return out
-
-
 @pytest.mark.parametrize("dtype,B,n,d,H,F,expect", [
-    ("f32", 3, 6, 1024, 8, 4096, [("16x32", 1), ("16x16", 1), ("32x16", 1), ("32x32", 8)]),
+    ("f32", 3, 6, 1024, 8, 4096, [("16x32", 1), ("16x16", 1), ("16x32", 1), ("16x32", 4)]),
     ("f32", 5, 50, 320, 5, 1280, [("32x32", 1), ("16x32", 1), ("32x64", 1), ("16x32", 1)]),
-    ("f32", 1, 85, 960, 15, 3840, [None, None, None, ("48x32", 4)]),
-    ("f32", 1, 200, 1024, 16, 4096, [("48x64", 1), None, ("64x64", 1), None]),
-    ("bf16", 1, 43, 1536, 24, 6144, [None, None, None, ("48x64", 8)]),
-    ("bf16", 1, 99, 1536, 24, 6144, [None, None, None, ("48x64", 4)]),
-    ("bf16", 1, 141, 4096, 32, 1024, [None, ("64x64", 1), None, None]),
-    ("bf16", 7, 14, 1024, 16, 4096, [None, None, None, ("32x16", 1)]),
-    ("bf16", 1, 48, 1920, 30, 7680, [("48x32", 1), ("16x32", 1), ("32x64", 1), None]),
-    ("bf16", 1, 15, 2048, 16, 8192, [("32x16", 1), ("16x16", 1), ("16x16", 1), ("16x16", 1)]),
+    ("f32", 1, 85, 960, 15, 3840, [("48x32", 1), None, None, ("48x32", 4)]),
+    ("f32", 1, 200, 1024, 16, 4096, [("48x64", 1), ("32x32", 1), ("64x64", 1), None]),
+    ("f32", 1, 3, 2048, 32, 64, [None, None, ("16x16", 8), None]),
+    ("f32", 1, 33, 768, 12, 5440, [None, None, None, ("48x32", 8)]),
+    ("f32", 1, 57, 1088, 17, 5440, [None, None, None, ("32x32", 2)]),
+    ("bf16", 1, 43, 1536, 24, 6144, [("48x32", 1), None, None, ("48x32", 4)]),
+    ("bf16", 1, 99, 1536, 24, 6144, [("48x64", 1), None, None, ("48x64", 4)]),
+    ("bf16", 1, 141, 4096, 32, 1024, [None, None, ("32x32", 1), ("64x64", 1)]),
+    ("bf16", 7, 14, 1024, 16, 4096, [("48x32", 1), ("16x32", 1), ("32x64", 1), None]),
+    ("bf16", 1, 48, 1920, 30, 7680, [("48x32", 1), ("16x32", 1), ("32x64", 1), ("32x64", 4)]),
+    ("bf16", 1, 33, 1920, 30, 7680, [None, None, None, ("64x64", 8)]),
+    ("bf16", 1, 3, 768, 12, 8192, [None, None, None, ("32x16", 8)]),
+    ("bf16", 3, 8, 4096, 32, 16384, [None, None, ("64x64", 1), ("32x32", 2)]),
     ("bf16", 2, 65, 1024, 16, 4096, [("48x64", 1), ("32x32", 1), None, ("32x32", 1)]),
 ])
 def test_instances_of_the_ring_kernel(dtype, B, n, d, H, F, expect):
     """tests/test_gpu_linear_plans.py is there for these."""
     got = linear_plans(dtype, B, n, d, H, F)
-    assert all(e is None or g == ("ring " + e[0], e[1]) for g, e in zip(got, expect)), got
+    assert all(e is None or got[l] == ("ring " + e[0], e[1], 1) for l, e in zip(LAYERS, expect)), got
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_plans_that_run_stay_within_the_workspace(dtype):
-    """Every call gets a plan within the scratch that its workspace holds (asserted in linear_plans)."""
-    for d, H, F in ((64, 1, 64), (192, 3, 256), (1024, 16, 4096), (1920, 30, 7680), (4096, 32, 1024)):
+    """Every call gets a plan whose partial results fit what its workspace has besides the activations."""
+    es, al = 2 if dtype == "bf16" else 4, lambda n: -(-n // 256) * 256
+    for d, H, F in ((64, 1, 64), (192, 3, 256), (1024, 16, 4096), (1920, 30, 7680), (4096, 32, 1024), (4096, 32, 16384)):
+        c = fv.Context(hidden=d, heads=H, head_dim=d // H, ffn_hidden=F, dtype=dtype)
         for B, n in ((1, 1), (1, 15), (3, 11), (1, 100), (2, 128), (1, 257), (4, 700), (32, 1600)):
-            linear_plans(dtype, B, n, d, H, F)
+            R = B * n
+            part = fv.fvar_block_workspace_bytes(c, B, n) - 4 * al(R * d * es) - al(R * d * 4) - al(R * F * es)
+            for p, N in zip(block_plan(dtype, B, n, d, H, F).layer, (3 * d, d, F, d)):
+                assert p.scratch_floats >= (p.nsplit * R * N if p.nsplit > 1 else 0)
+                assert 4 * p.scratch_floats <= part, (d, B, n, N)
+                assert p.cfg < len(TILES) + len(RINGS) and (p.cfg >= len(TILES) or dtype == "bf16")
 
 
 @pytest.mark.parametrize("B,n,d,H,F,expect", [
     (1, 436, 768, 12, 3072, ("64x64", 3)), (4, 100, 512, 8, 2048, ("64x64", 4)),
     (1, 72, 1920, 30, 7680, ("128x64", 8)), (1, 137, 1536, 24, 6144, ("64x128", 7)),
+    (1, 180, 1536, 24, 5440, ("64x128", 7)),
 ])
 def test_small_tiles_in_shares_stay_in_reach(B, n, d, H, F, expect):
     """tests/test_gpu_linear_plans.py runs these for the division of small tiles (their FC2)."""
-    assert linear_plans("bf16", B, n, d, H, F)[3] == expect
+    assert linear_plans("bf16", B, n, d, H, F)["fc2"] == expect + (1,)
 
 
 @pytest.mark.parametrize("B,n,L,H,Dh,groups,ranges", [
