@@ -230,6 +230,8 @@ fvar_status block_forward(fvar_ctx *c, hipStream_t st, const fvar_block_weights 
     const int d = c->cfg.hidden, H = c->cfg.heads, Dh = c->cfg.head_dim, F = c->cfg.ffn_hidden;
     const int R = B * rows, L = kv->len + rows;
 
+    bool launched = true;
+
     // gather (identity in the dense case) + LayerNorm 1; the dense case reads the residual from x
     const void *resid = idx ? (const void *)s.x_keep : x;
     timed(c, st, "gather_ln1", [&] {
@@ -242,7 +244,7 @@ fvar_status block_forward(fvar_ctx *c, hipStream_t st, const fvar_block_weights 
         e.bias = w->b_qkv; e.out0 = s.q; e.ld0 = d; e.split = d;
         e.kcache = kv->k; e.vcache = kv->v; e.hd = d; e.cap = kv->capacity; e.len = kv->len;
         e.rows_per_sample = rows;
-        fvar::launch_gemm(dt, s.u, w->w_qkv, R, 3 * d, d, e, s.qkv, s.part, st);
+        launched &= fvar::launch_gemm(dt, s.u, w->w_qkv, R, 3 * d, d, e, s.qkv, s.part, st);
     });
     timed(c, st, "attention", [&] {
         fvar::launch_attention(dt, s.q, kv->k, kv->v, B, rows, L, kv->capacity, H, Dh, c->scale, s.att,
@@ -252,7 +254,7 @@ fvar_status block_forward(fvar_ctx *c, hipStream_t st, const fvar_block_weights 
         fvar::GemmEpilogue e;
         e.bias = w->b_o; e.residual = resid; e.out0 = s.h1; e.ld0 = d; e.split = d;
         e.out_f32 = 1;
-        fvar::launch_gemm(dt, s.att, w->w_o, R, d, d, e, s.o, s.part, st);
+        launched &= fvar::launch_gemm(dt, s.att, w->w_o, R, d, d, e, s.o, s.part, st);
     });
     timed(c, st, "ln2", [&] {
         if (dt == DType::BF16)
@@ -264,13 +266,14 @@ fvar_status block_forward(fvar_ctx *c, hipStream_t st, const fvar_block_weights 
     timed(c, st, "gemm_fc1", [&] {
         fvar::GemmEpilogue e;
         e.bias = w->b_fc1; e.gelu = 1; e.out0 = s.hid; e.ld0 = F; e.split = F;
-        fvar::launch_gemm(dt, s.u, w->w_fc1, R, F, d, e, s.fc1, s.part, st);
+        launched &= fvar::launch_gemm(dt, s.u, w->w_fc1, R, F, d, e, s.fc1, s.part, st);
     });
     timed(c, st, "gemm_fc2", [&] {
         fvar::GemmEpilogue e;
         e.bias = w->b_fc2; e.residual = s.h1; e.res_f32 = 1; e.out0 = y; e.ld0 = d; e.split = d;
-        fvar::launch_gemm(dt, s.hid, w->w_fc2, R, d, F, e, s.fc2, s.part, st);
+        launched &= fvar::launch_gemm(dt, s.hid, w->w_fc2, R, d, F, e, s.fc2, s.part, st);
     });
+    if (!launched) return fail(c, FVAR_ERR_UNSUPPORTED, "%s: a linear layer has no plan that can be launched", who);
     const fvar_status ls = launch_status(c, who);
     if (ls != FVAR_OK || !c->debug_checks) return ls;
     unsigned char canary[kCanaryBytes];

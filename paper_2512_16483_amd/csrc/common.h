@@ -162,8 +162,9 @@ struct BlockPlan { GemmPlan layer[4]; size_t floats; };
 BlockPlan block_plan(DType dt, int B, int rows, int d, int H, int Dh, int F);
 // floats that no fp32 plan of up to `rows` rows and N columns exceeds; never falls as rows grow
 size_t gemm_f32_scratch_bound(int rows, int N);
-// `part`: plan.scratch_floats floats (unused when 0)
-void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
+// `part`: plan.scratch_floats floats (unused when 0).  False, and nothing launched, where the plan is not one that can
+// compute all N columns.
+[[nodiscard]] bool launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
                  const GemmEpilogue &ep, const GemmPlan &plan, float *part, hipStream_t st);
 
 // o[b,i,h,:] = softmax_t(scale * q[b,i,h,:] . K[b,t,h,:]) V[b,t,h,:], t in [0,L)

@@ -1489,13 +1489,23 @@ static void launch_gemm_ring(int i, const void *A, const void *W, int rows, int 
     case 4: launch_gemm_rows<T, 3, 2, 8, 2>(A, W, rows, N, K, ep, st, nsplit, part); break;
     case 5: launch_gemm_rows<T, 2, 4, 4, 2>(A, W, rows, N, K, ep, st, nsplit, part); break;
     case 6: launch_gemm_rows<T, 4, 4, 4, 2>(A, W, rows, N, K, ep, st, nsplit, part); break;
-    default: launch_gemm_rows<T, 3, 4, 4, 2>(A, W, rows, N, K, ep, st, nsplit, part); break;
+    case 7: launch_gemm_rows<T, 3, 4, 4, 2>(A, W, rows, N, K, ep, st, nsplit, part); break;
     }
 }
 
-void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
+// Every column has to belong to a workgroup: the instances of gemm_rows_kernel leave no remainder of their features.
+static bool launchable(DType dt, int N, const GemmPlan &plan)
+{
+    if (plan.nsplit < 1 || plan.tail < 1 || plan.cfg < 0) return false;
+    if (plan.cfg < kNumTiles) return dt == DType::BF16;
+    const int i = plan.cfg - kNumTiles;
+    return i < kNumRings && N % (16 * kRings[dt == DType::BF16][i].ft) == 0;
+}
+
+bool launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
                  const GemmEpilogue &e, const GemmPlan &plan, float *part, hipStream_t st)
 {
+    if (!launchable(dt, N, plan)) return false;
     EpiParams ep;
     ep.bias = e.bias; ep.residual = e.residual; ep.gelu = e.gelu;
     ep.out0 = e.out0; ep.ld0 = e.ld0; ep.split = e.split;
@@ -1548,6 +1558,7 @@ void launch_gemm(DType dt, const void *A, const void *W, int rows, int N, int K,
                    (const float *)part, plan.nsplit, rows, N, ep);
         }
     }
+    return true;
 }
 
 }  // namespace fvar

@@ -417,6 +417,21 @@ def test_small_tiles_in_shares_stay_in_reach(B, n, d, H, F, expect):
     assert linear_plans("bf16", B, n, d, H, F)["fc2"] == expect + (1,)
 
 
+@pytest.mark.parametrize("dtype,N,cfg,nsplit,tail", [
+    ("bf16", 1024, len(TILES) + 7, 1, 1), ("bf16", 2048, len(TILES) + 4, 1, 1),      # 48 features do not divide N
+    ("bf16", 1920, len(TILES) + len(RINGS), 1, 1), ("bf16", 1920, -1, 1, 1), ("f32", 1920, len(TILES) + len(RINGS), 1, 1),
+    ("f32", 1024, len(TILES) + 7, 1, 1), ("f32", 1920, 4, 1, 1),                     # tiles are bf16 only
+    ("bf16", 1920, 10, 0, 1), ("bf16", 1920, 10, 1, 0),
+])
+def test_plans_that_cannot_be_launched_are_refused(dtype, N, cfg, nsplit, tail):
+    """Such a plan would leave columns unwritten: the launcher says so and launches nothing."""
+    f = fv.load_library()["_ZN4fvar11launch_gemmENS_5DTypeEPKvS2_iiiRKNS_12GemmEpilogueERKNS_8GemmPlanEPfP12ihipStream_t"]
+    f.restype = C.c_bool
+    epilogue, plan = C.create_string_buffer(256), _Plan(cfg, nsplit, tail, 0)
+    null = C.c_void_p(None)
+    assert f(1 if dtype == "bf16" else 0, null, null, 64, N, 1920, epilogue, C.byref(plan), null, null) is False
+
+
 @pytest.mark.parametrize("B,n,L,H,Dh,groups,ranges", [
     (2, 2, 635, 32, 128, 1, 2),       # 12.7 us; two groups without ranges 15.0
     (5, 18, 1271, 30, 64, 1, 3),      # 14.8; 17.2
