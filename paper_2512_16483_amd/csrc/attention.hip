@@ -380,9 +380,9 @@ __global__ __launch_bounds__(256 * KG, 2) void attn_bf16_kernel(const uint16_t *
 #pragma unroll
         for (int j = 0; j < NQ; ++j) {
             const float2 other = xm[(((1 - kg) * 4 + wave) * NQ + j) * 64 + lane];
-            const float m = fmaxf(m_own[j], other.x);        // the second group always has a tile: finite
-            const float wo = __builtin_amdgcn_exp2f((m_own[j] - m) * c_log2);
-            const float wx = __builtin_amdgcn_exp2f((other.x - m) * c_log2);
+            const float m = fmaxf(m_own[j], other.x), m_fin = fmaxf(m, -1e30f);   // as in the loop: no finite score, no weight
+            const float wo = __builtin_amdgcn_exp2f((m_own[j] - m_fin) * c_log2);
+            const float wx = __builtin_amdgcn_exp2f((other.x - m_fin) * c_log2);
             const float l = l_own[j] * wo + other.y * wx;
             const int row = q0 + j * 32 + rl;
             if (row >= n) continue;
