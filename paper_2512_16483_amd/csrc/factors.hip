@@ -62,8 +62,8 @@ __global__ __launch_bounds__(kGramThreads) void gram_f32_kernel(const float *__r
 // four wavefronts.  Within a chunk the products (exact in fp32) are summed in fp32; chunk results
 // are added in fp64.  The slices' partial matrices are written to Spart[b][part] (both triangles)
 // and summed by the inverse, so the result does not depend on scheduling.  The inverse reads them through one
-// CU, so fewer is better there (128 KB each at rank 128): this and the inverse, with T beside it, take
-// 68.7 us at rank 128, 4 samples with four slices, 69.4 with two of eight wavefronts and 75 with one of sixteen.
+// CU, so fewer is better there (128 KB each at rank 128).  The whole call in two, four and eight slices: 94.3, 96.5 and
+// 105.1 us at rank 128, 4 x 4096 rows of 4096, 235, 233 and 239 for 40 x 1024, 68.8, 67.6 and 67.0 at rank 64.
 // The chunks come by DMA in whole 128-byte lines, two in flight per wavefront (a row per lane is a quarter of the
 // vector L1's rate, see gemm_rows_kernel): rank 128, 4 samples of width 4096 6.5 -> 4.9 us, 40 of them 35.4 -> 28.5.
 // Chunks past the end are not fetched: where a wavefront has one, as with d = 1024, those in their place tripled

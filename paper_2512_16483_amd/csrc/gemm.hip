@@ -1082,13 +1082,14 @@ __global__ __launch_bounds__(256) void gemm_f32_merge_kernel(const float *__rest
 // What bounds it: at few rows the operands' way through the CU's vector L1 (the rows are read again by
 // every feature tile, L2 hits), so the DMA fetches whole 128-byte lines.  Loads in the MFMA's own lane order, a row
 // per lane, would save the LDS but reach only 38 GB/s per CU where these reach 150: only neighbouring lanes'
-// addresses are taken together.  Rings of 64-byte rows are 20 to 30 % slower too, and more than two or three steps
-// in flight bring nothing.  us at 64 rows, hidden 2048, weights from HBM, against loads straight to registers or 64x64
-// tiles, whichever was faster: QKV 14.5 -> 10.3, O 11.0 -> 6.8, FC1 15.1 -> 11.1, FC2 15.9 -> 14.1 (the
-// weights alone take 7.2, 4.8, 8.9 and 8.9, an empty launch 2.4); at 16 rows QKV 10.8 -> 7.5, FC1 11.9 -> 8.6.
+// addresses are taken together.  Rings of 64-byte rows are 20 to 30 % slower too.  Two to four steps in flight are the
+// same within 3 % (16x16: 16 rows, 7680 to 1920 12.1, 12.0 and 11.9 us, fp32 1024 to 1024 4.2, 4.3 and 4.5); the larger instances
+// have LDS for two or three.  us, weights from HBM, against loads straight to registers or 64x64 tiles, whichever was
+// faster: 64 rows, hidden 2048, QKV 13.6 -> 8.9, O 10.8 -> 6.0, FC1 14.9 -> 11.0, FC2 15.5 -> 14.2 (the weights alone
+// take 7.2, 4.8, 8.9 and 8.9 in launches by themselves, an empty one 2.4); 16 rows QKV 10.5 -> 7.2, FC1 10.9 -> 8.6.
 // fp32, bound by the MFMA's rate (157 TFLOP/s, as the vector units) from a few hundred rows on, so what counts is
-// that every CU gets the same share: hidden 1024, 128 rows QKV 17.7 -> 11.1, O 10.6 -> 6.8, FC1 18.3 -> 13.9,
-// FC2 21.1 -> 14.9, 2048 rows FC1 227 -> 178.
+// that every CU gets the same share: hidden 1024, 128 rows QKV 16.9 -> 10.4, O 10.9 -> 6.4, FC1 17.8 -> 14.7,
+// FC2 21.1 -> 14.4, 2048 rows FC1 254 -> 190.
 template <typename T, int FT, int TT, int NW, int STAGES>
 __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(
     const T *__restrict__ A, const T *__restrict__ W, int rows, int N, int K, int row_tiles,
@@ -1146,8 +1147,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_rows_kernel(
 #pragma unroll
         for (int t = 0; t < TT; ++t) acc[f][t] = floatx4_t{0};
     // fp32: no accumulation runs over more than a step's 32 products; what these chains give is added up in a second
-    // set of registers.  (One chain per wavefront is as fast, but with four wavefronts its error against 64 bits is
-    // 3.0e-7 where eight of half the length have 2.2e-7.)
+    // set of registers.  (One chain per wavefront is as fast, but the block of 128 rows, hidden 1024, is then off by 3.0e-7 with
+    // four wavefronts and by 2.2e-7 with eight, against 1.35e-7.)
     constexpr bool CHAINS = sizeof(T) == 4;
     floatx4_t sum[CHAINS ? FT : 1][CHAINS ? TT : 1] = {};
     uint4 frag[2][NF];
