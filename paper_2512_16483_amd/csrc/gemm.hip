@@ -906,7 +906,7 @@ size_t batched_f32_room(int nbatch, int rows, int K)
 }
 
 // Tile height (256, 128 or 64 rows; one tile spans all N <= 128 columns) and shares of the contraction,
-// by the same prediction as gemm_plan; the consumer sums the shares, so they cost it a read each.
+// by the same prediction as tile_plan; the consumer sums the shares, so they cost it a read each.
 struct BatchedPlan { int bm, parts; };
 static BatchedPlan batched_f32_plan(int nbatch, int rows, int N, int K)
 {
@@ -970,7 +970,7 @@ bool kmajor_in_groups(int B, int M, int rows, int d)
 // Runs out[b] = qt[b] x[b] (qt: [rows][M] per sample or shared, x[b]: [M][d]) on the tiled MFMA
 // kernel (M a multiple of 8, d of 64).  Where not even 64 rows of qt fit 32-bit byte offsets (M of 2^25 and more),
 // as many rows at a time as do, sample by sample (8 rows of 2^25 tokens, width 64: 0.20 s; 15.8 by a thread per
-// column).  Tile by predicted time, constants as in gemm_plan plus
+// column).  Tile by predicted time, constants as in tile_plan plus
 // a tenth for the transposing reads (no 320x256 tile: with them it would not fit the 256 registers).  Even a
 // few tiles here beat many of a kernel that turns X around through registers, whose 64-token chunk takes
 // 1.7 us against 0.4 us of a 64x128 k-tile: 692 x 2304 x 2048 61 -> 17 us, 4 x (128 x 4096 x 4096)
@@ -1443,7 +1443,7 @@ static GemmPlan linear_plan(DType dt, int rows, int N, int K, size_t room, TileC
 
 BlockPlan block_plan(DType dt, int B, int rows, int d, int H, int Dh, int F)
 {
-    const int R = B * rows, shape[4][2] = {{3 * d, d}, {d, d}, {F, d}, {d, F}};   // N, K
+    const int R = (int)((size_t)B * rows), shape[4][2] = {{3 * d, d}, {d, d}, {F, d}, {d, F}};   // N, K
     BlockPlan p;
     TileChoice tile[4] = {};
     p.floats = attention_scratch_floats(dt, B, rows, H, Dh);
